@@ -20,7 +20,8 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libglassnet.so")
 ARCH = "gfx950"
 
-SOURCES = ["api.cpp", "layout.cpp", "serve.cpp", "fwd_mfma.hip", "planes.hip",
+SOURCES = ["api.cpp", "layout.cpp", "serve.cpp", "fwd_mfma.hip", "fwd_fp32.hip",
+           "planes.hip",
            "loss.hip", "optim.hip", "sr.hip", "spatial.hip"]
 
 

@@ -94,6 +94,7 @@ static gn_status precheck(gn_handle *h) {
 
 gn_status gn_prepare_weights(gn_handle *h, hipStream_t stream) {
   hipError_t e = gn::launch_pack_weights(h->d_master, h->d_packed, h->pl, h->act_scale, stream);
+  if (e == hipSuccess && h->cfg.precision == GN_FP32) e = gn_f32_pack(h, stream);
   return gn_check_device(h, e, "weight packing");
 }
 
@@ -168,6 +169,8 @@ gn_status glassnet_create(const gn_config *cfg, const float *host_weights, size_
   if (e == hipSuccess) e = hipMalloc((void **)&h->d_master, wbytes);
   if (e == hipSuccess) e = hipMalloc((void **)&h->d_packed, (size_t)h->pl.total_bytes);
   if (e == hipSuccess) e = hipMalloc((void **)&h->d_l1_partials, sizeof(float) * h->l1_npart);
+  const size_t f32_bytes = cfg->precision == GN_FP32 ? gn_f32_packed_bytes(h->W, cfg->pe_levels) : 0;
+  if (e == hipSuccess && f32_bytes) e = hipMalloc((void **)&h->d_f32, f32_bytes);
   const size_t sig_bytes = gn::mfma_sig_scratch_bytes(h->W, h->num_cus);
   if (cfg->precision != GN_FP32)
     for (int i = 0; i < 2 && e == hipSuccess; ++i)
@@ -189,7 +192,7 @@ gn_status glassnet_create(const gn_config *cfg, const float *host_weights, size_
       return fail(GN_E_DEVICE, "DSSIM scratch address: %s", hipGetErrorString(e));
     }
   }
-  h->bytes_held = wbytes + (size_t)h->pl.total_bytes + sizeof(float) * h->l1_npart +
+  h->bytes_held = f32_bytes + wbytes + (size_t)h->pl.total_bytes + sizeof(float) * h->l1_npart +
                   (cfg->precision == GN_FP32 ? 0 : 2 * sig_bytes);
   gn_status st = gn_prepare_weights(h, nullptr);
   if (st == GN_OK) {
@@ -219,6 +222,7 @@ gn_status glassnet_destroy(gn_handle *h) {
   if (!h->poisoned) (void)hipDeviceSynchronize();
   (void)hipFree(h->d_master);
   (void)hipFree(h->d_packed);
+  (void)hipFree(h->d_f32);
   (void)hipFree(h->d_l1_partials);
   (void)hipFree(h->d_loss_ws);
   (void)hipFree(h->d_sr_wt);
@@ -281,7 +285,7 @@ gn_status glassnet_calibrate(gn_handle *h, const gn_frame *frame, void *hip_stre
     (void)hipFree(amax);
     return gn_check_device(h, e, "calibration");
   }
-  st = gn_planes_calibrate(h, frame, amax, s);
+  st = gn_f32_calibrate(h, frame, amax, s);
   unsigned bits = 0;
   if (st == GN_OK) {
     e = hipMemcpyAsync(&bits, amax, sizeof bits, hipMemcpyDeviceToHost, s);
@@ -318,7 +322,7 @@ gn_status glassnet_forward(gn_handle *h, const gn_frame *frame, float *out, void
   b.n = frame->n;
   b.hw = frame->h * frame->w;
   b.k = frame->k;
-  if (h->cfg.precision == GN_FP32) return gn_planes_forward(h, frame, out, s);
+  if (h->cfg.precision == GN_FP32) return gn_f32_forward(h, frame, out, s);
   const int tpf = (b.hw + gn::kTilePx - 1) / gn::kTilePx;
   const hipError_t e = gn::launch_fwd_mfma(h->W, h->cfg.precision, h->cfg.pool, h->d_packed, h->pl,
                                            &b, nullptr, nullptr, b.n * tpf, h->act_scale,
@@ -335,8 +339,8 @@ static gn_status stream_geometry(gn_handle *h, int32_t n, int32_t hgt, int32_t w
   const int64_t hw = (int64_t)hgt * wid;
   if (hw * gn::kNG > INT32_MAX || (int64_t)n * hw > INT32_MAX)
     return fail(GN_E_INVAL, "frame too large (%d x %d x %d)", n, hgt, wid);
-  if (h->cfg.precision == GN_FP32) {          // plane pipeline: [sigma; Z; count] rows
-    *bytes = gn_planes_stream_bytes(h->W, (int64_t)n * hw);
+  if (h->cfg.precision == GN_FP32) {          // sigma, Z and the count of every pixel
+    *bytes = gn_f32_stream_bytes(h->W, (int64_t)n * hw);
     return GN_OK;
   }
   const uint64_t tiles = (uint64_t)n * (uint64_t)((hw + gn::kTilePx - 1) / gn::kTilePx);
@@ -344,7 +348,7 @@ static gn_status stream_geometry(gn_handle *h, int32_t n, int32_t hgt, int32_t w
   return GN_OK;
 }
 
-// One streaming launch: the fused kernel's mode, or the plane pipeline (GN_FP32).
+// One streaming launch: the fused kernel's mode, or the fp32 one's (GN_FP32).
 static gn_status stream_launch(gn_handle *h, const gn::FwdBatch &b, const gn_frame *f, int mode,
                                void *state, int state_load, float *out, hipStream_t s,
                                const char *what) {
@@ -354,7 +358,7 @@ static gn_status stream_launch(gn_handle *h, const gn::FwdBatch &b, const gn_fra
     pf.layers = b.layers;
     pf.scene = b.scene;
     pf.k = b.k;
-    return gn_planes_stream(h, &pf, mode, (float *)state, state_load ? 0 : 1, out, s);
+    return gn_f32_stream(h, &pf, mode, (float *)state, state_load ? 0 : 1, out, s);
   }
   const hipError_t e = gn::launch_fwd_stream(h->W, h->cfg.precision, h->cfg.pool, h->d_packed,
                                              h->pl, b, h->act_scale, h->num_cus, mode,

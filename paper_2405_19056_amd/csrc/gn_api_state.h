@@ -26,6 +26,7 @@ struct gn_handle {
   size_t nparams = 0;
   float *d_master = nullptr;      // fp32 master weights (flat layout)
   uint8_t *d_packed = nullptr;    // fragment-ordered bf16/fp8 weights + biases
+  uint8_t *d_f32 = nullptr;       // fp32 fragments and biases (fwd_fp32.hip)
   gn::PackedLayout pl{};
   uint8_t *d_sig_scratch[2] = {nullptr, nullptr};  // MFMA forward: caller streams, serving
   float *d_l1_partials = nullptr;
@@ -61,13 +62,16 @@ gn_status gn_prepare_weights(gn_handle *h, hipStream_t stream);
 gn_status gn_serve_init(gn_handle *h);
 void gn_serve_shutdown(gn_handle *h);
 void gn_bwd_free(gn_handle *h);
-// The fp32 plane pipeline (planes.hip): the FP32 forward and the FP8
-// calibration (amax: device float bits of the largest h-layer-1 activation).
-gn_status gn_planes_forward(gn_handle *h, const gn_frame *frame, float *out, hipStream_t s);
-gn_status gn_planes_calibrate(gn_handle *h, const gn_frame *frame, unsigned *amax, hipStream_t s);
-// Object streaming on the plane pipeline (GN_FP32): mode FWD_BEGIN, FWD_ACC or
-// FWD_FINISH; the state holds gn_planes_stream_bytes(W, n h w) bytes.
-size_t gn_planes_stream_bytes(int W, int64_t npx);
-gn_status gn_planes_stream(gn_handle *h, const gn_frame *frame, int mode, float *state, int fresh,
-                           float *out, hipStream_t s);
+// The fp32 kernels (fwd_fp32.hip): the packed weights of a handle, the FP32
+// forward and the FP8 calibration (amax: device float bits of the largest
+// h-layer-1 activation).
+size_t gn_f32_packed_bytes(int W, int pe);
+hipError_t gn_f32_pack(gn_handle *h, hipStream_t s);
+gn_status gn_f32_forward(gn_handle *h, const gn_frame *frame, float *out, hipStream_t s);
+gn_status gn_f32_calibrate(gn_handle *h, const gn_frame *frame, unsigned *amax, hipStream_t s);
+// Object streaming of GN_FP32 handles: mode FWD_BEGIN, FWD_ACC or FWD_FINISH;
+// the state holds gn_f32_stream_bytes(W, n h w) bytes.
+size_t gn_f32_stream_bytes(int W, int64_t npx);
+gn_status gn_f32_stream(gn_handle *h, const gn_frame *frame, int mode, float *state, int fresh,
+                        float *out, hipStream_t s);
 size_t gn_bwd_bytes(gn_handle *h);

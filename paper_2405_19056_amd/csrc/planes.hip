@@ -1075,52 +1075,6 @@ static gn_status with_device(gn_handle *h, Fn fn) {
   return st;
 }
 
-gn_status gn_planes_forward(gn_handle *h, const gn_frame *frame, float *out, hipStream_t s) {
-  return with_device(h, [&]() {
-    Pipeline p(h, s);
-    gn_status st = p.begin(frame, nullptr, "fp32 forward");
-    if (st != GN_OK) return st;
-    p.trunk();
-    p.slots();
-    p.head();
-    p.output(out);
-    return p.finish("fp32 forward");
-  });
-}
-
-gn_status gn_planes_calibrate(gn_handle *h, const gn_frame *frame, unsigned *amax, hipStream_t s) {
-  return with_device(h, [&]() {
-    Pipeline p(h, s);
-    gn_status st = p.begin(frame, nullptr, "calibration");
-    if (st != GN_OK) return st;
-    p.trunk();
-    p.calibrate(amax);
-    return p.finish("calibration");
-  });
-}
-
-// Object streaming on the plane pipeline (GN_FP32 handles); state holds
-// gn_planes_stream_bytes floats.
-size_t gn_planes_stream_bytes(int W, int64_t npx) {
-  return sizeof(float) * (size_t)(2 * W + 1) * (size_t)npx;   // sigma, Z, count
-}
-
-gn_status gn_planes_stream(gn_handle *h, const gn_frame *frame, int mode, float *state, int fresh,
-                           float *out, hipStream_t s) {
-  return with_device(h, [&]() {
-    Pipeline p(h, s);
-    gn_status st = p.begin(frame, nullptr, "fp32 stream", false);
-    if (st != GN_OK) return st;
-    if (mode == FWD_BEGIN)
-      p.stream_begin(state);
-    else if (mode == FWD_ACC)
-      p.stream_accumulate(state, fresh != 0);
-    else
-      p.stream_finish(state, fresh != 0, out);
-    return p.finish("fp32 stream");
-  });
-}
-
 extern "C" gn_status glassnet_backward(gn_handle *h, const gn_frame *frame,
                                        const float *grad_out, float *grad_w, void *hip_stream) {
   if (!h) return gn_set_error(GN_E_INVAL, "handle is NULL");

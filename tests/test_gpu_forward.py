@@ -334,6 +334,20 @@ def test_fp32_plane_workspace_reused_across_sizes_and_with_backward():
     assert np.all(np.isfinite(host(g)))
 
 
+@pytest.mark.parametrize("W", [64, 128])
+@pytest.mark.parametrize("n,h,w_,k", [(1, 1, 1, 1), (1, 3, 5, 9), (2, 1, 16, 2), (1, 17, 1, 8),
+                                      (1, 7, 9, 0), (3, 5, 13, 11), (1, 1, 129, 3)])
+def test_fp32_forward_at_tile_edges(W, n, h, w_, k):
+    """Pixel counts around the fp32 kernel's 16-pixel waves and 64-pixel tiles
+    (frames that share a tile among them), no slot, and more slots than its
+    lane groups rank in one step."""
+    wts, fr = frame(n, h, w_, k, W, seed=200 + k)
+    for pool in ("mean", "sum"):
+        ref = oracle.forward(wts, W, fr.gbuf, fr.layers, fr.scene, pool=pool)
+        with GlassNet(wts, W, k_max=16, pool=pool, precision="fp32") as net:
+            gate(run(net, fr), ref, TOL["fp32"], f"fp32 {(W, n, h, w_, k, pool)}")
+
+
 def test_fp32_forward_rejects_more_pixels_than_it_addresses():
     """The fp32 plane pipeline covers at most 3 * 2^20 pixels per call; beyond
     that the forward is an argument error raised before any launch."""
