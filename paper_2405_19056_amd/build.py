@@ -21,7 +21,7 @@ LIB = os.path.join(PKG, "libglassnet.so")
 ARCH = "gfx950"
 
 SOURCES = ["api.cpp", "layout.cpp", "serve.cpp", "fwd_mfma.hip", "fwd_fp32.hip",
-           "planes.hip",
+           "bwd_fp32.hip",
            "loss.hip", "optim.hip", "sr.hip", "spatial.hip"]
 
 
@@ -42,16 +42,10 @@ def common_flags():
     ]
 
 
-# Per-source extra flags.  The backward's fp32 plane GEMMs keep their
-# accumulators in VGPRs: in the default accumulator-register form the
-# allocator rotates them through copies every K group, at half the occupancy.
-EXTRA = {"planes.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
-
-
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, os.path.basename(src) + ".o")
     lang = ["-x", "hip"]
-    cmd = ([hipcc()] + common_flags() + EXTRA.get(src, []) + lang
+    cmd = ([hipcc()] + common_flags() + lang
            + ["-c", os.path.join(CSRC, src), "-o", obj])
     r = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"

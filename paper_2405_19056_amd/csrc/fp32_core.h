@@ -1,5 +1,5 @@
-// Shared core of the fp32 per-pixel kernels (fwd_fp32.hip): the networks'
-// linear maps on v_mfma_f32_16x16x4f32, chained in registers.
+// Shared core of the fp32 per-pixel kernels (fwd_fp32.hip, bwd_fp32.hip): the
+// networks' linear maps on v_mfma_f32_16x16x4f32, chained in registers.
 //
 // Formulation.  A wave owns 16 pixels.  Every map is D = A X with a 16-row
 // tile of A (weights) as the row operand and the 16 pixels as the columns.
@@ -32,35 +32,59 @@ constexpr int kTile = kWaves * 16;         // pixels per workgroup tile
 constexpr int kStageFrags = 16;
 constexpr int kStageBytes = kStageFrags * 1024;
 
-// The linear maps of the forward, in the order the kernel consumes them.
+// The linear maps of the forward and of the backward (the transposes), each
+// list in the order its kernel consumes them.
 enum Op {
   O_F1, O_F2, O_F3, O_T1S, O_T1A, O_T2, O_T3, O_B1S, O_B1T, O_B2, O_B3, O_R1P, O_R1L, O_R2, O_R3,
   kNumOps
 };
+enum BwdOp {
+  O_R3T, O_R2T, O_R1T, O_B3T, O_B2T, O_B1ST, O_B1TT, O_T3T, O_T2T, O_T1ST, O_F3T, O_F2T, kNumBwdOps
+};
 
-// Map o multiplies A (M x K): A[m][k] = W[m][col0 + k] of a layer.
+// Map o multiplies A (M x K): A[m][k] = W[m][col0 + k] of a layer, or
+// W[k][col0 + m] (trans).
 struct OpDesc {
   int64_t woff;      // float offset of the layer's matrix in the master vector
   int32_t ld;        // the layer's input count (master row length)
-  int32_t col0, M, K;
+  int32_t col0, M, K, trans;
   int32_t mt, kq;    // 16-row tiles, 16-deep K groups
   int32_t stage0, nstages;
 };
 
 struct OpTable {
   OpDesc op[kNumOps];
-  int32_t stages;                  // of every map together
+  int32_t nops, stages;            // stages of every map together
   LayerOff lo[kNumLayers];
   int32_t W, pe;
 };
 
 void make_ops(int W, int pe, OpTable *t);
+void make_bwd_ops(int W, int pe, OpTable *t);
 // The packed form: the stages, then the 12 biases (W floats each, in the
 // position order below; R3's 3 in natural order).
 inline size_t packed_bytes(const OpTable &t) {
   return (size_t)t.stages * kStageBytes + sizeof(float) * kNumLayers * t.W;
 }
 hipError_t launch_pack(const float *master, const OpTable &t, uint8_t *packed, hipStream_t s);
+
+// What the backward keeps of a slab of np pixels (a multiple of kTile, the
+// tail repeating the last pixel): blocks [pixel][width] in position order.
+// The slots' blocks follow each other slot by slot ([slot][pixel][width]).
+struct Planes {
+  int64_t p0, np;            // first pixel of the slab; its padded length
+  float *x;                  // F's encoded input, nx wide
+  float *a1, *a2, *sig, *zs, *tau, *d1, *d2, *phi, *g1, *g2;
+  float *z1, *bi;            // per slot: h's first activation; its encoded input, nb wide
+  float *inv, *bs;           // per pixel: 1 / max(c, 1) (mean) or 1; T3's bias scale
+  uint32_t *mask;            // [kMasks + 2 k][np / 16][64]: ReLU signs, bit 4 mt + r
+  // the deltas of the maps' outputs (dsig: sigma's; dz: Z's; dz1 per slot)
+  float *dg2, *dg1, *dphi, *dd2, *dd1, *dtau, *dsig, *dz, *du, *da2, *da1, *dz1, *dy;
+  int32_t nx, nb;
+};
+// Mask layers; then per slot z1's and z2's, the latter of active slots only.
+enum { K_A1, K_A2, K_D1, K_D2, K_G1, K_G2, kMasks };
+constexpr int kDyWidth = 16;
 
 // Position p of a W-row block (16 mt + 4 g + r) holds this neuron.
 __host__ __device__ inline int neuron_at(int p) {

@@ -1,7 +1,8 @@
 // The fp32 forward: the whole per-pixel network (Sec. 3.3-3.4) in one kernel
 // on the fp32 matrix cores, every activation in registers (fp32_core.h).  The
-// same kernel, cut at compile time, serves the FP32 form's object streaming
-// and the FP8 calibration.
+// same kernel, cut at compile time, serves the FP32 form's object streaming,
+// the FP8 calibration and the backward's recompute (SAVE: every activation
+// and ReLU sign the backward needs is written as it passes).
 //
 // A workgroup of four waves takes tiles of 64 pixels (16 per wave), two
 // workgroups per CU: their stage barriers are independent, so one's epilogues
@@ -23,26 +24,22 @@
 namespace gn {
 namespace f32 {
 
-void make_ops(int W, int pe, OpTable *t) {
+struct OpSpec { int op; Layer l; int col0, M, K; };
+
+static void fill_table(int W, int pe, const OpSpec *s, int n, int trans, OpTable *t) {
   layer_offsets(W, pe, t->lo);
   t->W = W;
   t->pe = pe;
-  const int nx = (kNG + kNS) * pe_blocks(pe), nb = kNL * pe_blocks(pe);
-  struct S { Op o; Layer l; int col0, M, K; };
-  const S s[kNumOps] = {
-      {O_F1, L_F1, 0, W, nx},  {O_F2, L_F2, 0, W, W},   {O_F3, L_F3, 0, W, W},
-      {O_T1S, L_T1, nb, W, W}, {O_T1A, L_T1, 0, W, nb}, {O_T2, L_T2, 0, W, W},
-      {O_T3, L_T3, 0, W, W},   {O_B1S, L_B1, 0, W, W},  {O_B1T, L_B1, W, W, W},
-      {O_B2, L_B2, 0, W, W},   {O_B3, L_B3, 0, W, W},   {O_R1P, L_R1, 0, W, W},
-      {O_R1L, L_R1, W, W, 3},  {O_R2, L_R2, 0, W, W},   {O_R3, L_R3, 0, kNOUT, W}};
+  t->nops = n;
   int stage = 0;
-  for (int i = 0; i < kNumOps; ++i) {
-    OpDesc &d = t->op[s[i].o];
+  for (int i = 0; i < n; ++i) {
+    OpDesc &d = t->op[s[i].op];
     d.woff = t->lo[s[i].l].w;
     d.ld = t->lo[s[i].l].in;
     d.col0 = s[i].col0;
     d.M = s[i].M;
     d.K = s[i].K;
+    d.trans = trans;
     d.mt = (d.M + 15) / 16;
     d.kq = (d.K + 15) / 16;
     d.stage0 = stage;
@@ -50,6 +47,27 @@ void make_ops(int W, int pe, OpTable *t) {
     stage += d.nstages;
   }
   t->stages = stage;
+}
+
+void make_ops(int W, int pe, OpTable *t) {
+  const int nx = (kNG + kNS) * pe_blocks(pe), nb = kNL * pe_blocks(pe);
+  const OpSpec s[kNumOps] = {
+      {O_F1, L_F1, 0, W, nx},  {O_F2, L_F2, 0, W, W},   {O_F3, L_F3, 0, W, W},
+      {O_T1S, L_T1, nb, W, W}, {O_T1A, L_T1, 0, W, nb}, {O_T2, L_T2, 0, W, W},
+      {O_T3, L_T3, 0, W, W},   {O_B1S, L_B1, 0, W, W},  {O_B1T, L_B1, W, W, W},
+      {O_B2, L_B2, 0, W, W},   {O_B3, L_B3, 0, W, W},   {O_R1P, L_R1, 0, W, W},
+      {O_R1L, L_R1, W, W, 3},  {O_R2, L_R2, 0, W, W},   {O_R3, L_R3, 0, kNOUT, W}};
+  fill_table(W, pe, s, kNumOps, 0, t);
+}
+
+void make_bwd_ops(int W, int pe, OpTable *t) {
+  const int nb = kNL * pe_blocks(pe);
+  const OpSpec s[kNumBwdOps] = {
+      {O_R3T, L_R3, 0, W, kNOUT}, {O_R2T, L_R2, 0, W, W},  {O_R1T, L_R1, 0, W, W},
+      {O_B3T, L_B3, 0, W, W},     {O_B2T, L_B2, 0, W, W},  {O_B1ST, L_B1, 0, W, W},
+      {O_B1TT, L_B1, W, W, W},    {O_T3T, L_T3, 0, W, W},  {O_T2T, L_T2, 0, W, W},
+      {O_T1ST, L_T1, nb, W, W},   {O_F3T, L_F3, 0, W, W},  {O_F2T, L_F2, 0, W, W}};
+  fill_table(W, pe, s, kNumBwdOps, 1, t);
 }
 
 // One thread per 16 bytes of a fragment; then the biases.  Fragment f of a
@@ -70,7 +88,7 @@ __global__ __launch_bounds__(kThreads) void f32_pack_kernel(const float *__restr
   }
   const int stage = e / (kStageFrags * 64);
   int o = 0;
-  while (o + 1 < kNumOps && stage >= t.op[o + 1].stage0) ++o;
+  while (o + 1 < t.nops && stage >= t.op[o + 1].stage0) ++o;
   const OpDesc d = t.op[o];
   const int f = (e >> 6) - d.stage0 * kStageFrags, lane = e & 63;
   const int q = f / d.mt, mt = f % d.mt, i = lane & 15;
@@ -80,7 +98,9 @@ __global__ __launch_bounds__(kThreads) void f32_pack_kernel(const float *__restr
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int k = 16 * q + 4 * j + (lane >> 4);
-    if (m < d.M && k < d.K) v[j] = master[d.woff + (int64_t)m * d.ld + d.col0 + k];
+    if (m < d.M && k < d.K)
+      v[j] = d.trans ? master[d.woff + (int64_t)k * d.ld + d.col0 + m]
+                     : master[d.woff + (int64_t)m * d.ld + d.col0 + k];
   }
   ((f32x4 *)packed)[e] = v;
 }
@@ -107,23 +127,25 @@ struct FwdArgs {
   float *sig, *z, *cnt;
   int32_t fresh;             // the state holds no sum yet
   unsigned *amax;            // calibration: float bits of the largest z1
+  Planes pl;                 // SAVE: what the backward keeps of the slab
 };
 
-enum Mode { M_FULL, M_BEGIN, M_ACC, M_FINISH, M_CAL };
+enum Mode { M_FULL, M_BEGIN, M_ACC, M_FINISH, M_CAL, M_SAVE };
 
 template <int W, int MODE>
-__global__ __launch_bounds__(kThreads, W == 128 ? 2 : 3) void f32_forward_kernel(FwdArgs a) {
+__global__ __launch_bounds__(kThreads, W == 128 || MODE == M_SAVE ? 2 : 3) void
+f32_forward_kernel(FwdArgs a) {
   constexpr int MT = W / 16;
-  constexpr bool kTrunk = MODE == M_FULL || MODE == M_BEGIN || MODE == M_CAL;
-  constexpr bool kSlots = MODE == M_FULL || MODE == M_ACC || MODE == M_CAL;
-  constexpr bool kHead = MODE == M_FULL || MODE == M_FINISH;
+  constexpr bool kSave = MODE == M_SAVE;
+  constexpr bool kTrunk = MODE == M_FULL || MODE == M_BEGIN || MODE == M_CAL || kSave;
+  constexpr bool kSlots = MODE == M_FULL || MODE == M_ACC || MODE == M_CAL || kSave;
+  constexpr bool kHead = MODE == M_FULL || MODE == M_FINISH || kSave;
   // LDS: two stages | biases | sigma per wave | slot order per pixel
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   float *l_bias = (float *)(lds + 2 * kStageBytes);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   f32x4 *l_sig = (f32x4 *)(l_bias + kNumLayers * W) + wave * MT * 64 + lane;
-  uint8_t *l_perm = (uint8_t *)(l_bias + kNumLayers * W) + (kHead ? kWaves * MT * 1024 : 0) +
-                    (wave * 16 + col) * a.kpad;
+  uint8_t *l_order = (uint8_t *)(l_bias + kNumLayers * W) + (kHead ? kWaves * MT * 1024 : 0);
   {
     const float *b = (const float *)(a.packed + (size_t)a.bias_stage * kStageBytes);
     for (int i = threadIdx.x; i < kNumLayers * W; i += kThreads) l_bias[i] = b[i];
@@ -131,22 +153,44 @@ __global__ __launch_bounds__(kThreads, W == 128 ? 2 : 3) void f32_forward_kernel
   Pipe<MT> pipe;
   pipe.start(a.packed, lds, a.pg);
   __syncthreads();
-  auto bias = [&](int layer, int mt) { return *(const f32x4 *)(l_bias + layer * W + 16 * mt + 4 * g); };
-  // in = act(acc + bias)
-  auto next = [&](f32x4 (&in)[MT], f32x4 (&acc)[MT], int layer, bool relu) {
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const f32x4 v = acc[mt] + bias(layer, mt);
-      in[mt] = relu ? relu4(v) : v;
-      acc[mt] = zero4();
-    }
-  };
   const int hw = a.hw, nblk = pe_blocks(a.pe);
-  const int64_t ntiles = (a.npx + kTile - 1) / kTile;
+  const int64_t ntiles = kSave ? a.pl.np / kTile : (a.npx + kTile - 1) / kTile;
   float amax = 0.0f;
 
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const int64_t p = tile * kTile + wave * 16 + col;
+    // Opaque per-tile copies of the lane's place keep the compiler from holding
+    // every address derived from them in registers across the tile loop.
+    int g = lane >> 4, col = lane & 15;
+    asm volatile("" : "+v"(g), "+v"(col));
+    const int64_t pl = tile * kTile + wave * 16 + col;      // SAVE: pixel of the slab
+    const int64_t p = (kSave ? a.pl.p0 : 0) + pl;
+    uint8_t *l_perm = l_order + (wave * 16 + col) * a.kpad;
+    auto bias = [&](int layer, int mt) { return *(const f32x4 *)(l_bias + layer * W + 16 * mt + 4 * g); };
+    // in = act(acc + bias)
+    auto next = [&](f32x4 (&in)[MT], f32x4 (&acc)[MT], int layer, bool relu) {
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        const f32x4 v = acc[mt] + bias(layer, mt);
+        in[mt] = relu ? relu4(v) : v;
+        acc[mt] = zero4();
+      }
+    };
+    // SAVE: a block of W values per pixel, the signs of a ReLU's outputs
+    // (32-bit offsets from a uniform base: the caller bounds a slab's blocks)
+    const uint32_t at = (uint32_t)pl * (W * 4) + 16 * g;
+    auto save = [&](float *plane, const f32x4 (&v)[MT]) {
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) *(f32x4 *)((char *)plane + at + 64 * mt) = v[mt];
+    };
+    auto signs = [&](int layer, const f32x4 (&v)[MT], bool keep) {
+      uint32_t b = 0;
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) b |= v[mt][r] > 0.0f ? 1u << (4 * mt + r) : 0u;
+      uint32_t *words = a.pl.mask + (int64_t)layer * (a.pl.np / 16) * 64;
+      words[(uint32_t)(tile * kThreads) + threadIdx.x] = keep ? b : 0u;
+    };
     const bool valid = p < a.npx;
     const int64_t pc = valid ? p : a.npx - 1;      // tail lanes recompute a real pixel
     const int f = (int)(pc / hw), q = (int)(pc - (int64_t)f * hw);
@@ -172,13 +216,25 @@ __global__ __launch_bounds__(kThreads, W == 128 ? 2 : 3) void f32_forward_kernel
           const float raw = c < kNG ? G[(size_t)c * hw] : S[c - kNG];
           x[j] = b < nblk ? pe_value(raw, b) : 0.0f;
         }
+        if constexpr (kSave) *(f32x4 *)(a.pl.x + (uint32_t)pl * a.pl.nx + 16 * qq + 4 * g) = x;
         return x;
       });
       next(in, acc, L_F1, true);
+      if constexpr (kSave) {
+        for (int i = a.kq_x; i < a.pl.nx / 16; ++i)          // the block's padding
+          *(f32x4 *)(a.pl.x + (uint32_t)pl * a.pl.nx + 16 * i + 4 * g) = zero4();
+        save(a.pl.a1, in);
+        signs(K_A1, in, true);
+      }
       pipe.chain(acc, in);
       next(in, acc, L_F2, true);
+      if constexpr (kSave) {
+        save(a.pl.a2, in);
+        signs(K_A2, in, true);
+      }
       pipe.chain(acc, in);
       next(in, acc, L_F3, false);                  // sigma
+      if constexpr (kSave) save(a.pl.sig, in);
     }
     if constexpr (MODE == M_BEGIN) {
       if (valid)
@@ -229,8 +285,14 @@ __global__ __launch_bounds__(kThreads, W == 128 ? 2 : 3) void f32_forward_kernel
             const float r = c == 0 ? raw[0] : (c == 1 ? raw[1] : raw[2]);
             x[j] = b < nblk ? pe_value(r, b) : 0.0f;
           }
+          if constexpr (kSave)
+            *(f32x4 *)(a.pl.bi + i * a.pl.np * a.pl.nb + (uint32_t)pl * a.pl.nb + 16 * qq + 4 * g) = x;
           return x;
         });
+        if constexpr (kSave)
+          for (int j = a.kq_b; j < a.pl.nb / 16; ++j)
+            *(f32x4 *)(a.pl.bi + i * a.pl.np * a.pl.nb + (uint32_t)pl * a.pl.nb + 16 * j + 4 * g) =
+                zero4();
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
           in[mt] = relu4(acc[mt] + u[mt]);
@@ -242,10 +304,17 @@ __global__ __launch_bounds__(kThreads, W == 128 ? 2 : 3) void f32_forward_kernel
             for (int mt = 0; mt < MT; ++mt)
               amax = fmaxf(amax, fmaxf(fmaxf(in[mt][0], in[mt][1]), fmaxf(in[mt][2], in[mt][3])));
         } else {
+          if constexpr (kSave) {
+            save(a.pl.z1 + (int64_t)i * a.pl.np * W, in);
+            signs(kMasks + 2 * i, in, true);
+          }
           pipe.chain(acc, in);
 #pragma unroll
+          for (int mt = 0; mt < MT; ++mt) acc[mt] = acc[mt] + bias(L_T2, mt);
+          if constexpr (kSave) signs(kMasks + 2 * i + 1, acc, al > 0.0f);
+#pragma unroll
           for (int mt = 0; mt < MT; ++mt) {
-            Z[mt] += relu4(acc[mt] + bias(L_T2, mt)) * m;
+            Z[mt] += relu4(acc[mt]) * m;
             acc[mt] = zero4();
           }
           cnt += m;
@@ -274,6 +343,13 @@ __global__ __launch_bounds__(kThreads, W == 128 ? 2 : 3) void f32_forward_kernel
       const float bs = a.mean ? (cnt > 0.0f ? 1.0f : 0.0f) : cnt;
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) in[mt] = Z[mt] * inv;
+      if constexpr (kSave) {
+        save(a.pl.zs, in);
+        if (g == 0) {
+          a.pl.inv[pl] = inv;
+          a.pl.bs[pl] = bs;
+        }
+      }
       pipe.chain(acc, in);
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
@@ -282,24 +358,43 @@ __global__ __launch_bounds__(kThreads, W == 128 ? 2 : 3) void f32_forward_kernel
         for (int r = 0; r < 4; ++r) in[mt][r] = fmaf(b[r], bs, acc[mt][r]);
         acc[mt] = zero4();
       }
+      if constexpr (kSave) save(a.pl.tau, in);
       pipe.gather(acc, MT, [&](int qq) { return l_sig[qq * 64]; });
       pipe.chain(acc, in);
       next(in, acc, L_B1, true);
+      if constexpr (kSave) {
+        save(a.pl.d1, in);
+        signs(K_D1, in, true);
+      }
       pipe.chain(acc, in);
       next(in, acc, L_B2, true);
+      if constexpr (kSave) {
+        save(a.pl.d2, in);
+        signs(K_D2, in, true);
+      }
       pipe.chain(acc, in);
       next(in, acc, L_B3, false);                  // phi
+      if constexpr (kSave) save(a.pl.phi, in);
       const float ld = g < 3 ? G[(size_t)(11 + g) * hw] : 0.0f;
       pipe.chain(acc, in);
       pipe.gather(acc, 1, [&](int) { return f32x4{ld, 0.f, 0.f, 0.f}; });
       next(in, acc, L_R1, true);
+      if constexpr (kSave) {
+        save(a.pl.g1, in);
+        signs(K_G1, in, true);
+      }
       pipe.chain(acc, in);
       next(in, acc, L_R2, true);
-      const f32x4 y = pipe.tail(in);
-      if (valid && g == 0) {
-        float *o = a.out + (size_t)f * kNOUT * hw + q;
+      if constexpr (kSave) {
+        save(a.pl.g2, in);
+        signs(K_G2, in, true);
+      } else {
+        const f32x4 y = pipe.tail(in);
+        if (valid && g == 0) {
+          float *o = a.out + (size_t)f * kNOUT * hw + q;
 #pragma unroll
-        for (int c = 0; c < kNOUT; ++c) o[(size_t)c * hw] = y[c] + l_bias[L_R3 * W + c];
+          for (int c = 0; c < kNOUT; ++c) o[(size_t)c * hw] = y[c] + l_bias[L_R3 * W + c];
+        }
       }
     }
   }
@@ -312,14 +407,14 @@ __global__ __launch_bounds__(kThreads, W == 128 ? 2 : 3) void f32_forward_kernel
 
 template <int W, int MODE>
 static hipError_t launch_mode(const FwdArgs &a, int num_cus, hipStream_t s) {
-  constexpr bool kHead = MODE == M_FULL || MODE == M_FINISH;
+  constexpr bool kHead = MODE == M_FULL || MODE == M_FINISH || MODE == M_SAVE;
   const size_t lds = 2 * kStageBytes + sizeof(float) * kNumLayers * W +
                      (kHead ? (size_t)kWaves * (W / 16) * 1024 : 0) + (size_t)kTile * a.kpad;
   static const hipError_t attr =     // per process; the attribute is per function
       hipFuncSetAttribute((const void *)f32_forward_kernel<W, MODE>,
                           hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
   if (attr != hipSuccess) return attr;
-  const int64_t ntiles = (a.npx + kTile - 1) / kTile;
+  const int64_t ntiles = MODE == M_SAVE ? a.pl.np / kTile : (a.npx + kTile - 1) / kTile;
   // persistent: two workgroups per CU at W = 128, three at 64 (registers)
   const unsigned grid = (unsigned)std::min<int64_t>(ntiles, (W == 128 ? 2 : 3) * num_cus);
   hipLaunchKernelGGL((f32_forward_kernel<W, MODE>), dim3(grid), dim3(kThreads), lds, s, a);
@@ -334,6 +429,7 @@ static hipError_t launch(int W, int mode, const FwdArgs &a, int num_cus, hipStre
     case M_ACC: return GO(M_ACC);
     case M_FINISH: return GO(M_FINISH);
     case M_CAL: return GO(M_CAL);
+    case M_SAVE: return GO(M_SAVE);
   }
 #undef GO
   return hipErrorInvalidValue;
@@ -357,13 +453,15 @@ hipError_t gn_f32_pack(gn_handle *h, hipStream_t s) {
 }
 
 // The handle's packed fp32 weights: GN_FP32 handles pack them with every
-// upload; the others hold none until a calibration asks, and pack per call.
+// upload; the others hold none until a calibration or a backward asks, and
+// pack per call.
 static gn_status f32_weights(gn_handle *h, hipStream_t s) {
   if (h->cfg.precision == GN_FP32) return GN_OK;
   hipError_t e = hipSuccess;
   if (!h->d_f32) {
-    e = hipMalloc((void **)&h->d_f32, gn_f32_packed_bytes(h->W, h->pl.pe));
-    if (e != hipSuccess) h->d_f32 = nullptr;
+    const size_t bytes = gn_f32_packed_bytes(h->W, h->pl.pe);
+    e = hipMalloc((void **)&h->d_f32, bytes);
+    if (e == hipSuccess) h->bytes_held += bytes; else h->d_f32 = nullptr;
   }
   if (e == hipSuccess) e = gn_f32_pack(h, s);
   return gn_check_device(h, e, "fp32 weight packing");
@@ -372,23 +470,24 @@ static gn_status f32_weights(gn_handle *h, hipStream_t s) {
 static gn_status f32_run(gn_handle *h, const gn_frame *fr, int mode, f32::FwdArgs &a, bool canonical,
                          const char *what, hipStream_t s) {
   const int64_t npx = (int64_t)fr->n * fr->h * fr->w;
-  // the limit of the backward's workspace, kept for every fp32 call
-  if ((npx + 4095) / 4096 * 4096 > ((int64_t)3 << 20))
+  if ((npx + 4095) / 4096 * 4096 > gn_f32_max_px)
     return gn_set_error(GN_E_INVAL, "more than 3 * 2^20 pixels in one call");
-  const gn_status st = f32_weights(h, s);
+  // (a backward of several slabs packs once)
+  const gn_status st = mode == f32::M_SAVE && a.pl.p0 > 0 ? GN_OK : f32_weights(h, s);
   if (st != GN_OK) return st;
   f32::OpTable t;
   f32::make_ops(h->W, h->pl.pe, &t);
   auto first = [&](f32::Op o) { return t.op[o].stage0; };
-  const bool trunk = mode == f32::M_FULL || mode == f32::M_BEGIN || mode == f32::M_CAL;
-  const bool slots = mode == f32::M_FULL || mode == f32::M_ACC || mode == f32::M_CAL;
-  const bool head = mode == f32::M_FULL || mode == f32::M_FINISH;
+  const bool keep = mode == f32::M_SAVE;
+  const bool trunk = mode == f32::M_FULL || mode == f32::M_BEGIN || mode == f32::M_CAL || keep;
+  const bool slots = mode == f32::M_FULL || mode == f32::M_ACC || mode == f32::M_CAL || keep;
+  const bool head = mode == f32::M_FULL || mode == f32::M_FINISH || keep;
   a.pg.pre0 = trunk ? first(f32::O_F1) : first(f32::O_T1S);
   a.pg.pre1 = slots ? first(f32::O_T1A) : (trunk ? first(f32::O_T1S) : a.pg.pre0);
   a.pg.loop0 = first(f32::O_T1A);
   a.pg.loop1 = !slots ? a.pg.loop0 : (mode == f32::M_CAL ? first(f32::O_T2) : first(f32::O_T3));
   a.pg.post0 = first(f32::O_T3);
-  a.pg.post1 = head ? t.stages : a.pg.post0;
+  a.pg.post1 = !head ? a.pg.post0 : (keep ? first(f32::O_R3) : t.stages);
   a.pg.k = fr->k;
   a.packed = h->d_f32;
   a.bias_stage = t.stages;
@@ -417,6 +516,13 @@ gn_status gn_f32_calibrate(gn_handle *h, const gn_frame *frame, unsigned *amax, 
   f32::FwdArgs a{};
   a.amax = amax;
   return f32_run(h, frame, f32::M_CAL, a, false, "calibration", s);
+}
+
+// The backward's recompute of one slab.
+gn_status gn_f32_save(gn_handle *h, const gn_frame *frame, const f32::Planes &pl, hipStream_t s) {
+  f32::FwdArgs a{};
+  a.pl = pl;
+  return f32_run(h, frame, f32::M_SAVE, a, true, "backward recompute", s);
 }
 
 // Object streaming of GN_FP32 handles: the state holds sigma and the running

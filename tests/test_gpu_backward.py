@@ -97,6 +97,45 @@ def test_backward_matches_oracle(W, pool, k):
     log(f"  worst per-tensor relF {worst:.3e}, whole {relF(g, ref):.3e}")
 
 
+@pytest.mark.parametrize("W", [64, 128])
+@pytest.mark.parametrize("n,h,w_,k", [(1, 1, 1, 1), (1, 1, 31, 9), (1, 3, 11, 2), (2, 4, 8, 0),
+                                      (1, 5, 13, 5), (3, 1, 43, 3)])
+def test_backward_at_tile_edges(W, n, h, w_, k):
+    """Pixel counts around the 16-pixel waves, 32-pixel product steps and
+    64-pixel tiles, no slot, more slots than the canonical fast paths take."""
+    wts, fr, s = frame(n, h, w_, k, W, seed=300 + k)
+    dy = s["noise"].normal(size=(n, 3, h, w_)).astype(np.float32)
+    for pool in ("mean", "sum"):
+        d = dy * kink_free(wts, W, fr, pool)[:, None]
+        ref = oracle.grad_from_dy(wts, W, fr.gbuf, fr.layers, fr.scene, d, pool=pool)
+        with GlassNet(wts, W, k_max=16, pool=pool, precision="fp32") as net:
+            check(gpu_grad(net, fr, d), ref, W)
+
+
+def test_backward_over_two_slabs_is_the_sum_of_its_halves():
+    """64 slots on two frames of 131,072 pixels exceed one slab of the
+    workspace: the gradient of the pair equals the sum of the frames' own
+    gradients up to the fp32 rounding of sums over 2^18 pixels (1e-5 of the
+    norm, about 40 rounding steps of 2^-24 times the square root of the
+    cancellation between the pixels' random signs)."""
+    torch = torch_dev()
+    W, k, h, w_ = 128, 64, 256, 512
+    g = torch.Generator(device="cuda:0").manual_seed(5)
+    r = lambda *shape: torch.randn(shape, generator=g, device="cuda:0")  # noqa: E731
+    gb, L, sc, dy = r(2, 14, h, w_), r(2, k, 12, h, w_), r(2, 16), r(2, 3, h, w_)
+    with GlassNet(synth.make_weights(W, np.random.default_rng(1)), W, k_max=k,
+                  precision="fp32") as net:
+        both = net.backward(gb, L, sc, dy).double()
+        one = [net.backward(gb[i:i + 1], L[i:i + 1], sc[i:i + 1], dy[i:i + 1]).double()
+               for i in range(2)]
+        assert net.workspace_bytes() < (18 << 30)
+        err = float((both - one[0] - one[1]).norm() / both.norm())
+    log(f"  two slabs against their halves: {err:.2e}")
+    assert err <= 1e-5
+    del gb, L
+    torch.cuda.empty_cache()
+
+
 def test_backward_rejects_more_pixels_than_it_addresses():
     """One call covers at most 3 * 2^20 pixels; beyond that it is an argument
     error raised before any launch (buffers are real, so nothing could fault)."""
