@@ -13,11 +13,13 @@
 //
 // Weights.  They stream through LDS as a sequence of 16 KiB stages of
 // fragments (64 lanes x 16 bytes: four K-steps of one row tile), in the order
-// the kernel consumes them, double-buffered: while stage s computes, stage
-// s + 1 is written to LDS from registers and stage s + 2 is loaded into them.
-// Through registers rather than by direct global->LDS copies: the compiler
-// makes every LDS read wait for the direct copies in flight, which would put
-// a memory latency into every stage.
+// the kernel consumes them, through a ring of three buffers with one barrier
+// in the middle of each stage: past it every wave is done with the stage
+// before, whose buffer then takes the stage after the next one, and the next
+// stage's first fragments are read before this one ends, so no wave starts a
+// stage by waiting for LDS.  The stages go through registers rather than by
+// direct global->LDS copies: the compiler makes every LDS read wait for the
+// direct copies in flight, which would put a memory latency into every stage.
 #pragma once
 
 #include "gn_internal.h"
@@ -107,50 +109,49 @@ __device__ __forceinline__ float pe_value(float x, int b) {
 }
 
 // The stages one tile consumes: [pre0, pre1), then [loop0, loop1) k times,
-// then [post0, post1); the next tile starts over.
+// then [post0, post1) if post; the next tile starts over.  None is empty.
 struct Program {
-  int32_t pre0, pre1, loop0, loop1, post0, post1, k;
+  int32_t pre0, pre1, loop0, loop1, post0, post1, k, post;
 };
+
+// Weights are loaded through a buffer resource: one lane offset, the stage's
+// a scalar.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+__device__ __forceinline__ rsrc_t make_rsrc(const void *base) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, -1, 0x00020000);
+}
+
+constexpr int kRing = 3;
 
 template <int MT>
 struct Pipe {
   static constexpr int kQ = kStageFrags / MT;    // K groups per stage of a full map
-  const uint8_t *base;
-  uint8_t *lds;          // two stage buffers
+  rsrc_t base;
+  uint8_t *lds;          // kRing stage buffers
   Program pg;
-  int phase, pos, slot;  // the stage to load next
-  int par;               // buffer of the stage to consume next
-  f32x4 hold[4];         // the stage after it
+  int pos, end, range;   // the stage to load next, in which range of the program
+  int cur;               // buffer of the stage being consumed
+  f32x4 hold[4];         // the stage two ahead of it
+  f32x4 w[2][4];         // fragments; w[0]: the first of the stage to consume
 
-  // The next stage of the program (wave-uniform).
+  // The next stage of the program (wave-uniform, without branches: it is
+  // inlined into every stage, and the code has to fit the instruction cache).
   __device__ __forceinline__ int next() {
-    for (;;) {
-      if (phase == 0) {
-        if (pos < pg.pre1) break;
-        phase = 1;
-        slot = 0;
-        pos = pg.loop0;
-      }
-      if (phase == 1) {
-        if (pos < pg.loop1 && slot < pg.k) break;
-        if (slot + 1 < pg.k && pg.loop0 < pg.loop1) {
-          ++slot;
-          pos = pg.loop0;
-          break;
-        }
-        phase = 2;
-        pos = pg.post0;
-      }
-      if (pos < pg.post1) break;
-      phase = 0;
-      pos = pg.pre0;
-    }
-    return pos++;
+    const int at = pos++;
+    const bool turn = pos == end;
+    const int r = range == pg.k + pg.post ? 0 : range + 1;
+    const bool loop = r <= pg.k;
+    range = turn ? r : range;
+    pos = turn ? (r == 0 ? pg.pre0 : (loop ? pg.loop0 : pg.post0)) : pos;
+    end = turn ? (r == 0 ? pg.pre1 : (loop ? pg.loop1 : pg.post1)) : end;
+    return at;
   }
   __device__ __forceinline__ void load() {
-    const f32x4 *src = (const f32x4 *)(base + (size_t)next() * kStageBytes) + threadIdx.x;
+    const uint32_t at = (uint32_t)next() * kStageBytes;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) hold[i] = src[i * kThreads];
+    for (int i = 0; i < 4; ++i)
+      hold[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                              base, threadIdx.x * 16, at + i * kThreads * 16, 0));
   }
   __device__ __forceinline__ void store(int buf) {
     f32x4 *dst = (f32x4 *)(lds + buf * kStageBytes) + threadIdx.x;
@@ -158,28 +159,35 @@ struct Pipe {
     for (int i = 0; i < 4; ++i) dst[i * kThreads] = hold[i];
   }
   __device__ __forceinline__ void start(const uint8_t *b, uint8_t *l, const Program &p) {
-    base = b;
+    base = make_rsrc(b);
     lds = l;
     pg = p;
-    phase = 0;
     pos = p.pre0;
-    slot = 0;
-    par = 0;
+    end = p.pre1;
+    range = 0;
+    cur = 0;
     load();
     store(0);
     load();
+    store(1);
+    load();
+    __syncthreads();
+    fetch(w[0], 0, 0);
   }
-  // The fragments of the next stage.  Every wave has written its part of it
-  // and is done with the stage before, whose buffer takes the one after.
-  // (Only LDS traffic is drained: the loads and stores in flight stay so.)
-  __device__ __forceinline__ const f32x4 *begin() {
+  // Four fragments of a buffer.
+  __device__ __forceinline__ void fetch(f32x4 (&d)[4], int buf, int group) {
+    const f32x4 *s = (const f32x4 *)(lds + buf * kStageBytes) + (threadIdx.x & 63) + group * 256;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) d[m] = s[m * 64];
+  }
+  __device__ __forceinline__ int after(int buf) const { return buf == kRing - 1 ? 0 : buf + 1; }
+  // The middle of a stage.  Only LDS traffic is drained: the loads and stores
+  // in flight stay so.
+  __device__ __forceinline__ void middle() {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    store(par ^ 1);
+    store(cur == 0 ? kRing - 1 : cur - 1);
     load();
     __builtin_amdgcn_sched_barrier(0);
-    const f32x4 *s = (const f32x4 *)(lds + par * kStageBytes) + (threadIdx.x & 63);
-    par ^= 1;
-    return s;
   }
 
   // One stage: K groups q0 .. of a map of MT row tiles; group q0 + i is used
@@ -188,18 +196,14 @@ struct Pipe {
   // barrier keeps them there).
   template <class X>
   __device__ __forceinline__ void stage(f32x4 (&acc)[MT], int q0, int kq, X x) {
-    const f32x4 *s = begin();
-    f32x4 w[2][4], xv = zero4();
-#pragma unroll
-    for (int m = 0; m < 4; ++m) w[0][m] = s[m * 64];
+    f32x4 xv = zero4();
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       constexpr int kPer = MT / 4;               // fragment groups per K group
       const int q = q0 + i / kPer, m0 = 4 * (i % kPer);
-      if (i < 3) {
-#pragma unroll
-        for (int m = 0; m < 4; ++m) w[(i + 1) & 1][m] = s[(4 * (i + 1) + m) * 64];
-      }
+      if (i == 2) middle();
+      if (i < 3) fetch(w[(i + 1) & 1], cur, i + 1);
+      else fetch(w[0], after(cur), 0);
       __builtin_amdgcn_sched_barrier(0);
       if (q < kq) {
         if (i % kPer == 0) xv = x(i / kPer);
@@ -212,6 +216,7 @@ struct Pipe {
       }
       __builtin_amdgcn_sched_barrier(0);
     }
+    cur = after(cur);
   }
   // A map over W inputs held in registers, in[q] K group q.
   __device__ __forceinline__ void chain(f32x4 (&acc)[MT], const f32x4 (&in)[MT]) {
@@ -226,15 +231,16 @@ struct Pipe {
   }
   // A map of one row tile over W inputs in registers.
   __device__ __forceinline__ f32x4 tail(const f32x4 (&in)[MT]) {
-    const f32x4 *s = begin();
     f32x4 acc = zero4();
+    if (MT > 4) fetch(w[1], cur, 1);
+    middle();
 #pragma unroll
-    for (int q = 0; q < MT; ++q) {
-      const f32x4 w = s[q * 64];
+    for (int q = 0; q < MT; ++q)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[j], in[q][j], acc, 0, 0, 0);
-    }
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[q >> 2][q & 3][j], in[q][j], acc, 0, 0, 0);
+    cur = after(cur);
+    fetch(w[0], cur, 0);
     return acc;
   }
 };

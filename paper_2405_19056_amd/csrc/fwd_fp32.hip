@@ -132,7 +132,9 @@ struct FwdArgs {
 
 enum Mode { M_FULL, M_BEGIN, M_ACC, M_FINISH, M_CAL, M_SAVE };
 
-template <int W, int MODE>
+// ENC: with positional encoding (a form of its own: the sine and cosine's code
+// and registers stay out of the plain one).
+template <int W, int MODE, bool ENC>
 __global__ __launch_bounds__(kThreads, W == 128 || MODE == M_SAVE ? 2 : 3) void
 f32_forward_kernel(FwdArgs a) {
   constexpr int MT = W / 16;
@@ -140,30 +142,78 @@ f32_forward_kernel(FwdArgs a) {
   constexpr bool kTrunk = MODE == M_FULL || MODE == M_BEGIN || MODE == M_CAL || kSave;
   constexpr bool kSlots = MODE == M_FULL || MODE == M_ACC || MODE == M_CAL || kSave;
   constexpr bool kHead = MODE == M_FULL || MODE == M_FINISH || kSave;
-  // LDS: two stages | biases | sigma per wave | slot order per pixel
+  // LDS: the stage ring | biases | sigma per wave | slot order per pixel.
+  // At W = 128 two workgroups leave room for six of sigma's eight row tiles;
+  // the last two stay in registers.  (SAVE reads it back from its plane.)
+  constexpr int kSigLds = MT < 6 ? MT : 6;
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
-  float *l_bias = (float *)(lds + 2 * kStageBytes);
+  float *l_bias = (float *)(lds + kRing * kStageBytes);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  f32x4 *l_sig = (f32x4 *)(l_bias + kNumLayers * W) + wave * MT * 64 + lane;
-  uint8_t *l_order = (uint8_t *)(l_bias + kNumLayers * W) + (kHead ? kWaves * MT * 1024 : 0);
+  f32x4 *l_sig = (f32x4 *)(l_bias + kNumLayers * W) + wave * kSigLds * 64 + lane;
+  uint8_t *l_order = (uint8_t *)(l_bias + kNumLayers * W) + (kHead && !kSave ? kWaves * kSigLds * 1024 : 0);
   {
     const float *b = (const float *)(a.packed + (size_t)a.bias_stage * kStageBytes);
     for (int i = threadIdx.x; i < kNumLayers * W; i += kThreads) l_bias[i] = b[i];
   }
   Pipe<MT> pipe;
-  pipe.start(a.packed, lds, a.pg);
-  __syncthreads();
-  const int hw = a.hw, nblk = pe_blocks(a.pe);
+  pipe.start(a.packed, lds, a.pg);       // ends with a barrier
+  const int hw = a.hw, nblk = ENC ? pe_blocks(a.pe) : 1;
   const int64_t ntiles = kSave ? a.pl.np / kTile : (a.npx + kTile - 1) / kTile;
   float amax = 0.0f;
+
+  // A lane's pixel of a tile (tail lanes recompute a real pixel), and the
+  // first loads it waits for: the inputs of F1 (without encoding) and the
+  // alphas its slots are ranked by (up to kFastK slots).  FULL and SAVE issue
+  // them a tile ahead, in the head, where u and Z have left their registers.
+  constexpr bool kAhead = kTrunk && kHead && !kSave;
+  constexpr int kFastK = 8;
+  struct Pixel {
+    int64_t p;
+    int f, q;
+    bool valid;
+  };
+  auto locate = [&](int64_t tile, int col) {
+    Pixel x;
+    x.p = (kSave ? a.pl.p0 : 0) + tile * kTile + wave * 16 + col;
+    x.valid = x.p < a.npx;
+    const int64_t pc = x.valid ? x.p : a.npx - 1;
+    x.f = (int)(pc / hw);
+    x.q = (int)(pc - (int64_t)x.f * hw);
+    return x;
+  };
+  const bool fast = kSlots && a.canon && a.k <= kFastK;
+  auto first_loads = [&](const Pixel &x, int g, f32x4 (&xr)[2], float (&al)[kFastK]) {
+    if constexpr (kTrunk && !ENC) {
+      const float *G = a.gbuf + (size_t)x.f * kNG * hw + x.q, *S = a.scene + (size_t)x.f * kNS;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int c = 4 * i + g;
+        xr[i >> 2][i & 3] =
+            c < kNG ? G[(size_t)c * hw] : (c < kNG + kNS ? S[c - kNG] : 0.0f);
+      }
+    }
+    if (fast) {
+      const float *L = a.layers + (size_t)x.f * a.k * kNL * hw + x.q;
+#pragma unroll
+      for (int j = 0; j < kFastK; ++j) al[j] = j < a.k ? L[((size_t)j * kNL + kAlpha) * hw] : 0.0f;
+    }
+  };
+  Pixel nx = locate(blockIdx.x, lane & 15);
+  f32x4 xr[2];
+  float alk[kFastK];
+  if constexpr (kAhead) first_loads(nx, lane >> 4, xr, alk);
 
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     // Opaque per-tile copies of the lane's place keep the compiler from holding
     // every address derived from them in registers across the tile loop.
     int g = lane >> 4, col = lane & 15;
     asm volatile("" : "+v"(g), "+v"(col));
-    const int64_t pl = tile * kTile + wave * 16 + col;      // SAVE: pixel of the slab
-    const int64_t p = (kSave ? a.pl.p0 : 0) + pl;
+    const Pixel px = kAhead ? nx : locate(tile, col);
+    if constexpr (!kAhead) first_loads(px, g, xr, alk);
+    const int64_t pl = tile * kTile + wave * 16 + col, p = px.p;      // pl: pixel of a SAVE's slab
+    const bool valid = px.valid;
+    const int64_t pc = valid ? p : a.npx - 1;
+    const int f = px.f, q = px.q;
     uint8_t *l_perm = l_order + (wave * 16 + col) * a.kpad;
     auto bias = [&](int layer, int mt) { return *(const f32x4 *)(l_bias + layer * W + 16 * mt + 4 * g); };
     // in = act(acc + bias)
@@ -185,15 +235,14 @@ f32_forward_kernel(FwdArgs a) {
     auto signs = [&](int layer, const f32x4 (&v)[MT], bool keep) {
       uint32_t b = 0;
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
+      for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) b |= v[mt][r] > 0.0f ? 1u << (4 * mt + r) : 0u;
+        asm volatile("" : "+v"(b));
+      }
       uint32_t *words = a.pl.mask + (int64_t)layer * (a.pl.np / 16) * 64;
       words[(uint32_t)(tile * kThreads) + threadIdx.x] = keep ? b : 0u;
     };
-    const bool valid = p < a.npx;
-    const int64_t pc = valid ? p : a.npx - 1;      // tail lanes recompute a real pixel
-    const int f = (int)(pc / hw), q = (int)(pc - (int64_t)f * hw);
     const float *G = a.gbuf + (size_t)f * kNG * hw + q;
     const float *L = a.layers + (size_t)f * a.k * kNL * hw + q;
     const float *S = a.scene + (size_t)f * kNS;
@@ -201,28 +250,66 @@ f32_forward_kernel(FwdArgs a) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt] = zero4();
 
-    // the pixel's slots in canonical order: lane group g ranks slots g, g + 4, ...
-    // (read back by the same wave)
-    if (kSlots && a.canon)
-      for (int i = g; i < a.k; i += 4) l_perm[slot_rank(L, (size_t)hw, a.k, i)] = (uint8_t)i;
+    // The pixel's slots in canonical order: lane group g ranks slots g, g + 4,
+    // ... (read back by the same wave).  Keys: the bits of alpha for active
+    // slots, above them the inactive ones by index; equal alphas (and more
+    // than kFastK slots) take the full comparison.
+    if (kSlots && a.canon) {
+      if (fast) {
+        uint32_t key[kFastK];
+#pragma unroll
+        for (int j = 0; j < kFastK; ++j)
+          key[j] = j >= a.k ? 0xFFFFFFFFu
+                            : (alk[j] > 0.0f ? __float_as_uint(alk[j]) : 0xFFFFFF00u + j);
+#pragma unroll
+        for (int h = 0; h < kFastK; h += 4) {
+          const uint32_t ki = g < 2 ? (g == 0 ? key[h] : key[h + 1]) : (g == 2 ? key[h + 2] : key[h + 3]);
+          int lt = 0, le = 0;
+#pragma unroll
+          for (int j = 0; j < kFastK; ++j) {
+            lt += key[j] < ki ? 1 : 0;
+            le += key[j] <= ki ? 1 : 0;
+          }
+          const int i = h + g;
+          if (i < a.k) l_perm[le == lt + 1 ? lt : slot_rank(L, (size_t)hw, a.k, i)] = (uint8_t)i;
+        }
+      } else {
+        for (int i = g; i < a.k; i += 4) l_perm[slot_rank(L, (size_t)hw, a.k, i)] = (uint8_t)i;
+      }
+    }
+    // A slot's raw channels g, 4 + g, 8 + g and its alpha.
+    auto load = [&](int i, float (&r)[3], float &alpha) {
+      const int slot = a.canon ? (int)l_perm[i] : i;
+      const float *Li = L + (size_t)slot * kNL * hw;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) r[j] = Li[(size_t)(4 * j + g) * hw];
+      alpha = Li[(size_t)kAlpha * hw];
+    };
+    float raw[3] = {0.f, 0.f, 0.f}, al = 0.0f;
+    if (kSlots && a.k > 0) load(0, raw, al);
 
     if constexpr (kTrunk) {
       // F on the (encoded) [G; s]: input k is channel k % 30 of block k / 30
-      pipe.gather(acc, a.kq_x, [&](int qq) {
+      pipe.gather(acc, ENC ? a.kq_x : 2, [&](int qq) {
         f32x4 x;
+        if constexpr (!ENC) {
+          x = qq == 0 ? xr[0] : xr[1];
+        } else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int k = 16 * qq + 4 * j + g, b = k / (kNG + kNS), c = k - b * (kNG + kNS);
-          const float raw = c < kNG ? G[(size_t)c * hw] : S[c - kNG];
-          x[j] = b < nblk ? pe_value(raw, b) : 0.0f;
+          for (int j = 0; j < 4; ++j) {
+            const int k = 16 * qq + 4 * j + g, b = k / (kNG + kNS), c = k - b * (kNG + kNS);
+            const float raw = c < kNG ? G[(size_t)c * hw] : S[c - kNG];
+            x[j] = b < nblk ? pe_value(raw, b) : 0.0f;
+          }
         }
         if constexpr (kSave) *(f32x4 *)(a.pl.x + (uint32_t)pl * a.pl.nx + 16 * qq + 4 * g) = x;
         return x;
       });
       next(in, acc, L_F1, true);
       if constexpr (kSave) {
-        for (int i = a.kq_x; i < a.pl.nx / 16; ++i)          // the block's padding
-          *(f32x4 *)(a.pl.x + (uint32_t)pl * a.pl.nx + 16 * i + 4 * g) = zero4();
+        if constexpr (ENC)                                   // the block's padding
+          for (int i = a.kq_x; i < a.pl.nx / 16; ++i)
+            *(f32x4 *)(a.pl.x + (uint32_t)pl * a.pl.nx + 16 * i + 4 * g) = zero4();
         save(a.pl.a1, in);
         signs(K_A1, in, true);
       }
@@ -246,9 +333,12 @@ f32_forward_kernel(FwdArgs a) {
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) in[mt] = *(const f32x4 *)(a.sig + pc * W + 16 * mt + 4 * g);
     }
-    if constexpr (kHead) {
+    f32x4 sig[MT - kSigLds + 1];
+    if constexpr (kHead && !kSave) {
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) l_sig[mt * 64] = in[mt];
+      for (int mt = 0; mt < MT; ++mt)
+        if (mt < kSigLds) l_sig[mt * 64] = in[mt];
+        else sig[mt - kSigLds] = in[mt];
     }
     float cnt = 0.0f;
     if constexpr (kSlots) {
@@ -261,35 +351,27 @@ f32_forward_kernel(FwdArgs a) {
         Z[mt] = MODE == M_ACC && !a.fresh ? *(const f32x4 *)(a.z + pc * W + 16 * mt + 4 * g) : zero4();
       }
       // per slot: z1 = relu(W_T1,b b_i + u), Z += m_i relu(W_T2 z1 + b_T2).
-      // Lane group g holds raw channels g, 4 + g, 8 + g of the slot, the
-      // inputs of K-steps 0..2 of every encoding block (12 channels, three
-      // steps).
-      float raw[3], al = 0.0f;
-      auto load = [&](int i, float (&r)[3], float &alpha) {
-        const int slot = a.canon ? (int)l_perm[i] : i;
-        const float *Li = L + (size_t)slot * kNL * hw;
-#pragma unroll
-        for (int j = 0; j < 3; ++j) r[j] = Li[(size_t)(4 * j + g) * hw];
-        alpha = Li[(size_t)kAlpha * hw];
-      };
-      if (a.k > 0) load(0, raw, al);
+      // Lane group g's raw channels are the inputs of K-steps 0..2 of every
+      // encoding block (12 channels, three steps).
       for (int i = 0; i < a.k; ++i) {
         float rn[3] = {0.f, 0.f, 0.f}, an = 0.0f;
         if (i + 1 < a.k) load(i + 1, rn, an);
         const float m = al > 0.0f ? 1.0f : 0.0f;
-        pipe.gather(acc, a.kq_b, [&](int qq) {
-          f32x4 x;
+        pipe.gather(acc, ENC ? a.kq_b : 1, [&](int qq) {
+          f32x4 x = {raw[0], raw[1], raw[2], 0.0f};
+          if constexpr (ENC) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int s = 4 * qq + j, b = s / 3, c = s - 3 * b;
-            const float r = c == 0 ? raw[0] : (c == 1 ? raw[1] : raw[2]);
-            x[j] = b < nblk ? pe_value(r, b) : 0.0f;
+            for (int j = 0; j < 4; ++j) {
+              const int s = 4 * qq + j, b = s / 3, c = s - 3 * b;
+              const float r = c == 0 ? raw[0] : (c == 1 ? raw[1] : raw[2]);
+              x[j] = b < nblk ? pe_value(r, b) : 0.0f;
+            }
           }
           if constexpr (kSave)
             *(f32x4 *)(a.pl.bi + i * a.pl.np * a.pl.nb + (uint32_t)pl * a.pl.nb + 16 * qq + 4 * g) = x;
           return x;
         });
-        if constexpr (kSave)
+        if constexpr (kSave && ENC)                          // the block's padding
           for (int j = a.kq_b; j < a.pl.nb / 16; ++j)
             *(f32x4 *)(a.pl.bi + i * a.pl.np * a.pl.nb + (uint32_t)pl * a.pl.nb + 16 * j + 4 * g) =
                 zero4();
@@ -338,6 +420,11 @@ f32_forward_kernel(FwdArgs a) {
         Z[mt] = a.fresh ? zero4() : *(const f32x4 *)(a.z + pc * W + 16 * mt + 4 * g);
     }
     if constexpr (kHead) {
+      const float ld = g < 3 ? G[(size_t)(11 + g) * hw] : 0.0f;
+      if constexpr (kAhead) {
+        nx = locate(std::min<int64_t>(tile + gridDim.x, ntiles - 1), col);
+        first_loads(nx, g, xr, alk);
+      }
       // the pool, T3 (tau), B on [sigma; tau], R on [phi; L_d]
       const float inv = a.mean ? 1.0f / fmaxf(cnt, 1.0f) : 1.0f;
       const float bs = a.mean ? (cnt > 0.0f ? 1.0f : 0.0f) : cnt;
@@ -359,7 +446,14 @@ f32_forward_kernel(FwdArgs a) {
         acc[mt] = zero4();
       }
       if constexpr (kSave) save(a.pl.tau, in);
-      pipe.gather(acc, MT, [&](int qq) { return l_sig[qq * 64]; });
+      {
+        f32x4 s[MT];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+          s[mt] = kSave ? *(const f32x4 *)((const char *)a.pl.sig + at + 64 * mt)
+                        : (mt < kSigLds ? l_sig[mt * 64] : sig[mt - kSigLds]);
+        pipe.chain(acc, s);
+      }
       pipe.chain(acc, in);
       next(in, acc, L_B1, true);
       if constexpr (kSave) {
@@ -375,7 +469,6 @@ f32_forward_kernel(FwdArgs a) {
       pipe.chain(acc, in);
       next(in, acc, L_B3, false);                  // phi
       if constexpr (kSave) save(a.pl.phi, in);
-      const float ld = g < 3 ? G[(size_t)(11 + g) * hw] : 0.0f;
       pipe.chain(acc, in);
       pipe.gather(acc, 1, [&](int) { return f32x4{ld, 0.f, 0.f, 0.f}; });
       next(in, acc, L_R1, true);
@@ -405,24 +498,28 @@ f32_forward_kernel(FwdArgs a) {
   }
 }
 
-template <int W, int MODE>
+template <int W, int MODE, bool ENC>
 static hipError_t launch_mode(const FwdArgs &a, int num_cus, hipStream_t s) {
-  constexpr bool kHead = MODE == M_FULL || MODE == M_FINISH || MODE == M_SAVE;
-  const size_t lds = 2 * kStageBytes + sizeof(float) * kNumLayers * W +
-                     (kHead ? (size_t)kWaves * (W / 16) * 1024 : 0) + (size_t)kTile * a.kpad;
+  constexpr bool kSig = MODE == M_FULL || MODE == M_FINISH;
+  const size_t lds = kRing * kStageBytes + sizeof(float) * kNumLayers * W +
+                     (kSig ? (size_t)kWaves * std::min(W / 16, 6) * 1024 : 0) + (size_t)kTile * a.kpad;
   static const hipError_t attr =     // per process; the attribute is per function
-      hipFuncSetAttribute((const void *)f32_forward_kernel<W, MODE>,
-                          hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+      hipFuncSetAttribute((const void *)f32_forward_kernel<W, MODE, ENC>,
+                          hipFuncAttributeMaxDynamicSharedMemorySize, 84 * 1024);
   if (attr != hipSuccess) return attr;
   const int64_t ntiles = MODE == M_SAVE ? a.pl.np / kTile : (a.npx + kTile - 1) / kTile;
   // persistent: two workgroups per CU at W = 128, three at 64 (registers)
   const unsigned grid = (unsigned)std::min<int64_t>(ntiles, (W == 128 ? 2 : 3) * num_cus);
-  hipLaunchKernelGGL((f32_forward_kernel<W, MODE>), dim3(grid), dim3(kThreads), lds, s, a);
+  hipLaunchKernelGGL((f32_forward_kernel<W, MODE, ENC>), dim3(grid), dim3(kThreads), lds, s, a);
   return hipGetLastError();
 }
 
 static hipError_t launch(int W, int mode, const FwdArgs &a, int num_cus, hipStream_t s) {
-#define GO(M) (W == 128 ? launch_mode<128, M>(a, num_cus, s) : launch_mode<64, M>(a, num_cus, s))
+#define GO(M)                                                                          \
+  (a.pe > 0 ? (W == 128 ? launch_mode<128, M, true>(a, num_cus, s)                     \
+                        : launch_mode<64, M, true>(a, num_cus, s))                     \
+            : (W == 128 ? launch_mode<128, M, false>(a, num_cus, s)                    \
+                        : launch_mode<64, M, false>(a, num_cus, s)))
   switch (mode) {
     case M_FULL: return GO(M_FULL);
     case M_BEGIN: return GO(M_BEGIN);
@@ -482,20 +579,23 @@ static gn_status f32_run(gn_handle *h, const gn_frame *fr, int mode, f32::FwdArg
   const bool trunk = mode == f32::M_FULL || mode == f32::M_BEGIN || mode == f32::M_CAL || keep;
   const bool slots = mode == f32::M_FULL || mode == f32::M_ACC || mode == f32::M_CAL || keep;
   const bool head = mode == f32::M_FULL || mode == f32::M_FINISH || keep;
-  a.pg.pre0 = trunk ? first(f32::O_F1) : first(f32::O_T1S);
-  a.pg.pre1 = slots ? first(f32::O_T1A) : (trunk ? first(f32::O_T1S) : a.pg.pre0);
+  // (an ACC call starts with T1's sigma part, a FINISH call with T3)
+  const int k = slots ? fr->k : 0;
+  a.pg.pre0 = trunk ? first(f32::O_F1) : first(slots ? f32::O_T1S : f32::O_T3);
+  a.pg.pre1 = slots ? first(f32::O_T1A) : (trunk ? first(f32::O_T1S) : t.stages);
   a.pg.loop0 = first(f32::O_T1A);
-  a.pg.loop1 = !slots ? a.pg.loop0 : (mode == f32::M_CAL ? first(f32::O_T2) : first(f32::O_T3));
+  a.pg.loop1 = first(mode == f32::M_CAL ? f32::O_T2 : f32::O_T3);
   a.pg.post0 = first(f32::O_T3);
-  a.pg.post1 = !head ? a.pg.post0 : (keep ? first(f32::O_R3) : t.stages);
-  a.pg.k = fr->k;
+  a.pg.post1 = keep ? first(f32::O_R3) : t.stages;
+  a.pg.k = k;
+  a.pg.post = slots && head ? 1 : 0;
   a.packed = h->d_f32;
   a.bias_stage = t.stages;
   a.gbuf = fr->gbuf;
   a.layers = fr->layers;
   a.scene = fr->scene;
   a.hw = fr->h * fr->w;
-  a.k = slots ? fr->k : 0;
+  a.k = k;
   a.mean = h->cfg.pool == GN_POOL_MEAN ? 1 : 0;
   a.pe = h->pl.pe;
   a.canon = canonical && gn_slot_kmax(h) > 1 && fr->k > 1 ? 1 : 0;
