@@ -177,7 +177,7 @@ constexpr int kMaxJobs = 20;
 struct DwArgs {
   DwJob job[kMaxJobs];
   int32_t njobs, per, accumulate;
-  int64_t np, steps;         // pixels; steps per slot (the first slab's: a shorter one skips)
+  int64_t np, steps;         // pixels; steps per slot (the first slab's)
   float *part;
 };
 constexpr int kStep = 32;
@@ -188,8 +188,8 @@ constexpr int part_floats(int W, int MI) { return W * 16 * MI + W + 16 * MI; }
 // narrow one.  Each 32-pixel step of both blocks is loaded to registers while
 // the step before computes, then written to LDS; row p of a block keeps its
 // 16-byte unit c at c ^ swz(p), so that the four pixels that the lane groups
-// read fall into distinct banks.  What bounds it: at W = 128 a step's 32 KB
-// take as long at the HBM's rate as its 16 x 8 MFMAs per wave at theirs.
+// read fall into distinct banks.  A step is one 32-deep group of the bf16 matrix
+// cores on operands split in three (fp32_core.h).
 template <int W, int MI>
 __global__ __launch_bounds__(kThreads, 2) void f32_dw_kernel(DwArgs a) {
   constexpr int MO = W / 16;
@@ -210,18 +210,19 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dw_kernel(DwArgs a) {
   for (int j = 0; j < a.njobs; ++j) {
     const DwJob &job = a.job[j];
     const int64_t jend = first + job.slots * a.steps;
-    const int64_t s0 = std::max(step, first) - first, s1 = std::min(end, jend) - first;
+    // (a short last slab ends its jobs early: its partials are complete)
+    const int64_t s0 = std::max(step, first) - first;
+    const int64_t s1 = std::min(std::min(end, jend) - first, job.slots * (a.np / kStep));
     first = jend;
     if (s0 >= s1) continue;
     f32x4 hd[ND], ha[NA];
     uint32_t hm[ND];
     float hw = 1.0f;
-    bool live = false;
     auto load = [&](int64_t s) {
       s = std::min(s, s1 - 1);
-      const int64_t slot = s / a.steps, px = (s - slot * a.steps) * kStep;
-      live = px < a.np;                                      // a short last slab
-      if (!live) return;
+      // pixels first, a pixel block's slots in turn (dZ, the same for all of
+      // them, then comes from L2)
+      const int64_t ps = s / job.slots, slot = s - ps * job.slots, px = ps * kStep;
       const float *D = job.D + slot * job.dslot + px * W;
       const float *A = job.A + slot * job.aslot + px * job.lda;
 #pragma unroll
@@ -245,7 +246,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dw_kernel(DwArgs a) {
 #pragma unroll
       for (int i = 0; i < ND; ++i) {
         const int e = tid + i * kThreads, p = e / DU, u = e % DU;
-        f32x4 v = live ? hd[i] : zero4();
+        f32x4 v = hd[i];
         if (job.mask) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) v[r] = hm[i] & (1u << r) ? v[r] : 0.0f;
@@ -256,7 +257,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dw_kernel(DwArgs a) {
       for (int i = 0; i < NA; ++i) {
         const int e = tid + i * kThreads, p = e / AU, u = e % AU;
         if (kStep * AU % kThreads == 0 || e < kStep * AU)
-          la[b][p * AU + (u ^ aswz(p))] = live ? ha[i] : zero4();
+          la[b][p * AU + (u ^ aswz(p))] = ha[i];
       }
       if (tid < kStep) lw[b][tid] = hw;
     };
@@ -282,26 +283,34 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dw_kernel(DwArgs a) {
       load(s + 2);
       __builtin_amdgcn_sched_barrier(0);
       const float *D = (const float *)ld[b], *A = (const float *)la[b];
+      // a lane's eight pixels of a row: 4 t + g (dswz(p) = 4 g for each)
+      float w8[8];
 #pragma unroll
-      for (int t = 0; t < kStep / 4; ++t) {
-        const int p = 4 * t + g;                 // dswz(p) = 4 g for every t
-        float d[TO], x[TI];
+      for (int t = 0; t < 8; ++t) w8[t] = lw[b][4 * t + g];
+      Split d[TO];
 #pragma unroll
-        for (int o = 0; o < TO; ++o)
-          d[o] = D[p * W + ((4 * (wr * TO + o)) ^ dswz(p)) * 4 + l];
+      for (int o = 0; o < TO; ++o) {
+        float v[8];
 #pragma unroll
-        for (int i = 0; i < TI; ++i)
-          x[i] = A[p * 16 * MI + ((4 * (wc * TI + i)) ^ aswz(p)) * 4 + l];
+        for (int t = 0; t < 8; ++t) {
+          const int p = 4 * t + g;
+          v[t] = D[p * W + ((4 * (wr * TO + o)) ^ dswz(p)) * 4 + l];
+          if (wc == 0) dsum[o] = fmaf(v[t], w8[t], dsum[o]);
+        }
+        d[o] = split8(v);
+      }
 #pragma unroll
-        for (int o = 0; o < TO; ++o)
+      for (int i = 0; i < TI; ++i) {
+        float v[8];
 #pragma unroll
-          for (int i = 0; i < TI; ++i)
-            acc[o][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[o], x[i], acc[o][i], 0, 0, 0);
-        const float w = lw[b][p];
+        for (int t = 0; t < 8; ++t) {
+          const int p = 4 * t + g;
+          v[t] = A[p * 16 * MI + ((4 * (wc * TI + i)) ^ aswz(p)) * 4 + l];
+          if (!kSquare) asum[i] += v[t];
+        }
+        const Split x = split8(v);
 #pragma unroll
-        for (int o = 0; o < TO; ++o) dsum[o] = fmaf(d[o], w, dsum[o]);
-#pragma unroll
-        for (int i = 0; i < TI; ++i) asum[i] += x[i];
+        for (int o = 0; o < TO; ++o) acc[o][i] = mma_split(d[o], x, acc[o][i]);
       }
     }
     float *P = a.part + (size_t)(blockIdx.x + j) * part_floats(W, MI);

@@ -99,6 +99,62 @@ __device__ __forceinline__ f32x4 relu4(f32x4 v) {
   return f32x4{fmaxf(v[0], 0.f), fmaxf(v[1], 0.f), fmaxf(v[2], 0.f), fmaxf(v[3], 0.f)};
 }
 
+// fp32 operands of the bf16 matrix cores: x = hi + mid + lo in bf16, each the
+// rounding of what the ones before leave (24 bits: exact but for the last
+// bits of the smallest magnitudes).  A product takes the six partial products
+// down to 2^-16 of the first; the three left out are below 2^-25 of it, under
+// fp32's own rounding.  Six 16-cycle instructions replace eight 32-cycle ones.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+struct Split {
+  u32x4 hi, mid, lo;
+};
+
+__device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+__device__ __forceinline__ float bf16_lo(uint32_t v) { return __uint_as_float(v << 16); }
+__device__ __forceinline__ float bf16_hi(uint32_t v) { return __uint_as_float(v & 0xFFFF0000u); }
+
+// An infinite x keeps its infinite hi: what is left of it (inf - inf) becomes
+// a finite value instead of a NaN.
+__device__ __forceinline__ float left_of(float x, float h) {
+  return __builtin_amdgcn_fmed3f(x - h, -6.7e35f, 6.7e35f);
+}
+
+__device__ __forceinline__ Split split8(const float (&x)[8]) {
+  Split s;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float a = x[2 * i], b = x[2 * i + 1];
+    const uint32_t h = pk_bf16(a, b);
+    const float ra = left_of(a, bf16_lo(h)), rb = left_of(b, bf16_hi(h));
+    const uint32_t m = pk_bf16(ra, rb);
+    s.hi[i] = h;
+    s.mid[i] = m;
+    s.lo[i] = pk_bf16(ra - bf16_lo(m), rb - bf16_hi(m));
+  }
+  return s;
+}
+
+__device__ __forceinline__ f32x4 mma_bf16(u32x4 a, u32x4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// c + a b, the small partial products first.
+__device__ __forceinline__ f32x4 mma_split(const Split &a, const Split &b, f32x4 c) {
+  c = mma_bf16(a.lo, b.hi, c);
+  c = mma_bf16(a.hi, b.lo, c);
+  c = mma_bf16(a.mid, b.mid, c);
+  c = mma_bf16(a.mid, b.hi, c);
+  c = mma_bf16(a.hi, b.mid, c);
+  return mma_bf16(a.hi, b.hi, c);
+}
+
 // Positional-encoding block b of x (Sec. 3.4): x for b = 0, then
 // sin(2^k pi x) for b = 2k + 1 and cos(2^k pi x) for b = 2k + 2 (sinpi and
 // cospi reduce the argument exactly; the scaling by 2^k is exact).
