@@ -2,18 +2,41 @@
 // trains the four networks jointly, end to end).
 //
 // Per slab of pixels:
-//   1. recompute (fwd_fp32.hip, SAVE): every activation a weight gradient
-//      needs, and the sign of every ReLU as one bit.
+//   1. recompute: the forward on v_mfma_f32_16x16x4f32, every activation a
+//      weight gradient needs written as it passes, and the sign of every ReLU
+//      as one bit.  It stays on the fp32 instruction, each sum over its
+//      inputs in natural order: a pre-activation within a rounding of zero
+//      takes the branch it has always taken, whatever the forward's form.
 //   2. deltas: one kernel chains the transposed maps in registers from dL/dy
-//      to F's first layer (fp32_core.h), the slots in between: dz2 = [z2 > 0]
-//      m_i dZ is a selection of dZ's registers, dz1 = [z1 > 0] W_T2^T dz2,
-//      du = sum dz1.  The ReLU derivatives are the stored bits.
+//      to F's first layer, the slots in between: dz2 = [z2 > 0] m_i dZ is a
+//      selection of dZ's registers, dz1 = [z1 > 0] W_T2^T dz2, du = sum dz1.
+//      The ReLU derivatives are the stored bits.
 //   3. weight gradients: sum_p delta_p a_p^T of every layer on the matrix
 //      cores, each pixel block read once per product.
 // Then one fixed-order reduction of the workgroups' partial sums into grad_w
 // (deterministic, no atomics).
 //
 // Slabs bound the workspace: a slab's blocks take at most kSlabBytes.
+//
+// Formulation.  A wave owns 16 pixels.  Every map is D = A X with a 16-row
+// tile of A (weights) as the row operand and the 16 pixels as the columns.
+// K-step s of the instruction takes inputs 4s .. 4s+3: lane group g (lane >>
+// 4) presents input 4s + g of its pixel (lane & 15).  The accumulator leaves
+// lane group g with tile rows 4g + r (r = 0..3), so the rows of A are stored
+// permuted: row 4g + r of tile mt is neuron 16 mt + 4r + g.  Register r of
+// tile mt is then neuron 4 (4 mt + r) + g, exactly what lane group g presents
+// in K-step 4 mt + r of the next map: activations go from map to map without
+// any cross-lane move, and every sum runs over its inputs in natural order.
+//
+// Weights.  They stream through LDS as a sequence of 16 KiB stages of
+// fragments (64 lanes x 16 bytes: four K-steps of one row tile), in the order
+// the kernel consumes them, through a ring of three buffers with one barrier
+// in the middle of each stage: past it every wave is done with the stage
+// before, whose buffer then takes the stage after the next one, and the next
+// stage's first fragments are read before this one ends, so no wave starts a
+// stage by waiting for LDS.  The stages go through registers rather than by
+// direct global->LDS copies: the compiler makes every LDS read wait for the
+// direct copies in flight, which would put a memory latency into every stage.
 #include <string.h>
 
 #include <algorithm>
@@ -31,6 +54,475 @@ struct BwdWorkspace {
 namespace f32 {
 
 constexpr size_t kSlabBytes = (size_t)16 << 30;
+constexpr int kThreads = 256, kWaves = 4;
+constexpr int kTile = kWaves * 16;         // pixels per workgroup tile
+constexpr int kStageFrags = 16;
+constexpr int kStageBytes = kStageFrags * 1024;
+
+// The linear maps of the forward and of the backward (the transposes), each
+// list in the order its kernel consumes them.
+enum Op {
+  O_F1, O_F2, O_F3, O_T1S, O_T1A, O_T2, O_T3, O_B1S, O_B1T, O_B2, O_B3, O_R1P, O_R1L, O_R2,
+  kNumOps
+};
+enum BwdOp {
+  O_R3T, O_R2T, O_R1T, O_B3T, O_B2T, O_B1ST, O_B1TT, O_T3T, O_T2T, O_T1ST, O_F3T, O_F2T, kNumBwdOps
+};
+
+// Map o multiplies A (M x K): A[m][k] = W[m][col0 + k] of a layer, or
+// W[k][col0 + m] (trans).
+struct OpDesc {
+  int64_t woff;      // float offset of the layer's matrix in the master vector
+  int32_t ld;        // the layer's input count (master row length)
+  int32_t col0, M, K, trans;
+  int32_t mt, kq;    // 16-row tiles, 16-deep K groups
+  int32_t stage0, nstages;
+};
+
+struct OpTable {
+  OpDesc op[kNumOps];
+  int32_t nops, stages;            // stages of every map together
+  LayerOff lo[kNumLayers];
+  int32_t W, pe;
+};
+
+// The packed form: the stages, then the 12 biases (W floats each, in the
+// position order below).
+static size_t packed_bytes(const OpTable &t) {
+  return ((size_t)t.stages * kStageBytes + sizeof(float) * kNumLayers * t.W + 1023) / 1024 * 1024;
+}
+
+// What the backward keeps of a slab of np pixels (a multiple of kTile, the
+// tail repeating the last pixel): blocks [pixel][width] in position order.
+// The slots' blocks follow each other slot by slot ([slot][pixel][width]).
+struct Planes {
+  int64_t p0, np;            // first pixel of the slab; its padded length
+  float *x;                  // F's encoded input, nx wide
+  float *a1, *a2, *sig, *zs, *tau, *d1, *d2, *phi, *g1, *g2;
+  float *z1, *bi;            // per slot: h's first activation; its encoded input, nb wide
+  float *inv, *bs;           // per pixel: 1 / max(c, 1) (mean) or 1; T3's bias scale
+  uint32_t *mask;            // [kMasks + 2 k][np / 16][64]: ReLU signs, bit 4 mt + r
+  // the deltas of the maps' outputs (dsig: sigma's; dz: Z's; dz1 per slot)
+  float *dg2, *dg1, *dphi, *dd2, *dd1, *dtau, *dsig, *dz, *du, *da2, *da1, *dz1, *dy;
+  int32_t nx, nb;
+};
+// Mask layers; then per slot z1's and z2's, the latter of active slots only.
+enum { K_A1, K_A2, K_D1, K_D2, K_G1, K_G2, kMasks };
+constexpr int kDyWidth = 16;
+
+// Position p of a W-row block (16 mt + 4 g + r) holds this neuron.
+__host__ __device__ inline int neuron_at(int p) {
+  return (p & ~15) + 4 * (p & 3) + ((p >> 2) & 3);
+}
+
+struct OpSpec { int op; Layer l; int col0, M, K; };
+
+static void fill_table(int W, int pe, const OpSpec *s, int n, int trans, OpTable *t) {
+  layer_offsets(W, pe, t->lo);
+  t->W = W;
+  t->pe = pe;
+  t->nops = n;
+  int stage = 0;
+  for (int i = 0; i < n; ++i) {
+    OpDesc &d = t->op[s[i].op];
+    d.woff = t->lo[s[i].l].w;
+    d.ld = t->lo[s[i].l].in;
+    d.col0 = s[i].col0;
+    d.M = s[i].M;
+    d.K = s[i].K;
+    d.trans = trans;
+    d.mt = (d.M + 15) / 16;
+    d.kq = (d.K + 15) / 16;
+    d.stage0 = stage;
+    d.nstages = (d.kq * d.mt + kStageFrags - 1) / kStageFrags;
+    stage += d.nstages;
+  }
+  t->stages = stage;
+}
+
+static void make_ops(int W, int pe, OpTable *t) {
+  const int nx = (kNG + kNS) * pe_blocks(pe), nb = kNL * pe_blocks(pe);
+  const OpSpec s[kNumOps] = {
+      {O_F1, L_F1, 0, W, nx},  {O_F2, L_F2, 0, W, W},   {O_F3, L_F3, 0, W, W},
+      {O_T1S, L_T1, nb, W, W}, {O_T1A, L_T1, 0, W, nb}, {O_T2, L_T2, 0, W, W},
+      {O_T3, L_T3, 0, W, W},   {O_B1S, L_B1, 0, W, W},  {O_B1T, L_B1, W, W, W},
+      {O_B2, L_B2, 0, W, W},   {O_B3, L_B3, 0, W, W},   {O_R1P, L_R1, 0, W, W},
+      {O_R1L, L_R1, W, W, 3},  {O_R2, L_R2, 0, W, W}};
+  fill_table(W, pe, s, kNumOps, 0, t);
+}
+
+static void make_bwd_ops(int W, int pe, OpTable *t) {
+  const int nb = kNL * pe_blocks(pe);
+  const OpSpec s[kNumBwdOps] = {
+      {O_R3T, L_R3, 0, W, kNOUT}, {O_R2T, L_R2, 0, W, W},  {O_R1T, L_R1, 0, W, W},
+      {O_B3T, L_B3, 0, W, W},     {O_B2T, L_B2, 0, W, W},  {O_B1ST, L_B1, 0, W, W},
+      {O_B1TT, L_B1, W, W, W},    {O_T3T, L_T3, 0, W, W},  {O_T2T, L_T2, 0, W, W},
+      {O_T1ST, L_T1, nb, W, W},   {O_F3T, L_F3, 0, W, W},  {O_F2T, L_F2, 0, W, W}};
+  fill_table(W, pe, s, kNumBwdOps, 1, t);
+}
+
+// One thread per 16 bytes of a fragment, then the biases; blockIdx.y selects
+// the forward's or the backward's maps.  Fragment f of a map is K group f / mt
+// of row tile f % mt; element j of lane l is A[row (l & 15)][16 q + 4 j +
+// (l >> 4)], zero outside M x K.
+struct PackArgs {
+  OpTable t[2];
+  uint8_t *packed[2];
+};
+__global__ __launch_bounds__(kThreads) void f32_pack_kernel(const float *__restrict__ master,
+                                                            PackArgs a) {
+  const OpTable &t = a.t[blockIdx.y];
+  uint8_t *packed = a.packed[blockIdx.y];
+  const int e = blockIdx.x * kThreads + threadIdx.x;
+  const int total = t.stages * kStageFrags * 64;
+  if (e >= total) {
+    const int b = e - total, l = b / t.W, p = b % t.W;
+    if (l < kNumLayers)
+      ((float *)(packed + (size_t)t.stages * kStageBytes))[b] =
+          neuron_at(p) < t.lo[l].out ? master[t.lo[l].b + neuron_at(p)] : 0.0f;
+    return;
+  }
+  const int stage = e / (kStageFrags * 64);
+  int o = 0;
+  while (o + 1 < t.nops && stage >= t.op[o + 1].stage0) ++o;
+  const OpDesc d = t.op[o];
+  const int f = (e >> 6) - d.stage0 * kStageFrags, lane = e & 63;
+  const int q = f / d.mt, mt = f % d.mt, i = lane & 15;
+  const int m = 16 * mt + 4 * (i & 3) + (i >> 2);       // rows in position order
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int k = 16 * q + 4 * j + (lane >> 4);
+    if (m < d.M && k < d.K)
+      v[j] = d.trans ? master[d.woff + (int64_t)k * d.ld + d.col0 + m]
+                     : master[d.woff + (int64_t)m * d.ld + d.col0 + k];
+  }
+  ((f32x4 *)packed)[e] = v;
+}
+
+template <int MT>
+struct Pipe {
+  static constexpr int kQ = kStageFrags / MT;    // K groups per stage of a full map
+  rsrc_t base;
+  uint8_t *lds;          // kRing stage buffers
+  Sequence seq;          // of the stages to load
+  int cur;               // buffer of the stage being consumed
+  f32x4 hold[4];         // the stage two ahead of it
+  f32x4 w[2][4];         // fragments; w[0]: the first of the stage to consume
+
+  __device__ __forceinline__ void load() {
+    const uint32_t at = (uint32_t)seq.next() * kStageBytes;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      hold[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                              base, threadIdx.x * 16, at + i * kThreads * 16, 0));
+  }
+  __device__ __forceinline__ void store(int buf) {
+    f32x4 *dst = (f32x4 *)(lds + buf * kStageBytes) + threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) dst[i * kThreads] = hold[i];
+  }
+  __device__ __forceinline__ void start(const uint8_t *b, uint8_t *l, const Program &p) {
+    base = make_rsrc(b);
+    lds = l;
+    seq.start(p);
+    cur = 0;
+    load();
+    store(0);
+    load();
+    store(1);
+    load();
+    __syncthreads();
+    fetch(w[0], 0, 0);
+  }
+  // Four fragments of a buffer.
+  __device__ __forceinline__ void fetch(f32x4 (&d)[4], int buf, int group) {
+    const f32x4 *s = (const f32x4 *)(lds + buf * kStageBytes) + (threadIdx.x & 63) + group * 256;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) d[m] = s[m * 64];
+  }
+  __device__ __forceinline__ int after(int buf) const { return buf == kRing - 1 ? 0 : buf + 1; }
+  // The middle of a stage.  Only LDS traffic is drained: the loads and stores
+  // in flight stay so.
+  __device__ __forceinline__ void middle() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    store(cur == 0 ? kRing - 1 : cur - 1);
+    load();
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
+  // One stage: K groups q0 .. of a map of MT row tiles; group q0 + i is used
+  // while q0 + i < kq.  x(q) gives the four K-steps' inputs.  Four fragments
+  // are read ahead of the sixteen MFMAs of the four before (a scheduling
+  // barrier keeps them there).
+  template <class X>
+  __device__ __forceinline__ void stage(f32x4 (&acc)[MT], int q0, int kq, X x) {
+    f32x4 xv = zero4();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      constexpr int kPer = MT / 4;               // fragment groups per K group
+      const int q = q0 + i / kPer, m0 = 4 * (i % kPer);
+      if (i == 2) middle();
+      if (i < 3) fetch(w[(i + 1) & 1], cur, i + 1);
+      else fetch(w[0], after(cur), 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (q < kq) {
+        if (i % kPer == 0) xv = x(i / kPer);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int m = 0; m < 4; ++m)
+            acc[m0 + m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i & 1][m][j], xv[j], acc[m0 + m],
+                                                                0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    cur = after(cur);
+  }
+  // A map over W inputs held in registers, in[q] K group q.
+  __device__ __forceinline__ void chain(f32x4 (&acc)[MT], const f32x4 (&in)[MT]) {
+#pragma unroll
+    for (int st = 0; st < MT / kQ; ++st)
+      stage(acc, st * kQ, MT, [&](int i) { return in[st * kQ + i]; });
+  }
+  // A map over kq K groups whose inputs x(q) computes.
+  template <class X>
+  __device__ __forceinline__ void gather(f32x4 (&acc)[MT], int kq, X x) {
+    for (int q0 = 0; q0 < kq; q0 += kQ) stage(acc, q0, kq, [&](int i) { return x(q0 + i); });
+  }
+};
+
+// ---- the recompute ------------------------------------------------------------------
+struct SaveArgs {
+  const uint8_t *packed;
+  int32_t bias_stage;        // the biases follow this many stages
+  Program pg;
+  const float *gbuf, *layers, *scene;
+  int32_t hw, k, mean, pe, kpad;
+  int32_t canon;             // pool in canonical order
+  int32_t kq_x, kq_b;        // K groups of F1 and of T1's slot columns
+  int64_t npx;
+  Planes pl;
+};
+
+// ENC: with positional encoding (a form of its own: the sine and cosine's code
+// and registers stay out of the plain one).
+template <int W, bool ENC>
+__global__ __launch_bounds__(kThreads, 2) void f32_save_kernel(SaveArgs a) {
+  constexpr int MT = W / 16;
+  // LDS: the stage ring | biases | slot order per pixel
+  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+  float *l_bias = (float *)(lds + kRing * kStageBytes);
+  uint8_t *l_order = (uint8_t *)(l_bias + kNumLayers * W);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  {
+    const float *b = (const float *)(a.packed + (size_t)a.bias_stage * kStageBytes);
+    for (int i = threadIdx.x; i < kNumLayers * W; i += kThreads) l_bias[i] = b[i];
+  }
+  Pipe<MT> pipe;
+  pipe.start(a.packed, lds, a.pg);       // ends with a barrier
+  const int hw = a.hw, nblk = ENC ? pe_blocks(a.pe) : 1;
+  const int64_t ntiles = a.pl.np / kTile;
+
+  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    // Opaque per-tile copies of the lane's place keep the compiler from holding
+    // every address derived from them in registers across the tile loop.
+    int g = lane >> 4, col = lane & 15;
+    asm volatile("" : "+v"(g), "+v"(col));
+    const int64_t pl = tile * kTile + wave * 16 + col;         // pixel of the slab
+    const int64_t pc = std::min<int64_t>(a.pl.p0 + pl, a.npx - 1);   // tail: a real pixel again
+    const int f = (int)(pc / hw), q = (int)(pc - (int64_t)f * hw);
+    const float *G = a.gbuf + (size_t)f * kNG * hw + q;
+    const float *L = a.layers + (size_t)f * a.k * kNL * hw + q;
+    const float *S = a.scene + (size_t)f * kNS;
+    uint8_t *order = l_order + (wave * 16 + col) * a.kpad;
+    auto bias = [&](int layer, int mt) { return *(const f32x4 *)(l_bias + layer * W + 16 * mt + 4 * g); };
+    // in = act(acc + bias)
+    auto next = [&](f32x4 (&in)[MT], f32x4 (&acc)[MT], int layer, bool relu) {
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        const f32x4 v = acc[mt] + bias(layer, mt);
+        in[mt] = relu ? relu4(v) : v;
+        acc[mt] = zero4();
+      }
+    };
+    // a block of W values per pixel (32-bit offsets from a uniform base: the
+    // caller bounds a slab's blocks), the signs of a ReLU's outputs
+    const uint32_t at = (uint32_t)pl * (W * 4) + 16 * g;
+    auto save = [&](float *plane, const f32x4 (&v)[MT]) {
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) *(f32x4 *)((char *)plane + at + 64 * mt) = v[mt];
+    };
+    auto signs = [&](int layer, const f32x4 (&v)[MT], bool keep) {
+      uint32_t b = 0;
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) b |= v[mt][r] > 0.0f ? 1u << (4 * mt + r) : 0u;
+        asm volatile("" : "+v"(b));
+      }
+      uint32_t *words = a.pl.mask + (int64_t)layer * (a.pl.np / 16) * 64;
+      words[(uint32_t)(tile * kThreads) + threadIdx.x] = keep ? b : 0u;
+    };
+    auto keep = [&](float *plane, int layer, const f32x4 (&v)[MT]) {
+      save(plane, v);
+      signs(layer, v, true);
+    };
+    f32x4 in[MT], acc[MT], u[MT], Z[MT], xr[2];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[mt] = zero4();
+    if constexpr (!ENC) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int c = 4 * i + g;
+        xr[i >> 2][i & 3] = c < kNG ? G[(size_t)c * hw] : (c < kNG + kNS ? S[c - kNG] : 0.0f);
+      }
+    }
+    if (a.canon) {                      // read back by the same wave
+      if (a.k <= kFastK) {
+        float al[kFastK];
+#pragma unroll
+        for (int j = 0; j < kFastK; ++j)
+          al[j] = j < a.k ? L[((size_t)j * kNL + kAlpha) * hw] : 0.0f;
+        rank_slots(al, L, hw, a.k, g, order);
+      } else {
+        for (int i = g; i < a.k; i += 4) order[slot_rank(L, (size_t)hw, a.k, i)] = (uint8_t)i;
+      }
+    }
+    // A slot's raw channels g, 4 + g, 8 + g (the inputs of K-steps 0..2 of
+    // every encoding block: 12 channels, three steps) and its alpha.
+    auto load = [&](int i, float (&r)[3], float &alpha) {
+      const int slot = a.canon ? (int)order[i] : i;
+      const float *Li = L + (size_t)slot * kNL * hw;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) r[j] = Li[(size_t)(4 * j + g) * hw];
+      alpha = Li[(size_t)kAlpha * hw];
+    };
+    float raw[3] = {0.f, 0.f, 0.f}, al = 0.0f;
+    if (a.k > 0) load(0, raw, al);
+
+    // F on the (encoded) [G; s]: input k is channel k % 30 of block k / 30
+    pipe.gather(acc, ENC ? a.kq_x : 2, [&](int qq) {
+      f32x4 x;
+      if constexpr (!ENC) {
+        x = qq == 0 ? xr[0] : xr[1];
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int k = 16 * qq + 4 * j + g, b = k / (kNG + kNS), c = k - b * (kNG + kNS);
+          const float v = c < kNG ? G[(size_t)c * hw] : S[c - kNG];
+          x[j] = b < nblk ? pe_value(v, b) : 0.0f;
+        }
+      }
+      *(f32x4 *)(a.pl.x + (uint32_t)pl * a.pl.nx + 16 * qq + 4 * g) = x;
+      return x;
+    });
+    next(in, acc, L_F1, true);
+    if constexpr (ENC)                                   // the block's padding
+      for (int i = a.kq_x; i < a.pl.nx / 16; ++i)
+        *(f32x4 *)(a.pl.x + (uint32_t)pl * a.pl.nx + 16 * i + 4 * g) = zero4();
+    keep(a.pl.a1, K_A1, in);
+    pipe.chain(acc, in);
+    next(in, acc, L_F2, true);
+    keep(a.pl.a2, K_A2, in);
+    pipe.chain(acc, in);
+    next(in, acc, L_F3, false);                          // sigma
+    save(a.pl.sig, in);
+    // u = W_T1,sigma sigma + b_T1 (the sigma-hoist)
+    pipe.chain(acc, in);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      u[mt] = acc[mt] + bias(L_T1, mt);
+      acc[mt] = zero4();
+      Z[mt] = zero4();
+    }
+    // per slot: z1 = relu(W_T1,b b_i + u), Z += m_i relu(W_T2 z1 + b_T2)
+    float cnt = 0.0f;
+    for (int i = 0; i < a.k; ++i) {
+      float rn[3] = {0.f, 0.f, 0.f}, an = 0.0f;
+      if (i + 1 < a.k) load(i + 1, rn, an);
+      const float m = al > 0.0f ? 1.0f : 0.0f;
+      float *bi = a.pl.bi + i * a.pl.np * a.pl.nb;
+      pipe.gather(acc, ENC ? a.kq_b : 1, [&](int qq) {
+        f32x4 x = {raw[0], raw[1], raw[2], 0.0f};
+        if constexpr (ENC) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int s = 4 * qq + j, b = s / 3, c = s - 3 * b;
+            const float r = c == 0 ? raw[0] : (c == 1 ? raw[1] : raw[2]);
+            x[j] = b < nblk ? pe_value(r, b) : 0.0f;
+          }
+        }
+        *(f32x4 *)(bi + (uint32_t)pl * a.pl.nb + 16 * qq + 4 * g) = x;
+        return x;
+      });
+      if constexpr (ENC)                                 // the block's padding
+        for (int j = a.kq_b; j < a.pl.nb / 16; ++j)
+          *(f32x4 *)(bi + (uint32_t)pl * a.pl.nb + 16 * j + 4 * g) = zero4();
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        in[mt] = relu4(acc[mt] + u[mt]);
+        acc[mt] = zero4();
+      }
+      keep(a.pl.z1 + (int64_t)i * a.pl.np * W, kMasks + 2 * i, in);
+      pipe.chain(acc, in);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) acc[mt] = acc[mt] + bias(L_T2, mt);
+      signs(kMasks + 2 * i + 1, acc, al > 0.0f);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        Z[mt] += relu4(acc[mt]) * m;
+        acc[mt] = zero4();
+      }
+      cnt += m;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) raw[j] = rn[j];
+      al = an;
+    }
+    // the pool, T3 (tau), B on [sigma; tau], R on [phi; L_d]
+    const float ld = g < 3 ? G[(size_t)(11 + g) * hw] : 0.0f;
+    const float inv = a.mean ? 1.0f / fmaxf(cnt, 1.0f) : 1.0f;
+    const float bs = a.mean ? (cnt > 0.0f ? 1.0f : 0.0f) : cnt;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) in[mt] = Z[mt] * inv;
+    save(a.pl.zs, in);
+    if (g == 0) {
+      a.pl.inv[pl] = inv;
+      a.pl.bs[pl] = bs;
+    }
+    pipe.chain(acc, in);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      const f32x4 b = bias(L_T3, mt);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) in[mt][r] = fmaf(b[r], bs, acc[mt][r]);
+      acc[mt] = zero4();
+    }
+    save(a.pl.tau, in);
+    {
+      f32x4 s[MT];                                       // sigma, back from its block
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) s[mt] = *(const f32x4 *)((const char *)a.pl.sig + at + 64 * mt);
+      pipe.chain(acc, s);
+    }
+    pipe.chain(acc, in);
+    next(in, acc, L_B1, true);
+    keep(a.pl.d1, K_D1, in);
+    pipe.chain(acc, in);
+    next(in, acc, L_B2, true);
+    keep(a.pl.d2, K_D2, in);
+    pipe.chain(acc, in);
+    next(in, acc, L_B3, false);                          // phi
+    save(a.pl.phi, in);
+    pipe.chain(acc, in);
+    pipe.gather(acc, 1, [&](int) { return f32x4{ld, 0.f, 0.f, 0.f}; });
+    next(in, acc, L_R1, true);
+    keep(a.pl.g1, K_G1, in);
+    pipe.chain(acc, in);
+    next(in, acc, L_R2, true);
+    keep(a.pl.g2, K_G2, in);
+  }
+}
 
 // ---- deltas ---------------------------------------------------------------------
 struct DeltaArgs {
@@ -555,6 +1047,18 @@ class Gradient {
   DwGroup g_[3];             // W x W, W x 16, W x 32
 };
 
+template <int W, bool ENC>
+static hipError_t launch_save(const SaveArgs &a, int num_cus, hipStream_t s) {
+  static const hipError_t attr =     // per process; the attribute is per function
+      hipFuncSetAttribute((const void *)f32_save_kernel<W, ENC>,
+                          hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
+  if (attr != hipSuccess) return attr;
+  const size_t lds = kRing * kStageBytes + sizeof(float) * kNumLayers * W + (size_t)kTile * a.kpad;
+  const unsigned grid = (unsigned)std::min<int64_t>(a.pl.np / kTile, 2 * num_cus);
+  hipLaunchKernelGGL((f32_save_kernel<W, ENC>), dim3(grid), dim3(kThreads), lds, s, a);
+  return hipGetLastError();
+}
+
 template <int W>
 static hipError_t launch_delta(const DeltaArgs &a, int num_cus, hipStream_t s) {
   const unsigned grid = (unsigned)std::min<int64_t>(a.pl.np / kTile, 2 * num_cus);
@@ -582,16 +1086,18 @@ static gn_status backward(gn_handle *h, const gn_frame *frame, const float *dy, 
   const int64_t npx = (int64_t)frame->n * frame->h * frame->w;
   if (f32::rup(npx, 4096) > gn_f32_max_px)
     return gn_set_error(GN_E_INVAL, "more than 3 * 2^20 pixels in one call");
-  f32::OpTable t;
-  f32::make_bwd_ops(W, pe, &t);
+  f32::PackArgs pk;
+  f32::make_ops(W, pe, &pk.t[0]);
+  f32::make_bwd_ops(W, pe, &pk.t[1]);
+  const f32::OpTable &tf = pk.t[0], &tb = pk.t[1];
   // slabs of equal length (the last may be shorter) within the workspace bound
   const int64_t per_px = f32::px_floats(W, pe, k) * (int64_t)sizeof(float);
   const int64_t most = (int64_t)(f32::kSlabBytes / per_px), slabs = (npx + most - 1) / most;
   const int64_t np = f32::rup((npx + slabs - 1) / slabs, f32::kTile);
   f32::Gradient grad(W, pe, k, h->num_cus);
   const size_t part = grad.split(np) * sizeof(float);
-  const size_t planes = f32::rup(np * per_px, 1024), packed = f32::rup(f32::packed_bytes(t), 1024);
-  const size_t need = planes + packed + part;
+  const size_t planes = f32::rup(np * per_px, 1024);
+  const size_t need = planes + f32::packed_bytes(tf) + f32::packed_bytes(tb) + part;
   if (!h->bwd) h->bwd = new BwdWorkspace();
   BwdWorkspace *ws = h->bwd;
   hipError_t e = hipSuccess;
@@ -607,24 +1113,50 @@ static gn_status backward(gn_handle *h, const gn_frame *frame, const float *dy, 
     gn_bwd_free(h);
     return gn_check_device(h, e, "backward workspace");
   }
-  uint8_t *frag = ws->mem + planes;
-  grad.bind((float *)(frag + packed));
-  e = f32::launch_pack(h->d_master, t, frag, s);
+  pk.packed[0] = ws->mem + planes;
+  pk.packed[1] = pk.packed[0] + f32::packed_bytes(tf);
+  grad.bind((float *)(pk.packed[1] + f32::packed_bytes(tb)));
+  const int64_t pieces = (int64_t)std::max(tf.stages, tb.stages) * f32::kStageFrags * 64 +
+                         kNumLayers * W;
+  hipLaunchKernelGGL(f32::f32_pack_kernel, dim3((unsigned)((pieces + 255) / 256), 2), dim3(256), 0, s,
+                     h->d_master, pk);
+  e = hipGetLastError();
+  f32::SaveArgs a{};
+  a.packed = pk.packed[0];
+  a.bias_stage = tf.stages;
+  a.pg = f32::Program{0, tf.op[f32::O_T1A].stage0, tf.op[f32::O_T1A].stage0, tf.op[f32::O_T3].stage0,
+                      tf.op[f32::O_T3].stage0, tf.stages, k, 1};
+  a.gbuf = frame->gbuf;
+  a.layers = frame->layers;
+  a.scene = frame->scene;
+  a.hw = frame->h * frame->w;
+  a.k = k;
+  a.mean = h->cfg.pool == GN_POOL_MEAN ? 1 : 0;
+  a.pe = pe;
+  a.canon = gn_slot_kmax(h) > 1 && k > 1 ? 1 : 0;
+  a.kpad = a.canon ? (k + 3) & ~3 : 0;
+  a.kq_x = tf.op[f32::O_F1].kq;
+  a.kq_b = tf.op[f32::O_T1A].kq;
+  a.npx = npx;
+  f32::DeltaArgs d{};
+  d.packed = pk.packed[1];
+  d.pg = f32::Program{0, tb.op[f32::O_T2T].stage0, tb.op[f32::O_T2T].stage0, tb.op[f32::O_T1ST].stage0,
+                      tb.op[f32::O_T1ST].stage0, tb.stages, k, 1};
+  d.dy = dy;
+  d.hw = a.hw;
+  d.k = k;
+  d.npx = npx;
+  const int cus = h->num_cus;
   for (int64_t p0 = 0; p0 < npx && e == hipSuccess; p0 += np) {
     f32::Planes pl = f32::carve((float *)ws->mem, W, pe, k, std::min(np, f32::rup(npx - p0, f32::kTile)));
     pl.p0 = p0;
-    const gn_status st = gn_f32_save(h, frame, pl, s);
-    if (st != GN_OK) return st;
-    f32::DeltaArgs d{};
-    d.packed = frag;
-    d.pg = f32::Program{0, t.op[f32::O_T2T].stage0, t.op[f32::O_T2T].stage0, t.op[f32::O_T1ST].stage0,
-                        t.op[f32::O_T1ST].stage0, t.stages, k, 1};
-    d.pl = pl;
-    d.dy = dy;
-    d.hw = frame->h * frame->w;
-    d.k = k;
-    d.npx = npx;
-    e = W == 128 ? f32::launch_delta<128>(d, h->num_cus, s) : f32::launch_delta<64>(d, h->num_cus, s);
+    a.pl = d.pl = pl;
+    if (W == 128)
+      e = pe > 0 ? f32::launch_save<128, true>(a, cus, s) : f32::launch_save<128, false>(a, cus, s);
+    else
+      e = pe > 0 ? f32::launch_save<64, true>(a, cus, s) : f32::launch_save<64, false>(a, cus, s);
+    if (e == hipSuccess)
+      e = W == 128 ? f32::launch_delta<128>(d, cus, s) : f32::launch_delta<64>(d, cus, s);
     if (e == hipSuccess) e = grad.accumulate(pl, p0 == 0, s);
   }
   if (e == hipSuccess) e = grad.reduce(grad_w, s);

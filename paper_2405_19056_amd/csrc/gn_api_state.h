@@ -64,12 +64,9 @@ void gn_serve_shutdown(gn_handle *h);
 void gn_bwd_free(gn_handle *h);
 // The fp32 kernels (fwd_fp32.hip): the packed weights of a handle, the FP32
 // forward and the FP8 calibration (amax: device float bits of the largest
-// h-layer-1 activation), the backward's recompute.  Every fp32 call covers
-// at most gn_f32_max_px pixels (rounded up to 4096).
-namespace gn { namespace f32 { struct Planes; } }
+// h-layer-1 activation).  Every fp32 call (and the backward) covers at most
+// gn_f32_max_px pixels (rounded up to 4096).
 constexpr int64_t gn_f32_max_px = (int64_t)3 << 20;
-gn_status gn_f32_save(gn_handle *h, const gn_frame *frame, const gn::f32::Planes &pl,
-                      hipStream_t s);
 size_t gn_f32_packed_bytes(int W, int pe);
 hipError_t gn_f32_pack(gn_handle *h, hipStream_t s);
 gn_status gn_f32_forward(gn_handle *h, const gn_frame *frame, float *out, hipStream_t s);
