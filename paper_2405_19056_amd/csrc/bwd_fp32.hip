@@ -7,6 +7,8 @@
 //      as one bit.  It stays on the fp32 instruction, each sum over its
 //      inputs in natural order: a pre-activation within a rounding of zero
 //      takes the branch it has always taken, whatever the forward's form.
+//      (The FP8 calibration is the same kernel up to h's first layer: its
+//      scale decides every fp8 rounding of a handle.)
 //   2. deltas: one kernel chains the transposed maps in registers from dL/dy
 //      to F's first layer, the slots in between: dz2 = [z2 > 0] m_i dZ is a
 //      selection of dZ's registers, dz1 = [z1 > 0] W_T2^T dz2, du = sum dz1.
@@ -303,11 +305,13 @@ struct SaveArgs {
   int32_t kq_x, kq_b;        // K groups of F1 and of T1's slot columns
   int64_t npx;
   Planes pl;
+  unsigned *amax;            // calibration: float bits of the largest z1
 };
 
-// ENC: with positional encoding (a form of its own: the sine and cosine's code
+// CAL: the FP8 calibration, which keeps no block and ends after h's first
+// layer of every slot.  ENC: with positional encoding (a form of its own: the sine and cosine's code
 // and registers stay out of the plain one).
-template <int W, bool ENC>
+template <int W, bool ENC, bool CAL>
 __global__ __launch_bounds__(kThreads, 2) void f32_save_kernel(SaveArgs a) {
   constexpr int MT = W / 16;
   // LDS: the stage ring | biases | slot order per pixel
@@ -323,6 +327,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_save_kernel(SaveArgs a) {
   pipe.start(a.packed, lds, a.pg);       // ends with a barrier
   const int hw = a.hw, nblk = ENC ? pe_blocks(a.pe) : 1;
   const int64_t ntiles = a.pl.np / kTile;
+  float amax = 0.0f;
 
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     // Opaque per-tile copies of the lane's place keep the compiler from holding
@@ -350,10 +355,12 @@ __global__ __launch_bounds__(kThreads, 2) void f32_save_kernel(SaveArgs a) {
     // caller bounds a slab's blocks), the signs of a ReLU's outputs
     const uint32_t at = (uint32_t)pl * (W * 4) + 16 * g;
     auto save = [&](float *plane, const f32x4 (&v)[MT]) {
+      if constexpr (CAL) return;
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) *(f32x4 *)((char *)plane + at + 64 * mt) = v[mt];
     };
     auto signs = [&](int layer, const f32x4 (&v)[MT], bool keep) {
+      if constexpr (CAL) return;
       uint32_t b = 0;
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
@@ -414,11 +421,11 @@ __global__ __launch_bounds__(kThreads, 2) void f32_save_kernel(SaveArgs a) {
           x[j] = b < nblk ? pe_value(v, b) : 0.0f;
         }
       }
-      *(f32x4 *)(a.pl.x + (uint32_t)pl * a.pl.nx + 16 * qq + 4 * g) = x;
+      if constexpr (!CAL) *(f32x4 *)(a.pl.x + (uint32_t)pl * a.pl.nx + 16 * qq + 4 * g) = x;
       return x;
     });
     next(in, acc, L_F1, true);
-    if constexpr (ENC)                                   // the block's padding
+    if constexpr (ENC && !CAL)                           // the block's padding
       for (int i = a.kq_x; i < a.pl.nx / 16; ++i)
         *(f32x4 *)(a.pl.x + (uint32_t)pl * a.pl.nx + 16 * i + 4 * g) = zero4();
     keep(a.pl.a1, K_A1, in);
@@ -453,10 +460,10 @@ __global__ __launch_bounds__(kThreads, 2) void f32_save_kernel(SaveArgs a) {
             x[j] = b < nblk ? pe_value(r, b) : 0.0f;
           }
         }
-        *(f32x4 *)(bi + (uint32_t)pl * a.pl.nb + 16 * qq + 4 * g) = x;
+        if constexpr (!CAL) *(f32x4 *)(bi + (uint32_t)pl * a.pl.nb + 16 * qq + 4 * g) = x;
         return x;
       });
-      if constexpr (ENC)                                 // the block's padding
+      if constexpr (ENC && !CAL)                         // the block's padding
         for (int j = a.kq_b; j < a.pl.nb / 16; ++j)
           *(f32x4 *)(bi + (uint32_t)pl * a.pl.nb + 16 * j + 4 * g) = zero4();
 #pragma unroll
@@ -464,21 +471,29 @@ __global__ __launch_bounds__(kThreads, 2) void f32_save_kernel(SaveArgs a) {
         in[mt] = relu4(acc[mt] + u[mt]);
         acc[mt] = zero4();
       }
-      keep(a.pl.z1 + (int64_t)i * a.pl.np * W, kMasks + 2 * i, in);
-      pipe.chain(acc, in);
+      if constexpr (CAL) {
+        if (a.pl.p0 + pl < a.npx)
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) acc[mt] = acc[mt] + bias(L_T2, mt);
-      signs(kMasks + 2 * i + 1, acc, al > 0.0f);
+          for (int mt = 0; mt < MT; ++mt)
+            amax = fmaxf(amax, fmaxf(fmaxf(in[mt][0], in[mt][1]), fmaxf(in[mt][2], in[mt][3])));
+      } else {
+        keep(a.pl.z1 + (int64_t)i * a.pl.np * W, kMasks + 2 * i, in);
+        pipe.chain(acc, in);
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        Z[mt] += relu4(acc[mt]) * m;
-        acc[mt] = zero4();
+        for (int mt = 0; mt < MT; ++mt) acc[mt] = acc[mt] + bias(L_T2, mt);
+        signs(kMasks + 2 * i + 1, acc, al > 0.0f);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          Z[mt] += relu4(acc[mt]) * m;
+          acc[mt] = zero4();
+        }
+        cnt += m;
       }
-      cnt += m;
 #pragma unroll
       for (int j = 0; j < 3; ++j) raw[j] = rn[j];
       al = an;
     }
+    if constexpr (CAL) continue;
     // the pool, T3 (tau), B on [sigma; tau], R on [phi; L_d]
     const float ld = g < 3 ? G[(size_t)(11 + g) * hw] : 0.0f;
     const float inv = a.mean ? 1.0f / fmaxf(cnt, 1.0f) : 1.0f;
@@ -521,6 +536,11 @@ __global__ __launch_bounds__(kThreads, 2) void f32_save_kernel(SaveArgs a) {
     pipe.chain(acc, in);
     next(in, acc, L_R2, true);
     keep(a.pl.g2, K_G2, in);
+  }
+  if constexpr (CAL) {
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) amax = fmaxf(amax, __shfl_xor(amax, d));
+    if (lane == 0) atomicMax(a.amax, __float_as_uint(amax));   // non-negative: bit order
   }
 }
 
@@ -1047,16 +1067,60 @@ class Gradient {
   DwGroup g_[3];             // W x W, W x 16, W x 32
 };
 
-template <int W, bool ENC>
-static hipError_t launch_save(const SaveArgs &a, int num_cus, hipStream_t s) {
+template <int W, bool ENC, bool CAL>
+static hipError_t launch_save_form(const SaveArgs &a, int num_cus, hipStream_t s) {
   static const hipError_t attr =     // per process; the attribute is per function
-      hipFuncSetAttribute((const void *)f32_save_kernel<W, ENC>,
+      hipFuncSetAttribute((const void *)f32_save_kernel<W, ENC, CAL>,
                           hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
   if (attr != hipSuccess) return attr;
   const size_t lds = kRing * kStageBytes + sizeof(float) * kNumLayers * W + (size_t)kTile * a.kpad;
   const unsigned grid = (unsigned)std::min<int64_t>(a.pl.np / kTile, 2 * num_cus);
-  hipLaunchKernelGGL((f32_save_kernel<W, ENC>), dim3(grid), dim3(kThreads), lds, s, a);
+  hipLaunchKernelGGL((f32_save_kernel<W, ENC, CAL>), dim3(grid), dim3(kThreads), lds, s, a);
   return hipGetLastError();
+}
+
+template <bool CAL>
+static hipError_t launch_save(int W, const SaveArgs &a, int num_cus, hipStream_t s) {
+  if (W == 128)
+    return a.pe > 0 ? launch_save_form<128, true, CAL>(a, num_cus, s)
+                    : launch_save_form<128, false, CAL>(a, num_cus, s);
+  return a.pe > 0 ? launch_save_form<64, true, CAL>(a, num_cus, s)
+                  : launch_save_form<64, false, CAL>(a, num_cus, s);
+}
+
+// Packs the maps of up to two tables.
+static hipError_t launch_pack(const float *master, const PackArgs &p, int tables, hipStream_t s) {
+  int64_t n = 0;
+  for (int i = 0; i < tables; ++i)
+    n = std::max<int64_t>(n, (int64_t)p.t[i].stages * kStageFrags * 64 + kNumLayers * p.t[i].W);
+  hipLaunchKernelGGL(f32_pack_kernel, dim3((unsigned)((n + kThreads - 1) / kThreads), tables),
+                     dim3(kThreads), 0, s, master, p);
+  return hipGetLastError();
+}
+
+// The recompute's arguments of a frame (but for its slab), packed weights of
+// table t; cal: up to h's first layer.
+static SaveArgs save_args(gn_handle *h, const gn_frame *frame, const OpTable &t, const uint8_t *packed,
+                          bool cal) {
+  SaveArgs a{};
+  a.packed = packed;
+  a.bias_stage = t.stages;
+  const int slots = t.op[O_T1A].stage0, head = t.op[O_T3].stage0;
+  a.pg = cal ? Program{0, slots, slots, t.op[O_T2].stage0, 0, 0, frame->k, 0}
+             : Program{0, slots, slots, head, head, t.stages, frame->k, 1};
+  a.gbuf = frame->gbuf;
+  a.layers = frame->layers;
+  a.scene = frame->scene;
+  a.hw = frame->h * frame->w;
+  a.k = frame->k;
+  a.mean = h->cfg.pool == GN_POOL_MEAN ? 1 : 0;
+  a.pe = h->pl.pe;
+  a.canon = !cal && gn_slot_kmax(h) > 1 && frame->k > 1 ? 1 : 0;
+  a.kpad = a.canon ? (frame->k + 3) & ~3 : 0;
+  a.kq_x = t.op[O_F1].kq;
+  a.kq_b = t.op[O_T1A].kq;
+  a.npx = (int64_t)frame->n * frame->h * frame->w;
+  return a;
 }
 
 template <int W>
@@ -1116,28 +1180,8 @@ static gn_status backward(gn_handle *h, const gn_frame *frame, const float *dy, 
   pk.packed[0] = ws->mem + planes;
   pk.packed[1] = pk.packed[0] + f32::packed_bytes(tf);
   grad.bind((float *)(pk.packed[1] + f32::packed_bytes(tb)));
-  const int64_t pieces = (int64_t)std::max(tf.stages, tb.stages) * f32::kStageFrags * 64 +
-                         kNumLayers * W;
-  hipLaunchKernelGGL(f32::f32_pack_kernel, dim3((unsigned)((pieces + 255) / 256), 2), dim3(256), 0, s,
-                     h->d_master, pk);
-  e = hipGetLastError();
-  f32::SaveArgs a{};
-  a.packed = pk.packed[0];
-  a.bias_stage = tf.stages;
-  a.pg = f32::Program{0, tf.op[f32::O_T1A].stage0, tf.op[f32::O_T1A].stage0, tf.op[f32::O_T3].stage0,
-                      tf.op[f32::O_T3].stage0, tf.stages, k, 1};
-  a.gbuf = frame->gbuf;
-  a.layers = frame->layers;
-  a.scene = frame->scene;
-  a.hw = frame->h * frame->w;
-  a.k = k;
-  a.mean = h->cfg.pool == GN_POOL_MEAN ? 1 : 0;
-  a.pe = pe;
-  a.canon = gn_slot_kmax(h) > 1 && k > 1 ? 1 : 0;
-  a.kpad = a.canon ? (k + 3) & ~3 : 0;
-  a.kq_x = tf.op[f32::O_F1].kq;
-  a.kq_b = tf.op[f32::O_T1A].kq;
-  a.npx = npx;
+  e = f32::launch_pack(h->d_master, pk, 2, s);
+  f32::SaveArgs a = f32::save_args(h, frame, tf, pk.packed[0], false);
   f32::DeltaArgs d{};
   d.packed = pk.packed[1];
   d.pg = f32::Program{0, tb.op[f32::O_T2T].stage0, tb.op[f32::O_T2T].stage0, tb.op[f32::O_T1ST].stage0,
@@ -1151,16 +1195,33 @@ static gn_status backward(gn_handle *h, const gn_frame *frame, const float *dy, 
     f32::Planes pl = f32::carve((float *)ws->mem, W, pe, k, std::min(np, f32::rup(npx - p0, f32::kTile)));
     pl.p0 = p0;
     a.pl = d.pl = pl;
-    if (W == 128)
-      e = pe > 0 ? f32::launch_save<128, true>(a, cus, s) : f32::launch_save<128, false>(a, cus, s);
-    else
-      e = pe > 0 ? f32::launch_save<64, true>(a, cus, s) : f32::launch_save<64, false>(a, cus, s);
+    e = f32::launch_save<false>(W, a, cus, s);
     if (e == hipSuccess)
       e = W == 128 ? f32::launch_delta<128>(d, cus, s) : f32::launch_delta<64>(d, cus, s);
     if (e == hipSuccess) e = grad.accumulate(pl, p0 == 0, s);
   }
   if (e == hipSuccess) e = grad.reduce(grad_w, s);
   return gn_check_device(h, e, "backward launch");
+}
+
+// The largest first-layer activation of h over every slot of every pixel, as
+// float bits in *amax (device).  The packed weights it needs live for the call.
+gn_status gn_f32_calibrate(gn_handle *h, const gn_frame *frame, unsigned *amax, hipStream_t s) {
+  const int64_t npx = (int64_t)frame->n * frame->h * frame->w;
+  if (f32::rup(npx, 4096) > gn_f32_max_px)
+    return gn_set_error(GN_E_INVAL, "more than 3 * 2^20 pixels in one call");
+  f32::PackArgs pk{};
+  f32::make_ops(h->W, h->pl.pe, &pk.t[0]);
+  hipError_t e = hipMalloc((void **)&pk.packed[0], f32::packed_bytes(pk.t[0]));
+  if (e != hipSuccess) return gn_check_device(h, e, "calibration");
+  e = f32::launch_pack(h->d_master, pk, 1, s);
+  f32::SaveArgs a = f32::save_args(h, frame, pk.t[0], pk.packed[0], true);
+  a.pl.np = f32::rup(npx, f32::kTile);
+  a.amax = amax;
+  if (e == hipSuccess) e = f32::launch_save<true>(h->W, a, h->num_cus, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  (void)hipFree(pk.packed[0]);
+  return gn_check_device(h, e, "calibration");
 }
 
 extern "C" gn_status glassnet_backward(gn_handle *h, const gn_frame *frame,

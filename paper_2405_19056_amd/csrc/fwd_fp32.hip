@@ -1,8 +1,7 @@
 // The fp32 forward: the whole per-pixel network (Sec. 3.3-3.4) in one kernel,
 // every activation in registers, fp32 arithmetic on the bf16 matrix cores
 // (fp32_core.h: operands split in three, six partial products).  The same
-// kernel, cut at compile time, serves the FP32 form's object streaming and
-// the FP8 calibration.
+// kernel, cut at compile time, serves the FP32 form's object streaming.
 //
 // Formulation.  Every map is D = A X with a 16-row tile of A (weights) as the
 // row operand and 16 pixels, one wave's, as the columns of
@@ -157,10 +156,9 @@ struct FwdArgs {
   // [pixel]
   float *sig, *z, *cnt;
   int32_t fresh;             // the state holds no sum yet
-  unsigned *amax;            // calibration: float bits of the largest z1
 };
 
-enum Mode { M_FULL, M_BEGIN, M_ACC, M_FINISH, M_CAL };
+enum Mode { M_FULL, M_BEGIN, M_ACC, M_FINISH };
 
 template <int MT, int WAVES>
 struct Pipe {
@@ -283,8 +281,8 @@ struct Pipe {
 template <int W, int MODE, bool ENC, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void f32_forward_kernel(FwdArgs a) {
   constexpr int MT = W / 16, KS = W / 32, kTile = WAVES * 16;
-  constexpr bool kTrunk = MODE == M_FULL || MODE == M_BEGIN || MODE == M_CAL;
-  constexpr bool kSlots = MODE == M_FULL || MODE == M_ACC || MODE == M_CAL;
+  constexpr bool kTrunk = MODE == M_FULL || MODE == M_BEGIN;
+  constexpr bool kSlots = MODE == M_FULL || MODE == M_ACC;
   constexpr bool kHead = MODE == M_FULL || MODE == M_FINISH;
   // LDS: the stage ring | biases | sigma per wave | slot order per pixel
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
@@ -300,7 +298,6 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void f32_forward_kernel(FwdA
   pipe.start(a.packed, lds, a.pg);       // ends with a barrier
   const int hw = a.hw, nblk = ENC ? pe_blocks(a.pe) : 1;
   const int64_t ntiles = (a.npx + kTile - 1) / kTile;
-  float amax = 0.0f;
 
   // A lane's pixel of a tile (tail lanes recompute a real pixel), and the
   // first loads it waits for: the inputs of F1 (without encoding) and the
@@ -452,20 +449,12 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void f32_forward_kernel(FwdA
           }
           return split8(x);
         });
-        if constexpr (MODE == M_CAL) {
-          if (valid)
+        put(acc, true);
+        bias(L_T2);
+        pipe.chain(acc, in);
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-              for (int r = 0; r < 4; ++r) amax = fmaxf(amax, acc[mt][r]);
-        } else {
-          put(acc, true);
-          bias(L_T2);
-          pipe.chain(acc, in);
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) Z[mt] += relu4(acc[mt]) * m;
-          cnt += m;
-        }
+        for (int mt = 0; mt < MT; ++mt) Z[mt] += relu4(acc[mt]) * m;
+        cnt += m;
 #pragma unroll
         for (int j = 0; j < 3; ++j) raw[j] = rn[j];
         al = an;
@@ -535,11 +524,6 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void f32_forward_kernel(FwdA
       }
     }
   }
-  if constexpr (MODE == M_CAL) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) amax = fmaxf(amax, __shfl_xor(amax, d));
-    if (lane == 0) atomicMax(a.amax, __float_as_uint(amax));   // non-negative: bit order
-  }
 }
 
 template <int W, int MODE, bool ENC, int WAVES>
@@ -581,7 +565,6 @@ static hipError_t launch(int W, int mode, const FwdArgs &a, int num_cus, hipStre
     case M_BEGIN: return GO(M_BEGIN);
     case M_ACC: return GO(M_ACC);
     case M_FINISH: return launch_width<M_FINISH, false>(W, a, num_cus, s);   // reads no encoded input
-    case M_CAL: return GO(M_CAL);
   }
 #undef GO
   return hipErrorInvalidValue;
@@ -607,39 +590,23 @@ hipError_t gn_f32_pack(gn_handle *h, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The handle's packed fp32 weights: GN_FP32 handles pack them with every
-// upload; the others hold none until a calibration asks, and pack per call.
-static gn_status f32_weights(gn_handle *h, hipStream_t s) {
-  if (h->cfg.precision == GN_FP32) return GN_OK;
-  hipError_t e = hipSuccess;
-  if (!h->d_f32) {
-    const size_t bytes = gn_f32_packed_bytes(h->W, h->pl.pe);
-    e = hipMalloc((void **)&h->d_f32, bytes);
-    if (e == hipSuccess) h->bytes_held += bytes; else h->d_f32 = nullptr;
-  }
-  if (e == hipSuccess) e = gn_f32_pack(h, s);
-  return gn_check_device(h, e, "fp32 weight packing");
-}
-
 static gn_status f32_run(gn_handle *h, const gn_frame *fr, int mode, f32::FwdArgs &a, bool canonical,
                          const char *what, hipStream_t s) {
   const int64_t npx = (int64_t)fr->n * fr->h * fr->w;
   if ((npx + 4095) / 4096 * 4096 > gn_f32_max_px)
     return gn_set_error(GN_E_INVAL, "more than 3 * 2^20 pixels in one call");
-  const gn_status st = f32_weights(h, s);
-  if (st != GN_OK) return st;
   f32::OpTable t;
   f32::make_ops(h->W, h->pl.pe, &t);
   auto first = [&](f32::Op o) { return t.op[o].stage0; };
-  const bool trunk = mode == f32::M_FULL || mode == f32::M_BEGIN || mode == f32::M_CAL;
-  const bool slots = mode == f32::M_FULL || mode == f32::M_ACC || mode == f32::M_CAL;
+  const bool trunk = mode == f32::M_FULL || mode == f32::M_BEGIN;
+  const bool slots = mode == f32::M_FULL || mode == f32::M_ACC;
   const bool head = mode == f32::M_FULL || mode == f32::M_FINISH;
   const int k = slots ? fr->k : 0;
   // (an ACC call starts with T1's sigma part, a FINISH call with T3)
   a.pg.pre0 = trunk ? first(f32::O_F1) : first(slots ? f32::O_T1S : f32::O_T3);
   a.pg.pre1 = slots ? first(f32::O_T1A) : (trunk ? first(f32::O_T1S) : t.stages);
   a.pg.loop0 = first(f32::O_T1A);
-  a.pg.loop1 = first(mode == f32::M_CAL ? f32::O_T2 : f32::O_T3);
+  a.pg.loop1 = first(f32::O_T3);
   a.pg.post0 = first(f32::O_T3);
   a.pg.post1 = t.stages;
   a.pg.k = k;
@@ -665,12 +632,6 @@ gn_status gn_f32_forward(gn_handle *h, const gn_frame *frame, float *out, hipStr
   f32::FwdArgs a{};
   a.out = out;
   return f32_run(h, frame, f32::M_FULL, a, true, "fp32 forward", s);
-}
-
-gn_status gn_f32_calibrate(gn_handle *h, const gn_frame *frame, unsigned *amax, hipStream_t s) {
-  f32::FwdArgs a{};
-  a.amax = amax;
-  return f32_run(h, frame, f32::M_CAL, a, false, "calibration", s);
 }
 
 // Object streaming of GN_FP32 handles: the state holds sigma and the running

@@ -62,9 +62,9 @@ gn_status gn_prepare_weights(gn_handle *h, hipStream_t stream);
 gn_status gn_serve_init(gn_handle *h);
 void gn_serve_shutdown(gn_handle *h);
 void gn_bwd_free(gn_handle *h);
-// The fp32 kernels (fwd_fp32.hip): the packed weights of a handle, the FP32
-// forward and the FP8 calibration (amax: device float bits of the largest
-// h-layer-1 activation).  Every fp32 call (and the backward) covers at most
+// The fp32 kernels: a GN_FP32 handle's packed weights and forward
+// (fwd_fp32.hip), the FP8 calibration (bwd_fp32.hip; amax: device float bits of
+// the largest h-layer-1 activation).  Every fp32 call (and the backward) covers at most
 // gn_f32_max_px pixels (rounded up to 4096).
 constexpr int64_t gn_f32_max_px = (int64_t)3 << 20;
 size_t gn_f32_packed_bytes(int W, int pe);
