@@ -50,7 +50,7 @@ constexpr int kFrag = 1024;            // one bf16 A fragment: 64 lanes x 16 B
 struct MfmaArgs {
   const uint8_t *packed;
   int64_t stage_off[kMaxStages + 1];
-  int64_t res_off, res_bytes, bias_off, t2q_off, t2s_off;
+  int64_t res_off, res_bytes, stage_max, bias_off, t2q_off, t2s_off;
   FwdBatch b;
   const FrameDesc *frames;
   const TileRef *tiles;
@@ -122,7 +122,16 @@ __device__ __forceinline__ f32x4 mma_fp8(i32x8 a, i32x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 0, 0, 0, 127, 0, 127);
 }
 
-__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// s_waitcnt for at most VM vector-memory and LGKM LDS/scalar operations in
+// flight (15: any).  The builtin and not inline assembly, so that the compiler
+// knows what has landed and puts no wait of its own before its use.
+template <int VM, int LGKM>
+__device__ __forceinline__ void wait_cnt() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | (LGKM << 8) | ((VM >> 4) << 14));
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void wait_vm() { wait_cnt<0, 15>(); }
 
 // The positional-encoding blocks of x (Sec. 3.4) up to block NB - 1: x, then
 // sin(2^k pi x) (block 2k + 1) and cos(2^k pi x) (block 2k + 2).  Level 0
@@ -156,8 +165,12 @@ __device__ __forceinline__ void pe_blocks_of(float x, float (&e)[NB]) {
 // LDS once vmcnt <= N; LDS traffic is drained and every wave has arrived.
 template <int N>
 __device__ __forceinline__ void stage_sync_after_stores() {
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+  wait_cnt<N, 0>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
+// Stage boundary: the next stage's copy has landed, every wave has arrived.
+__device__ __forceinline__ void stage_sync() { stage_sync_after_stores<0>(); }
 
 // Copy `bytes` (a multiple of 1 KiB) from global to LDS: each wave moves whole
 // 1 KiB blocks, lane i writing bytes [16 i, 16 i + 16) of its block.
@@ -167,6 +180,20 @@ __device__ __forceinline__ void lds_fill(uint8_t *dst, const uint8_t *src, int64
     __builtin_amdgcn_global_load_lds(
         (const void *)(src + off + lane * 16),
         (__attribute__((address_space(3))) void *)(dst + off), 16, 0, 0);
+  }
+}
+
+// The same for a compile-time size: straight-line copies.
+template <int BYTES>
+__device__ __forceinline__ void lds_copy(uint8_t *dst, const uint8_t *src, int wave, int lane) {
+  constexpr int kBlocks = BYTES / kFrag;
+#pragma unroll
+  for (int i = 0; i < (kBlocks + kWaves - 1) / kWaves; ++i) {
+    const int b = i * kWaves + wave;
+    if (kBlocks % kWaves == 0 || i < kBlocks / kWaves || b < kBlocks)
+      __builtin_amdgcn_global_load_lds((const void *)(src + (uint32_t)(b * kFrag + lane * 16)),
+                                       (__attribute__((address_space(3))) void *)(dst + b * kFrag),
+                                       16, 0, 0);
   }
 }
 
@@ -325,6 +352,28 @@ struct Shape {
   static constexpr int kBiasBytes = kNumLayers * W * 4;
 };
 
+// Bytes of the resident weights (T1's slot columns, T2 and, in fp8, T2's row
+// scales) and of a stage buffer (the largest stage: R's first layer, or half
+// of the encoded F1).
+template <int W, int PREC, int PE>
+struct LdsMap {
+  static constexpr int MT = W / 16, KS = W / 32;
+  static constexpr int kT1A = (MT * (PE > 0 ? pe_k16_steps(PE) : 1) * 512 + 1023) & ~1023;
+  static constexpr int kRes =
+      kT1A + (PREC == GN_FP8_T ? MT * 2048 + ((W * 4 + 1023) & ~1023) : MT * KS * kFrag);
+  static constexpr int kF1 = PE > 0 ? (pe_blocks(PE) + 1) / 2 : 0;
+  static constexpr int kStage = MT * (KS + 1 > kF1 ? KS + 1 : kF1) * kFrag;
+  static constexpr int kStatic = kRes + Shape<W>::kBiasBytes + 2 * kStage;
+  // bytes of stage s (without encoding F1 and F2 share stage 0)
+  static constexpr int stage_bytes(int s) {
+    const int sq = MT * KS * kFrag, last = kNumStages + stage_shift(PE) - 1;
+    if (s == last) return sq + KS * kFrag;                       // R2, R3
+    if (s == last - 1) return sq + MT * kFrag;                   // R1
+    if (PE == 0) return s == 0 ? MT * kFrag + sq : sq;
+    return s == 0 ? kF1 * MT * kFrag : (s == 1 ? (pe_blocks(PE) - kF1) * MT * kFrag : sq);
+  }
+};
+
 // Object-streaming state of one tile (modes other than FWD_FULL): sigma as
 // bf16 B fragments [wave][t][ks][lane], the running masked sum Z of h's hidden
 // layer as fp32 accumulator rows [wave][t][mt][lane], the active-slot count
@@ -348,7 +397,7 @@ struct StreamTile {
 template <int W, int PREC, int MODE, int PE>
 __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
   constexpr int MT = Shape<W>::MT, KS = Shape<W>::KS;
-  constexpr int kShift = stage_shift(PE), kStages = kNumStages + kShift;
+  constexpr int kShift = stage_shift(PE);
   // stage of each weight group (F1 and F2 share stage 0 without encoding)
   constexpr int sF1 = 0, sF1B = 1, sF2 = kShift, sF3 = 1 + kShift, sT1S = 2 + kShift,
                 sT3 = 3 + kShift, sB1S = 4 + kShift, sB1T = 5 + kShift, sB2 = 6 + kShift,
@@ -360,44 +409,42 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
   constexpr bool kSlots = MODE == FWD_FULL || MODE == FWD_ACC;     // runs the slot loop
   constexpr bool kTrunk = MODE == FWD_FULL || MODE == FWD_BEGIN;   // runs F
   constexpr bool kHead = MODE == FWD_FULL || MODE == FWD_FINISH;   // runs T3, B, R
-  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   const int wave = threadIdx.x >> 6;
 
-  // LDS map: [resident | biases | slot order | stage buffer 0 | stage buffer 1]
-  const int64_t res_bytes = a.res_bytes;
-  uint8_t *L_res = lds;
-  float *L_bias = (float *)(lds + res_bytes);
-  int64_t stage_max = 0;
-#pragma unroll
-  for (int s = 0; s < kStages; ++s)
-    stage_max = max(stage_max, a.stage_off[s + 1] - a.stage_off[s]);
+  // LDS: the resident weights, the biases and the two stage buffers are arrays
+  // of their own (the compiler makes an LDS read wait for every direct
+  // global->LDS copy in flight that may write the array it reads: with one
+  // array for all, each stage began by waiting for the copy of the next one),
+  // then [slot order | alphas | sigma] of a size the launch decides.
+  using LM = LdsMap<W, PREC, PE>;
+  __shared__ __attribute__((aligned(1024))) uint8_t L_res[LM::kRes];
+  __shared__ __attribute__((aligned(1024))) float L_bias[kNumLayers * W];
+  __shared__ __attribute__((aligned(1024))) uint8_t L_stage0[LM::kStage];
+  __shared__ __attribute__((aligned(1024))) uint8_t L_stage1[LM::kStage];
+  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+  constexpr int res_bytes = LM::kRes, stage_max = LM::kStage;
   // slot-order table: for each pixel of the tile, its slots' indices in
   // canonical order (kpad bytes per pixel, a multiple of 4), and the tile's
   // alphas [slot][pixel] that the order is computed from (aslots slots)
   // (in sigma's LDS parking area, free until F's last layer ends, when that
   // area holds at least the table)
-  uint8_t *L_perm = lds + res_bytes + Shape<W>::kBiasBytes;
-  uint8_t *L_stage0 =
+  uint8_t *L_perm = lds;
+  float *L_alpha = (float *)(L_perm + (size_t)kTilePx * a.kpad);
+  uint8_t *L_sig =
       L_perm + (size_t)kTilePx * a.kpad + (a.alpha_alias ? 0 : (size_t)kTilePx * 4 * a.aslots);
-  uint8_t *L_stage1 = L_stage0 + stage_max;
-  float *L_alpha = a.alpha_alias ? (float *)(L_stage1 + stage_max)
-                                 : (float *)(L_perm + (size_t)kTilePx * a.kpad);
   // FWD_FINISH runs an odd number of stages per tile, so its buffer parity
   // flips from one tile to the next (par); every other mode keeps par = 0.
   int par = 0;
   auto stage_buf = [&](int s) { return ((s + par) & 1) ? L_stage1 : L_stage0; };
   // resident weights of the slot loop and all biases, once per workgroup
   const int lane0 = threadIdx.x & 63;
-  auto fill_stage0 = [&](int s) {
-    lds_fill(stage_buf(s), a.packed + a.stage_off[s], a.stage_off[s + 1] - a.stage_off[s], wave,
-             lane0);
-  };
+#define FILL0(s) lds_copy<LM::stage_bytes(s)>(stage_buf(s), a.packed + a.stage_off[s], wave, lane0)
   // bf16: [T1A | T2 (bf16)]; fp8: [T1A | T2 (fp8, 2 KiB fragments) | T2 row scales]
   constexpr bool kFp8 = PREC == GN_FP8_T;
   // fragment reads held ahead of their MFMAs (layer, mm): everywhere in bf16;
   // in fp8 everywhere but T3 and B's first layer (it spills there)
   constexpr bool kEarly = true, kEarlyT3B1 = !kFp8;
-  constexpr int kT1ABytes = (MT * kNK16 * 512 + 1023) & ~1023;   // K=16 fragments of 512 B
+  constexpr int kT1ABytes = LM::kT1A;   // K=16 fragments of 512 B
   if constexpr (kSlots) {
     if (kFp8) {
       constexpr int64_t t1a = kT1ABytes;
@@ -412,13 +459,13 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
     // FULL streams every stage; BEGIN (without encoding) and ACC keep their
     // few stages resident for the whole launch; BEGIN with encoding streams
     // its four stages per tile; FINISH starts its pipeline at T3's stage.
-    if constexpr (MODE == FWD_FULL) fill_stage0(sF1);
+    if constexpr (MODE == FWD_FULL) FILL0(sF1);
     if constexpr (MODE == FWD_BEGIN) {
-      fill_stage0(sF1);
-      if constexpr (PE == 0) fill_stage0(sF3);
+      FILL0(sF1);
+      if constexpr (PE == 0) FILL0(sF3);
     }
-    if constexpr (MODE == FWD_ACC) fill_stage0(sT1S);
-    if constexpr (MODE == FWD_FINISH) fill_stage0(sT3);
+    if constexpr (MODE == FWD_ACC) FILL0(sT1S);
+    if constexpr (MODE == FWD_FINISH) FILL0(sT3);
   }
   wait_vm();
   __syncthreads();
@@ -515,10 +562,7 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
     const uint8_t *packed = a.packed;
     asm volatile("" : "+v"(lane), "+s"(packed));
     const int g = lane >> 4, col = lane & 15;
-    auto fill_stage = [&](int s) {
-      lds_fill(stage_buf(s), packed + a.stage_off[s], a.stage_off[s + 1] - a.stage_off[s], wave,
-               lane);
-    };
+#define FILL(s) lds_copy<LM::stage_bytes(s)>(stage_buf(s), packed + a.stage_off[s], wave, lane)
     // ---- the tile's frame (resolved one tile ahead)
     const TileInfo ti = nti;
     gcfloat *Gp = ti.G, *Lp = ti.L;
@@ -550,7 +594,7 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
     // fewer) while sigma is parked, so their tails serve the last waves.
     const bool sig_in_lds = wave < a.sig_lds_waves;
     const int nfree = a.sig_lds_waves - a.sig_tail_waves;
-    uint8_t *sig_lds = wave < nfree ? L_stage1 + stage_max + (size_t)wave * kSigBytes
+    uint8_t *sig_lds = wave < nfree ? L_sig + (size_t)wave * kSigBytes
                                     : ((wave - nfree) & 1 ? L_stage1 : L_stage0) + stage_max -
                                           (size_t)(1 + (wave - nfree) / 2) * kSigBytes;
     uint8_t *sig_slot = a.sig_scratch + ((size_t)blockIdx.x * kWaves + wave) * kSigBytes;
@@ -574,26 +618,28 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
       u32x4 h2[kNT][KS];
       if constexpr (PE == 0) {
         // ================= stage 0: F layers 1-2 =================
-        if constexpr (MODE == FWD_FULL) fill_stage(sF3);
+        // (xr is read before the copies are issued: waiting for it behind them
+        // would wait for them too)
+        u32x4 x[kNT][1];
+#pragma unroll
+        for (int t = 0; t < kNT; ++t)
+          x[t][0] = u32x4{pk_bf16(xr[t][0], xr[t][1]), pk_bf16(xr[t][2], xr[t][3]),
+                          pk_bf16(xr[t][4], xr[t][5]), pk_bf16(xr[t][6], xr[t][7])};
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (MODE == FWD_FULL) FILL(sF3);
         if (canon_fast) copy_alphas();
         {
-          u32x4 x[kNT][1];
-#pragma unroll
-          for (int t = 0; t < kNT; ++t)
-            x[t][0] = u32x4{pk_bf16(xr[t][0], xr[t][1]), pk_bf16(xr[t][2], xr[t][3]),
-                            pk_bf16(xr[t][4], xr[t][5]), pk_bf16(xr[t][6], xr[t][7])};
           const uint8_t *S = stage_buf(sF1);
           u32x4 h1[kNT][KS];
           layer<MT, 1, true, kEarly>(h1, S, x, bF1, g, lane);
           layer<MT, KS, true, kEarly>(h2, S + f1_bytes, h1, bF2, g, lane);
         }
         if constexpr (MODE == FWD_FULL) {
-          wait_vm();
-          __syncthreads();
+          stage_sync();
         }
       } else {
         // ====== stages 0-1: F layer 1 on the encoded input; stage 2: F layer 2 ======
-        fill_stage(sF1B);
+        FILL(sF1B);
         f32x4 acc[kNT][MT];
         bias_init(acc, bF1, g);
         {
@@ -601,9 +647,8 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
           enc_frags<0, kF1A>(xr, x);
           mm<MT, kF1A, kEarly>(acc, stage_buf(sF1), x, lane);
         }
-        wait_vm();
-        __syncthreads();
-        fill_stage(sF2);
+        stage_sync();
+        FILL(sF2);
         u32x4 h1[kNT][KS];
         {
           u32x4 x[kNT][kF1B];
@@ -611,17 +656,15 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
           mm<MT, kF1B, kEarly>(acc, stage_buf(sF1B), x, lane);
           to_frags<MT, true>(acc, h1);
         }
-        wait_vm();
-        __syncthreads();
-        fill_stage(sF3);
+        stage_sync();
+        FILL(sF3);
         if (canon_fast) copy_alphas();
         layer<MT, KS, true, kEarly>(h2, stage_buf(sF2), h1, bF2, g, lane);
-        wait_vm();
-        __syncthreads();
+        stage_sync();
       }
 
       // ================= F layer 3 -> sigma =================
-      if constexpr (MODE == FWD_FULL) fill_stage(sT1S);
+      if constexpr (MODE == FWD_FULL) FILL(sT1S);
       // Canonical order of each pixel's slots, into this wave's part of the
       // LDS table (byte r of a pixel's entry: its slot of rank r).  Keys: the
       // bits of alpha for active slots, 0xFFFFFF00 + j for an inactive slot j
@@ -693,7 +736,7 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
       // before any wave parks sigma there
       if (canon_fast && a.alpha_alias) __syncthreads();
       if constexpr (MODE == FWD_BEGIN && PE > 0) {
-        if (has_next) fill_stage(sF1);      // the next tile's first stage
+        if (has_next) FILL(sF1);      // the next tile's first stage
       }
       layer<MT, KS, false, kEarly>(sig, stage_buf(sF3), h2, bF3, g, lane);
       if constexpr (MODE == FWD_BEGIN) {
@@ -708,8 +751,7 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
         }
         if constexpr (PE > 0) {
           // the next tile's first stage has landed; this stage's buffer is free
-          wait_vm();
-          __syncthreads();
+          stage_sync();
         }
       } else {
         if (sig_in_lds) {
@@ -734,7 +776,7 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
 
     if constexpr (kSlots) {
       // ================= stage 2: u = W1s sigma + c1, then the slot loop =======
-      if constexpr (MODE == FWD_FULL) fill_stage(sT3);
+      if constexpr (MODE == FWD_FULL) FILL(sT3);
       if constexpr (MODE == FWD_ACC) {
 #pragma unroll
         for (int t = 0; t < kNT; ++t)
@@ -983,14 +1025,12 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
         }
         if (has_next) nti = resolve(tile + gridDim.x);
       } else {
-        wait_vm();
-        __syncthreads();
+        stage_sync();
       }
     }
 
     if constexpr (kHead) {
       // ================= stage 3: pool and h layer 3 -> tau =================
-      fill_stage(sB1S);
       u32x4 sig2[kNT][KS];
       if constexpr (MODE == FWD_FINISH) {
         // the pool state and sigma come from the streaming state
@@ -1003,14 +1043,21 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
 #pragma unroll
           for (int k = 0; k < KS; ++k) sig2[t][k] = st_sig[(t * KS + k) * 64];
         }
+      } else if (sig_in_lds) {
+#pragma unroll
+        for (int t = 0; t < kNT; ++t)
+#pragma unroll
+          for (int k = 0; k < KS; ++k)
+            sig2[t][k] = *(const u32x4 *)(sig_lds + (t * KS + k) * kFrag + lane * 16);
       } else {
 #pragma unroll
         for (int t = 0; t < kNT; ++t)
 #pragma unroll
           for (int k = 0; k < KS; ++k)
-            sig2[t][k] = sig_in_lds ? *(const u32x4 *)(sig_lds + (t * KS + k) * kFrag + lane * 16)
-                                    : *(const u32x4 *)(sig_slot + (t * KS + k) * kFrag + lane * 16);
+            sig2[t][k] = *(gu32x4 *)(sig_slot + (t * KS + k) * kFrag + lane * 16);
       }
+      __builtin_amdgcn_sched_barrier(0);
+      FILL(sB1S);
       u32x4 tau[kNT][KS];
       {
         // fp8: the running sum is in units of the dequantisation factor s
@@ -1044,26 +1091,23 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
         mm<MT, KS, kEarlyT3B1>(acc, stage_buf(sT3), zs, lane);
         to_frags<MT, false>(acc, tau);
       }
-      wait_vm();
-      __syncthreads();
+      stage_sync();
 
       // ================= stages 4-5: B layer 1 on [sigma; tau] =================
-      fill_stage(sB1T);
+      FILL(sB1T);
       f32x4 accB[kNT][MT];
       bias_init(accB, bB1, g);
       mm<MT, KS, kEarlyT3B1>(accB, stage_buf(sB1S), sig2, lane);
-      wait_vm();
-      __syncthreads();
+      stage_sync();
 
-      fill_stage(sB2);
+      FILL(sB2);
       u32x4 hb[kNT][KS];
       mm<MT, KS, kEarlyT3B1>(accB, stage_buf(sB1T), tau, lane);
       to_frags<MT, true>(accB, hb);
-      wait_vm();
-      __syncthreads();
+      stage_sync();
 
       // ================= stage 6: B layer 2 =================
-      fill_stage(sB3);
+      FILL(sB3);
       // L_d for R's first layer (stage 8), requested two stages early
       float ldr[kNT][3];
 #pragma unroll
@@ -1078,18 +1122,16 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
 #pragma unroll
           for (int k = 0; k < KS; ++k) hb[t][k] = hb2[t][k];
       }
-      wait_vm();
-      __syncthreads();
+      stage_sync();
 
       // ================= stage 7: B layer 3 -> phi =================
-      fill_stage(sR1);
+      FILL(sR1);
       u32x4 phi[kNT][KS];
       layer<MT, KS, false, kEarly>(phi, stage_buf(sB3), hb, bB3, g, lane);
-      wait_vm();
-      __syncthreads();
+      stage_sync();
 
       // ================= stage 8: R layer 1 on [phi; L_d] =================
-      fill_stage(sR2);
+      FILL(sR2);
       u32x4 hr[kNT][KS];
       {
         u32x4 ld[kNT][1];
@@ -1102,19 +1144,21 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
         mm<MT, 1, kEarly>(acc, stage_buf(sR1) + r1p_bytes, ld, lane);
         to_frags<MT, true>(acc, hr);
       }
-      wait_vm();
-      __syncthreads();
+      stage_sync();
 
       // ================= stage 9: R layers 2-3 -> radiance =================
       if (has_next) {
+        // (the tile's frame first: reading its table behind the copies would
+        // wait for them)
         if constexpr (MODE == FWD_FULL) {
-          fill_stage(sF1);
           nti = resolve(tile + gridDim.x);
+          __builtin_amdgcn_sched_barrier(0);
+          FILL(sF1);
           load_x(nti, lane, xr);
         } else {
           // the next tile's T3 stage goes to the buffer this tile's R1 stage used
-          lds_fill(((sT3 + (par ^ 1)) & 1) ? L_stage1 : L_stage0, packed + a.stage_off[sT3],
-                   a.stage_off[sT3 + 1] - a.stage_off[sT3], wave, lane);
+          lds_copy<LM::stage_bytes(sT3)>(((sT3 + (par ^ 1)) & 1) ? L_stage1 : L_stage0,
+                                         packed + a.stage_off[sT3], wave, lane);
           nti = resolve(tile + gridDim.x);
         }
       }
@@ -1140,6 +1184,8 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
       if constexpr (MODE == FWD_FINISH) par ^= 1;
     }
   }
+#undef FILL0
+#undef FILL
 }
 
 // ---- weight packing ---------------------------------------------------------
@@ -1315,6 +1361,11 @@ static hipError_t launch_one(const MfmaArgs &a, int grid, size_t lds, hipStream_
   // The attribute is per function; a layout of a different size (another
   // handle's) raises it again.
   static size_t attr_lds = 0;
+  // `lds` counts every array; the launch passes what the kernel does not declare
+  using LM = LdsMap<W, PREC, PE>;
+  if (lds < (size_t)LM::kStatic || a.res_bytes != LM::kRes || a.stage_max != LM::kStage)
+    return hipErrorInvalidValue;
+  lds -= LM::kStatic;
   if (lds > attr_lds) {
     hipError_t e = hipFuncSetAttribute((const void *)fwd_mfma_kernel<W, PREC, MODE, PE>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1384,6 +1435,9 @@ static hipError_t launch_impl(int W, int precision, int pool, const uint8_t *pac
   for (int s = 0; s <= kMaxStages; ++s) a.stage_off[s] = s <= pl.nstages ? pl.stage_off[s] : 0;
   a.res_off = pl.resident_off;
   a.res_bytes = resident_bytes(pl, precision);
+  a.stage_max = 0;
+  for (int s = 0; s < pl.nstages; ++s)
+    a.stage_max = std::max(a.stage_max, pl.stage_off[s + 1] - pl.stage_off[s]);
   a.bias_off = pl.bias_off;
   a.t2q_off = pl.t2q_off;
   a.t2s_off = pl.t2scale_off;
