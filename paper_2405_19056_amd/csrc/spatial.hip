@@ -22,22 +22,26 @@
 // and read through a 2 x 2 nearest upsample (the U-Net's skip join), so the
 // concatenation and the upsample are never materialised.
 //
-// Work split.  A workgroup of 8 waves owns 512 output pixels, each wave 64
-// consecutive pixels of one row (4 N-tiles) and every output channel (up to
-// 8 M-tiles: 32 accumulators of 4 floats).  The weights stream through LDS
-// in chunks of kChunk K-steps (direct global->LDS copies, two buffers, one
-// chunk ahead), every fragment read once per wave and used for its 4 N-tiles.
-// The input fragments of the next K-step are loaded while the current one's
-// MFMAs run.
+// Work split (sp_conv_kernel).  A workgroup of four waves owns a tile of TR
+// rows x 16 columns and every output channel.  It stages the tile's inputs and
+// a one-pixel halo, all channels, in LDS once (each value is read nine times
+// from there, from L2 before), then runs the K loop without a barrier: each
+// wave takes half of the output channels of half of the rows, its weight
+// fragments straight from L2 into registers several K-steps ahead, its input
+// fragments from LDS one step ahead.  Every output is the same sum in the same
+// order (tap, then channel block) whatever the tile.
 //
-// Epilogues: bias, ReLU, then one of: bf16 activation store, fp32 store, or
-// R's 3 outputs to the caller's [n][3][H][W] fp32 image.
+// Epilogues, through the LDS the halo has left: bias and ReLU, then a bf16
+// store (with the U-Net's 2 x 2 average where that is the next input), an fp32
+// store, or the following 1 x 1 convolution (the U-Nets' and R's last ones),
+// whose input then never leaves the chip.
 //
 // h over the buffers, the pool and T's last layer run in one kernel of their
 // own (sp_slots_kernel below): the per-buffer activations and the running
 // sum stay on the chip.  (The generic table also packs T's layers as
 // ordinary convs; only their biases are read from it.)
 #include <algorithm>
+#include <type_traits>
 
 #include "gn_internal.h"
 
@@ -50,19 +54,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kWaves = 8, kThreads = kWaves * 64;
-// N-tiles (16 pixels) per wave of the generic conv: 4 for the narrow convs,
-// 2 for the W = 128 ones (half the registers: two workgroups per CU, four
-// waves per SIMD to hide the input loads' latency)
-constexpr int kChunk = 4;                    // K-steps per LDS weight chunk (even)
-static_assert(kChunk % 2 == 0, "the conv loop takes the steps of a chunk in pairs");
+constexpr int kWaves = 8, kThreads = kWaves * 64;    // sp_slots_kernel's workgroup
 
-// K-steps of a conv's packed weights: taps x 32-channel blocks, rounded up to
-// whole chunks with zero fragments (the conv loop then runs whole chunks,
-// straight-line code the compiler keeps its loads ahead in).
-__host__ __device__ inline int padded_steps(int taps, int cbt) {
-  return (taps * cbt + kChunk - 1) / kChunk * kChunk;
-}
 constexpr int kFrag = 1024;                  // one A fragment: 64 lanes x 16 bytes
 
 __device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
@@ -72,10 +65,6 @@ __device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
 __device__ __forceinline__ f32x4 mma(u32x4 a, u32x4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
-__device__ __forceinline__ float bf16_to_f32(uint16_t v) {
-  return __uint_as_float((uint32_t)v << 16);
 }
 
 // Input loads go through buffer resources bounded by the input's size: a
@@ -93,195 +82,324 @@ __device__ __forceinline__ u32x4 bld(rsrc_t r, uint32_t off) {
 
 }  // namespace
 
-// One convolution launch (host fills it; see SpConv in the launcher).
+// One 3 x 3 convolution launch.
 struct SpConvArgs {
-  const uint8_t *in0;       // bf16 [n][H][W][c0]
-  const uint8_t *in1;       // bf16 [n][H1][W1][c1] or null; up1: H1 = H / 2, W1 = W / 2
-  int c0, c1, up1;
+  const uint8_t *in0;       // bf16 [n][H][W][C0], or null: F's input from the caller's planes
+  const uint8_t *in1;       // bf16 [n][H1][W1][C1] (Src: half or full resolution)
+  const float *gbuf, *scene;  // planes of F's input or of L_d
   const uint8_t *wfrag;     // A fragments [step][mt][lane] (16 B each)
-  const float *bias;        // [MT * 16] (zero past the real outputs)
-  int steps;                // K-steps = taps x (c0 + c1) / 32
-  int steps_pad;            // the packed steps: steps rounded up to whole chunks
-  int ksize;                // 1 or 3
+  const float *bias;        // [MT * 16]
+  const uint8_t *wfrag1;    // the following 1 x 1 conv's, its bias
+  const float *bias1;
   int n, H, Wd;             // output (= in0) size
-  int cout_pad;             // output channel count of the bf16 / fp32 layouts (MT * 16)
-  // epilogue
-  int relu;
-  uint8_t *out_bf;          // bf16 [n][H][W][cout_pad], or null
-  float *out_f32;           // fp32 [n][H][W][cout_pad], or null
-  float *out_rgb;           // fp32 [n][3][H][W] (3 real outputs), or null
+  uint8_t *out;             // bf16 [n][H][W][W], or fp32 (E_F32), or the image (E_RGB)
+  uint8_t *pool;            // bf16 [n][H/2][W/2][W]: the 2 x 2 average, or null
 };
 
 namespace {
 
-template <int MT, int kNT>
-__global__ __launch_bounds__(kThreads, kNT == 2 ? 4 : 1) void sp_conv_kernel(SpConvArgs a) {
-  constexpr int kWavePx = kNT * 16;            // pixels per wave (one row segment)
+// The second source: none, at full resolution, at half resolution through a
+// 2 x 2 nearest upsample, or L_d's planes.
+enum Src { S_NONE, S_FULL, S_HALF, S_LIGHT };
+// ReLU and a bf16 store (and average); an fp32 store; ReLU, then the 1 x 1
+// conv to W channels, or to the image.
+enum Epi { E_ACT, E_F32, E_CONV1, E_RGB };
+
+constexpr int kConvThreads = 256, kTC = 16, kHW = kTC + 2;   // tile columns, halo columns
+
+// LDS position (bytes) of 16-byte unit u of a pixel with UN units: XORed by
+// the pixel so that 16 neighbouring pixels' same unit fills all banks.
+template <int UN>
+__device__ __forceinline__ uint32_t unit_at(int px, int u) {
+  constexpr int kShift = UN >= 16 ? 0 : (UN == 8 ? 1 : 2);
+  return (uint32_t)(px * UN + (u ^ ((px >> kShift) & (UN < 16 ? UN - 1 : 15)))) * 16;
+}
+
+// A block of bf16 activations [..][C] around (y0, x0), `rows` x `cols` pixels,
+// into LDS; pixels outside the frame's H x Wd read zero.
+template <int CB, int ROWS, int COLS>
+__device__ __forceinline__ void stage_act(uint8_t *dst, const uint8_t *src, int n, int f, int H, int Wd,
+                                          int y0, int x0) {
+  constexpr int UN = 4 * CB, N = ROWS * COLS * UN, kIt = (N + kConvThreads - 1) / kConvThreads;
+  constexpr int kG = kIt < 11 ? kIt : 11;             // loads in flight per thread
+  const rsrc_t rs = make_rsrc(src, (uint32_t)((int64_t)n * H * Wd * CB * 64));
+#pragma unroll
+  for (int i0 = 0; i0 < kIt; i0 += kG) {
+    u32x4 v[kG];
+#pragma unroll
+    for (int j = 0; j < kG; ++j) {
+      const int e = min((int)threadIdx.x + (i0 + j) * kConvThreads, N - 1), px = e / UN, u = e % UN;
+      const int y = y0 + px / COLS, x = x0 + px % COLS;
+      const bool ok = y >= 0 && y < H && x >= 0 && x < Wd;
+      if (i0 + j < kIt)
+        v[j] = bld(rs, ok ? (uint32_t)((((int64_t)f * H + y) * Wd + x) * (CB * 64) + u * 16) : kOutside);
+    }
+#pragma unroll
+    for (int j = 0; j < kG; ++j) {
+      const int e = (int)threadIdx.x + (i0 + j) * kConvThreads, px = e / UN, u = e % UN;
+      if (i0 + j < kIt && e < N) *(u32x4 *)(dst + unit_at<UN>(px, u)) = v[j];
+    }
+  }
+}
+
+// The same for 32-channel blocks made from the caller's planes: F's input
+// [G 0..13; scene 0..15; 0, 0], or L_d (G 11..13) and zeros.
+template <bool LIGHT, int ROWS>
+__device__ __forceinline__ void stage_planes(uint8_t *dst, const float *gbuf, const float *scene,
+                                             int f, int H, int Wd, int y0, int x0) {
+  const int64_t hw = (int64_t)H * Wd;
+  for (int px = threadIdx.x; px < ROWS * kHW; px += kConvThreads) {
+    const int y = y0 + px / kHW, x = x0 + px % kHW;
+    const bool ok = y >= 0 && y < H && x >= 0 && x < Wd;
+    float c[32];
+#pragma unroll
+    for (int j = 0; j < 32; ++j) c[j] = 0.0f;
+    if (ok) {
+      const float *G = gbuf + (int64_t)f * kNG * hw + (int64_t)y * Wd + x;
+      if constexpr (LIGHT) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) c[j] = G[(11 + j) * hw];
+      } else {
+#pragma unroll
+        for (int j = 0; j < kNG; ++j) c[j] = G[j * hw];
+#pragma unroll
+        for (int j = 0; j < kNS; ++j) c[kNG + j] = scene[(int64_t)f * kNS + j];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      *(u32x4 *)(dst + unit_at<4>(px, u)) =
+          u32x4{pk_bf16(c[8 * u], c[8 * u + 1]), pk_bf16(c[8 * u + 2], c[8 * u + 3]),
+                pk_bf16(c[8 * u + 4], c[8 * u + 5]), pk_bf16(c[8 * u + 6], c[8 * u + 7])};
+  }
+}
+
+// LDS bytes of a tile: the two sources' halos, or the tile itself afterwards.
+template <int MT, int TR, int CB0, int SRC1, int CB1>
+struct ConvLds {
+  static constexpr int k0 = (TR + 2) * kHW * CB0 * 64;
+  static constexpr int k1 = SRC1 == S_NONE   ? 0
+                            : SRC1 == S_HALF ? (TR / 2 + 2) * (kTC / 2 + 2) * CB1 * 64
+                                             : (TR + 2) * kHW * CB1 * 64;
+  static constexpr int kTile = TR * kTC * MT * 32;
+  static constexpr int kBytes = k0 + k1 > kTile ? k0 + k1 : kTile;
+};
+
+// MT: output channels / 16; CB0, CB1: 32-channel blocks of the sources; PLANES:
+// the first source is F's input, made from the planes.
+//
+// What bounds it: at W = 128 and 8 rows a wave's K-step is 16 MFMAs (256
+// cycles) for 4 KiB of LDS reads and 4 KiB of weights, 64 bytes of each per
+// cycle and CU: half the LDS rate, the whole of L1's.  Two workgroups share a
+// CU; a 256^2 frame is one round of them, so a launch's halo loads and
+// epilogues (about half of its 19 us) overlap little.  256^2, W -> W: 19-24 us
+// against 35-40 with inputs read nine times through L2; the whole forward
+// (K = 4) 248 us against 470.
+template <int MT, int TR, int CB0, int SRC1, int CB1, bool PLANES, int EPI>
+__global__ __launch_bounds__(kConvThreads, 2) void sp_conv_kernel(SpConvArgs a) {
+  constexpr int MW = MT / 2, NT = TR / 2;               // a wave's tiles
+  constexpr int kCbt = CB0 + CB1, kSteps = 9 * kCbt;
+  constexpr int kAhead = TR == 8 ? 4 : 6;   // K-steps of weights in flight
+  constexpr int kWUn = MT * 2;                          // 16-byte units of an output pixel
+  using LD = ConvLds<MT, TR, CB0, SRC1, CB1>;
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g = lane >> 4, col = lane & 15;
+  uint8_t *L0 = lds, *L1 = lds + LD::k0;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, col = lane & 15, wm = wave & 1, wn = wave >> 1;
   const int H = a.H, Wd = a.Wd;
-  const int segs = (Wd + kWavePx - 1) / kWavePx;          // row segments per row
+  const int tx_n = (Wd + kTC - 1) / kTC, ty_n = (H + TR - 1) / TR;
   // Workgroups reach the 8 XCDs round-robin: give each XCD a contiguous run
-  // of tiles, so that the rows a 3 x 3 conv reads twice more (for the rows
-  // above and below) are mostly in its own L2.
+  // of tiles, so that neighbours' halos are mostly in its own L2.
   const int full = gridDim.x & ~7;
   const int tile = (int)blockIdx.x < full ? (blockIdx.x & 7) * (full >> 3) + (blockIdx.x >> 3)
                                           : (int)blockIdx.x;
-  const int64_t seg = (int64_t)tile * kWaves + wave;
-  const int64_t nseg = (int64_t)a.n * H * segs;
-  const bool live = seg < nseg;
-  const int64_t sg = live ? seg : nseg - 1;
-  // the wave's row segment (wave-uniform)
-  const int f = __builtin_amdgcn_readfirstlane((int)(sg / ((int64_t)H * segs)));
-  const int rem = (int)(sg - (int64_t)f * H * segs);
-  const int y = __builtin_amdgcn_readfirstlane(rem / segs);
-  const int x0 = __builtin_amdgcn_readfirstlane((rem - (rem / segs) * segs) * kWavePx);
-  const int r = a.ksize >> 1;
-  const int cb0 = a.c0 >> 5;                              // 32-channel blocks of in0
-  const int cbt = (a.c0 + a.c1) >> 5;
+  const int f = tile / (tx_n * ty_n), rem = tile - f * (tx_n * ty_n);
+  const int y0 = rem / tx_n * TR, x0 = rem % tx_n * kTC;
 
-  constexpr int kChunkBytes = kChunk * MT * kFrag;
-  const int nchunks = a.steps_pad / kChunk;
-  auto fill = [&](int c) {
-    const uint8_t *src = a.wfrag + (int64_t)c * kChunkBytes;
-    // a compile-time count of copies per wave (the compiler then knows how
-    // many vector-memory operations are in flight behind them)
-    constexpr int kCopies = (kChunk * MT + kWaves - 1) / kWaves;
+  // weight fragments of step s, this wave's half of the rows
+  const rsrc_t rw = make_rsrc(a.wfrag, (uint32_t)(kSteps * MT * kFrag));
+  auto load_a = [&](int s, u32x4 (&w)[MW]) {
 #pragma unroll
-    for (int i = 0; i < kCopies; ++i) {
-      const int off = (i * kWaves + wave) * kFrag;
-      if (off >= kChunkBytes) break;
-      __builtin_amdgcn_global_load_lds((const void *)(src + off + lane * 16),
-                                       (__attribute__((address_space(3))) void *)(lds + (c & 1) * kChunkBytes + off),
-                                       16, 0, 0);
+    for (int m = 0; m < MW; ++m)
+      w[m] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                           rw, lane * 16, (s * MT + wm * MW + m) * kFrag, 0));
+  };
+  u32x4 w[kAhead][MW];
+#pragma unroll
+  for (int s = 0; s < kAhead; ++s) load_a(s, w[s]);
+
+  if constexpr (PLANES) stage_planes<false, TR + 2>(L0, a.gbuf, a.scene, f, H, Wd, y0 - 1, x0 - 1);
+  else stage_act<CB0, TR + 2, kHW>(L0, a.in0, a.n, f, H, Wd, y0 - 1, x0 - 1);
+  if constexpr (SRC1 == S_FULL) stage_act<CB1, TR + 2, kHW>(L1, a.in1, a.n, f, H, Wd, y0 - 1, x0 - 1);
+  if constexpr (SRC1 == S_HALF)
+    stage_act<CB1, TR / 2 + 2, kTC / 2 + 2>(L1, a.in1, a.n, f, H / 2, Wd / 2, y0 / 2 - 1, x0 / 2 - 1);
+  if constexpr (SRC1 == S_LIGHT)
+    stage_planes<true, TR + 2>(L1, a.gbuf, nullptr, f, H, Wd, y0 - 1, x0 - 1);
+  __syncthreads();
+
+  // B fragments of step i of tap row dy (column i / kCbt, channel block i % kCbt)
+  auto load_b = [&](int dy, int i, u32x4 (&b)[NT]) {
+    const int cb = i % kCbt, dx = i / kCbt;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int r = wn * NT + t + dy, c = col + dx;      // halo coordinates
+      if (cb < CB0) {
+        b[t] = *(const u32x4 *)(L0 + unit_at<4 * CB0>(r * kHW + c, 4 * cb + g));
+      } else if constexpr (SRC1 == S_HALF) {
+        // full-resolution row y0 - 1 + r is half-resolution row (r + 1) / 2 of the block
+        const int h = ((r + 1) >> 1) * (kTC / 2 + 2) + ((c + 1) >> 1);
+        b[t] = *(const u32x4 *)(L1 + unit_at<4 * CB1>(h, 4 * (cb - CB0) + g));
+      } else if constexpr (SRC1 != S_NONE) {
+        b[t] = *(const u32x4 *)(L1 + unit_at<4 * CB1>(r * kHW + c, 4 * (cb - CB0) + g));
+      }
     }
   };
-
-  // B fragment of K-step s for N-tile t: pixel (y + dy - r, x0 + 16 t + col + dx - r),
-  // channels 32 cb + 8 g .. + 7 of the concatenated input; outside the frame
-  // the offset is past the buffer's bound and the load returns zeros.  Every
-  // lane loads, so each step issues exactly kNT loads: the chunk waits below
-  // count on that.
-  const int H1 = a.up1 ? H >> 1 : H, W1 = a.up1 ? Wd >> 1 : Wd;
-  const uint8_t *in0 = a.in0, *in1 = a.in1 ? a.in1 : a.in0;
-  const uint32_t bytes0 = (uint32_t)((int64_t)a.n * H * Wd * a.c0 * 2);
-  const uint32_t bytes1 = (uint32_t)((int64_t)a.n * H1 * W1 * a.c1 * 2);
-  auto load_b = [&](int s, u32x4 (&b)[kNT]) {
-    const int tap = s / cbt, cb = s - tap * cbt;
-    const int dy = tap / a.ksize - r, dx = tap % a.ksize - r;
-    const int yy = y + dy;
-    const bool yok = yy >= 0 && yy < H;
-    const int yc = min(max(yy, 0), H - 1);
-    const bool first = cb < cb0;
-    const int shift = first ? 0 : a.up1;
-    const int cs = first ? a.c0 : a.c1;
-    // byte offset of the row's first pixel and the channel block
-    const uint32_t rowoff =
-        first ? (uint32_t)((((int64_t)f * H + yc) * Wd * a.c0 + 32 * cb) * 2)
-              : (uint32_t)((((int64_t)f * H1 + (yc >> shift)) * W1 * a.c1 + 32 * (cb - cb0)) * 2);
-    uint32_t off[kNT];
+  f32x4 acc[NT][MW];
 #pragma unroll
-    for (int t = 0; t < kNT; ++t) {
-      const int xx = x0 + 16 * t + col + dx;
-      const bool ok = yok && xx >= 0 && xx < Wd;
-      off[t] = ok ? rowoff + (uint32_t)((((xx >> shift) * cs) + 8 * g) * 2) : kOutside;
-    }
-    // the source is wave-uniform: its resource is built in scalar registers
-    const rsrc_t rs = make_rsrc(first ? in0 : in1, first ? bytes0 : bytes1);
+  for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int t = 0; t < kNT; ++t) b[t] = bld(rs, off[t]);
-  };
-
-  f32x4 acc[kNT][MT];
+    for (int m = 0; m < MW; ++m) acc[t][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // one tap row: kRow steps, straight-line; the rows are a loop where all
+  // three would be too much code
+  constexpr int kRow = 3 * kCbt;
+  u32x4 b[2][NT];
+  load_b(0, 0, b[0]);
+  auto tap_row = [&](int dy, auto base) {
+    constexpr int s0 = base;                     // its first step, as far as the buffers go
 #pragma unroll
-  for (int t = 0; t < kNT; ++t)
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[t][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // one K-step: all MT weight fragments requested from LDS first (held there
-  // by a scheduling barrier, else each read sinks next to its MFMAs and is
-  // waited for alone), then the MFMAs
-  // (With two N-tiles per wave the fragments come in two groups of MT / 2,
-  // the second group's reads issued behind the first group's MFMAs: fewer
-  // registers, for four waves per SIMD.)
-  auto step = [&](const uint8_t *Ws, const u32x4 (&b)[kNT]) {
-    constexpr int kG = kNT >= 4 || MT < 8 ? MT : MT / 2;
-#pragma unroll
-    for (int m0 = 0; m0 < MT; m0 += kG) {
-      u32x4 w[kG];
-#pragma unroll
-      for (int i = 0; i < kG; ++i) w[i] = *(const u32x4 *)(Ws + (m0 + i) * kFrag + lane * 16);
+    for (int i = 0; i < kRow; ++i) {
+      const int q = s0 + i;
+      if (i + 1 < kRow) load_b(dy, i + 1, b[(q + 1) & 1]);
+      else load_b(min(dy + 1, 2), 0, b[(q + 1) & 1]);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int i = 0; i < kG; ++i)
+      for (int m = 0; m < MW; ++m)
 #pragma unroll
-        for (int t = 0; t < kNT; ++t) acc[t][m0 + i] = mma(w[i], b[t], acc[t][m0 + i]);
+        for (int t = 0; t < NT; ++t) acc[t][m] = mma(w[q % kAhead][m], b[q & 1][t], acc[t][m]);
       __builtin_amdgcn_sched_barrier(0);
+      load_a(min(dy * kRow + i + kAhead, kSteps - 1), w[q % kAhead]);   // past the last: re-read
     }
   };
-
-  fill(0);
-  // Two input sets: b0 holds the current step's fragments (chunks have an
-  // even step count, so each chunk starts with its first step in b0); the
-  // next step's loads (clamped to the last step: a harmless re-read) are in
-  // flight while the current step's MFMAs run.
-  u32x4 b0[kNT], b1[kNT];
-  load_b(0, b0);
-  for (int c = 0; c < nchunks; ++c) {
-    // The chunk's weights have landed: each wave waits for its own copies,
-    // then for everyone's.  Issued after the copies of chunk c (at the start
-    // of chunk c - 1) are only the input loads of chunk c - 1's steps, kNT per
-    // step, the last kChunk kNT of them still allowed in flight.
-    // (A plain __syncthreads would also drain those input loads.)  The
-    // LDS reads of the buffer the next fill overwrites are drained too.
-    if (c == 0)
-      asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    else
-      asm volatile("s_waitcnt vmcnt(%0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::"n"(kChunk * kNT)
-                   : "memory");
-    if (c + 1 < nchunks) fill(c + 1);
-    const uint8_t *Wc = lds + (c & 1) * kChunkBytes;
-    const int s0 = c * kChunk;
-    // steps past the real ones multiply zero weights (their inputs re-read
-    // the last real step's)
-#pragma unroll
-    for (int j = 0; j < kChunk; j += 2) {
-      load_b(min(s0 + j + 1, a.steps - 1), b1);
-      __builtin_amdgcn_sched_barrier(0);
-      step(Wc + j * MT * kFrag, b0);
-      load_b(min(s0 + j + 2, a.steps - 1), b0);
-      __builtin_amdgcn_sched_barrier(0);
-      step(Wc + (j + 1) * MT * kFrag, b1);
-    }
+  if constexpr (kSteps <= 45) {
+    tap_row(0, std::integral_constant<int, 0>());
+    tap_row(1, std::integral_constant<int, kRow>());
+    tap_row(2, std::integral_constant<int, 2 * kRow>());
+  } else {
+    static_assert(kSteps <= 45 || (kRow % kAhead == 0 && kRow % 2 == 0), "buffers repeat every tap row");
+#pragma unroll 1
+    for (int dy = 0; dy < 3; ++dy) tap_row(dy, std::integral_constant<int, 0>());
   }
 
-  if (!live) return;
-  // ---- epilogue: lane (g, col) holds output channels 16 mt + 4 g + j of pixel col
+  // ---- epilogue: lane (g, col) holds output channels 16 mt + 4 g + j of its pixel
+  auto value = [&](const f32x4 (&ac)[MW], const float *bias, int m, bool relu) {
+    f32x4 v = ac[m] + *(const f32x4 *)(bias + 16 * (wm * MW + m) + 4 * g);
+    if (relu) {
 #pragma unroll
-  for (int t = 0; t < kNT; ++t) {
-    const int xx = x0 + 16 * t + col;
-    if (xx >= Wd) continue;
-    const int64_t px = ((int64_t)f * H + y) * Wd + xx;
+      for (int j = 0; j < 4; ++j) v[j] = fmaxf(v[j], 0.0f);
+    }
+    return v;
+  };
+  if constexpr (EPI == E_F32) {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const int c0 = 16 * mt + 4 * g;
-      f32x4 v = acc[t][mt] + *(const f32x4 *)(a.bias + c0);
-      if (a.relu) {
+    for (int t = 0; t < NT; ++t) {
+      const int y = y0 + wn * NT + t, x = x0 + col;
+      if (y >= H || x >= Wd) continue;
+      float *o = (float *)a.out + (((int64_t)f * H + y) * Wd + x) * (MT * 16) + 4 * g;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = fmaxf(v[j], 0.0f);
+      for (int m = 0; m < MW; ++m) *(f32x4 *)(o + 16 * (wm * MW + m)) = value(acc[t], a.bias, m, false);
+    }
+    return;
+  }
+  // the tile as bf16 [row][column][channel] in the LDS the halo has left
+  auto put = [&](const f32x4 (&ac)[NT][MW], const float *bias, bool relu) {
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int m = 0; m < MW; ++m) {
+        const f32x4 v = value(ac[t], bias, m, relu);
+        const int px = (wn * NT + t) * kTC + col, u = 2 * (wm * MW + m) + (g >> 1);
+        *(uint2 *)(lds + unit_at<kWUn>(px, u) + 8 * (g & 1)) =
+            uint2{pk_bf16(v[0], v[1]), pk_bf16(v[2], v[3])};
       }
-      if (a.out_bf) {
-        uint2 pk = {pk_bf16(v[0], v[1]), pk_bf16(v[2], v[3])};
-        *(uint2 *)(a.out_bf + (px * a.cout_pad + c0) * 2) = pk;
+    __syncthreads();
+  };
+  put(acc, a.bias, true);
+  if constexpr (EPI == E_CONV1) {
+    // the 1 x 1 conv on the tile: K-step cb is channel block cb
+    const rsrc_t r1 = make_rsrc(a.wfrag1, (uint32_t)(MT / 2 * MT * kFrag));
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int m = 0; m < MW; ++m) acc[t][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int cb = 0; cb < MT / 2; ++cb) {
+      u32x4 w1[MW], b1[NT];
+#pragma unroll
+      for (int m = 0; m < MW; ++m)
+        w1[m] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                              r1, lane * 16, (cb * MT + wm * MW + m) * kFrag, 0));
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        b1[t] = *(const u32x4 *)(lds + unit_at<kWUn>((wn * NT + t) * kTC + col, 4 * cb + g));
+#pragma unroll
+      for (int m = 0; m < MW; ++m)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t][m] = mma(w1[m], b1[t], acc[t][m]);
+    }
+    put(acc, a.bias1, false);
+  }
+  if constexpr (EPI == E_RGB) {
+    // one row tile (3 real outputs); the waves share the tile's rows
+    const rsrc_t r1 = make_rsrc(a.wfrag1, (uint32_t)(MT / 2 * kFrag));
+    u32x4 w1[MT / 2];
+#pragma unroll
+    for (int cb = 0; cb < MT / 2; ++cb)
+      w1[cb] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r1, lane * 16, cb * kFrag, 0));
+    for (int r = wave; r < TR; r += 4) {
+      f32x4 y = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int cb = 0; cb < MT / 2; ++cb)
+        y = mma(w1[cb], *(const u32x4 *)(lds + unit_at<kWUn>(r * kTC + col, 4 * cb + g)), y);
+      const int yy = y0 + r, x = x0 + col;
+      if (g == 0 && yy < H && x < Wd) {
+        const int64_t hw = (int64_t)H * Wd, q = (int64_t)yy * Wd + x;
+        float *o = (float *)a.out + (int64_t)f * 3 * hw + q;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) o[c * hw] = y[c] + a.bias1[c];
       }
-      if (a.out_f32) *(f32x4 *)(a.out_f32 + px * a.cout_pad + c0) = v;
-      if (a.out_rgb && mt == 0 && g == 0) {
-        const int64_t hw = (int64_t)H * Wd, q = (int64_t)y * Wd + xx;
-        a.out_rgb[((int64_t)f * 3 + 0) * hw + q] = v[0];
-        a.out_rgb[((int64_t)f * 3 + 1) * hw + q] = v[1];
-        a.out_rgb[((int64_t)f * 3 + 2) * hw + q] = v[2];
+    }
+    return;
+  }
+  // bf16 store, 16 bytes per lane of consecutive units
+  for (int e = threadIdx.x; e < TR * kTC * kWUn; e += kConvThreads) {
+    const int px = e / kWUn, u = e % kWUn, y = y0 + px / kTC, x = x0 + px % kTC;
+    if (y < H && x < Wd)
+      *(u32x4 *)(a.out + (((int64_t)f * H + y) * Wd + x) * (MT * 32) + u * 16) =
+          *(const u32x4 *)(lds + unit_at<kWUn>(px, u));
+  }
+  if (EPI == E_ACT && a.pool) {
+    // the 2 x 2 average of the stored values (H and Wd are even, as are the
+    // tile's corners), the sum in fp32
+    const int H2 = H >> 1, W2 = Wd >> 1;
+    for (int e = threadIdx.x; e < TR / 2 * (kTC / 2) * kWUn; e += kConvThreads) {
+      const int p2 = e / kWUn, u = e % kWUn, r = p2 / (kTC / 2), c = p2 % (kTC / 2);
+      const int y = y0 / 2 + r, x = x0 / 2 + c;
+      if (y >= H2 || x >= W2) continue;
+      float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const u32x4 v =
+            *(const u32x4 *)(lds + unit_at<kWUn>((2 * r + (q >> 1)) * kTC + 2 * c + (q & 1), u));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          s[2 * j] += __uint_as_float(v[j] << 16);
+          s[2 * j + 1] += __uint_as_float(v[j] & 0xFFFF0000u);
+        }
       }
+      *(u32x4 *)(a.pool + (((int64_t)f * H2 + y) * W2 + x) * (MT * 32) + u * 16) =
+          u32x4{pk_bf16(0.25f * s[0], 0.25f * s[1]), pk_bf16(0.25f * s[2], 0.25f * s[3]),
+                pk_bf16(0.25f * s[4], 0.25f * s[5]), pk_bf16(0.25f * s[6], 0.25f * s[7])};
     }
   }
 }
@@ -448,47 +566,7 @@ __global__ __launch_bounds__(kThreads) void sp_slots_kernel(SpSlotsArgs a) {
   }
 }
 
-// ---- input packing and the pooling steps ------------------------------------
-// x = [G 0..13; scene 0..15; 0, 0] as bf16 [n][H][W][32].
-__global__ void sp_pack_x_kernel(const float *__restrict__ gbuf, const float *__restrict__ scene,
-                                 int64_t npx, int hw, uint8_t *__restrict__ x) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= npx) return;
-  const int f = (int)(p / hw), q = (int)(p - (int64_t)f * hw);
-  uint32_t w[16];
-  for (int j = 0; j < 16; ++j) {
-    float v[2];
-    for (int e = 0; e < 2; ++e) {
-      const int c = 2 * j + e;
-      v[e] = c < kNG ? gbuf[((int64_t)f * kNG + c) * hw + q]
-                     : (c < kNG + kNS ? scene[(int64_t)f * kNS + c - kNG] : 0.0f);
-    }
-    w[j] = pk_bf16(v[0], v[1]);
-  }
-  u32x4 *dst = (u32x4 *)(x + p * 64);
-  for (int j = 0; j < 4; ++j) dst[j] = u32x4{w[4 * j], w[4 * j + 1], w[4 * j + 2], w[4 * j + 3]};
-}
-
-// `nch` planes (plane stride hw, frame stride fstride floats) from `src` as
-// bf16 [n][H][W][32], zero past nch.
-__global__ void sp_pack_planes_kernel(const float *__restrict__ src, int nch, int64_t fstride,
-                                      int64_t npx, int hw, uint8_t *__restrict__ x) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= npx) return;
-  const int f = (int)(p / hw), q = (int)(p - (int64_t)f * hw);
-  uint32_t w[16];
-  for (int j = 0; j < 16; ++j) {
-    float v[2];
-    for (int e = 0; e < 2; ++e) {
-      const int c = 2 * j + e;
-      v[e] = c < nch ? src[(int64_t)f * fstride + (int64_t)c * hw + q] : 0.0f;
-    }
-    w[j] = pk_bf16(v[0], v[1]);
-  }
-  u32x4 *dst = (u32x4 *)(x + p * 64);
-  for (int j = 0; j < 4; ++j) dst[j] = u32x4{w[4 * j], w[4 * j + 1], w[4 * j + 2], w[4 * j + 3]};
-}
-
+// ---- input and weight packing -------------------------------------------------
 // Every buffer's 12 planes as bf16 [n][k][H][W][16] (zero channels 12..15):
 // one thread per (frame, buffer, pixel).
 __global__ void sp_pack_slots_kernel(const float *__restrict__ layers, int64_t total, int hw,
@@ -508,58 +586,6 @@ __global__ void sp_pack_slots_kernel(const float *__restrict__ layers, int64_t t
   dst[1] = u32x4{w[4], w[5], w[6], w[7]};
 }
 
-// The fragments of sp_slots_kernel: blockIdx.y 0 packs conv3_b (T1's buffer
-// columns, master [W][12 + W][3][3]), 1 and 2 pack A2 and A3 ([W][W]) in
-// register order.  Fragment (s, mt), lane l = 16 g + m, element j.
-__global__ void sp_pack_slots_frag_kernel(const float *__restrict__ master, int W, int64_t t1,
-                                          int64_t t2, int64_t t3, uint8_t *__restrict__ out) {
-  const int MT = W / 16, KS = MT / 2, which = blockIdx.y;
-  const int steps = which == 0 ? kSlotSteps1 : KS;
-  const int64_t base = which == 0 ? 0 : (int64_t)(kSlotSteps1 + (which - 1) * KS) * MT * 512;
-  const int64_t n = (int64_t)steps * MT * 512;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int j = (int)(e & 7), l = (int)((e >> 3) & 63);
-    const int64_t frag = e >> 9;
-    const int mt = (int)(frag % MT), s = (int)(frag / MT);
-    const int g = l >> 4, row = 16 * mt + (l & 15);
-    float v = 0.0f;
-    if (which == 0) {
-      const int tap = 2 * s + (g >> 1), ch = 8 * (g & 1) + j;
-      if (tap < 9 && ch < kNL) v = master[t1 + ((int64_t)row * (kNL + W) + ch) * 9 + tap];
-    } else {
-      const int ch = 32 * s + (j < 4 ? 4 * g + j : 16 + 4 * g + j - 4);
-      v = master[(which == 1 ? t2 : t3) + (int64_t)row * W + ch];
-    }
-    ((__bf16 *)(out + base * 2))[e] = (__bf16)v;
-  }
-}
-
-// 2 x 2 average of a bf16 [n][H][W][C] block (H, W even) into [n][H/2][W/2][C]:
-// one thread per output pixel and 8 channels, the sum in fp32.
-__global__ void sp_avgpool_kernel(const uint8_t *__restrict__ in, int n, int H, int Wd, int C,
-                                  uint8_t *__restrict__ out) {
-  const int H2 = H >> 1, W2 = Wd >> 1, cg = C >> 3;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t total = (int64_t)n * H2 * W2 * cg;
-  if (i >= total) return;
-  const int c8 = (int)(i % cg);
-  const int64_t p = i / cg;
-  const int x = (int)(p % W2);
-  const int64_t fy = p / W2;
-  const int yy = (int)(fy % H2), f = (int)(fy / H2);
-  float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int dy = 0; dy < 2; ++dy)
-    for (int dx = 0; dx < 2; ++dx) {
-      const uint16_t *src =
-          (const uint16_t *)(in + ((((int64_t)f * H + 2 * yy + dy) * Wd + 2 * x + dx) * C + 8 * c8) * 2);
-      for (int j = 0; j < 8; ++j) s[j] += bf16_to_f32(src[j]);
-    }
-  uint32_t w[4];
-  for (int j = 0; j < 4; ++j) w[j] = pk_bf16(0.25f * s[2 * j], 0.25f * s[2 * j + 1]);
-  *(u32x4 *)(out + (p * C + 8 * c8) * 2) = u32x4{w[0], w[1], w[2], w[3]};
-}
-
 // Weight fragments of one conv: element e of fragment (step, mt), lane l,
 // position j holds W[16 mt + (l & 15)][ci][tap] for step = tap * cbt + cb and
 // concatenated input channel 32 cb + 8 (l >> 4) + j, mapped to the master
@@ -573,47 +599,71 @@ struct SpPackDesc {
   int mt;                   // M-tiles
 };
 
-// All convolutions in one launch: blockIdx.y selects the conv; the biases
-// (padded to whole M-tiles, zero past cout and for T1's buffer part, whose
-// bias T1's sigma part carries) go after the fragments.
+// Everything in one launch: blockIdx.y selects the conv (15), then the
+// fragments of sp_slots_kernel: 15 packs conv3_b (T1's buffer columns, master
+// [W][12 + W][3][3]), 16 and 17 A2 and A3 ([W][W]) in register order.  The
+// biases (padded to whole M-tiles, zero past cout and for T1's buffer part,
+// whose bias T1's sigma part carries) go after the convs' fragments.
+constexpr int kPackJobs = 18;
 struct SpPackAll {
   SpPackDesc d[15];
   int64_t bias_src[15];     // master float offset of each conv's bias (-1: none)
   int64_t bias_dst[15];     // float offset in the packed bias block
   int64_t bias_block;       // byte offset of the bias block
+  int64_t slots_off, t[3];  // sp_slots_kernel's fragments; T's three weight tensors
+  int W;
 };
 
-__global__ void sp_pack_all_kernel(const float *__restrict__ master, SpPackAll all,
-                                   uint8_t *__restrict__ packed) {
-  const SpPackDesc &d = all.d[blockIdx.y];
-  const int64_t e0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (blockIdx.x == 0 && threadIdx.x < 16 * d.mt) {
-    const int o = threadIdx.x;
-    const int64_t src = all.bias_src[blockIdx.y];
-    ((float *)(packed + all.bias_block))[all.bias_dst[blockIdx.y] + o] =
-        src >= 0 && o < d.cout ? master[src + o] : 0.0f;
-  }
-  const int cbt = (d.c0pad + d.c1pad) >> 5;
-  const int steps = d.k * d.k * cbt;
-  const int64_t n = (int64_t)padded_steps(d.k * d.k, cbt) * d.mt * 64 * 8;
-  for (int64_t e = e0; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-    const int j = (int)(e & 7), l = (int)((e >> 3) & 63);
-    const int64_t frag = e >> 9;
-    const int mt = (int)(frag % d.mt), step = (int)(frag / d.mt);
-    const int tap = step / cbt, cb = step - tap * cbt;
-    const int row = 16 * mt + (l & 15);
-    const int cc = 32 * cb + 8 * (l >> 4) + j;           // concatenated padded channel
-    int ci = -1;
-    if (cc < d.c0pad) {
-      if (cc < d.c0real) ci = cc;
-    } else if (cc - d.c0pad < d.c1real) {
-      ci = d.c0real + (cc - d.c0pad);
+// A thread per lane of a fragment: its 8 elements, one 16-byte store.
+__global__ __launch_bounds__(256) void sp_pack_all_kernel(const float *__restrict__ master,
+                                                          SpPackAll all, uint8_t *__restrict__ packed) {
+  const int job = blockIdx.y, i = blockIdx.x * 256 + threadIdx.x, l = i & 63;
+  float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  uint8_t *dst;
+  if (job < 15) {
+    const SpPackDesc &d = all.d[job];
+    if (i < 16 * d.mt) {
+      const int64_t src = all.bias_src[job];
+      ((float *)(packed + all.bias_block))[all.bias_dst[job] + i] =
+          src >= 0 && i < d.cout ? master[src + i] : 0.0f;
     }
-    float v = 0.0f;
-    if (step < steps && row < d.cout && ci >= 0)      // padding steps stay zero
-      v = master[d.woff + (((int64_t)row * d.cin + d.col0 + ci) * d.k * d.k) + tap];
-    ((__bf16 *)(packed + d.out_off))[e] = (__bf16)v;
+    const int cbt = (d.c0pad + d.c1pad) >> 5, kk = d.k * d.k;
+    if (i >= kk * cbt * d.mt * 64) return;
+    const int mt = (i >> 6) % d.mt, step = (i >> 6) / d.mt, tap = step / cbt, cb = step % cbt;
+    const int row = 16 * mt + (l & 15);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int cc = 32 * cb + 8 * (l >> 4) + j;         // concatenated padded channel
+      int ci = -1;
+      if (cc < d.c0pad) {
+        if (cc < d.c0real) ci = cc;
+      } else if (cc - d.c0pad < d.c1real) {
+        ci = d.c0real + (cc - d.c0pad);
+      }
+      if (row < d.cout && ci >= 0)
+        v[j] = master[d.woff + ((int64_t)row * d.cin + d.col0 + ci) * kk + tap];
+    }
+    dst = packed + d.out_off;
+  } else {
+    const int W = all.W, MT = W / 16, KS = MT / 2, which = job - 15;
+    const int steps = which == 0 ? kSlotSteps1 : KS;
+    if (i >= steps * MT * 64) return;
+    const int mt = (i >> 6) % MT, s = (i >> 6) / MT, g = l >> 4, row = 16 * mt + (l & 15);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (which == 0) {
+        const int tap = 2 * s + (g >> 1), ch = 8 * (g & 1) + j;
+        if (tap < 9 && ch < kNL) v[j] = master[all.t[0] + ((int64_t)row * (kNL + W) + ch) * 9 + tap];
+      } else {
+        const int ch = 32 * s + (j < 4 ? 4 * g + j : 16 + 4 * g + j - 4);
+        v[j] = master[all.t[which] + (int64_t)row * W + ch];
+      }
+    }
+    dst = packed + all.slots_off +
+          (which == 0 ? 0 : (int64_t)(kSlotSteps1 + (which - 1) * KS) * MT * kFrag);
   }
+  *(u32x4 *)(dst + (int64_t)i * 16) = u32x4{pk_bf16(v[0], v[1]), pk_bf16(v[2], v[3]),
+                                            pk_bf16(v[4], v[5]), pk_bf16(v[6], v[7])};
 }
 
 }  // namespace
@@ -691,7 +741,7 @@ static SpLayout sp_layout(int W) {
     d.c1pad = m.c1pad;
     d.mt = (d.cout + 15) / 16;
     d.out_off = fb;
-    fb += (int64_t)padded_steps(d.k * d.k, (d.c0pad + d.c1pad) / 32) * d.mt * kFrag;
+    fb += (int64_t)d.k * d.k * ((d.c0pad + d.c1pad) / 32) * d.mt * kFrag;
     L.bias_off[c] = bf;
     bf += d.mt * 16;
   }
@@ -726,10 +776,9 @@ size_t spatial_weight_bytes(int W) {
 // needs.
 size_t spatial_workspace_bytes(int W, int n, int H, int Wd, int k) {
   const int64_t px = (int64_t)n * H * Wd, half = px / 4;
-  // bf16: x/L_d (32 ch), e1, e2, sigma, tau, phi, r1, r2 (W ch each), half-res
-  // d and m (W ch), the k buffers (16 ch each); fp32: u (W ch); rounding slack
-  return (size_t)(2 * (px * 32 + 7 * px * W + 2 * half * W + px * 16 * (int64_t)k) +
-                  4 * px * W + 16 * 256);
+  // bf16: e1, sigma, tau, phi, r1 (W ch each), half-res d and m (W ch), the k
+  // buffers (16 ch each); fp32: u (W ch); rounding slack
+  return (size_t)(2 * (5 * px * W + 2 * half * W + px * 16 * (int64_t)k) + 4 * px * W + 16 * 256);
 }
 
 hipError_t spatial_pack(const float *master, int W, uint8_t *packed, hipStream_t s) {
@@ -744,15 +793,16 @@ hipError_t spatial_pack(const float *master, int W, uint8_t *packed, hipStream_t
     all.bias_src[c] = zero ? -1 : bo;
     all.bias_dst[c] = L.bias_off[c];
     const SpPackDesc &d = L.d[c];
-    most = std::max<int64_t>(most, (int64_t)padded_steps(d.k * d.k, (d.c0pad + d.c1pad) / 32) *
-                                       d.mt * 512);
+    most = std::max<int64_t>(most, (int64_t)d.k * d.k * ((d.c0pad + d.c1pad) / 32) * d.mt * 64);
   }
   all.bias_block = L.frag_bytes;
-  const unsigned bx = (unsigned)std::min<int64_t>((most + 255) / 256, 1024);
-  hipLaunchKernelGGL(sp_pack_all_kernel, dim3(bx, kSpConvs), dim3(256), 0, s, master, all,
-                     packed);
-  hipLaunchKernelGGL(sp_pack_slots_frag_kernel, dim3(64, 3), dim3(256), 0, s, master, W, L.t1,
-                     L.t2, L.t3, packed + L.slots_off);
+  all.slots_off = L.slots_off;
+  all.t[0] = L.t1;
+  all.t[1] = L.t2;
+  all.t[2] = L.t3;
+  all.W = W;
+  hipLaunchKernelGGL(sp_pack_all_kernel, dim3((unsigned)((most + 255) / 256), kPackJobs), dim3(256),
+                     0, s, master, all, packed);
   return hipGetLastError();
 }
 
@@ -775,147 +825,124 @@ static hipError_t sp_slots_launch(const SpSlotsArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int MT, int NT>
+template <int MT, int TR, int CB0, int SRC1, int CB1, bool PLANES, int EPI>
 static hipError_t sp_launch(const SpConvArgs &a, hipStream_t s) {
-  static bool attr = false;
-  const size_t lds = 2 * (size_t)kChunk * MT * kFrag;
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void *)sp_conv_kernel<MT, NT>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
-  const int64_t segs = (int64_t)a.n * a.H * ((a.Wd + 16 * NT - 1) / (16 * NT));
-  const unsigned grid = (unsigned)((segs + kWaves - 1) / kWaves);
-  hipLaunchKernelGGL((sp_conv_kernel<MT, NT>), dim3(grid), dim3(kThreads), lds, s, a);
+  constexpr int lds = ConvLds<MT, TR, CB0, SRC1, CB1>::kBytes;
+  static const hipError_t attr =
+      hipFuncSetAttribute((const void *)sp_conv_kernel<MT, TR, CB0, SRC1, CB1, PLANES, EPI>,
+                          hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (attr != hipSuccess) return attr;
+  const int64_t tiles = (int64_t)a.n * ((a.H + TR - 1) / TR) * ((a.Wd + kTC - 1) / kTC);
+  hipLaunchKernelGGL((sp_conv_kernel<MT, TR, CB0, SRC1, CB1, PLANES, EPI>), dim3((unsigned)tiles),
+                     dim3(kConvThreads), lds, s, a);
   return hipGetLastError();
 }
 
-static hipError_t sp_conv(const SpConvArgs &a0, int mt, hipStream_t s) {
-  switch (mt) {
-    case 1: return sp_launch<1, 4>(a0, s);
-    case 4: return sp_launch<4, 4>(a0, s);
-    case 8: return sp_launch<8, 2>(a0, s);
-  }
-  return hipErrorInvalidValue;
+// The rows of a tile: 8 while that leaves a tile for every CU, else 4.  (16 rows
+// halve the weight traffic but leave one workgroup and one wave per SIMD to a
+// CU, whose halo load and epilogue nothing overlaps: the 256^2 W = 128 convs
+// took 20-41 us, with 8 rows 19-37.)
+template <int MT, int CB0, int SRC1, int CB1, bool PLANES, int EPI>
+static hipError_t sp_conv(const SpConvArgs &a, hipStream_t s) {
+  constexpr int kCus = 256;
+  const int64_t cols = (int64_t)a.n * ((a.Wd + kTC - 1) / kTC);
+  if (cols * ((a.H + 7) / 8) >= kCus) return sp_launch<MT, 8, CB0, SRC1, CB1, PLANES, EPI>(a, s);
+  return sp_launch<MT, 4, CB0, SRC1, CB1, PLANES, EPI>(a, s);
 }
 
-hipError_t spatial_forward(const uint8_t *packed, int W, int pool, const float *gbuf,
-                           const float *layers, const float *scene, int n, int H, int Wd, int k,
-                           float *out, uint8_t *ws, hipStream_t s) {
-  const SpLayout L = sp_layout(W);
+template <int MT>
+static hipError_t spatial_run(const SpLayout &L, const uint8_t *packed, int pool, const float *gbuf,
+                              const float *layers, const float *scene, int n, int H, int Wd, int k,
+                              float *out, uint8_t *ws, hipStream_t s) {
+  constexpr int W = MT * 16, CB = MT / 2;
   const float *bias = (const float *)(packed + L.frag_bytes);
   const int64_t px = (int64_t)n * H * Wd, half = px / 4;
   const int hw = H * Wd;
   // workspace carve-up (see spatial_workspace_bytes)
   uint8_t *p = ws;
   auto take = [&](int64_t bytes) { uint8_t *q = p; p += (bytes + 255) & ~(int64_t)255; return q; };
-  uint8_t *x32 = take(px * 32 * 2);                   // x, then each b_i, then L_d
-  uint8_t *e1 = take(px * W * 2), *e2 = take(px * W * 2), *sig = take(px * W * 2);
-  uint8_t *tau = take(px * W * 2);
-  uint8_t *phi = take(px * W * 2), *r1 = take(px * W * 2), *r2 = take(px * W * 2);
+  uint8_t *e1 = take(px * W * 2), *sig = take(px * W * 2), *tau = take(px * W * 2);
+  uint8_t *phi = take(px * W * 2), *r1 = take(px * W * 2);
   uint8_t *dh = take(half * W * 2), *mh = take(half * W * 2);
   uint8_t *bpk = take(px * 16 * 2 * (int64_t)k);
   float *u = (float *)take(px * W * 4);
-  const int MT = W / 16;
-  const unsigned pg = (unsigned)((px + 255) / 256);
   hipError_t e = hipSuccess;
 
-  auto conv = [&](int c, const uint8_t *in0, int c0, const uint8_t *in1, int c1, int up1,
-                  int Hc, int Wc) {
+  auto args = [&](int c, const uint8_t *in0, const uint8_t *in1, void *o, int Hc, int Wc) {
     SpConvArgs a = {};
-    const SpPackDesc &d = L.d[c];
     a.in0 = in0;
     a.in1 = in1;
-    a.c0 = c0;
-    a.c1 = c1;
-    a.up1 = up1;
-    a.wfrag = packed + d.out_off;
+    a.gbuf = gbuf;
+    a.scene = scene;
+    a.wfrag = packed + L.d[c].out_off;
     a.bias = bias + L.bias_off[c];
-    a.ksize = d.k;
-    a.steps = d.k * d.k * ((c0 + c1) / 32);
-    a.steps_pad = padded_steps(d.k * d.k, (c0 + c1) / 32);
     a.n = n;
     a.H = Hc;
     a.Wd = Wc;
-    a.cout_pad = d.mt * 16;
+    a.out = (uint8_t *)o;
     return a;
   };
-  auto run = [&](const SpConvArgs &a, int mt) {
-    if (e == hipSuccess) e = sp_conv(a, mt, s);
+  // the following 1 x 1 conv
+  auto then = [&](SpConvArgs a, int c) {
+    a.wfrag1 = packed + L.d[c].out_off;
+    a.bias1 = bias + L.bias_off[c];
+    return a;
   };
-  auto unet = [&](int c1st, const uint8_t *in0, int c0, const uint8_t *in1, int c1, uint8_t *outp) {
-    SpConvArgs a = conv(c1st, in0, c0, in1, c1, 0, H, Wd);        // e1
-    a.relu = 1;
-    a.out_bf = e1;
-    run(a, MT);
-    const int64_t tot = half * (W / 8);
-    hipLaunchKernelGGL(sp_avgpool_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, e1,
-                       n, H, Wd, W, dh);
-    a = conv(c1st + 1, dh, W, nullptr, 0, 0, H / 2, Wd / 2);      // m (half resolution)
-    a.relu = 1;
-    a.out_bf = mh;
-    run(a, MT);
-    a = conv(c1st + 2, e1, W, mh, W, 1, H, Wd);                   // e2 = relu(conv3 [e1; up m])
-    a.relu = 1;
-    a.out_bf = e2;
-    run(a, MT);
-    a = conv(c1st + 3, e2, W, nullptr, 0, 0, H, Wd);              // out = conv1 e2
-    a.out_bf = outp;
-    run(a, MT);
+  auto ok = [&](hipError_t r) { if (e == hipSuccess) e = r; };
+  // e1's average d, m = relu(conv3 d) at half resolution, then
+  // conv1 relu(conv3 [e1; up m])
+  auto unet_tail = [&](int c1st, uint8_t *outp) {
+    ok(sp_conv<MT, CB, S_NONE, 0, false, E_ACT>(args(c1st + 1, dh, nullptr, mh, H / 2, Wd / 2), s));
+    ok(sp_conv<MT, CB, S_HALF, CB, false, E_CONV1>(then(args(c1st + 2, e1, mh, outp, H, Wd), c1st + 3), s));
   };
 
   // F: sigma = U-Net([G; s])
-  hipLaunchKernelGGL(sp_pack_x_kernel, dim3(pg), dim3(256), 0, s, gbuf, scene, px, hw, x32);
-  unet(SP_F1, x32, 32, nullptr, 0, sig);
+  SpConvArgs a = args(SP_F1, nullptr, nullptr, e1, H, Wd);
+  a.pool = dh;
+  ok(sp_conv<MT, 1, S_NONE, 0, true, E_ACT>(a, s));
+  unet_tail(SP_F1, sig);
   // T: u = conv3 sigma (T1's sigma columns) + c1; then, in one kernel, per
   // buffer z1 = relu(conv3 b_i + u), Z += [alpha_i > 0] relu(A2 z1 + c2), and
   // tau = A3 (Z / max(c, 1)) + [c > 0] c3 (mean) or A3 Z + c c3 (sum)
-  {
-    SpConvArgs a = conv(SP_T1S, sig, W, nullptr, 0, 0, H, Wd);
-    a.out_f32 = u;
-    run(a, MT);
-  }
+  ok(sp_conv<MT, CB, S_NONE, 0, false, E_F32>(args(SP_T1S, sig, nullptr, u, H, Wd), s));
   if (k > 0) {
     const int64_t tot = px * k;
     hipLaunchKernelGGL(sp_pack_slots_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s,
                        layers, tot, hw, bpk);
   }
   {
-    SpSlotsArgs a;
-    a.frag = packed + L.slots_off;
-    a.bias = bias + L.bias_off[SP_T2];       // c2, then c3 (T3's bias block follows T2's)
-    a.bpk = bpk;
-    a.layers = layers;
-    a.u = u;
-    a.tau = tau;
-    a.n = n;
-    a.H = H;
-    a.Wd = Wd;
-    a.k = k;
-    a.mean = pool == GN_POOL_MEAN ? 1 : 0;
-    if (e == hipSuccess) e = MT == 8 ? sp_slots_launch<8>(a, s) : sp_slots_launch<4>(a, s);
+    SpSlotsArgs t;
+    t.frag = packed + L.slots_off;
+    t.bias = bias + L.bias_off[SP_T2];       // c2, then c3 (T3's bias block follows T2's)
+    t.bpk = bpk;
+    t.layers = layers;
+    t.u = u;
+    t.tau = tau;
+    t.n = n;
+    t.H = H;
+    t.Wd = Wd;
+    t.k = k;
+    t.mean = pool == GN_POOL_MEAN ? 1 : 0;
+    ok(sp_slots_launch<MT>(t, s));
   }
   // B: phi = U-Net([sigma; tau])
-  unet(SP_B1, sig, W, tau, W, phi);
+  a = args(SP_B1, sig, tau, e1, H, Wd);
+  a.pool = dh;
+  ok(sp_conv<MT, CB, S_FULL, CB, false, E_ACT>(a, s));
+  unet_tail(SP_B1, phi);
   // R: y = conv1 relu(conv3 relu(conv3 [phi; L_d]))
-  hipLaunchKernelGGL(sp_pack_planes_kernel, dim3(pg), dim3(256), 0, s, gbuf + 11 * hw, 3,
-                     (int64_t)kNG * hw, px, hw, x32);
-  {
-    SpConvArgs a = conv(SP_R1, phi, W, x32, 32, 0, H, Wd);
-    a.relu = 1;
-    a.out_bf = r1;
-    run(a, MT);
-    a = conv(SP_R2, r1, W, nullptr, 0, 0, H, Wd);
-    a.relu = 1;
-    a.out_bf = r2;
-    run(a, MT);
-    a = conv(SP_R3, r2, W, nullptr, 0, 0, H, Wd);
-    a.out_rgb = out;
-    run(a, 1);
-  }
+  ok(sp_conv<MT, CB, S_LIGHT, 1, false, E_ACT>(args(SP_R1, phi, nullptr, r1, H, Wd), s));
+  ok(sp_conv<MT, CB, S_NONE, 0, false, E_RGB>(then(args(SP_R2, r1, nullptr, out, H, Wd), SP_R3), s));
   if (e == hipSuccess) e = hipGetLastError();
   return e;
+}
+
+hipError_t spatial_forward(const uint8_t *packed, int W, int pool, const float *gbuf,
+                           const float *layers, const float *scene, int n, int H, int Wd, int k,
+                           float *out, uint8_t *ws, hipStream_t s) {
+  const SpLayout L = sp_layout(W);
+  return W == 128 ? spatial_run<8>(L, packed, pool, gbuf, layers, scene, n, H, Wd, k, out, ws, s)
+                  : spatial_run<4>(L, packed, pool, gbuf, layers, scene, n, H, Wd, k, out, ws, s);
 }
 
 }  // namespace gn

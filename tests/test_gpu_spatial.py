@@ -52,6 +52,22 @@ def test_spatial_forward_matches_oracle(W, n, h, w, k, pool):
     gate(y, ref, TOL, f"spatial W={W} {n}x{h}x{w} K={k}")
 
 
+@pytest.mark.parametrize("W,n,h,w,k", [(128, 1, 2, 2, 1), (64, 2, 4, 16, 2), (128, 3, 8, 18, 1),
+                                       (64, 1, 10, 14, 8), (128, 1, 130, 258, 1),
+                                       (64, 3, 62, 208, 1), (64, 2, 126, 130, 2)])
+def test_spatial_forward_at_tile_edges(W, n, h, w, k):
+    """One pixel quad, whole and ragged tiles of 4 x 16 and of 8 x 16 (chosen
+    when those give every CU one: the last three, at both scales or at full
+    resolution only)."""
+    wts, fr = frame(n, h, w, k, W, seed=400 + h + w)
+    log(f"spatial tile edges W={W} {n}x{h}x{w} K={k}")
+    ref = so.forward(wts, W, fr.gbuf, fr.layers, fr.scene)
+    with GlassNet(synth.make_weights(W, np.random.default_rng(0)), W, k_max=8,
+                  precision="bf16") as net:
+        y = run(net, wts, fr)
+    gate(y, ref, TOL, f"spatial tile edges W={W} {n}x{h}x{w} K={k}")
+
+
 def test_spatial_256sq_k4_whole_frame():
     W = 128
     wts, fr = frame(1, 256, 256, 4, W, seed=301)
