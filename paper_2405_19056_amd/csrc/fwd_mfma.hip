@@ -374,10 +374,14 @@ struct LdsMap {
   }
 };
 
-// Object-streaming state of one tile (modes other than FWD_FULL): sigma as
-// bf16 B fragments [wave][t][ks][lane], the running masked sum Z of h's hidden
-// layer as fp32 accumulator rows [wave][t][mt][lane], the active-slot count
-// [wave][t][pixel column].  Every access is a whole 16-byte lane vector.
+// Object-streaming state of one tile (modes other than FWD_FULL), pixel by
+// pixel: sigma as bf16 B fragments [pixel][ks][g], the running masked sum Z of
+// h's hidden layer as fp32 accumulator rows [pixel][mt][g] (16-byte lane vectors
+// each), the active-slot count [pixel].  What bounds the accumulate calls is
+// this state's traffic, and with a pixel's values side by side the pixels an
+// object does not cover move none of it (512^2, W = 128, half of the pixels
+// covered: 35 us a call, 54 when all of it moved).  A pixel whose count is zero
+// has no valid Z: nobody reads it.
 template <int W>
 struct StreamTile {
   static constexpr int64_t kSig = (int64_t)kWaves * kNT * (W / 32) * kFrag;
@@ -385,6 +389,26 @@ struct StreamTile {
   static constexpr int64_t kCnt = (int64_t)kWaves * kNT * 16 * 4;
   static constexpr int64_t kBytes = kSig + kZ + kCnt;
 };
+
+// The state is reached through a buffer resource of the tile's size: a lane
+// whose offset lies outside it loads zeros and stores nothing.
+constexpr int kOutside = 0x40000000;
+
+__device__ __forceinline__ u32x4 state_load16(__amdgpu_buffer_rsrc_t r, int off) {
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+
+__device__ __forceinline__ void state_store16(__amdgpu_buffer_rsrc_t r, int off, u32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, 0);
+}
+
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+template <class T>
+__device__ __forceinline__ T *uniform(T *p) {
+  const uint64_t v = (uint64_t)p;
+  return (T *)((uint64_t)(uint32_t)uniform((int)(v >> 32)) << 32 | (uint32_t)uniform((int)v));
+}
 
 // MODE selects the part of the path one launch runs: FWD_FULL the whole
 // forward; FWD_BEGIN stages 0-1 (sigma into the state); FWD_ACC stage 2 (the
@@ -507,11 +531,14 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
   auto resolve = [&](int tile) {
     TileInfo ti;
     if (a.tiles) {
+      // (the tables come through vector loads: without the move to scalar
+      // registers every later load would first check whether they have landed)
       const TileRef tr = a.tiles[tile];
-      const FrameDesc fd = a.frames[tr.frame];
-      ti.G = (gcfloat *)fd.g; ti.L = (gcfloat *)fd.L; ti.S = (gcfloat *)fd.s;
-      ti.O = (gfloat *)fd.out; ti.hw = fd.hw; ti.K = fd.k;
-      ti.q0 = tr.q0;
+      const FrameDesc fd = a.frames[uniform(tr.frame)];
+      ti.G = (gcfloat *)uniform(fd.g); ti.L = (gcfloat *)uniform(fd.L);
+      ti.S = (gcfloat *)uniform(fd.s); ti.O = (gfloat *)uniform(fd.out);
+      ti.hw = uniform(fd.hw); ti.K = uniform(fd.k);
+      ti.q0 = uniform(tr.q0);
     } else {
       const int f = tile / a.tiles_per_frame;
       ti.hw = a.b.hw;
@@ -525,7 +552,9 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
     return ti;
   };
   // F's input (G-buffer planes 0..13, scene 0..15, zero pad) of a tile: lane
-  // group g holds columns 8g..8g+7 of its pixel.  Loaded one tile ahead.
+  // group g holds columns 8g..8g+7 of its pixel.  Loaded one tile ahead, from
+  // selected addresses: with a branch per kind of column every load waited for
+  // the one before it (FWD_BEGIN at 512^2: 40 us, now 27).
   auto load_x = [&](const TileInfo &ti, int ln, float (&xr)[kNT][8]) {
     const int gg = ln >> 4, cc = ln & 15;
 #pragma unroll
@@ -535,9 +564,20 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int c = 8 * gg + j;
-        xr[t][j] = c < kNG ? ti.G[(size_t)c * ti.hw + qq] : (c < kNG + kNS ? ti.S[c - kNG] : 0.0f);
+        uint64_t p = (uint64_t)(c < kNG ? ti.G + ((size_t)c * ti.hw + qq)
+                                        : ti.S + min(c - kNG, kNS - 1));
+        asm volatile("" : "+v"(p));     // (else the compiler makes the branches again)
+        xr[t][j] = *(gcfloat *)p;
       }
     }
+  };
+  // zeroes the pad columns where the values are used
+  auto pad_x = [&](int ln, float (&xr)[kNT][8]) {
+#pragma unroll
+    for (int t = 0; t < kNT; ++t)
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (24 + j >= kNG + kNS) xr[t][j] = (ln >> 4) == 3 ? 0.0f : xr[t][j];
   };
   // Canonical slot order (FULL mode, if the handle asks for it): each
   // pixel's slots are pooled in an order that depends only on their records,
@@ -545,11 +585,55 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
   // passed them in.  With up to kFastK slots the tile's alphas are copied to
   // LDS during F's last layer and ranked at the start of the slot stage.
   constexpr int kFastK = 8;
+  // this lane's pieces of a tile's streaming state
+  using ST = StreamTile<W>;
+  auto st_rsrc = [&](int tile) {
+    return __builtin_amdgcn_make_buffer_rsrc(a.state + (size_t)tile * ST::kBytes, (short)0,
+                                             (int)ST::kBytes, 0x00020000);
+  };
+  auto st_px = [&](int ln, int t) { return wave * (kNT * 16) + t * 16 + (ln & 15); };
+  auto st_sig = [&](int ln, int t) { return st_px(ln, t) * (W * 2) + (ln >> 4) * 16; };
+  auto st_z = [&](int ln, int t) { return (int)ST::kSig + st_px(ln, t) * (W * 4) + (ln >> 4) * 16; };
+  auto st_cnt = [&](int ln, int t) { return (int)(ST::kSig + ST::kZ) + st_px(ln, t) * 4; };
+  auto load_cnt = [&](int tile, int ln, float (&c)[kNT]) {
+    const auto r = st_rsrc(tile);
+#pragma unroll
+    for (int t = 0; t < kNT; ++t)
+      c[t] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                           r, a.state_load ? st_cnt(ln, t) : kOutside, 0, 0));
+  };
+  // ACC: the largest alpha of a tile's pixels over the call's objects (NaN
+  // counts as inactive, as in the slot loop); loaded one tile ahead, as the
+  // counts are.
+  auto load_alpha = [&](const TileInfo &ti, int ln, float (&al)[kNT]) {
+#pragma unroll
+    for (int t = 0; t < kNT; ++t) {
+      const int q = min(ti.q0 + st_px(ln, t), ti.hw - 1);
+      al[t] = ti.L[(size_t)kAlpha * ti.hw + q];
+      for (int j = 1; j < ti.K; ++j)
+        al[t] = fmaxf(al[t], ti.L[((size_t)j * kNL + kAlpha) * ti.hw + q]);
+    }
+  };
+  // FINISH: the running sum of the pixels that have one
+  auto load_z = [&](int tile, int ln, const float (&c)[kNT], f32x4 (&z)[kNT][MT]) {
+    const auto r = st_rsrc(tile);
+#pragma unroll
+    for (int t = 0; t < kNT; ++t) {
+      const int off = c[t] > 0.0f ? st_z(ln, t) : kOutside;
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) z[t][mt] = __builtin_bit_cast(f32x4, state_load16(r, off + mt * 64));
+    }
+  };
   float xr[kNT][8];
+  float nal[kNT], ncnt[kNT];   // ACC: load_alpha's values; ACC, FINISH: the counts
+  f32x4 nz[kNT][MT];           // FINISH: the next tile's running sum
   TileInfo nti;
   if ((int)blockIdx.x < a.ntiles) {
     nti = resolve(blockIdx.x);
     if constexpr (kTrunk) load_x(nti, lane0, xr);
+    if constexpr (MODE == FWD_ACC) load_alpha(nti, lane0, nal);
+    if constexpr (MODE == FWD_ACC || MODE == FWD_FINISH) load_cnt(blockIdx.x, lane0, ncnt);
+    if constexpr (MODE == FWD_FINISH) load_z(blockIdx.x, lane0, ncnt, nz);
   }
 
   for (int tile = blockIdx.x; tile < a.ntiles; tile += gridDim.x) {
@@ -576,14 +660,35 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
       valid[t] = q < hw;
       qc[t] = valid[t] ? q : hw - 1;          // tail lanes recompute a real pixel
     }
-    // this wave's part of the tile's streaming state
-    uint8_t *st = a.state + (size_t)tile * StreamTile<W>::kBytes;
-    gu32x4 *st_sig = (gu32x4 *)(st + (size_t)wave * (kNT * KS * kFrag)) + lane;
-    gf32x4 *st_z = (gf32x4 *)(st + StreamTile<W>::kSig + (size_t)wave * (kNT * MT * kFrag)) + lane;
-    gfloat *st_cnt = (gfloat *)(st + StreamTile<W>::kSig + StreamTile<W>::kZ) + wave * (kNT * 16) + col;
     u32x4 sig[kNT][KS];   // sigma: from F (FULL, BEGIN) or from the state (ACC)
     f32x4 Z[kNT][MT];     // running masked sum of h's hidden layer, and
     float cnt[kNT];       // the number of active slots it holds
+    bool touched[kNT];    // ACC: an object of this call covers the pixel
+    if constexpr (MODE == FWD_ACC) {
+      bool any = false;
+#pragma unroll
+      for (int t = 0; t < kNT; ++t) {
+        touched[t] = nal[t] > 0.0f;
+        cnt[t] = ncnt[t];
+        any = any || touched[t];
+      }
+      if (has_next) {
+        nti = resolve(tile + gridDim.x);
+        load_alpha(nti, lane, nal);
+        load_cnt(tile + gridDim.x, lane, ncnt);
+      }
+      // no pixel of this wave's part takes part: only a first call's counts
+      // are left to write
+      if (__builtin_amdgcn_ballot_w64(any) == 0) {
+        if (!a.state_load && g == 0) {
+          const auto sr = st_rsrc(tile);
+#pragma unroll
+          for (int t = 0; t < kNT; ++t)
+            __builtin_amdgcn_raw_buffer_store_b32(0u, sr, st_cnt(lane, t), 0, 0);
+        }
+        continue;
+      }
+    }
 
     // FULL: sigma is needed again only by B's first layer: park it in this wave's
     // scratch instead of holding 32 registers through the slot loop
@@ -614,6 +719,14 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
       }
     };
 
+    // BEGIN: the next tile's F input, requested ahead of this tile's stores
+    // (loads issued behind stores wait for them)
+    auto next_x = [&]() {
+      if (!has_next) return;
+      nti = resolve(tile + gridDim.x);
+      load_x(nti, lane, xr);
+    };
+
     if constexpr (kTrunk) {
       u32x4 h2[kNT][KS];
       if constexpr (PE == 0) {
@@ -621,12 +734,14 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
         // (xr is read before the copies are issued: waiting for it behind them
         // would wait for them too)
         u32x4 x[kNT][1];
+        pad_x(lane, xr);
 #pragma unroll
         for (int t = 0; t < kNT; ++t)
           x[t][0] = u32x4{pk_bf16(xr[t][0], xr[t][1]), pk_bf16(xr[t][2], xr[t][3]),
                           pk_bf16(xr[t][4], xr[t][5]), pk_bf16(xr[t][6], xr[t][7])};
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (MODE == FWD_FULL) FILL(sF3);
+        if constexpr (MODE == FWD_BEGIN) next_x();
         if (canon_fast) copy_alphas();
         {
           const uint8_t *S = stage_buf(sF1);
@@ -639,6 +754,8 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
         }
       } else {
         // ====== stages 0-1: F layer 1 on the encoded input; stage 2: F layer 2 ======
+        pad_x(lane, xr);
+        __builtin_amdgcn_sched_barrier(0);
         FILL(sF1B);
         f32x4 acc[kNT][MT];
         bias_init(acc, bF1, g);
@@ -737,18 +854,16 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
       if (canon_fast && a.alpha_alias) __syncthreads();
       if constexpr (MODE == FWD_BEGIN && PE > 0) {
         if (has_next) FILL(sF1);      // the next tile's first stage
+        next_x();
       }
       layer<MT, KS, false, kEarly>(sig, stage_buf(sF3), h2, bF3, g, lane);
       if constexpr (MODE == FWD_BEGIN) {
-        // sigma goes to the streaming state; the next tile's F input is requested
+        // sigma goes to the streaming state
+        const auto sr = st_rsrc(tile);
 #pragma unroll
         for (int t = 0; t < kNT; ++t)
 #pragma unroll
-          for (int k = 0; k < KS; ++k) st_sig[(t * KS + k) * 64] = sig[t][k];
-        if (has_next) {
-          nti = resolve(tile + gridDim.x);
-          load_x(nti, lane, xr);
-        }
+          for (int k = 0; k < KS; ++k) state_store16(sr, st_sig(lane, t) + k * 64, sig[t][k]);
         if constexpr (PE > 0) {
           // the next tile's first stage has landed; this stage's buffer is free
           stage_sync();
@@ -778,46 +893,27 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
       // ================= stage 2: u = W1s sigma + c1, then the slot loop =======
       if constexpr (MODE == FWD_FULL) FILL(sT3);
       if constexpr (MODE == FWD_ACC) {
+        // sigma, and the running sum that earlier calls left
+        const auto sr = st_rsrc(tile);
 #pragma unroll
-        for (int t = 0; t < kNT; ++t)
+        for (int t = 0; t < kNT; ++t) {
+          const int off = touched[t] ? st_sig(lane, t) : kOutside;
 #pragma unroll
-          for (int k = 0; k < KS; ++k) sig[t][k] = st_sig[(t * KS + k) * 64];
+          for (int k = 0; k < KS; ++k) sig[t][k] = state_load16(sr, off + k * 64);
+        }
+#pragma unroll
+        for (int t = 0; t < kNT; ++t) {
+          const int off = touched[t] && cnt[t] > 0.0f ? st_z(lane, t) : kOutside;
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt)
+            Z[t][mt] = __builtin_bit_cast(f32x4, state_load16(sr, off + mt * 64));
+        }
       }
       {
         // the slot-order table of this tile (written above): the lane's pixel
         // of N-tile t has its entry at byte pofs + 16 t kpad
         const bool canon = MODE == FWD_FULL && a.canon && K > 1;
         const uint32_t pofs = (uint32_t)(wave * (kNT * 16) + col) * a.kpad;
-        // u = W1s sigma + c1 in fp32 accumulator layout: the C operand of h's
-        // first layer for every slot
-        f32x4 u[kNT][MT];
-        bias_init(u, bT1, g);
-        mm<MT, KS, kEarly>(u, stage_buf(sT1S), sig, lane);
-
-        if constexpr (kFp8) {
-          // fp8: h's first layer runs in units of the activation scale (its
-          // inputs b_i and u are divided by it), so its output quantises directly
-#pragma unroll
-          for (int t = 0; t < kNT; ++t)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) u[t][mt] *= a.inv_sa;
-        }
-#pragma unroll
-        for (int t = 0; t < kNT; ++t) {
-          cnt[t] = 0.0f;
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) Z[t][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-        if constexpr (MODE == FWD_ACC) {
-          if (a.state_load) {     // continue the running sum of earlier calls
-#pragma unroll
-            for (int t = 0; t < kNT; ++t) {
-              cnt[t] = st_cnt[t * 16];
-#pragma unroll
-              for (int mt = 0; mt < MT; ++mt) Z[t][mt] = st_z[(t * MT + mt) * 64];
-            }
-          }
-        }
         // Slot inputs: lane group g < 3 carries planes 4g..4g+3 of its pixel (the
         // K=16 operand of h's first layer; with encoding, lane group g carries
         // planes 3g..3g+2 and their encodings); the next slot's planes are
@@ -835,7 +931,7 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
 #pragma unroll
           for (int t = 0; t < kNT; ++t) {
             const int si = canon ? (int)L_perm[pofs + t * 16 * a.kpad + i] : i;
-            act[t] = si != 0xFF;
+            act[t] = MODE == FWD_ACC ? touched[t] : si != 0xFF;
             qs[t] = (uint32_t)si * (uint32_t)(kNL * hw) + (uint32_t)qc[t];
             asm volatile("" : "+v"(qs[t]));   // per-slot addresses stay in the loop body
           }
@@ -850,6 +946,28 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
             }
         };
         if (K > 0) load_slot(0);
+        // u = W1s sigma + c1 in fp32 accumulator layout: the C operand of h's
+        // first layer for every slot
+        f32x4 u[kNT][MT];
+        bias_init(u, bT1, g);
+        mm<MT, KS, kEarly>(u, stage_buf(sT1S), sig, lane);
+
+        if constexpr (kFp8) {
+          // fp8: h's first layer runs in units of the activation scale (its
+          // inputs b_i and u are divided by it), so its output quantises directly
+#pragma unroll
+          for (int t = 0; t < kNT; ++t)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) u[t][mt] *= a.inv_sa;
+        }
+        if constexpr (MODE == FWD_FULL) {
+#pragma unroll
+          for (int t = 0; t < kNT; ++t) {
+            cnt[t] = 0.0f;
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) Z[t][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+          }
+        }
         for (int i = 0; i < K; ++i) {
           float cur[kNT][kRaw];
 #pragma unroll
@@ -1017,13 +1135,18 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
         }
       }
       if constexpr (MODE == FWD_ACC) {
+        const auto sr = st_rsrc(tile);
 #pragma unroll
         for (int t = 0; t < kNT; ++t) {
-          if (g == 0) st_cnt[t * 16] = cnt[t];
+          // (Z is zero in pixels that stay without objects, and left unwritten)
+          const int off = touched[t] ? st_z(lane, t) : kOutside;
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt) st_z[(t * MT + mt) * 64] = Z[t][mt];
+          for (int mt = 0; mt < MT; ++mt)
+            state_store16(sr, off + mt * 64, __builtin_bit_cast(u32x4, Z[t][mt]));
+          __builtin_amdgcn_raw_buffer_store_b32(
+              __builtin_bit_cast(uint32_t, cnt[t]), sr,
+              g == 0 && (touched[t] || !a.state_load) ? st_cnt(lane, t) : kOutside, 0, 0);
         }
-        if (has_next) nti = resolve(tile + gridDim.x);
       } else {
         stage_sync();
       }
@@ -1033,15 +1156,16 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
       // ================= stage 3: pool and h layer 3 -> tau =================
       u32x4 sig2[kNT][KS];
       if constexpr (MODE == FWD_FINISH) {
-        // the pool state and sigma come from the streaming state
+        // the pool state (requested a tile ahead) and sigma come from the
+        // streaming state
+        const auto sr = st_rsrc(tile);
 #pragma unroll
         for (int t = 0; t < kNT; ++t) {
-          cnt[t] = a.state_load ? st_cnt[t * 16] : 0.0f;
+          cnt[t] = ncnt[t];
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt)
-            Z[t][mt] = a.state_load ? st_z[(t * MT + mt) * 64] : f32x4{0.f, 0.f, 0.f, 0.f};
+          for (int mt = 0; mt < MT; ++mt) Z[t][mt] = nz[t][mt];
 #pragma unroll
-          for (int k = 0; k < KS; ++k) sig2[t][k] = st_sig[(t * KS + k) * 64];
+          for (int k = 0; k < KS; ++k) sig2[t][k] = state_load16(sr, st_sig(lane, t) + k * 64);
         }
       } else if (sig_in_lds) {
 #pragma unroll
@@ -1132,6 +1256,9 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
 
       // ================= stage 8: R layer 1 on [phi; L_d] =================
       FILL(sR2);
+      if constexpr (MODE == FWD_FINISH) {
+        if (has_next) load_cnt(tile + gridDim.x, lane, ncnt);
+      }
       u32x4 hr[kNT][KS];
       {
         u32x4 ld[kNT][1];
@@ -1160,6 +1287,7 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
           lds_copy<LM::stage_bytes(sT3)>(((sT3 + (par ^ 1)) & 1) ? L_stage1 : L_stage0,
                                          packed + a.stage_off[sT3], wave, lane);
           nti = resolve(tile + gridDim.x);
+          load_z(tile + gridDim.x, lane, ncnt, nz);
         }
       }
       {

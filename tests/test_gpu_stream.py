@@ -95,6 +95,33 @@ def test_progressive_results_after_each_object(precision):
             assert np.array_equal(y, fused(net, fr, k=i + 1)), i
 
 
+@pytest.mark.parametrize("precision,W,first", [("bf16", 128, 0), ("bf16", 64, 1), ("fp8_t", 128, 2),
+                                               ("fp32", 64, 0), ("fp32", 128, 1)])
+def test_objects_covering_parts_of_the_frame_leave_the_rest(precision, W, first):
+    """Slot 0 covers nothing, slot 1 every third pixel, slot 2 a rectangle;
+    state memory that held NaN: pixels without objects are an empty pool."""
+    torch = torch_dev()
+    log(f"stream parts {precision} W={W} first={first}")
+    wts, fr = frame(1, 23, 45, 3, W, seed=41)
+    alpha = np.zeros((3, 23, 45), np.float32)
+    alpha[1].reshape(-1)[::3] = 0.5
+    alpha[2, 4:19, 7:40] = 0.25
+    fr.layers[0, :, 9] = alpha
+    order = [(first + i) % 3 for i in range(3)]
+    with open_net(wts, W, precision) as net:
+        sub = synth.Frame(fr.gbuf, np.ascontiguousarray(fr.layers[:, order]), fr.scene)
+        want = fused(net, sub)
+        g, sc = dev(fr.gbuf), dev(fr.scene)
+        st = net.stream_state(1, 23, 45)
+        st[: st.numel() // 4 * 4].view(torch.float32).fill_(float("nan"))
+        net.stream_begin(g, sc, st)
+        for i in order:
+            net.stream_accumulate(dev(fr.layers[:, i:i + 1]), st)
+        y = host(net.stream_finish(g, st))
+        net.stream_release(st)
+    np.testing.assert_array_equal(y, want)
+
+
 @pytest.mark.parametrize("precision", ["bf16", "fp32"])
 def test_no_objects_is_the_k0_forward(precision):
     wts, fr = frame(2, 23, 29, 3, 128, seed=73)
