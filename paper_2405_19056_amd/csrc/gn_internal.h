@@ -170,11 +170,12 @@ hipError_t launch_dssim(const float *out, const float *target, int planes, int h
 constexpr int kSrWidth = 32, kSrIn = 3 + 14, kSrOut = 3;
 constexpr int kSrParams = kSrWidth * kSrIn * 9 + kSrWidth + kSrWidth * kSrWidth * 9 + kSrWidth +
                           kSrOut * kSrWidth + kSrOut;
-// Floats of the kernel's re-laid weight copy (conv1's K padded to 20 input
-// channels per tap).
-constexpr int kSrWtFloats = (9 * 20 / 4) * 2 * 64 + kSrWidth + (9 * kSrWidth / 4) * 2 * 64 +
-                            kSrWidth + kSrOut * kSrWidth + kSrOut +
-                            (9 * kSrWidth / 4) * 2 * 64;  // + conv2's transpose (backward)
+// Floats of the kernels' re-laid weight copy: fp32 fragments (conv1's K padded
+// to 20 input channels per tap), biases and head, rounded up to 16 bytes, then
+// split fragments of conv1 (5 K-steps of 32), conv2 and its transpose (9 each).
+constexpr int kSrWtFloats = ((9 * 20 / 4) * 2 * 64 + kSrWidth + (9 * kSrWidth / 4) * 2 * 64 +
+                             kSrWidth + kSrOut * kSrWidth + kSrOut + 3) / 4 * 4 +
+                            (5 + 9 + 9) * 2 * 3 * 64 * 4;
 // w: packed weights (device, kSrParams floats); wt: kSrWtFloats floats of
 // device scratch for their re-laid copy; lowres [n][3][h][w], gbuf
 // [n][14][2h][2w], out [n][3][2h][2w].

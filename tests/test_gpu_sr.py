@@ -45,6 +45,28 @@ def test_sr_matches_oracle(n, h, w):
     assert err <= 1e-5
 
 
+@pytest.mark.parametrize("n,h,w", [(1, 7, 9), (2, 8, 16), (1, 9, 7), (1, 17, 24), (1, 1, 8)])
+def test_sr_forward_and_gradient_at_tile_edges(n, h, w):
+    """Outputs of 14, 16, 18 and 34 rows or columns around the 16 x 16 tiles,
+    every channel of the input on its own scale (the operands are split in
+    three per value); the bars of the tests around this one."""
+    torch = torch_dev()
+    wts = synth.make_sr_weights(np.random.default_rng(h * 31 + w))
+    lo, g = synth.make_sr_inputs(n, h, w, seed=3 * h + w)
+    g = g * (10.0 ** np.arange(-6, 8)).astype(np.float32)[None, :, None, None] ** 0.25
+    g = np.ascontiguousarray(g, dtype=np.float32)
+    dy = np.random.default_rng(h + w).normal(size=(n, 3, 2 * h, 2 * w)).astype(np.float32)
+    log(f"sr tile edges {n}x{h}x{w}")
+    with net64() as net:
+        y = run(net, wts, lo, g)
+        gw = net.sr_backward(dev(wts), dev(lo), dev(g), dev(dy))
+        torch.cuda.synchronize()
+        gw = host(gw)
+    assert relF(y, oracle.sr_forward(wts, lo, g)) <= 1e-5
+    errs = _per_tensor_relF(gw, oracle.sr_grad(wts, lo, g, dy))
+    assert max(errs.values()) <= 1e-4, errs
+
+
 def test_sr_full_frame_256_to_512():
     wts = synth.make_sr_weights(np.random.default_rng(7))
     lo, g = synth.make_sr_inputs(1, 256, 256, seed=7)
