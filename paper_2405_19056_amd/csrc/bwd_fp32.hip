@@ -12,7 +12,8 @@
 //   2. deltas: one kernel chains the transposed maps in registers from dL/dy
 //      to F's first layer, the slots in between: dz2 = [z2 > 0] m_i dZ is a
 //      selection of dZ's registers, dz1 = [z1 > 0] W_T2^T dz2, du = sum dz1.
-//      The ReLU derivatives are the stored bits.
+//      The ReLU derivatives are the stored bits; the arithmetic is fp32 on the
+//      bf16 matrix cores (operands split in three).
 //   3. weight gradients: sum_p delta_p a_p^T of every layer on the matrix
 //      cores, each pixel block read once per product.
 // Then one fixed-order reduction of the workgroups' partial sums into grad_w
@@ -20,7 +21,8 @@
 //
 // Slabs bound the workspace: a slab's blocks take at most kSlabBytes.
 //
-// Formulation.  A wave owns 16 pixels.  Every map is D = A X with a 16-row
+// Formulation of the recompute (the deltas' weights: SplitPipe of fp32_core.h).
+// A wave owns 16 pixels.  Every map is D = A X with a 16-row
 // tile of A (weights) as the row operand and the 16 pixels as the columns.
 // K-step s of the instruction takes inputs 4s .. 4s+3: lane group g (lane >>
 // 4) presents input 4s + g of its pixel (lane & 15).  The accumulator leaves
@@ -76,14 +78,15 @@ enum BwdOp {
 struct OpDesc {
   int64_t woff;      // float offset of the layer's matrix in the master vector
   int32_t ld;        // the layer's input count (master row length)
-  int32_t col0, M, K, trans;
-  int32_t mt, kq;    // 16-row tiles, 16-deep K groups
+  int32_t col0, M, K;
+  int32_t mt, kq;    // 16-row tiles, K groups (16 deep; the backward's 32)
   int32_t stage0, nstages;
 };
 
 struct OpTable {
   OpDesc op[kNumOps];
   int32_t nops, stages;            // stages of every map together
+  int32_t stage_bytes;
   LayerOff lo[kNumLayers];
   int32_t W, pe;
 };
@@ -91,10 +94,10 @@ struct OpTable {
 // The packed form: the stages, then the 12 biases (W floats each, in the
 // position order below).
 static size_t packed_bytes(const OpTable &t) {
-  return ((size_t)t.stages * kStageBytes + sizeof(float) * kNumLayers * t.W + 1023) / 1024 * 1024;
+  return ((size_t)t.stages * t.stage_bytes + sizeof(float) * kNumLayers * t.W + 1023) / 1024 * 1024;
 }
 
-// What the backward keeps of a slab of np pixels (a multiple of kTile, the
+// What the backward keeps of a slab of np pixels (a multiple of 2 kTile, the
 // tail repeating the last pixel): blocks [pixel][width] in position order.
 // The slots' blocks follow each other slot by slot ([slot][pixel][width]).
 struct Planes {
@@ -124,6 +127,8 @@ static void fill_table(int W, int pe, const OpSpec *s, int n, int trans, OpTable
   t->W = W;
   t->pe = pe;
   t->nops = n;
+  // the forward's maps as fp32 fragments, the backward's split in three
+  t->stage_bytes = trans ? kSplitStage : kStageBytes;
   int stage = 0;
   for (int i = 0; i < n; ++i) {
     OpDesc &d = t->op[s[i].op];
@@ -132,11 +137,10 @@ static void fill_table(int W, int pe, const OpSpec *s, int n, int trans, OpTable
     d.col0 = s[i].col0;
     d.M = s[i].M;
     d.K = s[i].K;
-    d.trans = trans;
     d.mt = (d.M + 15) / 16;
-    d.kq = (d.K + 15) / 16;
+    d.kq = trans ? (d.K + 31) / 32 : (d.K + 15) / 16;
     d.stage0 = stage;
-    d.nstages = (d.kq * d.mt + kStageFrags - 1) / kStageFrags;
+    d.nstages = (d.kq * d.mt * (trans ? 3 : 1) * 1024 + t->stage_bytes - 1) / t->stage_bytes;
     stage += d.nstages;
   }
   t->stages = stage;
@@ -164,9 +168,12 @@ static void make_bwd_ops(int W, int pe, OpTable *t) {
 }
 
 // One thread per 16 bytes of a fragment, then the biases; blockIdx.y selects
-// the forward's or the backward's maps.  Fragment f of a map is K group f / mt
-// of row tile f % mt; element j of lane l is A[row (l & 15)][16 q + 4 j +
-// (l >> 4)], zero outside M x K.
+// the forward's or the backward's maps.  Fragment f of a forward's map is K
+// group f / mt of row tile f % mt; element j of lane l is A[row (l & 15)][16 q
+// + 4 j + (l >> 4)], zero outside M x K.  The backward's: a thread per lane of
+// a K group's row tile (its three parts); element e of lane group g is input
+// 32 q + 16 (e / 4) + 4 (e % 4) + g, what it holds in element e of the map
+// before (R3's three: input g in element 0).
 struct PackArgs {
   OpTable t[2];
   uint8_t *packed[2];
@@ -176,6 +183,27 @@ __global__ __launch_bounds__(kThreads) void f32_pack_kernel(const float *__restr
   const OpTable &t = a.t[blockIdx.y];
   uint8_t *packed = a.packed[blockIdx.y];
   const int e = blockIdx.x * kThreads + threadIdx.x;
+  if (blockIdx.y == 1) {
+    const int n = e >> 6, lane = e & 63, g = lane >> 4, i = lane & 15;
+    if (n >= t.stages * (kSplitFrags / 3)) return;
+    int o = 0;
+    while (o + 1 < t.nops && n / (kSplitFrags / 3) >= t.op[o + 1].stage0) ++o;
+    const OpDesc d = t.op[o];
+    const int f = n - d.stage0 * (kSplitFrags / 3), q = f / d.mt;
+    const int m = 16 * (f % d.mt) + 4 * (i & 3) + (i >> 2);   // rows in position order
+    float x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int k = d.K < 16 ? (j == 0 ? g : d.K) : 32 * q + 16 * (j >> 2) + 4 * (j & 3) + g;
+      x[j] = q < d.kq && m < d.M && k < d.K ? master[d.woff + (int64_t)k * d.ld + d.col0 + m] : 0.0f;
+    }
+    const Split s = split8(x);
+    u32x4 *dst = (u32x4 *)packed + (size_t)n * 3 * 64 + lane;
+    dst[0] = s.hi;
+    dst[64] = s.mid;
+    dst[128] = s.lo;
+    return;
+  }
   const int total = t.stages * kStageFrags * 64;
   if (e >= total) {
     const int b = e - total, l = b / t.W, p = b % t.W;
@@ -196,8 +224,7 @@ __global__ __launch_bounds__(kThreads) void f32_pack_kernel(const float *__restr
   for (int j = 0; j < 4; ++j) {
     const int k = 16 * q + 4 * j + (lane >> 4);
     if (m < d.M && k < d.K)
-      v[j] = d.trans ? master[d.woff + (int64_t)k * d.ld + d.col0 + m]
-                     : master[d.woff + (int64_t)m * d.ld + d.col0 + k];
+      v[j] = master[d.woff + (int64_t)m * d.ld + d.col0 + k];
   }
   ((f32x4 *)packed)[e] = v;
 }
@@ -554,40 +581,62 @@ struct DeltaArgs {
   int64_t npx;
 };
 
-template <int W>
-__global__ __launch_bounds__(kThreads, 2) void f32_delta_kernel(DeltaArgs a) {
-  constexpr int MT = W / 16;
+// A wave owns 16 pixels, a workgroup WAVES * 16.  The maps run on split operands
+// (fp32_core.h); sigma's delta waits in LDS while the slots run.  Every other
+// wave computes the negative of its deltas: the bf16 instruction rounds its sums
+// towards minus infinity, by a fraction of an ulp that a sum over many pixels
+// would collect (1e-5 of a gradient over 2^18 pixels with random dy).
+//
+// What bounds it: HBM and the matrix cores in turn.  16 x 128^2, K = 4, W = 128:
+// 2.3 GB of deltas written (450 us at the copy rate) and 340 us of matrix-core
+// work take 841 us; on the fp32 instruction, with 900 us of such work, 1132.
+template <int W, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, WAVES / 4) void f32_delta_kernel(DeltaArgs a) {
+  constexpr int MT = W / 16, KS = W / 32, kPx = WAVES * 16;
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   const int wave = threadIdx.x >> 6;
-  Pipe<MT> pipe;
+  f32x4 *l_dsig = (f32x4 *)(lds + kRing * kSplitStage) + wave * MT * 64 + (threadIdx.x & 63);
+  SplitPipe<MT, WAVES> pipe;
   pipe.start(a.packed, lds, a.pg);
-  const int64_t ntiles = a.pl.np / kTile;
+  const float sign = wave & 1 ? -1.0f : 1.0f;
+  const int64_t ntiles = a.pl.np / kPx;
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     int g = (threadIdx.x & 63) >> 4, col = threadIdx.x & 15;
     asm volatile("" : "+v"(g), "+v"(col));      // per-tile copies, as in the forward
-    const int64_t pl = tile * kTile + wave * 16 + col, p = a.pl.p0 + pl;
+    const int64_t pl = tile * kPx + wave * 16 + col, p = a.pl.p0 + pl;
     const uint32_t at = (uint32_t)pl * (W * 4) + 16 * g;
-    f32x4 in[MT], acc[MT];
-    auto save = [&](float *plane, const f32x4 (&v)[MT]) {
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) *(f32x4 *)((char *)plane + at + 64 * mt) = v[mt];
-    };
+    f32x4 acc[MT];
+    Split in[KS];
     auto signs = [&](int layer) {
       const uint32_t *words = a.pl.mask + (int64_t)layer * (a.pl.np / 16) * 64;
-      return words[(uint32_t)(tile * kThreads) + threadIdx.x];
+      return words[(uint32_t)(tile * (WAVES * 64)) + threadIdx.x];
     };
-    // out = the accumulators where the bits say so
-    auto masked = [&](f32x4 (&out)[MT], uint32_t bits) {
+    // v to its plane; v, split, to the next map
+    auto put = [&](float *plane, const f32x4 (&v)[MT]) {
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) *(f32x4 *)((char *)plane + at + 64 * mt) = sign * v[mt];
+    };
+    auto feed = [&](const f32x4 (&v)[MT]) {
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        float x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = v[2 * s + (j >> 2)][j & 3];
+        in[s] = split8(x);
+      }
+    };
+    // v where the bits say so
+    auto mask = [&](f32x4 (&v)[MT], uint32_t bits) {
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          out[mt][r] = bits & (1u << (4 * mt + r)) ? acc[mt][r] : 0.0f;
-          acc[mt][r] = 0.0f;
-        }
+        for (int r = 0; r < 4; ++r) v[mt][r] = bits & (1u << (4 * mt + r)) ? v[mt][r] : 0.0f;
     };
+    auto clear = [&]() {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[mt] = zero4();
+      for (int mt = 0; mt < MT; ++mt) acc[mt] = zero4();
+    };
+    clear();
     // dL/dy of the pixel: lane group g < 3 channel g (padding pixels: zero, so
     // every delta of theirs is zero)
     float dy = 0.0f;
@@ -596,39 +645,48 @@ __global__ __launch_bounds__(kThreads, 2) void f32_delta_kernel(DeltaArgs a) {
       dy = a.dy[(f * kNOUT + g) * a.hw + (p - f * a.hw)];
     }
     *(f32x4 *)(a.pl.dy + (uint32_t)pl * kDyWidth + 4 * g) = f32x4{dy, 0.f, 0.f, 0.f};
+    dy *= sign;
     uint32_t bits = signs(K_G2), nbits = signs(K_G1);
-    pipe.gather(acc, 1, [&](int) { return f32x4{dy, 0.f, 0.f, 0.f}; });
-    masked(in, bits);
-    save(a.pl.dg2, in);
+    pipe.gather(acc, 1, [&](int) {
+      const float x[8] = {dy, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      return split8(x);
+    });
+    auto next = [&](float *plane) {            // the accumulators are this plane's delta
+      put(plane, acc);
+      feed(acc);
+      clear();
+    };
+    mask(acc, bits);
+    next(a.pl.dg2);
     bits = signs(K_D2);
     pipe.chain(acc, in);
-    masked(in, nbits);
-    save(a.pl.dg1, in);
+    mask(acc, nbits);
+    next(a.pl.dg1);
     pipe.chain(acc, in);
-    masked(in, ~0u);
-    save(a.pl.dphi, in);
+    next(a.pl.dphi);
     nbits = signs(K_D1);
     pipe.chain(acc, in);
-    masked(in, bits);
-    save(a.pl.dd2, in);
+    mask(acc, bits);
+    next(a.pl.dd2);
     const float inv = a.pl.inv[(uint32_t)pl];
     pipe.chain(acc, in);
-    masked(in, nbits);
-    save(a.pl.dd1, in);
-    f32x4 dsig[MT], dz[MT], du[MT];
+    mask(acc, nbits);
+    next(a.pl.dd1);
     pipe.chain(acc, in);
-    masked(dsig, ~0u);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) l_dsig[mt * 64] = acc[mt];
+    clear();
     pipe.chain(acc, in);
-    masked(in, ~0u);                            // dtau
-    save(a.pl.dtau, in);
+    next(a.pl.dtau);
     pipe.chain(acc, in);
+    f32x4 dz[MT], du[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       dz[mt] = acc[mt] * inv;                   // dZ = W_T3^T dtau / max(c, 1)
-      acc[mt] = zero4();
       du[mt] = zero4();
     }
-    save(a.pl.dz, dz);
+    clear();
+    put(a.pl.dz, dz);
     uint32_t b2 = 0, b1 = 0;
     if (a.k > 0) {
       b1 = signs(kMasks);
@@ -641,33 +699,36 @@ __global__ __launch_bounds__(kThreads, 2) void f32_delta_kernel(DeltaArgs a) {
         n2 = signs(kMasks + 2 * i + 3);
       }
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
+      for (int s = 0; s < KS; ++s) {
+        float x[8];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) in[mt][r] = b2 & (1u << (4 * mt + r)) ? dz[mt][r] : 0.0f;
+        for (int j = 0; j < 8; ++j)
+          x[j] = b2 & (1u << (8 * s + j)) ? dz[2 * s + (j >> 2)][j & 3] : 0.0f;
+        in[s] = split8(x);
+      }
       pipe.chain(acc, in);
-      masked(in, b1);
-      save(a.pl.dz1 + (int64_t)i * a.pl.np * W, in);
+      mask(acc, b1);
+      put(a.pl.dz1 + (int64_t)i * a.pl.np * W, acc);
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) du[mt] += in[mt];
+      for (int mt = 0; mt < MT; ++mt) du[mt] += acc[mt];
+      clear();
       b1 = n1;
       b2 = n2;
     }
-    save(a.pl.du, du);
+    put(a.pl.du, du);
+    feed(du);
     bits = signs(K_A2);
     nbits = signs(K_A1);
-    pipe.chain(acc, du);
+    pipe.chain(acc, in);
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      in[mt] = acc[mt] + dsig[mt];
-      acc[mt] = zero4();
-    }
-    save(a.pl.dsig, in);
+    for (int mt = 0; mt < MT; ++mt) acc[mt] += l_dsig[mt * 64];
+    next(a.pl.dsig);
     pipe.chain(acc, in);
-    masked(in, bits);
-    save(a.pl.da2, in);
+    mask(acc, bits);
+    next(a.pl.da2);
     pipe.chain(acc, in);
-    masked(in, nbits);
-    save(a.pl.da1, in);
+    mask(acc, nbits);
+    put(a.pl.da1, acc);
   }
 }
 
@@ -701,7 +762,8 @@ constexpr int part_floats(int W, int MI) { return W * 16 * MI + W + 16 * MI; }
 // the step before computes, then written to LDS; row p of a block keeps its
 // 16-byte unit c at c ^ swz(p), so that the four pixels that the lane groups
 // read fall into distinct banks.  A step is one 32-deep group of the bf16 matrix
-// cores on operands split in three (fp32_core.h).
+// cores on operands split in three (fp32_core.h); every other workgroup sums the
+// negative of its product, as the deltas do.
 template <int W, int MI>
 __global__ __launch_bounds__(kThreads, 2) void f32_dw_kernel(DwArgs a) {
   constexpr int MO = W / 16;
@@ -715,6 +777,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dw_kernel(DwArgs a) {
   __shared__ float lw[2][kStep];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, l = lane & 15;
   const int wr = wave / WC, wc = wave % WC;
+  const float sign = blockIdx.x & 1 ? -1.0f : 1.0f;
   auto dswz = [](int p) { return 4 * (p & 3); };
   auto aswz = [](int p) { return MI >= 4 ? 4 * (p & 3) : (MI == 2 ? 4 * ((p >> 1) & 1) : 0); };
 
@@ -769,7 +832,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dw_kernel(DwArgs a) {
       for (int i = 0; i < NA; ++i) {
         const int e = tid + i * kThreads, p = e / AU, u = e % AU;
         if (kStep * AU % kThreads == 0 || e < kStep * AU)
-          la[b][p * AU + (u ^ aswz(p))] = ha[i];
+          la[b][p * AU + (u ^ aswz(p))] = sign * ha[i];
       }
       if (tid < kStep) lw[b][tid] = hw;
     };
@@ -833,7 +896,8 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dw_kernel(DwArgs a) {
       for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          put(P + (16 * (wr * TO + o) + 4 * g + r) * 16 * MI + 16 * (wc * TI + i) + l, acc[o][i][r]);
+          put(P + (16 * (wr * TO + o) + 4 * g + r) * 16 * MI + 16 * (wc * TI + i) + l,
+              sign * acc[o][i][r]);
 #pragma unroll
     for (int o = 0; o < TO; ++o) {
       dsum[o] += __shfl_xor(dsum[o], 16);
@@ -844,7 +908,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dw_kernel(DwArgs a) {
     for (int i = 0; i < TI; ++i) {
       asum[i] += __shfl_xor(asum[i], 16);
       asum[i] += __shfl_xor(asum[i], 32);
-      if (wr == 0 && g == 0) put(P + W * 16 * MI + W + 16 * (wc * TI + i) + l, asum[i]);
+      if (wr == 0 && g == 0) put(P + W * 16 * MI + W + 16 * (wc * TI + i) + l, sign * asum[i]);
     }
   }
 }
@@ -1092,7 +1156,8 @@ static hipError_t launch_save(int W, const SaveArgs &a, int num_cus, hipStream_t
 static hipError_t launch_pack(const float *master, const PackArgs &p, int tables, hipStream_t s) {
   int64_t n = 0;
   for (int i = 0; i < tables; ++i)
-    n = std::max<int64_t>(n, (int64_t)p.t[i].stages * kStageFrags * 64 + kNumLayers * p.t[i].W);
+    n = std::max<int64_t>(n, (int64_t)p.t[i].stages * (i ? kSplitFrags / 3 : kStageFrags) * 64 +
+                                 (i ? 0 : kNumLayers * p.t[i].W));
   hipLaunchKernelGGL(f32_pack_kernel, dim3((unsigned)((n + kThreads - 1) / kThreads), tables),
                      dim3(kThreads), 0, s, master, p);
   return hipGetLastError();
@@ -1123,11 +1188,23 @@ static SaveArgs save_args(gn_handle *h, const gn_frame *frame, const OpTable &t,
   return a;
 }
 
+template <int W, int WAVES>
+static hipError_t launch_delta_form(const DeltaArgs &a, int num_cus, hipStream_t s) {
+  constexpr int lds = kRing * kSplitStage + WAVES * (W / 16) * 1024;
+  static const hipError_t attr = hipFuncSetAttribute(
+      (const void *)f32_delta_kernel<W, WAVES>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (attr != hipSuccess) return attr;
+  const unsigned grid = (unsigned)std::min<int64_t>(a.pl.np / (WAVES * 16), num_cus);
+  hipLaunchKernelGGL((f32_delta_kernel<W, WAVES>), dim3(grid), dim3(WAVES * 64), lds, s, a);
+  return hipGetLastError();
+}
+
+// Four waves (64 pixels) a workgroup where eight would leave CUs idle, as in
+// the fp32 forward.
 template <int W>
 static hipError_t launch_delta(const DeltaArgs &a, int num_cus, hipStream_t s) {
-  const unsigned grid = (unsigned)std::min<int64_t>(a.pl.np / kTile, 2 * num_cus);
-  hipLaunchKernelGGL(f32_delta_kernel<W>, dim3(grid), dim3(kThreads), kRing * kStageBytes, s, a);
-  return hipGetLastError();
+  return a.pl.np <= (int64_t)num_cus * kTile ? launch_delta_form<W, 4>(a, num_cus, s)
+                                             : launch_delta_form<W, 8>(a, num_cus, s);
 }
 
 }  // namespace f32
@@ -1157,7 +1234,7 @@ static gn_status backward(gn_handle *h, const gn_frame *frame, const float *dy, 
   // slabs of equal length (the last may be shorter) within the workspace bound
   const int64_t per_px = f32::px_floats(W, pe, k) * (int64_t)sizeof(float);
   const int64_t most = (int64_t)(f32::kSlabBytes / per_px), slabs = (npx + most - 1) / most;
-  const int64_t np = f32::rup((npx + slabs - 1) / slabs, f32::kTile);
+  const int64_t np = f32::rup((npx + slabs - 1) / slabs, 2 * f32::kTile);
   f32::Gradient grad(W, pe, k, h->num_cus);
   const size_t part = grad.split(np) * sizeof(float);
   const size_t planes = f32::rup(np * per_px, 1024);
@@ -1192,7 +1269,7 @@ static gn_status backward(gn_handle *h, const gn_frame *frame, const float *dy, 
   d.npx = npx;
   const int cus = h->num_cus;
   for (int64_t p0 = 0; p0 < npx && e == hipSuccess; p0 += np) {
-    f32::Planes pl = f32::carve((float *)ws->mem, W, pe, k, std::min(np, f32::rup(npx - p0, f32::kTile)));
+    f32::Planes pl = f32::carve((float *)ws->mem, W, pe, k, std::min(np, f32::rup(npx - p0, 2 * f32::kTile)));
     pl.p0 = p0;
     a.pl = d.pl = pl;
     e = f32::launch_save<false>(W, a, cus, s);

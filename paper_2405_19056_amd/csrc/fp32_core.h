@@ -145,5 +145,130 @@ struct Sequence {
 
 constexpr int kRing = 3;     // stage buffers in LDS
 
+// The weights of the kernels with split operands.  Packed as the three parts'
+// fragments (64 lanes x 16 bytes) in the order the kernel consumes them, they
+// stream through LDS in 24 KiB stages (a K-step at W = 128, two at 64) by way of
+// registers, in a ring of three buffers with one barrier in the middle of each
+// stage: past it every wave is done with the stage before, whose buffer then
+// takes the stage after the next one, and the next stage's first fragments are
+// read before this one ends.
+constexpr int kSplitFrags = 24, kSplitStage = kSplitFrags * 1024;
+
+template <int MT, int WAVES>
+struct SplitPipe {
+  static constexpr int kThreads = WAVES * 64;
+  static constexpr int kHold = kSplitStage / 16 / kThreads;
+  static constexpr int kSteps = kSplitFrags / (3 * MT);    // K-steps per stage
+  static constexpr int KS = MT / 2;                        // K-steps of a W-wide map
+  rsrc_t base;
+  uint8_t *lds;          // kRing stage buffers
+  Sequence seq;          // of the stages to load
+  int cur;               // buffer of the stage being consumed
+  u32x4 hold[kHold];     // the stage two ahead of it
+  u32x4 w[2][6];         // two row tiles' three parts; w[0]: the first of the stage to consume
+
+  __device__ __forceinline__ void load() {
+    const uint32_t at = (uint32_t)seq.next() * kSplitStage;
+#pragma unroll
+    for (int i = 0; i < kHold; ++i)
+      hold[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                              base, threadIdx.x * 16, at + i * kThreads * 16, 0));
+  }
+  __device__ __forceinline__ void store(int buf) {
+    u32x4 *dst = (u32x4 *)(lds + buf * kSplitStage) + threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < kHold; ++i) dst[i * kThreads] = hold[i];
+  }
+  __device__ __forceinline__ void start(const uint8_t *b, uint8_t *l, const Program &p) {
+    base = make_rsrc(b);
+    lds = l;
+    seq.start(p);
+    cur = 0;
+    load();
+    store(0);
+    load();
+    store(1);
+    load();
+    __syncthreads();
+    fetch(w[0], 0, 0);
+  }
+  // Six fragments of a buffer: two row tiles of a K-step.
+  __device__ __forceinline__ void fetch(u32x4 (&d)[6], int buf, int group) {
+    const u32x4 *s = (const u32x4 *)(lds + buf * kSplitStage) + (threadIdx.x & 63) + group * 384;
+#pragma unroll
+    for (int m = 0; m < 6; ++m) d[m] = s[m * 64];
+  }
+  __device__ __forceinline__ int after(int buf) const { return buf == kRing - 1 ? 0 : buf + 1; }
+  // The middle of a stage.  Only LDS traffic is drained: the loads and stores
+  // in flight stay so.
+  __device__ __forceinline__ void middle() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    store(cur == 0 ? kRing - 1 : cur - 1);
+    load();
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
+  // One stage: K-steps s0 .. of a map; step s0 + i is used while s0 + i <
+  // steps.  x(i) gives its inputs.  Two row tiles' fragments are read ahead of
+  // the twelve MFMAs of the two before (a scheduling barrier keeps them there).
+  template <class X>
+  __device__ __forceinline__ void stage(f32x4 (&acc)[MT], int s0, int steps, X x) {
+    constexpr int kPer = MT / 2;                 // tile pairs per K-step
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int m0 = 2 * (i % kPer);
+      if (i == 2) middle();
+      if (i < 3) fetch(w[(i + 1) & 1], cur, i + 1);
+      else fetch(w[0], after(cur), 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (s0 + i / kPer < steps) {
+        const Split &b = x(i / kPer);
+        const u32x4(&a)[6] = w[i & 1];
+        // small partial products first, the two tiles in turn
+#pragma unroll
+        for (int p = 0; p < 6; ++p) {
+          constexpr int kA[6] = {2, 0, 1, 1, 0, 0}, kB[6] = {0, 2, 1, 0, 1, 0};
+          const u32x4 bv = kB[p] == 0 ? b.hi : (kB[p] == 1 ? b.mid : b.lo);
+#pragma unroll
+          for (int m = 0; m < 2; ++m) acc[m0 + m] = mma_bf16(a[3 * m + kA[p]], bv, acc[m0 + m]);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    cur = after(cur);
+  }
+  // A map over W inputs, in[s] K-step s.
+  __device__ __forceinline__ void chain(f32x4 (&acc)[MT], const Split (&in)[KS]) {
+#pragma unroll
+    for (int st = 0; st < KS / kSteps; ++st)
+      stage(acc, st * kSteps, KS, [&](int i) -> const Split & { return in[st * kSteps + i]; });
+  }
+  // A map of `steps` K-steps whose inputs x(s) computes.
+  template <class X>
+  __device__ __forceinline__ void gather(f32x4 (&acc)[MT], int steps, X x) {
+    for (int s0 = 0; s0 < steps; s0 += kSteps) {
+      Split v[kSteps];
+#pragma unroll
+      for (int i = 0; i < kSteps; ++i)
+        if (s0 + i < steps) v[i] = x(s0 + i);
+      stage(acc, s0, steps, [&](int i) -> const Split & { return v[i]; });
+    }
+  }
+  // A map of one row tile over W inputs: KS K-steps of three fragments.
+  __device__ __forceinline__ f32x4 tail(const Split (&in)[KS]) {
+    f32x4 acc = zero4();
+    if (KS > 2) fetch(w[1], cur, 1);
+    middle();
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const u32x4 *a = &w[s >> 1][3 * (s & 1)];
+      acc = mma_split(Split{a[0], a[1], a[2]}, in[s], acc);
+    }
+    cur = after(cur);
+    fetch(w[0], cur, 0);
+    return acc;
+  }
+};
+
 }  // namespace f32
 }  // namespace gn

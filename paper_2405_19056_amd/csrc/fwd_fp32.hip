@@ -11,13 +11,7 @@
 // columns are packed in that order, so activations go from map to map by a
 // ReLU and a split inside the lane.
 //
-// Weights.  Packed as the three parts' fragments (64 lanes x 16 bytes) in the
-// order the kernel consumes them, they stream through LDS in 24 KiB stages (a
-// K-step at W = 128, two at 64) by way of registers, in a ring of three
-// buffers with one barrier in the middle of each stage: past it every wave is
-// done with the stage before, whose buffer then takes the stage after the
-// next one, and the next stage's first fragments are read before this one
-// ends.
+// Weights: SplitPipe of fp32_core.h.
 //
 // Work split.  One workgroup of eight waves per CU takes tiles of 128 pixels
 // (four waves and 64 where 128 would leave CUs idle).  Per pixel and wave the
@@ -36,8 +30,6 @@
 
 namespace gn {
 namespace f32 {
-
-constexpr int kStageFrags = 24, kStageBytes = kStageFrags * 1024;
 
 // The linear maps in the order the kernel consumes them.
 enum Op {
@@ -93,14 +85,14 @@ static void make_ops(int W, int pe, OpTable *t) {
     d.steps = s[i].steps;
     d.mt = (d.M + 15) / 16;
     d.stage0 = stage;
-    stage += (d.steps * d.mt * 3 + kStageFrags - 1) / kStageFrags;
+    stage += (d.steps * d.mt * 3 + kSplitFrags - 1) / kSplitFrags;
   }
   t->stages = stage;
 }
 
 // The stages, then the 12 biases (W floats each).
 static size_t packed_bytes(const OpTable &t) {
-  return (size_t)t.stages * kStageBytes + sizeof(float) * kNumLayers * t.W;
+  return (size_t)t.stages * kSplitStage + sizeof(float) * kNumLayers * t.W;
 }
 
 // One thread per lane of a K-step's row tile (its three parts), then the
@@ -108,19 +100,19 @@ static size_t packed_bytes(const OpTable &t) {
 __global__ __launch_bounds__(256) void f32_split_pack_kernel(const float *__restrict__ master,
                                                              OpTable t, uint8_t *__restrict__ packed) {
   const int e = blockIdx.x * 256 + threadIdx.x;
-  const int total = t.stages * (kStageFrags / 3) * 64;
+  const int total = t.stages * (kSplitFrags / 3) * 64;
   if (e >= total) {
     const int b = e - total, l = b / t.W, o = b % t.W;
     if (l < kNumLayers)
-      ((float *)(packed + (size_t)t.stages * kStageBytes))[b] =
+      ((float *)(packed + (size_t)t.stages * kSplitStage))[b] =
           o < t.lo[l].out ? master[t.lo[l].b + o] : 0.0f;
     return;
   }
-  const int stage = e / (kStageFrags / 3 * 64);
+  const int stage = e / (kSplitFrags / 3 * 64);
   int o = 0;
   while (o + 1 < kNumOps && stage >= t.op[o + 1].stage0) ++o;
   const OpDesc d = t.op[o];
-  const int n = (e >> 6) - d.stage0 * (kStageFrags / 3), lane = e & 63, g = lane >> 4;
+  const int n = (e >> 6) - d.stage0 * (kSplitFrags / 3), lane = e & 63, g = lane >> 4;
   const int step = n / d.mt, m = 16 * (n % d.mt) + (lane & 15);
   float x[8];
 #pragma unroll
@@ -160,122 +152,6 @@ struct FwdArgs {
 
 enum Mode { M_FULL, M_BEGIN, M_ACC, M_FINISH };
 
-template <int MT, int WAVES>
-struct Pipe {
-  static constexpr int kThreads = WAVES * 64;
-  static constexpr int kHold = kStageBytes / 16 / kThreads;
-  static constexpr int kSteps = kStageFrags / (3 * MT);    // K-steps per stage
-  static constexpr int KS = MT / 2;                        // K-steps of a W-wide map
-  rsrc_t base;
-  uint8_t *lds;          // kRing stage buffers
-  Sequence seq;          // of the stages to load
-  int cur;               // buffer of the stage being consumed
-  u32x4 hold[kHold];     // the stage two ahead of it
-  u32x4 w[2][6];         // two row tiles' three parts; w[0]: the first of the stage to consume
-
-  __device__ __forceinline__ void load() {
-    const uint32_t at = (uint32_t)seq.next() * kStageBytes;
-#pragma unroll
-    for (int i = 0; i < kHold; ++i)
-      hold[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                              base, threadIdx.x * 16, at + i * kThreads * 16, 0));
-  }
-  __device__ __forceinline__ void store(int buf) {
-    u32x4 *dst = (u32x4 *)(lds + buf * kStageBytes) + threadIdx.x;
-#pragma unroll
-    for (int i = 0; i < kHold; ++i) dst[i * kThreads] = hold[i];
-  }
-  __device__ __forceinline__ void start(const uint8_t *b, uint8_t *l, const Program &p) {
-    base = make_rsrc(b);
-    lds = l;
-    seq.start(p);
-    cur = 0;
-    load();
-    store(0);
-    load();
-    store(1);
-    load();
-    __syncthreads();
-    fetch(w[0], 0, 0);
-  }
-  // Six fragments of a buffer: two row tiles of a K-step.
-  __device__ __forceinline__ void fetch(u32x4 (&d)[6], int buf, int group) {
-    const u32x4 *s = (const u32x4 *)(lds + buf * kStageBytes) + (threadIdx.x & 63) + group * 384;
-#pragma unroll
-    for (int m = 0; m < 6; ++m) d[m] = s[m * 64];
-  }
-  __device__ __forceinline__ int after(int buf) const { return buf == kRing - 1 ? 0 : buf + 1; }
-  // The middle of a stage.  Only LDS traffic is drained: the loads and stores
-  // in flight stay so.
-  __device__ __forceinline__ void middle() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    store(cur == 0 ? kRing - 1 : cur - 1);
-    load();
-    __builtin_amdgcn_sched_barrier(0);
-  }
-
-  // One stage: K-steps s0 .. of a map; step s0 + i is used while s0 + i <
-  // steps.  x(i) gives its inputs.  Two row tiles' fragments are read ahead of
-  // the twelve MFMAs of the two before (a scheduling barrier keeps them there).
-  template <class X>
-  __device__ __forceinline__ void stage(f32x4 (&acc)[MT], int s0, int steps, X x) {
-    constexpr int kPer = MT / 2;                 // tile pairs per K-step
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int m0 = 2 * (i % kPer);
-      if (i == 2) middle();
-      if (i < 3) fetch(w[(i + 1) & 1], cur, i + 1);
-      else fetch(w[0], after(cur), 0);
-      __builtin_amdgcn_sched_barrier(0);
-      if (s0 + i / kPer < steps) {
-        const Split &b = x(i / kPer);
-        const u32x4(&a)[6] = w[i & 1];
-        // small partial products first, the two tiles in turn
-#pragma unroll
-        for (int p = 0; p < 6; ++p) {
-          constexpr int kA[6] = {2, 0, 1, 1, 0, 0}, kB[6] = {0, 2, 1, 0, 1, 0};
-          const u32x4 bv = kB[p] == 0 ? b.hi : (kB[p] == 1 ? b.mid : b.lo);
-#pragma unroll
-          for (int m = 0; m < 2; ++m) acc[m0 + m] = mma_bf16(a[3 * m + kA[p]], bv, acc[m0 + m]);
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    cur = after(cur);
-  }
-  // A map over W inputs, in[s] K-step s.
-  __device__ __forceinline__ void chain(f32x4 (&acc)[MT], const Split (&in)[KS]) {
-#pragma unroll
-    for (int st = 0; st < KS / kSteps; ++st)
-      stage(acc, st * kSteps, KS, [&](int i) -> const Split & { return in[st * kSteps + i]; });
-  }
-  // A map of `steps` K-steps whose inputs x(s) computes.
-  template <class X>
-  __device__ __forceinline__ void gather(f32x4 (&acc)[MT], int steps, X x) {
-    for (int s0 = 0; s0 < steps; s0 += kSteps) {
-      Split v[kSteps];
-#pragma unroll
-      for (int i = 0; i < kSteps; ++i)
-        if (s0 + i < steps) v[i] = x(s0 + i);
-      stage(acc, s0, steps, [&](int i) -> const Split & { return v[i]; });
-    }
-  }
-  // A map of one row tile over W inputs: KS K-steps of three fragments.
-  __device__ __forceinline__ f32x4 tail(const Split (&in)[KS]) {
-    f32x4 acc = zero4();
-    if (KS > 2) fetch(w[1], cur, 1);
-    middle();
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      const u32x4 *a = &w[s >> 1][3 * (s & 1)];
-      acc = mma_split(Split{a[0], a[1], a[2]}, in[s], acc);
-    }
-    cur = after(cur);
-    fetch(w[0], cur, 0);
-    return acc;
-  }
-};
-
 // ENC: with positional encoding (a form of its own: the sine and cosine's code
 // and registers stay out of the plain one).
 template <int W, int MODE, bool ENC, int WAVES>
@@ -286,15 +162,15 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void f32_forward_kernel(FwdA
   constexpr bool kHead = MODE == M_FULL || MODE == M_FINISH;
   // LDS: the stage ring | biases | sigma per wave | slot order per pixel
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
-  float *l_bias = (float *)(lds + kRing * kStageBytes);
+  float *l_bias = (float *)(lds + kRing * kSplitStage);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   f32x4 *l_sig = (f32x4 *)(l_bias + kNumLayers * W) + wave * MT * 64 + lane;
   uint8_t *l_order = (uint8_t *)(l_bias + kNumLayers * W) + (kHead ? WAVES * MT * 1024 : 0);
   {
-    const float *b = (const float *)(a.packed + (size_t)a.bias_stage * kStageBytes);
+    const float *b = (const float *)(a.packed + (size_t)a.bias_stage * kSplitStage);
     for (int i = threadIdx.x; i < kNumLayers * W; i += WAVES * 64) l_bias[i] = b[i];
   }
-  Pipe<MT, WAVES> pipe;
+  SplitPipe<MT, WAVES> pipe;
   pipe.start(a.packed, lds, a.pg);       // ends with a barrier
   const int hw = a.hw, nblk = ENC ? pe_blocks(a.pe) : 1;
   const int64_t ntiles = (a.npx + kTile - 1) / kTile;
@@ -529,7 +405,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void f32_forward_kernel(FwdA
 template <int W, int MODE, bool ENC, int WAVES>
 static hipError_t launch_waves(const FwdArgs &a, int num_cus, hipStream_t s) {
   constexpr bool kHead = MODE == M_FULL || MODE == M_FINISH;
-  const size_t lds = kRing * kStageBytes + sizeof(float) * kNumLayers * W +
+  const size_t lds = kRing * kSplitStage + sizeof(float) * kNumLayers * W +
                      (kHead ? (size_t)WAVES * (W / 16) * 1024 : 0) + (size_t)WAVES * 16 * a.kpad;
   static const hipError_t attr =     // per process; the attribute is per function
       hipFuncSetAttribute((const void *)f32_forward_kernel<W, MODE, ENC, WAVES>,
@@ -584,7 +460,7 @@ size_t gn_f32_packed_bytes(int W, int pe) {
 hipError_t gn_f32_pack(gn_handle *h, hipStream_t s) {
   f32::OpTable t;
   f32::make_ops(h->W, h->pl.pe, &t);
-  const int n = t.stages * (f32::kStageFrags / 3) * 64 + kNumLayers * t.W;
+  const int n = t.stages * (f32::kSplitFrags / 3) * 64 + kNumLayers * t.W;
   hipLaunchKernelGGL(f32::f32_split_pack_kernel, dim3((n + 255) / 256), dim3(256), 0, s, h->d_master,
                      t, h->d_f32);
   return hipGetLastError();

@@ -636,6 +636,10 @@ __global__ __launch_bounds__(kThreads, 2) void sr_bwd_dz1_kernel(
   const int col = lane % 16, grp = lane / 16;
   const int64_t plane = (int64_t)H * W;
   const uint32_t pl = 4 * (uint32_t)plane;
+  // every other tile computes -dz1 from -dz2: the bf16 instruction rounds its
+  // sums towards minus infinity, by a fraction of an ulp that a gradient's sum
+  // over the pixels would collect (3e-6 over 2^16 of them, 4e-7 with the signs)
+  const float sign = (blockIdx.x ^ blockIdx.y) & 1 ? -1.0f : 1.0f;
   ConvWeights a;
   conv_first(a, wt + kOffF2T, lane);
   // a1 at the lane's outputs, requested ahead of the rest
@@ -673,7 +677,8 @@ __global__ __launch_bounds__(kThreads, 2) void sr_bwd_dz1_kernel(
       for (int j = 0; j < kG; ++j) {
         const int q = lane + 64 * (i0 + j);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) v[j][c] = dz2_of(w3, c, v[j][c], d[j][0], d[j][1], d[j][2]);
+        for (int c = 0; c < 8; ++c)
+          v[j][c] = sign * dz2_of(w3, c, v[j][c], d[j][0], d[j][1], d[j][2]);
         if (q < kP1) store_split(d_s + (wave * kP1 + q) * kRec, kPartH, f32::split8(v[j]));
       }
     }
@@ -694,7 +699,7 @@ __global__ __launch_bounds__(kThreads, 2) void sr_bwd_dz1_kernel(
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         dz1[((int64_t)f * kC + 16 * mt + 4 * grp + i) * plane + (int64_t)Y * W + X] =
-            m[jj][mt][i] > 0.0f ? acc[jj][mt][i] : 0.0f;
+            m[jj][mt][i] > 0.0f ? sign * acc[jj][mt][i] : 0.0f;
   }
 }
 
