@@ -93,8 +93,11 @@ static gn_status precheck(gn_handle *h) {
 }
 
 gn_status gn_prepare_weights(gn_handle *h, hipStream_t stream) {
-  hipError_t e = gn::launch_pack_weights(h->d_master, h->d_packed, h->pl, h->act_scale, stream);
-  if (e == hipSuccess && h->cfg.precision == GN_FP32) e = gn_f32_pack(h, stream);
+  // the form the handle's kernels read, and no other
+  const hipError_t e = h->cfg.precision == GN_FP32
+                           ? gn_f32_pack(h, stream)
+                           : gn::launch_pack_weights(h->d_master, h->d_packed, h->pl,
+                                                     h->cfg.precision, stream);
   return gn_check_device(h, e, "weight packing");
 }
 

@@ -1330,36 +1330,47 @@ __device__ __forceinline__ int chain_col(int ks, int g, int j) {
   return 32 * ks + (j < 4 ? 4 * g + j : 16 + 4 * g + (j - 4));
 }
 
-// One thread per bf16 element of one chunk (blockIdx.y = chunk).
-__global__ void pack_bf16_kernel(PackArgs p) {
+// One thread per lane of a fragment (8 elements, 4 in the K = 16 chunks), one
+// store; blockIdx.y: the chunk, then the biases.
+__global__ __launch_bounds__(256) void pack_bf16_kernel(PackArgs p) {
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  if (blockIdx.y == kNumChunks) {
+    const int l = e / p.W, o = e % p.W;
+    if (l < kNumLayers)
+      ((float *)(p.packed + p.bias_off))[e] = o < p.lo[l].out ? p.master[p.lo[l].b + o] : 0.0f;
+    return;
+  }
   const ChunkDesc d = p.chunk[blockIdx.y];
-  const int lg = d.kmap == KMAP_MEM16 || d.kmap == KMAP_PE16 ? 2 : 3;   // log2 elements per lane
-  const int64_t n = (int64_t)d.mt * d.ks * 64 << lg;
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  const int j = (int)(e & ((1 << lg) - 1));
-  const int lane = (int)((e >> lg) & 63);
-  const int fragi = (int)(e >> (lg + 6));
+  const bool half = d.kmap == KMAP_MEM16 || d.kmap == KMAP_PE16;
+  if (e >= d.mt * d.ks * 64) return;
+  const int lane = e & 63, fragi = e >> 6;
   const int mt = fragi / d.ks, ks = fragi - mt * d.ks;
   const int row = 16 * mt + (lane & 15);
   const int g = lane >> 4;
-  int k;
-  if (d.kmap == KMAP_ENC) {
-    const int c = 8 * g + j;
-    k = c < d.raw ? (d.ks0 + ks) * d.raw + c : d.ncols;
-  } else if (d.kmap == KMAP_PE16) {
-    const int v = 4 * ks + j, blk = v / 3;
-    k = blk < d.nblocks ? blk * d.raw + 3 * g + v % 3 : d.ncols;
-  } else {
-    k = d.kmap == KMAP_MEM     ? 32 * ks + 8 * g + j
-        : d.kmap == KMAP_MEM16 ? 16 * ks + 4 * g + j
-                               : chain_col(ks, g, j);
-  }
   const LayerOff lo = p.lo[d.layer];
-  float v = 0.0f;
-  if (row < d.nrows && k < d.ncols) v = p.master[lo.w + (int64_t)row * lo.in + d.col0 + k];
-  __bf16 h = (__bf16)v;
-  ((__bf16 *)(p.packed + d.offset))[e] = h;
+  float v[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    int k;
+    if (d.kmap == KMAP_ENC) {
+      const int c = 8 * g + j;
+      k = c < d.raw ? (d.ks0 + ks) * d.raw + c : d.ncols;
+    } else if (d.kmap == KMAP_PE16) {
+      const int q = 4 * ks + j, blk = q / 3;
+      k = blk < d.nblocks ? blk * d.raw + 3 * g + q % 3 : d.ncols;
+    } else {
+      k = d.kmap == KMAP_MEM     ? 32 * ks + 8 * g + j
+          : d.kmap == KMAP_MEM16 ? 16 * ks + 4 * g + j
+                                 : chain_col(ks, g, j);
+    }
+    const bool in = row < d.nrows && k < d.ncols && (j < 4 || !half);
+    v[j] = in ? p.master[lo.w + (int64_t)row * lo.in + d.col0 + k] : 0.0f;
+  }
+  const uint2 a = {pk_bf16(v[0], v[1]), pk_bf16(v[2], v[3])};
+  if (half)
+    ((uint2 *)(p.packed + d.offset))[e] = a;
+  else
+    ((u32x4 *)(p.packed + d.offset))[e] = u32x4{a.x, a.y, pk_bf16(v[4], v[5]), pk_bf16(v[6], v[7])};
 }
 
 // fp8 copy of h's second layer (the layer that runs once per slot): per output
@@ -1390,14 +1401,6 @@ __global__ void pack_fp8_t2_kernel(PackArgs p, uint8_t *q8, float *scale) {
   q8[(size_t)(n >> 4) * 2048 + (j >> 4) * 1024 + lane * 16 + (j & 15)] = b;
 }
 
-__global__ void pack_bias_kernel(PackArgs p) {
-  const int l = blockIdx.x, o = threadIdx.x;
-  if (o >= p.W) return;
-  const LayerOff lo = p.lo[l];
-  float v = o < lo.out ? p.master[lo.b + o] : 0.0f;
-  ((float *)(p.packed + p.bias_off))[(int64_t)l * p.W + o] = v;
-}
-
 }  // namespace
 
 size_t mfma_sig_scratch_bytes(int W, int grid) {
@@ -1405,8 +1408,7 @@ size_t mfma_sig_scratch_bytes(int W, int grid) {
 }
 
 hipError_t launch_pack_weights(const float *master, uint8_t *packed, const PackedLayout &pl,
-                               float fp8_act_scale, hipStream_t stream) {
-  (void)fp8_act_scale;
+                               int precision, hipStream_t stream) {
   PackArgs p;
   p.master = master;
   p.packed = packed;
@@ -1414,14 +1416,13 @@ hipError_t launch_pack_weights(const float *master, uint8_t *packed, const Packe
   layer_offsets(pl.W, pl.pe, p.lo);
   p.W = pl.W;
   p.bias_off = pl.bias_off;
-  int64_t maxn = 0;
-  for (int c = 0; c < kNumChunks; ++c)
-    maxn = std::max<int64_t>(maxn, (int64_t)pl.chunk[c].mt * pl.chunk[c].ks * 512);
-  hipLaunchKernelGGL(pack_bf16_kernel, dim3((unsigned)((maxn + 255) / 256), kNumChunks), dim3(256),
-                     0, stream, p);
-  hipLaunchKernelGGL(pack_bias_kernel, dim3(kNumLayers), dim3(pl.W), 0, stream, p);
-  hipLaunchKernelGGL(pack_fp8_t2_kernel, dim3(pl.W), dim3(pl.W), 0, stream, p,
-                     packed + pl.t2q_off, (float *)(packed + pl.t2scale_off));
+  int most = kNumLayers * pl.W;
+  for (int c = 0; c < kNumChunks; ++c) most = std::max(most, pl.chunk[c].mt * pl.chunk[c].ks * 64);
+  hipLaunchKernelGGL(pack_bf16_kernel, dim3((unsigned)((most + 255) / 256), kNumChunks + 1),
+                     dim3(256), 0, stream, p);
+  if (precision == GN_FP8_T)
+    hipLaunchKernelGGL(pack_fp8_t2_kernel, dim3(pl.W), dim3(pl.W), 0, stream, p,
+                       packed + pl.t2q_off, (float *)(packed + pl.t2scale_off));
   return hipGetLastError();
 }
 

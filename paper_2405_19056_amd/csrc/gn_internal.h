@@ -119,9 +119,9 @@ struct FwdBatch {
   int32_t n, hw, k;
 };
 
+// The packed form that a bf16 or fp8_t forward reads (fp8_t: h's second layer too).
 hipError_t launch_pack_weights(const float *master, uint8_t *packed, const PackedLayout &pl,
-                               float fp8_act_scale, hipStream_t stream);
-
+                               int precision, hipStream_t stream);
 
 // sig_scratch: mfma_sig_scratch_bytes(W, grid) bytes private to this launch
 // (launches that may overlap need different scratch buffers).  slot_kmax > 1:
