@@ -789,7 +789,8 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
       // kFastK slots each lane ranks its lane group's slots g and g + 4 from the
       // alphas in LDS (they landed by the last barrier); two active slots of
       // equal alpha (and more than kFastK slots) take the full comparison of
-      // slot_order.h.
+      // slot_order.h.  (All reads are unconditional: one behind a branch on K
+      // is waited for before the next.)
       if (MODE == FWD_FULL && a.canon && K > 1) {
         uint8_t *perm_px[kNT];
 #pragma unroll
@@ -801,7 +802,7 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
           for (int t = 0; t < kNT; ++t)
 #pragma unroll
             for (int j = 0; j < kFastK; ++j)
-              alk[t][j] = j < K ? L_alpha[j * kTilePx + wave * (kNT * 16) + t * 16 + col] : 0.0f;
+              alk[t][j] = L_alpha[min(j, K - 1) * kTilePx + wave * (kNT * 16) + t * 16 + col];
           unsigned slow = 0;
 #pragma unroll
           for (int t = 0; t < kNT; ++t) {
