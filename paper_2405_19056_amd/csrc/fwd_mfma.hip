@@ -363,7 +363,6 @@ struct LdsMap {
       kT1A + (PREC == GN_FP8_T ? MT * 2048 + ((W * 4 + 1023) & ~1023) : MT * KS * kFrag);
   static constexpr int kF1 = PE > 0 ? (pe_blocks(PE) + 1) / 2 : 0;
   static constexpr int kStage = MT * (KS + 1 > kF1 ? KS + 1 : kF1) * kFrag;
-  static constexpr int kStatic = kRes + Shape<W>::kBiasBytes + 2 * kStage;
   // bytes of stage s (without encoding F1 and F2 share stage 0)
   static constexpr int stage_bytes(int s) {
     const int sq = MT * KS * kFrag, last = kNumStages + stage_shift(PE) - 1;
@@ -372,7 +371,17 @@ struct LdsMap {
     if (PE == 0) return s == 0 ? MT * kFrag + sq : sq;
     return s == 0 ? kF1 * MT * kFrag : (s == 1 ? (pe_blocks(PE) - kF1) * MT * kFrag : sq);
   }
+  // offset of stage s in the packed form; every stage together
+  static constexpr int stage_at(int s) { return s == 0 ? 0 : stage_at(s - 1) + stage_bytes(s - 1); }
+  static constexpr int kAll = stage_at(kNumStages + stage_shift(PE));
 };
+
+// At W = 64 without encoding all of the forward's weights fit in LDS (90 KiB):
+// they stay there, and a tile has two barriers instead of eleven.  Its stages
+// are 32 matrix instructions a SIMD long, and each had waited for a barrier and
+// for L2.  256^2, K = 4: 14.7 -> 13.6 us; 512^2, K = 8: 80.0 -> 75.8 us.
+template <int W, int MODE, int PE>
+constexpr bool all_resident() { return W == 64 && MODE == FWD_FULL && PE == 0; }
 
 // Object-streaming state of one tile (modes other than FWD_FULL), pixel by
 // pixel: sigma as bf16 B fragments [pixel][ks][g], the running masked sum Z of
@@ -443,8 +452,9 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
   using LM = LdsMap<W, PREC, PE>;
   __shared__ __attribute__((aligned(1024))) uint8_t L_res[LM::kRes];
   __shared__ __attribute__((aligned(1024))) float L_bias[kNumLayers * W];
-  __shared__ __attribute__((aligned(1024))) uint8_t L_stage0[LM::kStage];
-  __shared__ __attribute__((aligned(1024))) uint8_t L_stage1[LM::kStage];
+  constexpr bool kAllRes = all_resident<W, MODE, PE>();
+  __shared__ __attribute__((aligned(1024))) uint8_t L_stage0[kAllRes ? LM::kAll : LM::kStage];
+  __shared__ __attribute__((aligned(1024))) uint8_t L_stage1[kAllRes ? 16 : LM::kStage];
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   constexpr int res_bytes = LM::kRes, stage_max = LM::kStage;
   // slot-order table: for each pixel of the tile, its slots' indices in
@@ -459,7 +469,14 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
   // FWD_FINISH runs an odd number of stages per tile, so its buffer parity
   // flips from one tile to the next (par); every other mode keeps par = 0.
   int par = 0;
-  auto stage_buf = [&](int s) { return ((s + par) & 1) ? L_stage1 : L_stage0; };
+  auto stage_buf = [&](int s) -> uint8_t * {
+    if constexpr (kAllRes) return L_stage0 + LM::stage_at(s);
+    return ((s + par) & 1) ? L_stage1 : L_stage0;
+  };
+  // the boundary between two stages of a tile
+  auto next_stage = [&]() {
+    if constexpr (!kAllRes) stage_sync();
+  };
   // resident weights of the slot loop and all biases, once per workgroup
   const int lane0 = threadIdx.x & 63;
 #define FILL0(s) lds_copy<LM::stage_bytes(s)>(stage_buf(s), a.packed + a.stage_off[s], wave, lane0)
@@ -483,7 +500,8 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
     // FULL streams every stage; BEGIN (without encoding) and ACC keep their
     // few stages resident for the whole launch; BEGIN with encoding streams
     // its four stages per tile; FINISH starts its pipeline at T3's stage.
-    if constexpr (MODE == FWD_FULL) FILL0(sF1);
+    if constexpr (kAllRes) lds_copy<LM::kAll>(L_stage0, a.packed, wave, lane0);
+    else if constexpr (MODE == FWD_FULL) FILL0(sF1);
     if constexpr (MODE == FWD_BEGIN) {
       FILL0(sF1);
       if constexpr (PE == 0) FILL0(sF3);
@@ -646,7 +664,9 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
     const uint8_t *packed = a.packed;
     asm volatile("" : "+v"(lane), "+s"(packed));
     const int g = lane >> 4, col = lane & 15;
-#define FILL(s) lds_copy<LM::stage_bytes(s)>(stage_buf(s), packed + a.stage_off[s], wave, lane)
+#define FILL(s) \
+  if constexpr (!kAllRes) \
+  lds_copy<LM::stage_bytes(s)>(stage_buf(s), packed + a.stage_off[s], wave, lane)
     // ---- the tile's frame (resolved one tile ahead)
     const TileInfo ti = nti;
     gcfloat *Gp = ti.G, *Lp = ti.L;
@@ -867,7 +887,7 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
           for (int k = 0; k < KS; ++k) state_store16(sr, st_sig(lane, t) + k * 64, sig[t][k]);
         if constexpr (PE > 0) {
           // the next tile's first stage has landed; this stage's buffer is free
-          stage_sync();
+          next_stage();
         }
       } else {
         if (sig_in_lds) {
@@ -883,10 +903,12 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
         }
         // the kNT x KS stores above stay in flight; the same wave reads them back
         // in stage 3, after stage 2's full wait
-        if (sig_in_lds)
-          stage_sync_after_stores<0>();
-        else
-          stage_sync_after_stores<kNT * KS>();
+        if constexpr (!kAllRes) {
+          if (sig_in_lds)
+            stage_sync_after_stores<0>();
+          else
+            stage_sync_after_stores<kNT * KS>();
+        }
       }
     }
 
@@ -1149,7 +1171,7 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
               g == 0 && (touched[t] || !a.state_load) ? st_cnt(lane, t) : kOutside, 0, 0);
         }
       } else {
-        stage_sync();
+        next_stage();
       }
     }
 
@@ -1216,20 +1238,20 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
         mm<MT, KS, kEarlyT3B1>(acc, stage_buf(sT3), zs, lane);
         to_frags<MT, false>(acc, tau);
       }
-      stage_sync();
+      next_stage();
 
       // ================= stages 4-5: B layer 1 on [sigma; tau] =================
       FILL(sB1T);
       f32x4 accB[kNT][MT];
       bias_init(accB, bB1, g);
       mm<MT, KS, kEarlyT3B1>(accB, stage_buf(sB1S), sig2, lane);
-      stage_sync();
+      next_stage();
 
       FILL(sB2);
       u32x4 hb[kNT][KS];
       mm<MT, KS, kEarlyT3B1>(accB, stage_buf(sB1T), tau, lane);
       to_frags<MT, true>(accB, hb);
-      stage_sync();
+      next_stage();
 
       // ================= stage 6: B layer 2 =================
       FILL(sB3);
@@ -1247,13 +1269,13 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
 #pragma unroll
           for (int k = 0; k < KS; ++k) hb[t][k] = hb2[t][k];
       }
-      stage_sync();
+      next_stage();
 
       // ================= stage 7: B layer 3 -> phi =================
       FILL(sR1);
       u32x4 phi[kNT][KS];
       layer<MT, KS, false, kEarly>(phi, stage_buf(sB3), hb, bB3, g, lane);
-      stage_sync();
+      next_stage();
 
       // ================= stage 8: R layer 1 on [phi; L_d] =================
       FILL(sR2);
@@ -1272,7 +1294,7 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
         mm<MT, 1, kEarly>(acc, stage_buf(sR1) + r1p_bytes, ld, lane);
         to_frags<MT, true>(acc, hr);
       }
-      stage_sync();
+      next_stage();
 
       // ================= stage 9: R layers 2-3 -> radiance =================
       if (has_next) {
@@ -1437,23 +1459,24 @@ static int64_t resident_bytes(const PackedLayout &pl, int precision) {
 }
 
 // order_bytes: the canonical order's LDS tables (order and alphas) per tile.
-static size_t mfma_base_lds_bytes(const PackedLayout &pl, int precision, int order_bytes) {
+// all: every stage has a place of its own (all_resident).
+static size_t mfma_base_lds_bytes(const PackedLayout &pl, int precision, int order_bytes, bool all) {
   int64_t stage_max = 0;
   for (int s = 0; s < pl.nstages; ++s)
     stage_max = std::max<int64_t>(stage_max, pl.stage_off[s + 1] - pl.stage_off[s]);
   return (size_t)(resident_bytes(pl, precision) + (int64_t)kNumLayers * pl.W * 4 +
-                  (int64_t)order_bytes + 2 * stage_max);
+                  (int64_t)order_bytes + (all ? pl.stage_off[pl.nstages] + 16 : 2 * stage_max));
 }
 
 // Waves whose sigma fits in the LDS the weights leave free (160 KiB per CU),
 // and how many of them sit in the stage buffers' tails: from F3's stage to
 // B1S's (stages 1-4, shifted by two with encoded inputs) buffer 1 holds the
 // first and third of them, buffer 0 the second and fourth.
-static void mfma_sig_lds(const PackedLayout &pl, int precision, int order_bytes, int *nlds,
-                         int *ntail) {
+static void mfma_sig_lds(const PackedLayout &pl, int precision, int order_bytes, bool all,
+                         int *nlds, int *ntail) {
   constexpr size_t kLdsMax = 160 * 1024;
   const size_t per_wave = (size_t)kNT * (pl.W / 32) * kFrag;
-  const size_t base = mfma_base_lds_bytes(pl, precision, order_bytes);
+  const size_t base = mfma_base_lds_bytes(pl, precision, order_bytes, all);
   int64_t stage_max = 0;
   for (int s = 0; s < pl.nstages; ++s)
     stage_max = std::max<int64_t>(stage_max, pl.stage_off[s + 1] - pl.stage_off[s]);
@@ -1464,7 +1487,7 @@ static void mfma_sig_lds(const PackedLayout &pl, int precision, int order_bytes,
   const int free_waves = base >= kLdsMax ? 0 : (int)((kLdsMax - base) / per_wave);
   int t = 0;
   // tails are used alternately (buffer 0, buffer 1, buffer 0, ...)
-  for (int64_t used0 = 0, used1 = 0;; ++t) {
+  for (int64_t used0 = 0, used1 = 0; !all; ++t) {
     int64_t &u = (t & 1) ? used1 : used0;
     const int64_t cap = (t & 1) ? tail1 : tail0;
     if (u + (int64_t)per_wave > cap) break;
@@ -1475,15 +1498,15 @@ static void mfma_sig_lds(const PackedLayout &pl, int precision, int order_bytes,
   *nlds = n;
 }
 
-static int mfma_sig_free_waves(const PackedLayout &pl, int precision, int order_bytes) {
+static int mfma_sig_free_waves(const PackedLayout &pl, int precision, int order_bytes, bool all) {
   int n, t;
-  mfma_sig_lds(pl, precision, order_bytes, &n, &t);
+  mfma_sig_lds(pl, precision, order_bytes, all, &n, &t);
   return n - t;
 }
 
-static size_t mfma_lds_bytes(const PackedLayout &pl, int precision, int order_bytes) {
-  return mfma_base_lds_bytes(pl, precision, order_bytes) +
-         (size_t)mfma_sig_free_waves(pl, precision, order_bytes) * kNT * (pl.W / 32) * kFrag;
+static size_t mfma_lds_bytes(const PackedLayout &pl, int precision, int order_bytes, bool all) {
+  return mfma_base_lds_bytes(pl, precision, order_bytes, all) +
+         (size_t)mfma_sig_free_waves(pl, precision, order_bytes, all) * kNT * (pl.W / 32) * kFrag;
 }
 
 template <int W, int PREC, int MODE, int PE>
@@ -1493,9 +1516,11 @@ static hipError_t launch_one(const MfmaArgs &a, int grid, size_t lds, hipStream_
   static size_t attr_lds = 0;
   // `lds` counts every array; the launch passes what the kernel does not declare
   using LM = LdsMap<W, PREC, PE>;
-  if (lds < (size_t)LM::kStatic || a.res_bytes != LM::kRes || a.stage_max != LM::kStage)
+  constexpr size_t fixed = LM::kRes + Shape<W>::kBiasBytes +
+                           (all_resident<W, MODE, PE>() ? LM::kAll + 16 : 2 * LM::kStage);
+  if (lds < fixed || a.res_bytes != LM::kRes || a.stage_max != LM::kStage)
     return hipErrorInvalidValue;
-  lds -= LM::kStatic;
+  lds -= fixed;
   if (lds > attr_lds) {
     hipError_t e = hipFuncSetAttribute((const void *)fwd_mfma_kernel<W, PREC, MODE, PE>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1554,12 +1579,13 @@ static hipError_t launch_impl(int W, int precision, int pool, const uint8_t *pac
   // the alpha table goes into sigma's parking area when that area holds it,
   // else into LDS of its own
   int order_bytes = kTilePx * a.kpad;
-  mfma_sig_lds(pl, precision, order_bytes, &a.sig_lds_waves, &a.sig_tail_waves);
+  const bool all = W == 64 && mode == FWD_FULL && pl.pe == 0;     // all_resident
+  mfma_sig_lds(pl, precision, order_bytes, all, &a.sig_lds_waves, &a.sig_tail_waves);
   const int alpha_bytes = kTilePx * 4 * a.aslots;
   a.alpha_alias = (a.sig_lds_waves - a.sig_tail_waves) * kNT * (W / 32) * kFrag >= alpha_bytes;
   if (!a.alpha_alias) {
     order_bytes += alpha_bytes;
-    mfma_sig_lds(pl, precision, order_bytes, &a.sig_lds_waves, &a.sig_tail_waves);
+    mfma_sig_lds(pl, precision, order_bytes, all, &a.sig_lds_waves, &a.sig_tail_waves);
   }
   a.packed = packed;
   for (int s = 0; s <= kMaxStages; ++s) a.stage_off[s] = s <= pl.nstages ? pl.stage_off[s] : 0;
@@ -1586,8 +1612,8 @@ static hipError_t launch_impl(int W, int precision, int pool, const uint8_t *pac
   a.inv_sa = 1.0f / fp8_act_scale;
   if (ntiles <= 0) return hipSuccess;
   grid = std::max(1, std::min(grid, ntiles));   // the scratch holds `grid` workgroups
-  const size_t lds = mfma_lds_bytes(pl, precision, order_bytes);
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
+  const size_t lds = mfma_lds_bytes(pl, precision, order_bytes, all);
+  if (lds > 160 * 1024 || (all && a.sig_lds_waves < kWaves)) return hipErrorInvalidValue;
   if (precision == GN_BF16) {
     if (W == 64) return launch_pe<64, GN_BF16>(pl.pe, mode, a, grid, lds, stream);
     if (W == 128) return launch_pe<128, GN_BF16>(pl.pe, mode, a, grid, lds, stream);

@@ -348,6 +348,20 @@ def test_fp32_forward_at_tile_edges(W, n, h, w_, k):
             gate(run(net, fr), ref, TOL["fp32"], f"fp32 {(W, n, h, w_, k, pool)}")
 
 
+@pytest.mark.parametrize("order", ["canonical", "input"])
+@pytest.mark.parametrize("n,h,w_,k,kmax", [(1, 16, 16, 0, 0), (2, 15, 17, 1, 1), (1, 17, 31, 64, 64),
+                                           (1, 257, 257, 3, 8), (3, 16, 16, 8, 8)])
+def test_bf16_w64_resident_weights_at_tile_edges(n, h, w_, k, kmax, order):
+    """Width 64, whose weights stay in LDS: one tile of 256 pixels, ragged
+    ones, more tiles than compute units (a workgroup takes a second one), the
+    largest slot-order table beside the weights and none."""
+    wts, fr = frame(n, h, w_, k, 64, seed=500 + k + h)
+    log(f"w64 resident {(n, h, w_, k, order)}")
+    ref = oracle.forward(wts, 64, fr.gbuf, fr.layers, fr.scene)
+    with GlassNet(wts, 64, k_max=kmax, precision="bf16", slot_order=order) as net:
+        gate(run(net, fr), ref, TOL["bf16"], f"bf16 {(n, h, w_, k, order)}")
+
+
 def test_fp32_forward_rejects_more_pixels_than_it_addresses():
     """The fp32 plane pipeline covers at most 3 * 2^20 pixels per call; beyond
     that the forward is an argument error raised before any launch."""
