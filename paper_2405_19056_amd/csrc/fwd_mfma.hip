@@ -216,21 +216,21 @@ __device__ __forceinline__ i32x8 ld_frag8(const uint8_t *chunk, int idx, int lan
   return i32x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
 }
 
-template <int MT_>
-__device__ __forceinline__ void bias_init(f32x4 (&acc)[kNT][MT_], const float *bias, int g) {
+template <int MT_, int NT>
+__device__ __forceinline__ void bias_init(f32x4 (&acc)[NT][MT_], const float *bias, int g) {
 #pragma unroll
   for (int mt = 0; mt < MT_; ++mt) {
     const f32x4 b = *(const f32x4 *)(bias + 16 * mt + 4 * g);
 #pragma unroll
-    for (int t = 0; t < kNT; ++t) acc[t][mt] = b;
+    for (int t = 0; t < NT; ++t) acc[t][mt] = b;
   }
 }
 
 // Accumulator rows -> next layer's B fragments (M-tiles 2j and 2j+1 make K-step j).
-template <int MT_, bool RELU>
-__device__ __forceinline__ void to_frags(const f32x4 (&acc)[kNT][MT_], u32x4 (&out)[kNT][MT_ / 2]) {
+template <int MT_, bool RELU, int NT>
+__device__ __forceinline__ void to_frags(const f32x4 (&acc)[NT][MT_], u32x4 (&out)[NT][MT_ / 2]) {
 #pragma unroll
-  for (int t = 0; t < kNT; ++t) {
+  for (int t = 0; t < NT; ++t) {
 #pragma unroll
     for (int mt = 0; mt < MT_; ++mt) {
       const f32x4 v = acc[t][mt];
@@ -254,9 +254,9 @@ __device__ __forceinline__ void to_frags(const f32x4 (&acc)[kNT][MT_], u32x4 (&o
 // to its MFMAs and waits for it alone): 3.5-5% of the bf16 frame, 2% of the
 // fp8 one, whose kernel spills with it in T3 and B's first layer and there
 // leaves the placement to the scheduler.
-template <int MT_, int KS_, bool RELU, bool EARLY>
-__device__ __forceinline__ void layer(u32x4 (&out)[kNT][MT_ / 2], const uint8_t *chunk,
-                                      const u32x4 (&in)[kNT][KS_], const float *bias, int g,
+template <int MT_, int KS_, bool RELU, bool EARLY, int NT>
+__device__ __forceinline__ void layer(u32x4 (&out)[NT][MT_ / 2], const uint8_t *chunk,
+                                      const u32x4 (&in)[NT][KS_], const float *bias, int g,
                                       int lane) {
   u32x4 wb[2][2][KS_];
 #pragma unroll
@@ -274,23 +274,23 @@ __device__ __forceinline__ void layer(u32x4 (&out)[kNT][MT_ / 2], const uint8_t 
           wb[cur ^ 1][h][ks] = ld_frag(chunk, (2 * (p + 1) + h) * KS_ + ks, lane);
     }
     if constexpr (EARLY) __builtin_amdgcn_sched_barrier(0);
-    f32x4 acc[kNT][2];
+    f32x4 acc[NT][2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const f32x4 b = *(const f32x4 *)(bias + 16 * (2 * p + h) + 4 * g);
 #pragma unroll
-      for (int t = 0; t < kNT; ++t) acc[t][h] = b;
+      for (int t = 0; t < NT; ++t) acc[t][h] = b;
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
       for (int ks = 0; ks < KS_; ++ks) {
 #pragma unroll
-        for (int t = 0; t < kNT; ++t) acc[t][h] = mma(wb[cur][h][ks], in[t][ks], acc[t][h]);
+        for (int t = 0; t < NT; ++t) acc[t][h] = mma(wb[cur][h][ks], in[t][ks], acc[t][h]);
       }
     }
 #pragma unroll
-    for (int t = 0; t < kNT; ++t) {
+    for (int t = 0; t < NT; ++t) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const f32x4 v = acc[t][h];
@@ -309,9 +309,9 @@ __device__ __forceinline__ void layer(u32x4 (&out)[kNT][MT_ / 2], const uint8_t 
 // acc[t][mt] += A(chunk) . in[t] over the chunk's KS_ K-steps, one M-tile's
 // fragments read ahead of its MFMAs and the next M-tile's requested early
 // (EARLY as for layer).
-template <int MT_, int KS_, bool EARLY>
-__device__ __forceinline__ void mm(f32x4 (&acc)[kNT][MT_], const uint8_t *chunk,
-                                   const u32x4 (&in)[kNT][KS_], int lane) {
+template <int MT_, int KS_, bool EARLY, int NT>
+__device__ __forceinline__ void mm(f32x4 (&acc)[NT][MT_], const uint8_t *chunk,
+                                   const u32x4 (&in)[NT][KS_], int lane) {
   u32x4 wb[2][KS_];
 #pragma unroll
   for (int ks = 0; ks < KS_; ++ks) wb[0][ks] = ld_frag(chunk, ks, lane);
@@ -326,16 +326,16 @@ __device__ __forceinline__ void mm(f32x4 (&acc)[kNT][MT_], const uint8_t *chunk,
 #pragma unroll
     for (int ks = 0; ks < KS_; ++ks)
 #pragma unroll
-      for (int t = 0; t < kNT; ++t) acc[t][mt] = mma(wb[cur][ks], in[t][ks], acc[t][mt]);
+      for (int t = 0; t < NT; ++t) acc[t][mt] = mma(wb[cur][ks], in[t][ks], acc[t][mt]);
   }
 }
 
 // F's encoded input as B fragments: K-step b (of N) is encoding block B0 + b
 // of the 8 raw channels the lane holds.
-template <int B0, int N>
-__device__ __forceinline__ void enc_frags(const float (&xr)[kNT][8], u32x4 (&x)[kNT][N]) {
+template <int B0, int N, int NT>
+__device__ __forceinline__ void enc_frags(const float (&xr)[NT][8], u32x4 (&x)[NT][N]) {
 #pragma unroll
-  for (int t = 0; t < kNT; ++t)
+  for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       float e0[B0 + N], e1[B0 + N];
@@ -393,9 +393,9 @@ constexpr bool all_resident() { return W == 64 && MODE == FWD_FULL && PE == 0; }
 // has no valid Z: nobody reads it.
 template <int W>
 struct StreamTile {
-  static constexpr int64_t kSig = (int64_t)kWaves * kNT * (W / 32) * kFrag;
-  static constexpr int64_t kZ = (int64_t)kWaves * kNT * (W / 16) * kFrag;
-  static constexpr int64_t kCnt = (int64_t)kWaves * kNT * 16 * 4;
+  static constexpr int64_t kSig = (int64_t)kTilePx * W * 2;
+  static constexpr int64_t kZ = (int64_t)kTilePx * W * 4;
+  static constexpr int64_t kCnt = (int64_t)kTilePx * 4;
   static constexpr int64_t kBytes = kSig + kZ + kCnt;
 };
 
@@ -427,8 +427,10 @@ __device__ __forceinline__ T *uniform(T *p) {
 // PE > 0: F's and h's inputs are positionally encoded with PE levels; F1 then
 // runs over two stages of its own (stage indices below), and h's first layer
 // takes pe_k16_steps(PE) 16-deep K-steps per slot.
-template <int W, int PREC, int MODE, int PE>
+// NT: N-tiles of 16 pixels per wave (n_tiles below).
+template <int W, int PREC, int MODE, int PE, int NT>
 __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
+  constexpr int kNT = NT, kTilePx = kWaves * NT * 16;
   constexpr int MT = Shape<W>::MT, KS = Shape<W>::KS;
   constexpr int kShift = stage_shift(PE);
   // stage of each weight group (F1 and F2 share stage 0 without encoding)
@@ -730,8 +732,9 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
     // ranked before its last.
     const bool canon_fast = MODE == FWD_FULL && a.canon && K > 1 && K <= kFastK;
     auto copy_alphas = [&]() {
-      for (int b = wave; b < 4 * K; b += kWaves) {
-        const int j = b >> 2, p0 = (b & 3) * 64;
+      constexpr int kBlk = kTilePx / 64;
+      for (int b = wave; b < kBlk * K; b += kWaves) {
+        const int j = b / kBlk, p0 = b % kBlk * 64;
         const int q = min(q0 + p0 + lane, hw - 1);
         __builtin_amdgcn_global_load_lds(
             (const void *)(Lp + ((size_t)j * kNL + kAlpha) * hw + q),
@@ -1473,9 +1476,9 @@ static size_t mfma_base_lds_bytes(const PackedLayout &pl, int precision, int ord
 // B1S's (stages 1-4, shifted by two with encoded inputs) buffer 1 holds the
 // first and third of them, buffer 0 the second and fourth.
 static void mfma_sig_lds(const PackedLayout &pl, int precision, int order_bytes, bool all,
-                         int *nlds, int *ntail) {
+                         int nt, int *nlds, int *ntail) {
   constexpr size_t kLdsMax = 160 * 1024;
-  const size_t per_wave = (size_t)kNT * (pl.W / 32) * kFrag;
+  const size_t per_wave = (size_t)nt * (pl.W / 32) * kFrag;
   const size_t base = mfma_base_lds_bytes(pl, precision, order_bytes, all);
   int64_t stage_max = 0;
   for (int s = 0; s < pl.nstages; ++s)
@@ -1498,65 +1501,69 @@ static void mfma_sig_lds(const PackedLayout &pl, int precision, int order_bytes,
   *nlds = n;
 }
 
-static int mfma_sig_free_waves(const PackedLayout &pl, int precision, int order_bytes, bool all) {
-  int n, t;
-  mfma_sig_lds(pl, precision, order_bytes, all, &n, &t);
-  return n - t;
+// LDS past the arrays that the kernel declares: the order's tables and sigma of
+// the waves that have no tail.
+static size_t mfma_dynamic_lds(const PackedLayout &pl, int order_bytes, int nt, int nlds, int ntail) {
+  return order_bytes + (size_t)(nlds - ntail) * nt * (pl.W / 32) * kFrag;
 }
 
-static size_t mfma_lds_bytes(const PackedLayout &pl, int precision, int order_bytes, bool all) {
-  return mfma_base_lds_bytes(pl, precision, order_bytes, all) +
-         (size_t)mfma_sig_free_waves(pl, precision, order_bytes, all) * kNT * (pl.W / 32) * kFrag;
-}
-
-template <int W, int PREC, int MODE, int PE>
+template <int W, int PREC, int MODE, int PE, int NT>
 static hipError_t launch_one(const MfmaArgs &a, int grid, size_t lds, hipStream_t stream) {
   // The attribute is per function; a layout of a different size (another
   // handle's) raises it again.
   static size_t attr_lds = 0;
-  // `lds` counts every array; the launch passes what the kernel does not declare
   using LM = LdsMap<W, PREC, PE>;
   constexpr size_t fixed = LM::kRes + Shape<W>::kBiasBytes +
                            (all_resident<W, MODE, PE>() ? LM::kAll + 16 : 2 * LM::kStage);
-  if (lds < fixed || a.res_bytes != LM::kRes || a.stage_max != LM::kStage)
+  if (a.res_bytes != LM::kRes || a.stage_max != LM::kStage || lds + fixed > 160 * 1024)
     return hipErrorInvalidValue;
-  lds -= fixed;
   if (lds > attr_lds) {
-    hipError_t e = hipFuncSetAttribute((const void *)fwd_mfma_kernel<W, PREC, MODE, PE>,
+    hipError_t e = hipFuncSetAttribute((const void *)fwd_mfma_kernel<W, PREC, MODE, PE, NT>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     attr_lds = lds;
   }
-  hipLaunchKernelGGL((fwd_mfma_kernel<W, PREC, MODE, PE>), dim3(grid), dim3(kThreads), lds, stream,
-                     a);
+  hipLaunchKernelGGL((fwd_mfma_kernel<W, PREC, MODE, PE, NT>), dim3(grid), dim3(kThreads), lds,
+                     stream, a);
   return hipGetLastError();
 }
 
+// N-tiles per wave.  Two: every weight fragment read from LDS then serves two
+// matrix instructions.  One, half a tile per workgroup, in whole forwards of a
+// batch whose 256-pixel tiles leave half of the CUs idle: W = 128, K = 4, 128^2
+// 28.4 -> 18.5 us, 128 x 256 28.5 -> 19.4; at 192^2 half tiles need a second
+// round, 34.4 us against 28.5.  (In the begin and accumulate calls, two
+// workgroups of half tiles to a CU took 30 and 49 us at 512^2 against 27 and 35.)
+static int n_tiles(int mode, bool batch, int ntiles, int grid) {
+  return mode == FWD_FULL && batch && 2 * ntiles <= grid ? 1 : 2;
+}
+
 template <int W, int PREC, int PE>
-static hipError_t launch_mode(int mode, const MfmaArgs &a, int grid, size_t lds,
+static hipError_t launch_mode(int mode, int nt, const MfmaArgs &a, int grid, size_t lds,
                               hipStream_t stream) {
   switch (mode) {
-    case FWD_FULL: return launch_one<W, PREC, FWD_FULL, PE>(a, grid, lds, stream);
-    case FWD_BEGIN: return launch_one<W, PREC, FWD_BEGIN, PE>(a, grid, lds, stream);
-    case FWD_ACC: return launch_one<W, PREC, FWD_ACC, PE>(a, grid, lds, stream);
-    case FWD_FINISH: return launch_one<W, PREC, FWD_FINISH, PE>(a, grid, lds, stream);
+    case FWD_FULL:
+      return nt == 1 ? launch_one<W, PREC, FWD_FULL, PE, 1>(a, grid, lds, stream)
+                     : launch_one<W, PREC, FWD_FULL, PE, 2>(a, grid, lds, stream);
+    case FWD_BEGIN: return launch_one<W, PREC, FWD_BEGIN, PE, 2>(a, grid, lds, stream);
+    case FWD_ACC: return launch_one<W, PREC, FWD_ACC, PE, 2>(a, grid, lds, stream);
+    case FWD_FINISH: return launch_one<W, PREC, FWD_FINISH, PE, 2>(a, grid, lds, stream);
   }
   return hipErrorInvalidValue;
 }
 
 template <int W, int PREC>
-static hipError_t launch_pe(int pe, int mode, const MfmaArgs &a, int grid, size_t lds,
+static hipError_t launch_pe(int pe, int mode, int nt, const MfmaArgs &a, int grid, size_t lds,
                             hipStream_t stream) {
   switch (pe) {
-    case 0: return launch_mode<W, PREC, 0>(mode, a, grid, lds, stream);
-    case 1: return launch_mode<W, PREC, 1>(mode, a, grid, lds, stream);
-    case 2: return launch_mode<W, PREC, 2>(mode, a, grid, lds, stream);
-    case 3: return launch_mode<W, PREC, 3>(mode, a, grid, lds, stream);
-    case 4: return launch_mode<W, PREC, 4>(mode, a, grid, lds, stream);
+    case 0: return launch_mode<W, PREC, 0>(mode, nt, a, grid, lds, stream);
+    case 1: return launch_mode<W, PREC, 1>(mode, nt, a, grid, lds, stream);
+    case 2: return launch_mode<W, PREC, 2>(mode, nt, a, grid, lds, stream);
+    case 3: return launch_mode<W, PREC, 3>(mode, nt, a, grid, lds, stream);
+    case 4: return launch_mode<W, PREC, 4>(mode, nt, a, grid, lds, stream);
   }
   return hipErrorInvalidValue;
 }
-static_assert(kMaxPe == 4, "launch_pe covers encoding levels 0..4");
 
 size_t stream_state_tile_bytes(int W) {
   return W == 64 ? (size_t)StreamTile<64>::kBytes : (size_t)StreamTile<128>::kBytes;
@@ -1578,14 +1585,15 @@ static hipError_t launch_impl(int W, int precision, int pool, const uint8_t *pac
   a.aslots = a.canon ? std::min(slot_kmax, 8) : 0;
   // the alpha table goes into sigma's parking area when that area holds it,
   // else into LDS of its own
-  int order_bytes = kTilePx * a.kpad;
+  const int nt = n_tiles(mode, batch != nullptr, ntiles, grid), tile_px = kWaves * nt * 16;
+  int order_bytes = tile_px * a.kpad;
   const bool all = W == 64 && mode == FWD_FULL && pl.pe == 0;     // all_resident
-  mfma_sig_lds(pl, precision, order_bytes, all, &a.sig_lds_waves, &a.sig_tail_waves);
-  const int alpha_bytes = kTilePx * 4 * a.aslots;
-  a.alpha_alias = (a.sig_lds_waves - a.sig_tail_waves) * kNT * (W / 32) * kFrag >= alpha_bytes;
+  mfma_sig_lds(pl, precision, order_bytes, all, nt, &a.sig_lds_waves, &a.sig_tail_waves);
+  const int alpha_bytes = tile_px * 4 * a.aslots;
+  a.alpha_alias = (a.sig_lds_waves - a.sig_tail_waves) * nt * (W / 32) * kFrag >= alpha_bytes;
   if (!a.alpha_alias) {
     order_bytes += alpha_bytes;
-    mfma_sig_lds(pl, precision, order_bytes, all, &a.sig_lds_waves, &a.sig_tail_waves);
+    mfma_sig_lds(pl, precision, order_bytes, all, nt, &a.sig_lds_waves, &a.sig_tail_waves);
   }
   a.packed = packed;
   for (int s = 0; s <= kMaxStages; ++s) a.stage_off[s] = s <= pl.nstages ? pl.stage_off[s] : 0;
@@ -1599,7 +1607,8 @@ static hipError_t launch_impl(int W, int precision, int pool, const uint8_t *pac
   a.t2s_off = pl.t2scale_off;
   if (batch) {
     a.b = *batch;
-    a.tiles_per_frame = (batch->hw + kTilePx - 1) / kTilePx;
+    a.tiles_per_frame = (batch->hw + tile_px - 1) / tile_px;
+    ntiles = batch->n * a.tiles_per_frame;
   } else {
     a.b = FwdBatch{};
     a.tiles_per_frame = 1;
@@ -1612,14 +1621,15 @@ static hipError_t launch_impl(int W, int precision, int pool, const uint8_t *pac
   a.inv_sa = 1.0f / fp8_act_scale;
   if (ntiles <= 0) return hipSuccess;
   grid = std::max(1, std::min(grid, ntiles));   // the scratch holds `grid` workgroups
-  const size_t lds = mfma_lds_bytes(pl, precision, order_bytes, all);
-  if (lds > 160 * 1024 || (all && a.sig_lds_waves < kWaves)) return hipErrorInvalidValue;
+  if (all && a.sig_lds_waves < kWaves) return hipErrorInvalidValue;
+  const size_t lds =
+      mfma_dynamic_lds(pl, order_bytes, nt, a.sig_lds_waves, a.sig_tail_waves);
   if (precision == GN_BF16) {
-    if (W == 64) return launch_pe<64, GN_BF16>(pl.pe, mode, a, grid, lds, stream);
-    if (W == 128) return launch_pe<128, GN_BF16>(pl.pe, mode, a, grid, lds, stream);
+    if (W == 64) return launch_pe<64, GN_BF16>(pl.pe, mode, nt, a, grid, lds, stream);
+    if (W == 128) return launch_pe<128, GN_BF16>(pl.pe, mode, nt, a, grid, lds, stream);
   }
   if (precision == GN_FP8_T && W == 128)
-    return launch_pe<128, GN_FP8_T>(pl.pe, mode, a, grid, lds, stream);
+    return launch_pe<128, GN_FP8_T>(pl.pe, mode, nt, a, grid, lds, stream);
   return hipErrorInvalidValue;
 }
 

@@ -362,6 +362,29 @@ def test_bf16_w64_resident_weights_at_tile_edges(n, h, w_, k, kmax, order):
         gate(run(net, fr), ref, TOL["bf16"], f"bf16 {(n, h, w_, k, order)}")
 
 
+@pytest.mark.parametrize("precision,W,pe,k", [("bf16", 128, 0, 4), ("bf16", 64, 0, 9), ("bf16", 64, 2, 3),
+                                              ("bf16", 128, 1, 0), ("fp8_t", 128, 0, 8)])
+def test_half_tiles_equal_whole_tiles_bitwise(precision, W, pe, k):
+    """Half tiles serve frames that leave half of the compute units idle: the
+    first rows of a frame just past that size (whole tiles) equal a frame of
+    those rows alone, down to one pixel, bit for bit."""
+    torch = torch_dev()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    h, w = cus // 2 + 1, 256
+    s = synth.streams(77 + k)
+    wts = synth.make_weights(W, s["weights"], pe)
+    fr = synth.Frame(synth.make_gbuf(1, h, w, s["gbuf"]),
+                     synth.make_layers(1, k, h, w, s["slots"], s["active"], "uniform_count"),
+                     synth.make_scene(1, s["gbuf"]))
+    log(f"half tiles {precision} W={W} pe={pe} k={k}")
+    with GlassNet(wts, W, k_max=max(k, 1), precision=precision, pe_levels=pe) as net:
+        want = run(net, fr)
+        for rows, cols in ((h - 1, w), (1, w), (3, 77), (1, 1)):
+            part = synth.Frame(np.ascontiguousarray(fr.gbuf[:, :, :rows, :cols]),
+                               np.ascontiguousarray(fr.layers[:, :, :, :rows, :cols]), fr.scene)
+            np.testing.assert_array_equal(run(net, part), want[:, :, :rows, :cols])
+
+
 def test_fp32_forward_rejects_more_pixels_than_it_addresses():
     """The fp32 plane pipeline covers at most 3 * 2^20 pixels per call; beyond
     that the forward is an argument error raised before any launch."""
