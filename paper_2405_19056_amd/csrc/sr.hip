@@ -770,9 +770,60 @@ constexpr int kNJ1 = (kIn * 9 + 1 + 15) / 16;      // conv1 column tiles (10)
 constexpr int kNJ1w = (kNJ1 + 3) / 4;              // per wave (3)
 static_assert((kC * 9 + 1 + 15) / 16 <= 4 * kNJ2, "conv2 columns and the ones column");
 
+// A tile's planes by way of registers: C channels at the thread's own pixel, or
+// over the tile and a one-pixel halo, position tid and then the 68 positions
+// past kThreads, channel by channel.  tile: first row and column.
+constexpr int kPast = kP1 - kThreads;
+constexpr int halo_loads(int C) { return C + (C * kPast + kThreads - 1) / kThreads; }
+
+struct TilePos {
+  int f, y0, x0;
+};
+
+__device__ __forceinline__ uint32_t image_offset(int Y, int X, int H, int W) {
+  return Y >= 0 && Y < H && X >= 0 && X < W ? 4 * ((uint32_t)Y * W + X) : kOutside;
+}
+
+template <int C>
+__device__ __forceinline__ void fetch_own(float (&v)[C], rsrc_t r, TilePos t, int tid, int H, int W) {
+  const uint32_t px = image_offset(t.y0 + tid / kT, t.x0 + tid % kT, H, W), pl = 4 * (uint32_t)(H * W);
+#pragma unroll
+  for (int c = 0; c < C; ++c) v[c] = load1(r, px, c * pl);
+}
+
+template <int C>
+__device__ __forceinline__ void fetch_halo(float (&v)[halo_loads(C)], rsrc_t r, TilePos t, int tid,
+                                           int H, int W) {
+  auto at = [&](int q) { return image_offset(t.y0 - 1 + q / kE1, t.x0 - 1 + q % kE1, H, W); };
+  const uint32_t px = at(tid), pl = 4 * (uint32_t)(H * W);
+#pragma unroll
+  for (int c = 0; c < C; ++c) v[c] = load1(r, px, c * pl);
+#pragma unroll
+  for (int i = C; i < halo_loads(C); ++i) {
+    const int e = tid + (i - C) * kThreads;
+    const uint32_t o = at(kThreads + e % kPast);
+    v[i] = load1(r, e < C * kPast && o != kOutside ? o + e / kPast * pl : kOutside, 0);
+  }
+}
+
+template <int C>
+__device__ __forceinline__ void put_halo(float *dst, const float (&v)[halo_loads(C)], int tid) {
+#pragma unroll
+  for (int c = 0; c < C; ++c) dst[c * kP1 + tid] = v[c];
+#pragma unroll
+  for (int i = C; i < halo_loads(C); ++i) {
+    const int e = tid + (i - C) * kThreads;
+    if (e < C * kPast) dst[e / kPast * kP1 + kThreads + e % kPast] = v[i];
+  }
+}
+
 // Persistent: workgroup b takes tiles b, b + gridDim.x, ... (in that order)
 // and keeps its running sums of every weight gradient in registers, written
-// once to partial[b].
+// once to partial[b].  Each phase's planes are requested a phase ahead.
+//
+// What bounds it: the fp32 matrix instruction (549k of 970k cycles at 16 x
+// 128^2), in phases that the two workgroups of a CU overlap in part.  404 us; 441
+// with each phase's planes staged between barriers, element by element.
 __global__ __launch_bounds__(kThreads, 2) void sr_bwd_wgrad_kernel(
     const float *__restrict__ lowres, const float *__restrict__ gbuf, const float *__restrict__ dy,
     const float *__restrict__ a1, const float *__restrict__ a2, const float *__restrict__ dz1,
@@ -781,88 +832,85 @@ __global__ __launch_bounds__(kThreads, 2) void sr_bwd_wgrad_kernel(
   const int H = 2 * h, W = 2 * w;
   const int tx_n = (W + kT - 1) / kT, ty_n = (H + kT - 1) / kT;
   const int ntiles = n * tx_n * ty_n;
-  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
+  const int tid = threadIdx.x, lane = tid % 64;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int col = lane % 16, grp = lane / 16;
   const int64_t plane = (int64_t)H * W, plane_lo = (int64_t)h * w;
+  const int64_t fb = 4 * kC * plane;   // bytes of one frame's 32 planes
   constexpr int kOffW2 = kC * kIn * 9 + kC, kOffB2p = kOffW2 + kC * kC * 9;
   constexpr int kOffW3p = kOffB2p + kC, kOffB3p = kOffW3p + kSrOut * kC;
+  constexpr int P = kT * kT, kG = kIn - 3;
+  static_assert(P == kThreads, "a thread per pixel");
   f32x4 acc2[kNJ2][2] = {}, acc1[kNJ1w][2] = {};
   // the head on waves 0..2: column tile `wave` of [a2^T | 1] against dy
   f32x4 acc_h = {0.f, 0.f, 0.f, 0.f};
-  float *dz_s = buf, *ones_s = buf + kC * kDzStride + kC * kP1;
+  float *dz_s = buf, *act_s = buf + kC * kDzStride, *ones_s = buf + kC * kDzStride + kC * kP1;
   for (int e = tid; e < kP1; e += kThreads) ones_s[e] = 1.0f;
+  auto tile_pos = [&](int t) {
+    return TilePos{t / (tx_n * ty_n), ((t / tx_n) % ty_n) * kT, (t % tx_n) * kT};
+  };
+  float v2[kC], vy[kSrOut];            // a2 and dy at the thread's pixel
+  auto fetch_head = [&](TilePos tp, int tid) {
+    fetch_own<kC>(v2, make_rsrc(a2 + (int64_t)tp.f * kC * plane, fb), tp, tid, H, W);
+    fetch_own<kSrOut>(vy, make_rsrc(dy + (int64_t)tp.f * kSrOut * plane, 4 * kSrOut * plane), tp,
+                      tid, H, W);
+  };
+  fetch_head(tile_pos(blockIdx.x), tid);
   for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    const int f = t / (tx_n * ty_n), oy0 = ((t / tx_n) % ty_n) * kT, ox0 = (t % tx_n) * kT;
-    // plane offsets of the tile's own pixel p and of halo position q (clamped
-    // into the image), and whether they lie inside it
-    // byte offsets of channel c at the tile's own pixel p and at halo
-    // position q within frame f's planes; kOutside outside the image
-    auto own = [&](int c, int p) {
-      const int Y = oy0 + p / kT, X = ox0 + p % kT;
-      return Y < H && X < W ? (uint32_t)(4 * (c * plane + (int64_t)Y * W + X)) : kOutside;
-    };
-    auto halo = [&](int c, int q) {
-      const int Y = oy0 - 1 + q / kE1, X = ox0 - 1 + q % kE1;
-      return Y >= 0 && Y < H && X >= 0 && X < W ? (uint32_t)(4 * (c * plane + (int64_t)Y * W + X))
-                                                : kOutside;
-    };
-    const int64_t fb = 4 * kC * plane;   // bytes of one frame's 32 planes
+    const TilePos tp = tile_pos(t);
+    // opaque per tile: what derives from the thread's index would otherwise be
+    // hoisted and take the registers
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid % 64, col = lane % 16, grp = lane / 16;
     // phase 0: the head, dW3[k][o] = sum_p dy[k][p] a2[o][p] and b3[k] =
     // sum_p dy[k][p] on the matrix cores: dy (3 rows of 16) the row operand,
     // [a2^T | 1] (33 of 48 columns) the column operand, over the tile's own
     // pixels (zero outside the image).  a2 [32][256] in dz_s, which becomes dz2
     // there, dy_s [3][256] in the activations' place.
-    constexpr int P = kT * kT;
-    float *act_s = buf + kC * kDzStride;
-    {
-      float *dy_s = act_s;
-      stage<kC * P>(tid, make_rsrc(a2 + (int64_t)f * kC * plane, fb),
-                    [&](int e) { return own(e / P, e % P); },
-                    [&](int e) { return dz_s + (e / P) * kDzStride + e % P; });
-      stage<kSrOut * P>(tid, make_rsrc(dy + (int64_t)f * kSrOut * plane, 4 * kSrOut * plane),
-                        [&](int e) { return own(e / P, e % P); }, [&](int e) { return dy_s + e; });
-      __syncthreads();
-      if (wave < 3) {
-        const int nc = 16 * wave + col;            // column: a2 channel, 32 = ones
+    float *dy_s = act_s;
+    float va[halo_loads(kC)];
+    fetch_halo<kC>(va, make_rsrc(a1 + (int64_t)tp.f * kC * plane, fb), tp, tid, H, W);
+#pragma unroll
+    for (int o = 0; o < kC; ++o) dz_s[o * kDzStride + tid] = v2[o];
+#pragma unroll
+    for (int k = 0; k < kSrOut; ++k) dy_s[k * P + tid] = vy[k];
+    __syncthreads();
+    if (wave < 3) {
+      const int nc = 16 * wave + col;            // column: a2 channel, 32 = ones
 #pragma unroll 8
-        for (int s = 0; s < kT * kT / 4; ++s) {
-          const int p = 4 * s + grp;
-          const float av = col < kSrOut ? dy_s[col * kT * kT + p] : 0.0f;
-          const float bv = nc < kC ? dz_s[nc * kDzStride + p] : (nc == kC ? 1.0f : 0.0f);
-          acc_h = mfma4(av, bv, acc_h);
-        }
+      for (int s = 0; s < P / 4; ++s) {
+        const int p = 4 * s + grp;
+        const float av = col < kSrOut ? dy_s[col * P + p] : 0.0f;
+        const float bv = nc < kC ? dz_s[nc * kDzStride + p] : (nc == kC ? 1.0f : 0.0f);
+        acc_h = mfma4(av, bv, acc_h);
       }
-      __syncthreads();
-      // thread p's column of a2 becomes dz2
-      static_assert(P == kThreads, "a thread per pixel");
-      const float d0 = dy_s[tid], d1 = dy_s[P + tid], d2 = dy_s[2 * P + tid];
-#pragma unroll 8
-      for (int o = 0; o < kC; ++o)
-        dz_s[o * kDzStride + tid] = dz2_of(w3, o, dz_s[o * kDzStride + tid], d0, d1, d2);
-      __syncthreads();
     }
+    __syncthreads();
     // phase A: conv2.  dz_s [32][256] = dz2 over the tile's own pixels and
     // act_s [32][18][18] = a1 over the tile and a one-pixel halo; zero
     // outside the image.
-    stage<kC * kP1>(tid, make_rsrc(a1 + (int64_t)f * kC * plane, fb),
-                    [&](int e) { return halo(e / kP1, e % kP1); }, [&](int e) { return act_s + e; });
+#pragma unroll
+    for (int o = 0; o < kC; ++o) dz_s[o * kDzStride + tid] = dz2_of(w3, o, v2[o], vy[0], vy[1], vy[2]);
+    put_halo<kC>(act_s, va, tid);
     __syncthreads();
+    float vd[kC], vx[halo_loads(kG)];
+    fetch_own<kC>(vd, make_rsrc(dz1 + (int64_t)tp.f * kC * plane, fb), tp, tid, H, W);
+    fetch_halo<kG>(vx, make_rsrc(gbuf + (int64_t)tp.f * kG * plane, 4 * kG * plane), tp, tid, H, W);
+    __builtin_amdgcn_sched_barrier(0);
     wgrad_gemm<kNJ2>(dz_s, act_s, ones_s, kC * 9, acc2, lane, wave);
     __syncthreads();
     // phase B: conv1.  dz_s = dz1 over the tile's own pixels, x_s
     // [17][18][18] = the input over the tile and a one-pixel halo.
-    float *x_s = buf + kC * kDzStride;
-    stage<kC * P>(tid, make_rsrc(dz1 + (int64_t)f * kC * plane, fb),
-                  [&](int e) { return own(e / P, e % P); },
-                  [&](int e) { return dz_s + (e / P) * kDzStride + e % P; });
-    // the 14 G-buffer channels, then the upsampled render
-    stage<(kIn - 3) * kP1>(tid, make_rsrc(gbuf + (int64_t)f * (kIn - 3) * plane,
-                                          4 * (kIn - 3) * plane),
-                           [&](int e) { return halo(e / kP1, e % kP1); },
-                           [&](int e) { return x_s + 3 * kP1 + e; });
-    stage_up<kE1>(tid, make_rsrc(lowres + (int64_t)f * 3 * plane_lo, 4 * 3 * plane_lo), h, w,
-                  oy0 - 1, ox0 - 1, x_s);
+    float *x_s = act_s;
+#pragma unroll
+    for (int o = 0; o < kC; ++o) dz_s[o * kDzStride + tid] = vd[o];
+    put_halo<kG>(x_s + 3 * kP1, vx, tid);
+    stage_up<kE1>(tid, make_rsrc(lowres + (int64_t)tp.f * 3 * plane_lo, 4 * 3 * plane_lo), h, w,
+                  tp.y0 - 1, tp.x0 - 1, x_s);
     __syncthreads();
+    if (t + (int)gridDim.x < ntiles) fetch_head(tile_pos(t + gridDim.x), tid);
+    __builtin_amdgcn_sched_barrier(0);
     wgrad_gemm<kNJ1w>(dz_s, x_s, ones_s, kIn * 9, acc1, lane, wave);
     __syncthreads();
   }
