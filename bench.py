@@ -297,17 +297,16 @@ def k_sweep(w, W, fr, pool, precision, torch, ks=(0, 1, 2, 4, 8), steps=50):
 
 
 def bwd_executed_flop_per_px(W, K):
-    """MFMA FLOP per pixel that one backward call executes: the plane GEMMs of
-    the forward recompute and of the backward (M x K operand shapes as padded
-    by the kernels: K rounded up to 32) and the dW GEMMs (o_pad x i_pad)."""
-    r32 = lambda x: (x + 31) // 32 * 32  # noqa: E731
-    RW = r32(W + 1)
+    """Matrix-core work per pixel of one backward call as fp32 products: the
+    recompute's maps (fp32 instruction, K rounded up to 16), the deltas' and the
+    weight gradients', each of whose products is six bf16 ones on operands
+    split in three and is counted once."""
     # F1 F2 F3 T1s T3 B1 B2 B3 R1 R2; per slot T1 (slot columns), T2
-    fwd = 2 * W * (32 + W + W + W + W + 2 * W + W + W + r32(W + 3) + W) + K * 2 * W * (32 + W)
-    # R3^T R2^T R1^T B3^T B2^T B1^T T3^T T1s^T F3^T F2^T; per slot z1, dz2, dz1
-    bwd = 2 * W * (32 + 4 * W + 2 * W + W + W + 2 * W) + K * 2 * W * (32 + 2 * W)
-    # dW of R3; R2 B3 B2 T3 F3 F2; R1; B1; T1s; F1; per slot T2, T1 slot columns
-    dw = 2 * (32 * RW + W * (6 * RW + r32(W + 4) + r32(2 * W + 1) + W + 32)) + K * 2 * W * (RW + 32)
+    fwd = 2 * W * (32 + W + W + W + W + 2 * W + W + W + W + 16 + W) + K * 2 * W * (16 + W)
+    # R3^T R2^T R1^T B3^T B2^T B1^T T3^T T1s^T F3^T F2^T; per slot T2^T
+    bwd = 2 * W * (32 + 4 * W + 2 * W + W + W + 2 * W) + K * 2 * W * W
+    # dW of R3; R2 R1 B3 B2 B1 (two) T3 T1s F3 F2; R1's L_d, F1; per slot T2, T1 slot columns
+    dw = 2 * W * (16 + 10 * W + 32 + 32) + K * 2 * W * (W + 16)
     return fwd + bwd + dw
 
 

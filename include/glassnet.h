@@ -58,11 +58,10 @@ typedef int32_t gn_status;
 #define GN_E_BUSY (-6)         /* serving: pending queue full */
 
 /* Arithmetic of the forward pass.
- *   GN_FP32    fp32 weights and activations on the fp32 matrix cores, layer by
- *              layer through a workspace of fp32 planes (about 14.5 KB per
- *              pixel at W = 128, kept by the handle and shared with the
- *              backward: FP32 forward and backward calls on different
- *              streams must be ordered by the caller).
+ *   GN_FP32    fp32 weights and activations: one fused kernel on the bf16
+ *              matrix cores, every operand split in three bf16 parts (fp32
+ *              products and sums to within fp32's own rounding), without a
+ *              workspace.
  *   GN_BF16    bf16 weights/activations on MFMA, fp32 accumulation, fp32 pool.
  *   GN_FP8_T   the per-slot hidden layer of h in FP8-E4M3 (per-output-channel
  *              fp32 weight scales, static activation scale), the rest as GN_BF16.
@@ -190,7 +189,7 @@ gn_status glassnet_set_act_scales(gn_handle *h, const float *scales, size_t n);
 /* GN_FP8_T calibration: evaluates h's first layer in fp32 over every slot of
  * every pixel of frame and sets the activation scale to (largest value)/448,
  * so the representative frame's range maps onto E4M3 without clipping.
- * Runs the fp32 plane pipeline of GN_FP32 (same workspace, same pixel limit).
+ * Same pixel limit as GN_FP32.
  * Synchronous (waits for hip_stream). */
 gn_status glassnet_calibrate(gn_handle *h, const gn_frame *frame, void *hip_stream);
 
@@ -201,17 +200,18 @@ gn_status glassnet_calibrate(gn_handle *h, const gn_frame *frame, void *hip_stre
  * the handle's slot order (gn_config.slot_order).
  * GN_FP32: at most 3 * 2^20 pixels (n * h * w) per call (GN_E_INVAL beyond).
  * Forward calls of one handle share a small device scratch (GN_BF16 /
- * GN_FP8_T) or the plane workspace (GN_FP32): calls on different streams must
- * be ordered by the caller.  Serving has its own. */
+ * GN_FP8_T): calls on different streams must be ordered by the caller.
+ * Serving has its own. */
 gn_status glassnet_forward(gn_handle *h, const gn_frame *frame, float *out, void *hip_stream);
 
 /* Backward of the forward above with respect to the weights (Sec. 3.5), fp32.
  * grad_out is dL/d(out), device, shaped like out.  grad_w (device, n_params
- * floats) is overwritten with dL/dw in the flat layout.  Per-slot activations
- * of h are recomputed, never stored for all k.  The transparency mask is a
- * hard selection: no gradient flows through alpha's threshold.  At most
- * 3 * 2^20 pixels (n * h * w) per call (GN_E_INVAL beyond).  The library keeps
- * a workspace of about 14.5 KB per pixel (W = 128) between calls. */
+ * floats) is overwritten with dL/dw in the flat layout.  The activations
+ * are recomputed.  The transparency mask is a hard selection: no gradient
+ * flows through alpha's threshold.  At most 3 * 2^20 pixels (n * h * w) per
+ * call (GN_E_INVAL beyond).  The library keeps a workspace between calls, about
+ * 11 KB + 1.1 KB k per pixel at W = 128, of at most 16 GiB and some partial
+ * sums: larger batches run in slabs of pixels. */
 gn_status glassnet_backward(gn_handle *h, const gn_frame *frame, const float *grad_out,
                             float *grad_w, void *hip_stream);
 
@@ -318,7 +318,7 @@ size_t glassnet_spatial_num_params(int32_t width);
  * at most 2^22 pixels per call; out [n][3][h][w] fp32 device.  A permutation
  * of the transparency buffers is a permutation of whole images (h sees a
  * buffer's neighbourhood).  The handle keeps the weight copy and a workspace
- * of about 3.5 KB per pixel at W = 128 (grown on a larger call, after the
+ * of up to 3.5 KB per pixel at W = 128 (grown on a larger call, after the
  * stream's earlier work).  GN_E_INVAL for odd sizes, bad frames or aliasing
  * buffers. */
 gn_status glassnet_spatial_forward(gn_handle *h, const float *sp_w, const gn_frame *frame,
@@ -327,13 +327,13 @@ gn_status glassnet_spatial_forward(gn_handle *h, const float *sp_w, const gn_fra
 /* Weight gradient of glassnet_sr_forward (Sec. 4.1 trains the super-sampling
  * network on its own), fp32: grad_out = dL/d(out) [n][3][2 height][2 width],
  * device; grad_w (device, glassnet_sr_num_params() floats, packed like sr_w)
- * is overwritten with dL/d(sr_w).  The forward is recomputed with the same
- * arithmetic as glassnet_sr_forward (so the ReLU masks are the ones behind
- * its output; the derivative of ReLU is 0 at 0), per-tile partial sums are
- * added in fp32 in a fixed order: the result is deterministic.  At most 2^22
+ * is overwritten with dL/d(sr_w).  The hidden layers are recomputed in
+ * fp32 (glassnet_sr_forward's sums differ from theirs in the last bits; the
+ * derivative of ReLU is 0 at 0), per-workgroup partial sums are added in fp32
+ * in a fixed order: the result is deterministic.  At most 2^22
  * output pixels per call (n 4 height width) and height, width <= 2^16
  * (GN_E_INVAL beyond, or for NULL, misaligned or aliasing pointers).  The
- * handle keeps a workspace of 512 bytes per output pixel plus at most 35 MB
+ * handle keeps a workspace of 384 bytes per output pixel plus at most 35 MB
  * (grown on a larger call, after the stream's earlier work). */
 gn_status glassnet_sr_backward(gn_handle *h, const float *sr_w, int32_t n, int32_t height,
                                int32_t width, const float *lowres, const float *gbuf_hi,
@@ -360,7 +360,8 @@ gn_status glassnet_l1_loss(gn_handle *h, const float *out, const float *target,
                            void *hip_stream);
 
 /* Device bytes the handle holds for forward work: weights, packed forms and
- * workspaces.  Independent of the slot count k (the pool is a running sum). */
+ * workspaces.  Independent of the slot count k (the pool is a running sum),
+ * but for the backward's workspace once a backward has run. */
 gn_status glassnet_workspace_bytes(gn_handle *h, uint64_t *bytes);
 
 /* Object streaming (Sec. 3.3, Eq. (5); Sec. 4.4.2 and Fig. "MemUsage"): tau
@@ -379,10 +380,10 @@ gn_status glassnet_workspace_bytes(gn_handle *h, uint64_t *bytes);
  * hidden layer and the active-slot count, in a layout private to the library
  * (GN_BF16 / GN_FP8_T: sigma in bf16, 772 bytes per pixel at W = 128, 388 at
  * W = 64; GN_FP32: sigma, the running sum and the count in fp32, (2 W + 1) x
- * 4 bytes per pixel, through the plane workspace of the FP32 forward with
- * its pixel limit).  Calls on one state
- * are ordered on the hip_stream each passes; calls on different streams must
- * be ordered by the caller. */
+ * 4 bytes per pixel, with the FP32 forward's pixel limit).  Pixels that an
+ * object does not cover are neither read nor written by its accumulate call.
+ * Calls on one state are ordered on the hip_stream each passes; calls on
+ * different streams must be ordered by the caller. */
 gn_status glassnet_stream_state_bytes(gn_handle *h, int32_t n, int32_t hgt, int32_t wid,
                                       uint64_t *bytes);
 

@@ -10,10 +10,11 @@
 // layer to the next by a ReLU and a bf16 convert, without leaving registers.
 //
 // Work split.  A workgroup of 8 waves owns a tile of 256 pixels (32 per wave,
-// two N-tiles).  Weights are staged into LDS chunk by chunk with direct
-// global->LDS loads, double-buffered: while a stage computes, the next
-// stage's chunk streams in.  The weights of the per-slot network h that run
-// inside the slot loop stay resident.  Grid = number of CUs; each workgroup
+// two N-tiles; 128 where that leaves half of the CUs idle, n_tiles).  Weights
+// are staged into LDS chunk by chunk with direct global->LDS loads,
+// double-buffered: while a stage computes, the next stage's chunk streams in.
+// The weights of the per-slot network h that run inside the slot loop stay
+// resident, at W = 64 all of them.  Grid = number of CUs; each workgroup
 // walks tiles with a stride of the grid (tiles may come from a table that
 // mixes frames of different sizes and slot counts).
 //
@@ -422,7 +423,7 @@ __device__ __forceinline__ T *uniform(T *p) {
 // MODE selects the part of the path one launch runs: FWD_FULL the whole
 // forward; FWD_BEGIN stages 0-1 (sigma into the state); FWD_ACC stage 2 (the
 // slot loop, continuing the state's running sum); FWD_FINISH stages 3-9 from
-// the state.  FWD_FULL compiles to the code it had before the modes existed.
+// the state.
 //
 // PE > 0: F's and h's inputs are positionally encoded with PE levels; F1 then
 // runs over two stages of its own (stage indices below), and h's first layer
