@@ -397,9 +397,10 @@ def train_phase(torch, steps=10, precision="bf16"):
 def stream_phase(net, g, L, s, out, torch, reps=30):
     """Object streaming on the bench frame: begin, the K objects in calls of
     one object each (and all K in one call), finish.  Also the accumulate
-    call alone, an HBM-bound kernel: per pixel it reads the state (sigma bf16
-    2W B, running sum fp32 4W B, count 4 B) and the object's 48 B and writes
-    the running sum and count back."""
+    call alone, an HBM-bound kernel: per pixel it reads the object's alpha and
+    the count (8 B), per pixel that the object covers the state (sigma bf16 2W B,
+    running sum fp32 4W B) and the object's other 44 B, and writes the running
+    sum and count back."""
     n, K, _, H, Wd = L.shape
     W = net.width
     px = n * H * Wd
@@ -427,7 +428,8 @@ def stream_phase(net, g, L, s, out, torch, reps=30):
     t1 = timed(lambda: frame(Ls), reps)
     tk = timed(lambda: frame([L]), reps)
     ta = timed(lambda: net.stream_accumulate(Ls[0], st), 4 * reps)
-    acc_bytes = px * ((2 * W + 4 * W + 4) + 48 + (4 * W + 4))
+    covered = float((Ls[0][:, :, 9] > 0).sum())    # plane 9: alpha
+    acc_bytes = px * 8 + covered * ((2 * W + 4 * W) + 44 + (4 * W + 4))
     net.stream_release(st)
     return {"state_bytes_per_px": net.stream_state_bytes(n, H, Wd) / px,
             "ms_per_frame_1_object_per_call": t1 * 1e3,
