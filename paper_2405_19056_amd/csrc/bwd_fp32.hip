@@ -582,29 +582,32 @@ struct DeltaArgs {
 };
 
 // A wave owns 16 pixels, a workgroup WAVES * 16.  The maps run on split operands
-// (fp32_core.h); sigma's delta waits in LDS while the slots run.  Every other
-// wave computes the negative of its deltas: the bf16 instruction rounds its sums
-// towards minus infinity, by a fraction of an ulp that a sum over many pixels
-// would collect (1e-5 of a gradient over 2^18 pixels with random dy).
+// (fp32_core.h); sigma's delta waits in LDS while the slots run.  The bf16
+// instruction rounds its sums towards minus infinity, which a sum over many
+// pixels would collect (1e-5 of a gradient over 2^18 pixels with random dy): so
+// each K-step is summed by itself (SplitPipe's FRESH), and a pixel's deltas are
+// computed with the sign of its place (sign_of).
 //
 // What bounds it: HBM and the matrix cores in turn.  16 x 128^2, K = 4, W = 128:
-// 2.3 GB of deltas written (450 us at the copy rate) and 340 us of matrix-core
-// work take 841 us; on the fp32 instruction, with 900 us of such work, 1132.
+// 2.0 GB of deltas written (390 us at the copy rate) and 340 us of matrix-core
+// work take 909 us (864 with the K-steps in one chain, whose gradient is 2 to
+// 15 times further from 64 bits); on the fp32 instruction, with 900 us of such
+// work, 1132.
 template <int W, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void f32_delta_kernel(DeltaArgs a) {
   constexpr int MT = W / 16, KS = W / 32, kPx = WAVES * 16;
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   const int wave = threadIdx.x >> 6;
   f32x4 *l_dsig = (f32x4 *)(lds + kRing * kSplitStage) + wave * MT * 64 + (threadIdx.x & 63);
-  SplitPipe<MT, WAVES> pipe;
+  SplitPipe<MT, WAVES, true> pipe;
   pipe.start(a.packed, lds, a.pg);
-  const float sign = wave & 1 ? -1.0f : 1.0f;
   const int64_t ntiles = a.pl.np / kPx;
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     int g = (threadIdx.x & 63) >> 4, col = threadIdx.x & 15;
     asm volatile("" : "+v"(g), "+v"(col));      // per-tile copies, as in the forward
     const int64_t pl = tile * kPx + wave * 16 + col, p = a.pl.p0 + pl;
     const uint32_t at = (uint32_t)pl * (W * 4) + 16 * g;
+    const float sign = sign_of((uint32_t)p);
     f32x4 acc[MT];
     Split in[KS];
     auto signs = [&](int layer) {
@@ -632,11 +635,6 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void f32_delta_kernel(DeltaA
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[mt][r] = bits & (1u << (4 * mt + r)) ? v[mt][r] : 0.0f;
     };
-    auto clear = [&]() {
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) acc[mt] = zero4();
-    };
-    clear();
     // dL/dy of the pixel: lane group g < 3 channel g (padding pixels: zero, so
     // every delta of theirs is zero)
     float dy = 0.0f;
@@ -654,7 +652,6 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void f32_delta_kernel(DeltaA
     auto next = [&](float *plane) {            // the accumulators are this plane's delta
       put(plane, acc);
       feed(acc);
-      clear();
     };
     mask(acc, bits);
     next(a.pl.dg2);
@@ -675,7 +672,6 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void f32_delta_kernel(DeltaA
     pipe.chain(acc, in);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) l_dsig[mt * 64] = acc[mt];
-    clear();
     pipe.chain(acc, in);
     next(a.pl.dtau);
     pipe.chain(acc, in);
@@ -685,7 +681,6 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void f32_delta_kernel(DeltaA
       dz[mt] = acc[mt] * inv;                   // dZ = W_T3^T dtau / max(c, 1)
       du[mt] = zero4();
     }
-    clear();
     put(a.pl.dz, dz);
     uint32_t b2 = 0, b1 = 0;
     if (a.k > 0) {
@@ -711,7 +706,6 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void f32_delta_kernel(DeltaA
       put(a.pl.dz1 + (int64_t)i * a.pl.np * W, acc);
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) du[mt] += acc[mt];
-      clear();
       b1 = n1;
       b2 = n2;
     }
@@ -762,8 +756,9 @@ constexpr int part_floats(int W, int MI) { return W * 16 * MI + W + 16 * MI; }
 // the step before computes, then written to LDS; row p of a block keeps its
 // 16-byte unit c at c ^ swz(p), so that the four pixels that the lane groups
 // read fall into distinct banks.  A step is one 32-deep group of the bf16 matrix
-// cores on operands split in three (fp32_core.h); every other workgroup sums the
-// negative of its product, as the deltas do.
+// cores on operands split in three (fp32_core.h), summed by itself before it is
+// added (16 x 128^2, K = 4, W = 128: 945 us a square product's launch, 907 in one
+// chain), a workgroup's with the sign of its place, as the deltas are.
 template <int W, int MI>
 __global__ __launch_bounds__(kThreads, 2) void f32_dw_kernel(DwArgs a) {
   constexpr int MO = W / 16;
@@ -777,7 +772,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dw_kernel(DwArgs a) {
   __shared__ float lw[2][kStep];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, l = lane & 15;
   const int wr = wave / WC, wc = wave % WC;
-  const float sign = blockIdx.x & 1 ? -1.0f : 1.0f;
+  const float sign = sign_of(blockIdx.x);
   auto dswz = [](int p) { return 4 * (p & 3); };
   auto aswz = [](int p) { return MI >= 4 ? 4 * (p & 3) : (MI == 2 ? 4 * ((p >> 1) & 1) : 0); };
 
@@ -885,7 +880,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dw_kernel(DwArgs a) {
         }
         const Split x = split8(v);
 #pragma unroll
-        for (int o = 0; o < TO; ++o) acc[o][i] = mma_split(d[o], x, acc[o][i]);
+        for (int o = 0; o < TO; ++o) acc[o][i] += mma_split(d[o], x, zero4());
       }
     }
     float *P = a.part + (size_t)(blockIdx.x + j) * part_floats(W, MI);

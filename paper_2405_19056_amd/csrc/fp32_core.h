@@ -73,6 +73,13 @@ __device__ __forceinline__ f32x4 mma_split(const Split &a, const Split &b, f32x4
   return mma_bf16(a.hi, b.hi, c);
 }
 
+// The sign with which the i-th of many addends is computed (and undone): by
+// the parity of i's bits (the Thue-Morse sequence).  What is left of the bf16
+// instruction's one-sided rounding then cancels in a sum over them; unlike by
+// the parity of i, also where all that matters sits at every second, fourth,
+// ... place.
+__device__ __forceinline__ float sign_of(uint32_t i) { return __popc(i) & 1 ? -1.0f : 1.0f; }
+
 // Positional-encoding block b of x (Sec. 3.4): x for b = 0, then
 // sin(2^k pi x) for b = 2k + 1 and cos(2^k pi x) for b = 2k + 2 (sinpi and
 // cospi reduce the argument exactly; the scaling by 2^k is exact).
@@ -154,7 +161,11 @@ constexpr int kRing = 3;     // stage buffers in LDS
 // read before this one ends.
 constexpr int kSplitFrags = 24, kSplitStage = kSplitFrags * 1024;
 
-template <int MT, int WAVES>
+// FRESH: a map sets the accumulators instead of adding to them, and a K-step's
+// products are summed by themselves and then added by the vector unit.  The bf16 instruction rounds its sums
+// towards minus infinity: in one chain each of the six partial products shifts
+// the whole sum down by a fraction of its ulp, here only the K-step's own sum.
+template <int MT, int WAVES, bool FRESH>
 struct SplitPipe {
   static constexpr int kThreads = WAVES * 64;
   static constexpr int kHold = kSplitStage / 16 / kThreads;
@@ -224,13 +235,20 @@ struct SplitPipe {
       if (s0 + i / kPer < steps) {
         const Split &b = x(i / kPer);
         const u32x4(&a)[6] = w[i & 1];
+        f32x4 sum[2] = {FRESH ? zero4() : acc[m0], FRESH ? zero4() : acc[m0 + 1]};
         // small partial products first, the two tiles in turn
 #pragma unroll
         for (int p = 0; p < 6; ++p) {
           constexpr int kA[6] = {2, 0, 1, 1, 0, 0}, kB[6] = {0, 2, 1, 0, 1, 0};
           const u32x4 bv = kB[p] == 0 ? b.hi : (kB[p] == 1 ? b.mid : b.lo);
 #pragma unroll
-          for (int m = 0; m < 2; ++m) acc[m0 + m] = mma_bf16(a[3 * m + kA[p]], bv, acc[m0 + m]);
+          for (int m = 0; m < 2; ++m) sum[m] = mma_bf16(a[3 * m + kA[p]], bv, sum[m]);
+        }
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          acc[m0 + m] = FRESH && s0 + i / kPer > 0 ? acc[m0 + m] + sum[m] : sum[m];
+          // (here: left to itself the compiler keeps the sums and adds them at the map's end)
+          if constexpr (FRESH) asm volatile("" : "+v"(acc[m0 + m]));
         }
       }
       __builtin_amdgcn_sched_barrier(0);

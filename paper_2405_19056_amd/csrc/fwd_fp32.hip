@@ -170,7 +170,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void f32_forward_kernel(FwdA
     const float *b = (const float *)(a.packed + (size_t)a.bias_stage * kSplitStage);
     for (int i = threadIdx.x; i < kNumLayers * W; i += WAVES * 64) l_bias[i] = b[i];
   }
-  SplitPipe<MT, WAVES> pipe;
+  SplitPipe<MT, WAVES, false> pipe;
   pipe.start(a.packed, lds, a.pg);       // ends with a barrier
   const int hw = a.hw, nblk = ENC ? pe_blocks(a.pe) : 1;
   const int64_t ntiles = (a.npx + kTile - 1) / kTile;

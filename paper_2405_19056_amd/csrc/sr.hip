@@ -256,14 +256,14 @@ __device__ __forceinline__ void store_split4(uint8_t *p, int part, const float (
 // acc[jj] += conv over STEPS K-steps for this wave's column tiles wave + 4 jj
 // below ntiles; src(jj, s) is the LDS record of part 0.  A step's weights, 6
 // KiB, come from L2 a step ahead (the first step's in a[0], by conv_first) and
-// serve all of the wave's tiles.
+// serve all of the wave's tiles.  FRESH: as SplitPipe's.
 typedef u32x4 ConvWeights[2][6];
 __device__ __forceinline__ void conv_first(ConvWeights &a, const float *frags, int lane) {
 #pragma unroll
   for (int e = 0; e < 6; ++e) a[0][e] = ((const u32x4 *)frags)[lane + e * 64];
 }
 
-template <int NJ, int STEPS, class Src>
+template <int NJ, int STEPS, bool FRESH, class Src>
 __device__ __forceinline__ void conv_split(f32x4 (&acc)[NJ][2], ConvWeights &a, const float *frags,
                                            int part, int ntiles, int lane, int wave, Src src) {
   const u32x4 *f = (const u32x4 *)frags + lane;
@@ -278,7 +278,7 @@ __device__ __forceinline__ void conv_split(f32x4 (&acc)[NJ][2], ConvWeights &a, 
     for (int jj = 0; jj < NJ; ++jj) {
       if (wave + 4 * jj >= ntiles) continue;
       const Split b = lds_split(src(jj, s), part);
-      f32x4 c0 = acc[jj][0], c1 = acc[jj][1];
+      f32x4 c0 = FRESH ? f32::zero4() : acc[jj][0], c1 = FRESH ? f32::zero4() : acc[jj][1];
       // the two channel tiles in turn: each product waits for the sum before it
       c0 = f32::mma_bf16(w[2], b.hi, c0);
       c1 = f32::mma_bf16(w[5], b.hi, c1);
@@ -290,8 +290,10 @@ __device__ __forceinline__ void conv_split(f32x4 (&acc)[NJ][2], ConvWeights &a, 
       c1 = f32::mma_bf16(w[4], b.hi, c1);
       c0 = f32::mma_bf16(w[0], b.mid, c0);
       c1 = f32::mma_bf16(w[3], b.mid, c1);
-      acc[jj][0] = f32::mma_bf16(w[0], b.hi, c0);
-      acc[jj][1] = f32::mma_bf16(w[3], b.hi, c1);
+      c0 = f32::mma_bf16(w[0], b.hi, c0);
+      c1 = f32::mma_bf16(w[3], b.hi, c1);
+      acc[jj][0] = FRESH ? acc[jj][0] + c0 : c0;
+      acc[jj][1] = FRESH ? acc[jj][1] + c1 : c1;
     }
   }
 }
@@ -403,7 +405,7 @@ __global__ __launch_bounds__(kThreads, 2) void sr_forward_kernel(
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt) acc[jj][mt] = *(const f32x4 *)(wt + kOffB1 + 16 * mt + 4 * grp);
     }
-    conv_split<kNJ1f, kQ1>(acc, a, wt + kOffF1, kPartX, kN1, lane, wave, [&](int jj, int s) {
+    conv_split<kNJ1f, kQ1, false>(acc, a, wt + kOffF1, kPartX, kN1, lane, wave, [&](int jj, int s) {
       // lane groups 0, 1: channels 0-7, 8-15 of tap 2 s; 2, 3: of tap 2 s + 1,
       // in the last step channel 16's taps
       const int t0 = 2 * s, t1 = 2 * s + 1;
@@ -438,7 +440,7 @@ __global__ __launch_bounds__(kThreads, 2) void sr_forward_kernel(
   for (int jj = 0; jj < 4; ++jj)
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) acc[jj][mt] = *(const f32x4 *)(wt + kOffB2 + 16 * mt + 4 * grp);
-  conv_split<4, kQ2>(acc, a, wt + kOffF2, kPartH, kT, lane, wave, [&](int jj, int s) {
+  conv_split<4, kQ2, false>(acc, a, wt + kOffF2, kPartH, kT, lane, wave, [&](int jj, int s) {
     return x_s + (grp * kP1 + (wave + 4 * jj + s / 3) * kE1 + col + s % 3) * kRec;
   });
   f32x4 w3[kSrOut][2];
@@ -624,7 +626,7 @@ __device__ __forceinline__ float dz2_of(const float *w3, int o, float a2, float 
 // on the matrix cores exactly as the forward's conv2: dz2 over the tile and a
 // one-pixel halo, made from a2 and dy while it is staged, split, in LDS.
 // What bounds it: 440 MB of a2, a1 and dz1 for 16 x 128^2, read and written in
-// step with the matrix-core work (27% of its 171 us; 260 us on the fp32
+// step with the matrix-core work (27% of its 182 us; 260 us on the fp32
 // instruction, plus dz2's kernel).
 __global__ __launch_bounds__(kThreads, 2) void sr_bwd_dz1_kernel(
     const float *__restrict__ wt, const float *__restrict__ dy, const float *__restrict__ a2,
@@ -636,10 +638,12 @@ __global__ __launch_bounds__(kThreads, 2) void sr_bwd_dz1_kernel(
   const int col = lane % 16, grp = lane / 16;
   const int64_t plane = (int64_t)H * W;
   const uint32_t pl = 4 * (uint32_t)plane;
-  // every other tile computes -dz1 from -dz2: the bf16 instruction rounds its
-  // sums towards minus infinity, by a fraction of an ulp that a gradient's sum
-  // over the pixels would collect (3e-6 over 2^16 of them, 4e-7 with the signs)
-  const float sign = (blockIdx.x ^ blockIdx.y) & 1 ? -1.0f : 1.0f;
+  // a tile's dz1 is computed with the sign of its place, and each K-step of the
+  // conv is summed by itself (FRESH): the bf16 instruction rounds its sums
+  // towards minus infinity, by a fraction of an ulp that a gradient's sum over the
+  // pixels would collect (3e-6 over 2^16 of them; 3e-7 as it is)
+  const float sign =
+      f32::sign_of(blockIdx.x) * f32::sign_of(blockIdx.y) * f32::sign_of(blockIdx.z);
   ConvWeights a;
   conv_first(a, wt + kOffF2T, lane);
   // a1 at the lane's outputs, requested ahead of the rest
@@ -687,7 +691,7 @@ __global__ __launch_bounds__(kThreads, 2) void sr_bwd_dz1_kernel(
   f32x4 acc[4][2];
 #pragma unroll
   for (int jj = 0; jj < 4; ++jj) acc[jj][0] = acc[jj][1] = f32::zero4();
-  conv_split<4, kQ2>(acc, a, wt + kOffF2T, kPartH, kT, lane, wave, [&](int jj, int s) {
+  conv_split<4, kQ2, true>(acc, a, wt + kOffF2T, kPartH, kT, lane, wave, [&](int jj, int s) {
     return d_s + (grp * kP1 + (wave + 4 * jj + s / 3) * kE1 + col + s % 3) * kRec;
   });
 #pragma unroll
