@@ -37,10 +37,16 @@ __device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
 __device__ __forceinline__ float bf16_lo(uint32_t v) { return __uint_as_float(v << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t v) { return __uint_as_float(v & 0xFFFF0000u); }
 
-// An infinite x keeps its infinite hi: what is left of it (inf - inf) becomes
-// a finite value instead of a NaN.
-__device__ __forceinline__ float left_of(float x, float h) {
-  return __builtin_amdgcn_fmed3f(x - h, -6.7e35f, 6.7e35f);
+// An infinite x is (bf16's largest, 2^120, infinity) with its sign: of its
+// partial products only lo's with the other operand's hi is infinite, and it has
+// the product's sign.  (As hi, infinity would also meet the other operand's mid
+// and lo, which may have the other sign or be zero: NaN, which a ReLU turns into
+// zero.)  hi's product with mid stays finite for other operands up to 256.  A NaN
+// x is one in lo.
+template <bool HI>
+__device__ __forceinline__ float part(float x) {
+  constexpr float kMost = HI ? 0x1.fep127f : 0x1p120f;
+  return __builtin_amdgcn_fmed3f(x, -kMost, kMost);
 }
 
 __device__ __forceinline__ Split split8(const float (&x)[8]) {
@@ -48,9 +54,9 @@ __device__ __forceinline__ Split split8(const float (&x)[8]) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const float a = x[2 * i], b = x[2 * i + 1];
-    const uint32_t h = pk_bf16(a, b);
-    const float ra = left_of(a, bf16_lo(h)), rb = left_of(b, bf16_hi(h));
-    const uint32_t m = pk_bf16(ra, rb);
+    const uint32_t h = pk_bf16(part<true>(a), part<true>(b));
+    const float ra = a - bf16_lo(h), rb = b - bf16_hi(h);
+    const uint32_t m = pk_bf16(part<false>(ra), part<false>(rb));
     s.hi[i] = h;
     s.mid[i] = m;
     s.lo[i] = pk_bf16(ra - bf16_lo(m), rb - bf16_hi(m));

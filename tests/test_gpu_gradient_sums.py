@@ -18,6 +18,7 @@ from paper_2405_19056_amd import synth
 from paper_2405_19056_amd.glassnet import GlassNet
 
 from gpu_util import log, torch_dev
+from ref64 import SR_SHAPES, columns, conv64, glassnet64, layers_of
 
 pytestmark = pytest.mark.gpu
 
@@ -26,36 +27,15 @@ def rel(a, b):
     return float((a - b).norm() / b.norm())
 
 
-def layers_of(w, shapes):
-    """The flat parameters as 64-bit (matrix [out][in], bias) leaves."""
-    torch = torch_dev()
-    v, out, at = torch.from_numpy(w).to("cuda:0").double(), [], 0
-    for o, i in shapes:
-        out += [v[at:at + o * i].reshape(o, i).clone().requires_grad_(True),
-                v[at + o * i:at + o * i + o].clone().requires_grad_(True)]
-        at += o * i + o
-    return out
-
-
 def glassnet_grad64(flat, G, L, S, dy):
-    """Gradient of sum(dy y) over pixels [P], dy masked near kinks (returned)."""
+    """Gradient of sum(dy y) over pixels, and dy, zeroed near kinks."""
     torch = torch_dev()
     margins = []
-
-    def lin(i, x):
-        return x @ flat[2 * i].t() + flat[2 * i + 1]
 
     def relu(z):
         margins.append(z.detach().abs().amin(1))
         return torch.relu(z)
-
-    def mlp(i, x):
-        return lin(i + 2, relu(lin(i + 1, relu(lin(i, x)))))
-    sigma = mlp(0, torch.cat([G, S], 1))
-    act = [(L[:, i, 9:10] > 0).double() for i in range(L.shape[1])]
-    tau = sum(a * mlp(3, torch.cat([L[:, i], sigma], 1)) for i, a in enumerate(act))
-    tau = tau / sum(act).clamp_min(1.0)
-    y = mlp(9, torch.cat([mlp(6, torch.cat([sigma, tau], 1)), G[:, 11:14]], 1))
+    y = glassnet64(flat, G, L, S, relu)
     dy = dy * (torch.stack(margins).amin(0) > 2e-5)[:, None]
     return torch.cat([t.reshape(-1) for t in torch.autograd.grad((y * dy).sum(), flat)]), dy
 
@@ -83,12 +63,10 @@ def test_backward_sums_over_many_pixels(W, where):
     dy = torch.randn((h * w_, 3), generator=gen, device="cuda:0").double()
     dy *= WHERE[where](torch.arange(h * w_, device="cuda:0"))[:, None]
     flat = layers_of(wts, synth.layer_shapes(W))
-    G = g[0].double().reshape(14, -1).t()
-    Ls = L[0].double().reshape(k, 12, -1).permute(2, 0, 1)
+    G, Ls, S = columns(g, L, s)
     ref, ds, step = 0, [], 1 << 15
     for i in range(0, h * w_, step):
-        gr, d = glassnet_grad64(flat, G[i:i + step], Ls[i:i + step],
-                                s.double().expand(step, 16), dy[i:i + step])
+        gr, d = glassnet_grad64(flat, G[i:i + step], Ls[i:i + step], S[i:i + step], dy[i:i + step])
         ref = ref + gr
         ds.append(d)
     d = torch.cat(ds).float().t().reshape(1, 3, h, w_).contiguous()
@@ -96,15 +74,6 @@ def test_backward_sums_over_many_pixels(W, where):
         err = rel(net.backward(g, L, s, d).double(), ref)
     log(f"  backward W={W}, dL/dy {where}: relF {err:.2e}")
     assert err <= 1.8e-6
-
-
-def conv64(x, A, b, k):
-    """x [h][w][C] -> [h][w][out]: k x k correlation, zero padding; A [out][C k k]."""
-    torch = torch_dev()
-    h, w, C = x.shape
-    A, r = A.reshape(A.shape[0], C, k, k), k // 2
-    p = torch.nn.functional.pad(x, (0, 0, r, r, r, r))
-    return b + sum(p[i:i + h, j:j + w] @ A[:, :, i, j].t() for i in range(k) for j in range(k))
 
 
 @pytest.mark.parametrize("where", ["every tile", "every second tile"])
@@ -124,7 +93,7 @@ def test_sr_gradient_sums_over_many_pixels(where):
     tile = torch.arange(2 * h, device="cuda:0")[:, None] // 16 + torch.arange(2 * w_, device="cuda:0") // 16
     if where == "every second tile":
         dy *= tile % 2 == 0
-    flat = layers_of(wts, [(32, 17 * 9), (32, 32 * 9), (3, 32)])
+    flat = layers_of(wts, SR_SHAPES)
     ref = 0
     for f in range(n):
         x = torch.cat([torch.full((2 * h, 2 * w_, 3), 0.5, device="cuda:0", dtype=torch.float64),
