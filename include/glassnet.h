@@ -206,12 +206,14 @@ gn_status glassnet_forward(gn_handle *h, const gn_frame *frame, float *out, void
 
 /* Backward of the forward above with respect to the weights (Sec. 3.5), fp32.
  * grad_out is dL/d(out), device, shaped like out.  grad_w (device, n_params
- * floats) is overwritten with dL/dw in the flat layout.  The activations
- * are recomputed.  The transparency mask is a hard selection: no gradient
- * flows through alpha's threshold.  At most 3 * 2^20 pixels (n * h * w) per
- * call (GN_E_INVAL beyond).  The library keeps a workspace between calls, about
- * 11 KB + 1.1 KB k per pixel at W = 128, of at most 16 GiB and some partial
- * sums: larger batches run in slabs of pixels. */
+ * floats) is overwritten with dL/dw in the flat layout.  The activations are
+ * recomputed, those of the k slots for a slab of pixels at a time.  The
+ * transparency mask is a hard selection: no gradient flows through alpha's
+ * threshold.  At most 3 * 2^20 pixels (n * h * w) per call (GN_E_INVAL beyond).
+ * The library keeps a workspace between calls that does not grow with k past
+ * four slots: what those take for the call's pixels, or for 32,768 of them if
+ * it has fewer (15.5 KB per pixel at W = 128, 8.1 KB at 64, without encoding),
+ * at most 16 GiB, and 62 MB of partial sums (31 MB). */
 gn_status glassnet_backward(gn_handle *h, const gn_frame *frame, const float *grad_out,
                             float *grad_w, void *hip_stream);
 
@@ -360,8 +362,8 @@ gn_status glassnet_l1_loss(gn_handle *h, const float *out, const float *target,
                            void *hip_stream);
 
 /* Device bytes the handle holds for forward work: weights, packed forms and
- * workspaces.  Independent of the slot count k (the pool is a running sum),
- * but for the backward's workspace once a backward has run. */
+ * workspaces.  Independent of the slot count k (the pool is a running sum);
+ * once a backward has run, its workspace as described there. */
 gn_status glassnet_workspace_bytes(gn_handle *h, uint64_t *bytes);
 
 /* Object streaming (Sec. 3.3, Eq. (5); Sec. 4.4.2 and Fig. "MemUsage"): tau

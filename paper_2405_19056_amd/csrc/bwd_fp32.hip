@@ -19,7 +19,8 @@
 // Then one fixed-order reduction of the workgroups' partial sums into grad_w
 // (deterministic, no atomics).
 //
-// Slabs bound the workspace: a slab's blocks take at most kSlabBytes.
+// Slabs bound the workspace (plane_bytes): it does not depend on the number of
+// slots, whose activations are recomputed for a slab at a time.
 //
 // Formulation of the recompute (the deltas' weights: SplitPipe of fp32_core.h).
 // A wave owns 16 pixels.  Every map is D = A X with a 16-row
@@ -57,7 +58,6 @@ struct BwdWorkspace {
 
 namespace f32 {
 
-constexpr size_t kSlabBytes = (size_t)16 << 30;
 constexpr int kThreads = 256, kWaves = 4;
 constexpr int kTile = kWaves * 16;         // pixels per workgroup tile
 constexpr int kStageFrags = 16;
@@ -973,6 +973,25 @@ static int64_t px_floats(int W, int pe, int k) {
          (int64_t)k * (2 * W + b_width(W, pe));
 }
 
+// The most bytes that a call's planes take: what its pixels, or kSlabLeast of
+// them, need with four slots, and never more than kSlabBytes.  A call of more
+// slots runs in more slabs instead (16 x 128^2, W = 128, K = 8: two), so that
+// the workspace does not grow with their number.  kSlabLeast: that many pixels
+// are one round of the recompute's workgroups; smaller slabs would leave CUs
+// idle (128^2, W = 128, K = 8: 512 us in one slab, 749 in two).
+constexpr size_t kSlabBytes = (size_t)16 << 30;
+constexpr int64_t kSlabStep = 2 * kTile, kSlabLeast = 32768;
+static int64_t most_plane_bytes(int W, int pe, int64_t npx) {
+  return std::min((int64_t)kSlabBytes, (int64_t)sizeof(float) * px_floats(W, pe, 4) *
+                                           std::max(rup(npx, kSlabStep), kSlabLeast));
+}
+// A slab's pixels: slabs of equal length (the last may be shorter).
+static int64_t slab_px(int W, int pe, int k, int64_t npx) {
+  const int64_t fit = most_plane_bytes(W, pe, npx) / ((int64_t)sizeof(float) * px_floats(W, pe, k));
+  const int64_t most = fit / kSlabStep * kSlabStep, slabs = (npx + most - 1) / most;
+  return rup((npx + slabs - 1) / slabs, kSlabStep);
+}
+
 static Planes carve(float *mem, int W, int pe, int k, int64_t np) {
   Planes p{};
   p.np = np;
@@ -1013,24 +1032,29 @@ class Gradient {
     g_[2].MI = 2;
     jobs(Planes{});
   }
-  // Splits the groups' steps over workgroups for slabs of np pixels; returns
-  // the floats of all partials.
-  size_t split(int64_t np) {
+  // As many workgroups as the CUs hold (LDS: two of 64 KB, four of the smaller
+  // ones).
+  static int64_t group_cap(int W, int MI, int cus) { return (int64_t)cus * (W == 128 && MI >= 4 ? 2 : 4); }
+  // The floats of all partials, whatever the call.
+  static size_t part_room(int W, int cus) {
+    size_t floats = 0;
+    for (int MI : {W / 16, 1, 2}) floats += (size_t)(group_cap(W, MI, cus) + kMaxJobs) * part_floats(W, MI);
+    return floats;
+  }
+  // Splits the groups' steps over workgroups for slabs of np pixels.
+  void split(int64_t np) {
     size_t floats = 0;
     for (DwGroup &g : g_) {
       g.a.steps = np / kStep;
       g.total = 0;
       for (int j = 0; j < g.a.njobs; ++j) g.total += g.a.job[j].slots * g.a.steps;
-      // as many workgroups as the CUs hold (LDS: two of 64 KB, four of the
-      // smaller ones), each with at least 4 steps (a partial costs about as
-      // much traffic as two)
-      const int64_t cap = (int64_t)cus_ * (W_ == 128 && g.MI >= 4 ? 2 : 4);
+      // at least 4 steps each (a partial costs about as much traffic as two)
+      const int64_t cap = group_cap(W_, g.MI, cus_);
       g.a.per = (int32_t)std::max<int64_t>((g.total + cap - 1) / cap, 4);
       g.grid = (int)((g.total + g.a.per - 1) / g.a.per);
       g.a.part = (float *)nullptr + floats;                  // an offset, until bind()
-      floats += (size_t)(g.grid + g.a.njobs) * part_floats(W_, g.MI);
+      floats += (size_t)(cap + kMaxJobs) * part_floats(W_, g.MI);
     }
-    return floats;
   }
   void bind(float *part) {
     for (DwGroup &g : g_) g.a.part = part + (g.a.part - (float *)nullptr);
@@ -1226,14 +1250,12 @@ static gn_status backward(gn_handle *h, const gn_frame *frame, const float *dy, 
   f32::make_ops(W, pe, &pk.t[0]);
   f32::make_bwd_ops(W, pe, &pk.t[1]);
   const f32::OpTable &tf = pk.t[0], &tb = pk.t[1];
-  // slabs of equal length (the last may be shorter) within the workspace bound
-  const int64_t per_px = f32::px_floats(W, pe, k) * (int64_t)sizeof(float);
-  const int64_t most = (int64_t)(f32::kSlabBytes / per_px), slabs = (npx + most - 1) / most;
-  const int64_t np = f32::rup((npx + slabs - 1) / slabs, 2 * f32::kTile);
+  const int64_t np = f32::slab_px(W, pe, k, npx);
   f32::Gradient grad(W, pe, k, h->num_cus);
-  const size_t part = grad.split(np) * sizeof(float);
-  const size_t planes = f32::rup(np * per_px, 1024);
-  const size_t need = planes + f32::packed_bytes(tf) + f32::packed_bytes(tb) + part;
+  grad.split(np);
+  const size_t planes = f32::rup(np * f32::px_floats(W, pe, k) * (int64_t)sizeof(float), 1024);
+  const size_t need = planes + f32::packed_bytes(tf) + f32::packed_bytes(tb) +
+                      sizeof(float) * f32::Gradient::part_room(W, h->num_cus);
   if (!h->bwd) h->bwd = new BwdWorkspace();
   BwdWorkspace *ws = h->bwd;
   hipError_t e = hipSuccess;

@@ -317,3 +317,49 @@ def test_autograd_scaled_loss_and_weights_changed_before_backward():
         loss.backward()
         torch.cuda.synchronize()
     check(host(w.grad) / 2.5, ref, W)
+
+
+@pytest.mark.parametrize("W", [64, 128])
+def test_backward_workspace_does_not_grow_with_the_slots(W):
+    """Four slots and 64 on 41,000 pixels (the handles hold nothing else that
+    differs); a quarter of a percent is the rounding of slabs to 128 pixels."""
+    torch = torch_dev()
+    h, w_ = 200, 205
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    r = lambda *shape: torch.rand(shape, generator=gen, device="cuda:0")  # noqa: E731
+    g, s, dy = r(1, 14, h, w_), r(1, 16), r(1, 3, h, w_)
+    held = {}
+    for k in (4, 64):
+        with GlassNet(synth.make_weights(W, np.random.default_rng(1)), W, k_max=64,
+                      precision="fp32") as net:
+            before = net.workspace_bytes()
+            net.backward(g, r(1, k, 12, h, w_), s, dy)
+            held[k] = net.workspace_bytes() - before
+    log(f"  backward workspace W={W}: {held[4] / 2**20:.0f} MiB with 4 slots, "
+        f"{held[64] / 2**20:.0f} with 64")
+    assert held[64] <= 1.0025 * held[4]
+
+
+@pytest.mark.parametrize("W,k", [(64, 20), (128, 13)])
+def test_backward_in_slabs_matches_oracle(W, k):
+    """39,203 pixels of many slots run in three and two slabs, of which the last
+    is shorter by two and by one step of 128 pixels.  dL/dy is non-zero on
+    sampled pixels, on both sides of the slabs' borders and at the frame's end,
+    which the oracle evaluates one by one."""
+    h, w_ = 197, 199
+    wts, fr, s = frame(1, h, w_, k, W, seed=77)
+    rng = np.random.default_rng(9)
+    flat = np.unique(np.concatenate([rng.choice(h * w_, size=1000, replace=False),
+                                     np.arange(127, h * w_, 128), np.arange(128, h * w_, 128),
+                                     np.arange(h * w_ - 300, h * w_)]))
+    flat = flat[kink_free(wts, W, fr, "mean", flat)]
+    dy = np.zeros((1, 3, h * w_), np.float32)
+    dy[0][:, flat] = rng.normal(size=(3, len(flat)))
+    dy = dy.reshape(1, 3, h, w_)
+    ref = oracle.grad_from_dy(
+        wts, W, fr.gbuf.reshape(14, -1)[:, flat][None, :, None, :],
+        fr.layers.reshape(k, 12, -1)[:, :, flat][None, :, :, None, :], fr.scene,
+        dy.reshape(3, -1)[:, flat][None, :, None, :], pool="mean")
+    with GlassNet(wts, W, k_max=k, precision="fp32") as net:
+        worst = check(gpu_grad(net, fr, dy), ref, W)
+    log(f"  backward in slabs W={W} k={k}: worst per-tensor relF {worst:.3e}")
