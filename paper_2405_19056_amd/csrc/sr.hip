@@ -132,7 +132,7 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
 // the next one issues; these are neither, so the compiler issues a group of
 // them before the first store.
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
-constexpr uint32_t kOutside = 0x80000000u;   // past every bound (buffers stay under 2 GiB)
+constexpr uint32_t kOutside = 0x80000000u;   // past every bound (resources stay under 2 GiB)
 __device__ __forceinline__ rsrc_t make_rsrc(const void *base, int64_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0,
                                            (int)std::min<int64_t>(bytes, kOutside), 0x00020000);
@@ -176,12 +176,13 @@ __device__ __forceinline__ void stage(int tid, rsrc_t r, Off off, Dst dst) {
 // zeros and the blend is zero; groups of 4 elements issue their 16 loads
 // before any store.
 struct UpTap {
-  uint32_t o[4];   // source elements within a plane
+  uint32_t o[4];   // source elements within a plane, from its row y0 on
   float fx, fy;
 };
-__device__ __forceinline__ UpTap up_tap(int Y, int X, int h, int w) {
+__device__ __forceinline__ UpTap up_tap(int Y, int X, int y0, int h, int w) {
   const int sy = (Y >> 1) - ((Y & 1) ? 0 : 1), sx = (X >> 1) - ((X & 1) ? 0 : 1);
-  const int ya = max(sy, 0), yb = min(sy + 1, h - 1), xa = max(sx, 0), xb = min(sx + 1, w - 1);
+  const int ya = max(sy, 0) - y0, yb = min(sy + 1, h - 1) - y0;
+  const int xa = max(sx, 0), xb = min(sx + 1, w - 1);
   return {{(uint32_t)(ya * w + xa), (uint32_t)(ya * w + xb), (uint32_t)(yb * w + xa),
            (uint32_t)(yb * w + xb)},
           (X & 1) ? 0.25f : 0.75f,
@@ -333,25 +334,29 @@ __global__ __launch_bounds__(kThreads, 2) void sr_forward_kernel(
   // before the first use
   {
     constexpr int kG = kIn - 3;
-    const rsrc_t rg = make_rsrc(gbuf + (int64_t)f * kG * plane_hi, 4 * kG * plane_hi);
-    const rsrc_t rlo = make_rsrc(lowres + (int64_t)f * 3 * plane_lo, 4 * 3 * plane_lo);
-    const uint32_t pl = 4 * (uint32_t)plane_hi, pl_lo = 4 * (uint32_t)plane_lo;
+    // a resource per plane, over the rows the tile reads: offsets stay small
+    // whatever the frame's size
+    const int y0 = max(oy0 - 2, 0), y1 = min(oy0 + kT + 2, H);
+    const int s0 = max(y0 / 2 - 1, 0), s1 = min((y1 - 1) / 2 + 1, h - 1) + 1;
+    const float *g0 = gbuf + (int64_t)f * kG * plane_hi + (int64_t)y0 * W;
+    const float *lo0 = lowres + (int64_t)f * 3 * plane_lo + (int64_t)s0 * w;
+    const int64_t g_bytes = 4 * (int64_t)(y1 - y0) * W, lo_bytes = 4 * (int64_t)(s1 - s0) * w;
     float gv[2][kG], uv[2][3][4], fx[2], fy[2];
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
       const int P = tid + r * kThreads, Y = oy0 - 2 + P / kE0, X = ox0 - 2 + P % kE0;
       const bool ok = P < kE2 && Y >= 0 && Y < H && X >= 0 && X < W;
-      const uint32_t px = ok ? 4 * ((uint32_t)Y * W + X) : kOutside;
+      const uint32_t px = ok ? 4 * ((uint32_t)(Y - y0) * W + X) : kOutside;
 #pragma unroll
-      for (int c = 0; c < kG; ++c) gv[r][c] = load1(rg, px, c * pl);
-      const UpTap u = up_tap(Y, X, h, w);
+      for (int c = 0; c < kG; ++c) gv[r][c] = load1(make_rsrc(g0 + c * plane_hi, g_bytes), px, 0);
+      const UpTap u = up_tap(Y, X, s0, h, w);
       fx[r] = u.fx;
       fy[r] = u.fy;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const uint32_t o = ok ? 4 * u.o[k] : kOutside;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) uv[r][c][k] = load1(rlo, o, c * pl_lo);
+        for (int c = 0; c < 3; ++c) uv[r][c][k] = load1(make_rsrc(lo0 + c * plane_lo, lo_bytes), o, 0);
       }
     }
 #pragma unroll
