@@ -142,9 +142,12 @@ def _stream(stream):
     torch = _torch()
     if stream is not None:
         return c_void_p(stream.cuda_stream)
-    # the current stream's handle without a Stream object around it: 0.4 us a
-    # call against 3.2, of the 10 that one forward call takes
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    # the current stream's handle without a Stream object around it (0.4 us a call
+    # against 3.2, of the 10 that one forward call takes), where torch has it
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return c_void_p(torch.cuda.current_stream().cuda_stream)
+    return raw(torch.cuda.current_device())
 
 
 def _state_ptr(t):

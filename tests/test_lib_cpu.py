@@ -97,3 +97,15 @@ def test_sr_num_params_agree():
     n = gb.sr_num_params()
     assert n == oracle.sr_n_params() == synth.make_sr_weights(np.random.default_rng(0)).size
     assert n == 14275
+
+
+def test_stream_handle_without_torch_s_private_call(monkeypatch):
+    """The current stream's handle comes from the public interface where torch
+    has no raw one; an explicit stream's always does."""
+    import types
+
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x40))
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert gb._stream(None).value == 0x40
+    assert gb._stream(types.SimpleNamespace(cuda_stream=0x80)).value == 0x80
