@@ -170,16 +170,21 @@ gn_status glassnet_create(const gn_config *cfg, const float *host_weights, size_
   const size_t wbytes = sizeof(float) * np;
   hipError_t e = hipSuccess;
   if (e == hipSuccess) e = hipMalloc((void **)&h->d_master, wbytes);
-  if (e == hipSuccess) e = hipMalloc((void **)&h->d_packed, (size_t)h->pl.total_bytes);
   if (e == hipSuccess) e = hipMalloc((void **)&h->d_l1_partials, sizeof(float) * h->l1_npart);
-  const size_t f32_bytes = cfg->precision == GN_FP32 ? gn_f32_packed_bytes(h->W, cfg->pe_levels) : 0;
-  if (e == hipSuccess && f32_bytes) e = hipMalloc((void **)&h->d_f32, f32_bytes);
+  // the packed weights that the precision's kernels read, and sigma's scratch
   const size_t sig_bytes = gn::mfma_sig_scratch_bytes(h->W, h->num_cus);
-  if (cfg->precision != GN_FP32)
+  size_t form_bytes;
+  if (cfg->precision == GN_FP32) {
+    form_bytes = gn_f32_packed_bytes(h->W, cfg->pe_levels);
+    if (e == hipSuccess) e = hipMalloc((void **)&h->d_f32, form_bytes);
+  } else {
+    form_bytes = (size_t)h->pl.total_bytes + 2 * sig_bytes;
+    if (e == hipSuccess) e = hipMalloc((void **)&h->d_packed, (size_t)h->pl.total_bytes);
+    if (e == hipSuccess) e = hipMemset(h->d_packed, 0, (size_t)h->pl.total_bytes);
     for (int i = 0; i < 2 && e == hipSuccess; ++i)
       e = hipMalloc((void **)&h->d_sig_scratch[i], sig_bytes);
+  }
   if (e == hipSuccess) e = hipMemcpy(h->d_master, host_weights, wbytes, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemset(h->d_packed, 0, (size_t)h->pl.total_bytes);
   if (e != hipSuccess) {
     gn_status st = (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation)
                        ? fail(GN_E_NOMEM, "device allocation failed: %s", hipGetErrorString(e))
@@ -195,8 +200,7 @@ gn_status glassnet_create(const gn_config *cfg, const float *host_weights, size_
       return fail(GN_E_DEVICE, "DSSIM scratch address: %s", hipGetErrorString(e));
     }
   }
-  h->bytes_held = f32_bytes + wbytes + (size_t)h->pl.total_bytes + sizeof(float) * h->l1_npart +
-                  (cfg->precision == GN_FP32 ? 0 : 2 * sig_bytes);
+  h->bytes_held = wbytes + form_bytes + sizeof(float) * h->l1_npart;
   gn_status st = gn_prepare_weights(h, nullptr);
   if (st == GN_OK) {
     e = hipDeviceSynchronize();

@@ -25,8 +25,8 @@ struct gn_handle {
   int num_cus = 0;
   size_t nparams = 0;
   float *d_master = nullptr;      // fp32 master weights (flat layout)
-  uint8_t *d_packed = nullptr;    // fragment-ordered bf16/fp8 weights + biases
-  uint8_t *d_f32 = nullptr;       // fp32 fragments and biases (fwd_fp32.hip)
+  uint8_t *d_packed = nullptr;    // bf16 / fp8_t: fragment-ordered weights + biases
+  uint8_t *d_f32 = nullptr;       // GN_FP32: split fragments and biases (fwd_fp32.hip)
   gn::PackedLayout pl{};
   uint8_t *d_sig_scratch[2] = {nullptr, nullptr};  // MFMA forward: caller streams, serving
   float *d_l1_partials = nullptr;

@@ -484,3 +484,15 @@ def test_fp8_calibration_sets_a_positive_scale_and_rejects_bad_scales():
         net.set_act_scale(0.02)
         with pytest.raises(GlassNetError):
             net.set_act_scale(-1.0)
+
+
+def test_fp32_handle_holds_no_form_that_it_does_not_read():
+    """W = 128: the master weights, 48 stages of 24 KiB of split fragments (four
+    for each of the eleven square maps, one for each of the four narrow ones),
+    the twelve layers' biases and the loss's partial sums (four per CU)."""
+    torch = torch_dev()
+    W = 128
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    n = synth.num_params(W)
+    with GlassNet(None, W, precision="fp32") as net:
+        assert net.workspace_bytes() == 4 * n + 48 * 24576 + 4 * 12 * W + 4 * 4 * cus
