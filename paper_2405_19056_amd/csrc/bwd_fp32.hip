@@ -48,6 +48,7 @@
 
 #include "fp32_core.h"
 #include "gn_api_state.h"
+#include "lds_limit.h"
 
 namespace gn {
 
@@ -1152,11 +1153,10 @@ class Gradient {
 
 template <int W, bool ENC, bool CAL>
 static hipError_t launch_save_form(const SaveArgs &a, int num_cus, hipStream_t s) {
-  static const hipError_t attr =     // per process; the attribute is per function
-      hipFuncSetAttribute((const void *)f32_save_kernel<W, ENC, CAL>,
-                          hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
-  if (attr != hipSuccess) return attr;
   const size_t lds = kRing * kStageBytes + sizeof(float) * kNumLayers * W + (size_t)kTile * a.kpad;
+  static LdsLimit limit;
+  const hipError_t e = limit.raise((const void *)f32_save_kernel<W, ENC, CAL>, lds);
+  if (e != hipSuccess) return e;
   const unsigned grid = (unsigned)std::min<int64_t>(a.pl.np / kTile, 2 * num_cus);
   hipLaunchKernelGGL((f32_save_kernel<W, ENC, CAL>), dim3(grid), dim3(kThreads), lds, s, a);
   return hipGetLastError();
@@ -1210,9 +1210,9 @@ static SaveArgs save_args(gn_handle *h, const gn_frame *frame, const OpTable &t,
 template <int W, int WAVES>
 static hipError_t launch_delta_form(const DeltaArgs &a, int num_cus, hipStream_t s) {
   constexpr int lds = kRing * kSplitStage + WAVES * (W / 16) * 1024;
-  static const hipError_t attr = hipFuncSetAttribute(
-      (const void *)f32_delta_kernel<W, WAVES>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  if (attr != hipSuccess) return attr;
+  static LdsLimit limit;
+  const hipError_t e = limit.raise((const void *)f32_delta_kernel<W, WAVES>, lds);
+  if (e != hipSuccess) return e;
   const unsigned grid = (unsigned)std::min<int64_t>(a.pl.np / (WAVES * 16), num_cus);
   hipLaunchKernelGGL((f32_delta_kernel<W, WAVES>), dim3(grid), dim3(WAVES * 64), lds, s, a);
   return hipGetLastError();

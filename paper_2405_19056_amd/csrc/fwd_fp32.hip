@@ -27,6 +27,7 @@
 
 #include "fp32_core.h"
 #include "gn_api_state.h"
+#include "lds_limit.h"
 
 namespace gn {
 namespace f32 {
@@ -407,10 +408,9 @@ static hipError_t launch_waves(const FwdArgs &a, int num_cus, hipStream_t s) {
   constexpr bool kHead = MODE == M_FULL || MODE == M_FINISH;
   const size_t lds = kRing * kSplitStage + sizeof(float) * kNumLayers * W +
                      (kHead ? (size_t)WAVES * (W / 16) * 1024 : 0) + (size_t)WAVES * 16 * a.kpad;
-  static const hipError_t attr =     // per process; the attribute is per function
-      hipFuncSetAttribute((const void *)f32_forward_kernel<W, MODE, ENC, WAVES>,
-                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  if (attr != hipSuccess) return attr;
+  static LdsLimit limit;
+  const hipError_t e = limit.raise((const void *)f32_forward_kernel<W, MODE, ENC, WAVES>, lds);
+  if (e != hipSuccess) return e;
   const int64_t ntiles = (a.npx + WAVES * 16 - 1) / (WAVES * 16);
   const unsigned grid = (unsigned)std::min<int64_t>(ntiles, num_cus);    // persistent
   hipLaunchKernelGGL((f32_forward_kernel<W, MODE, ENC, WAVES>), dim3(grid), dim3(WAVES * 64), lds, s,

@@ -26,6 +26,7 @@
 // sum_i m_i (A3 a_i + c3) = A3 (sum_i m_i a_i) + (sum_i m_i) c3.  The running
 // sum is fp32 in registers, so memory does not grow with the slot count.
 #include "gn_internal.h"
+#include "lds_limit.h"
 #include "slot_order.h"
 
 namespace gn {
@@ -1510,20 +1511,14 @@ static size_t mfma_dynamic_lds(const PackedLayout &pl, int order_bytes, int nt, 
 
 template <int W, int PREC, int MODE, int PE, int NT>
 static hipError_t launch_one(const MfmaArgs &a, int grid, size_t lds, hipStream_t stream) {
-  // The attribute is per function; a layout of a different size (another
-  // handle's) raises it again.
-  static size_t attr_lds = 0;
   using LM = LdsMap<W, PREC, PE>;
   constexpr size_t fixed = LM::kRes + Shape<W>::kBiasBytes +
                            (all_resident<W, MODE, PE>() ? LM::kAll + 16 : 2 * LM::kStage);
   if (a.res_bytes != LM::kRes || a.stage_max != LM::kStage || lds + fixed > 160 * 1024)
     return hipErrorInvalidValue;
-  if (lds > attr_lds) {
-    hipError_t e = hipFuncSetAttribute((const void *)fwd_mfma_kernel<W, PREC, MODE, PE, NT>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    attr_lds = lds;
-  }
+  static LdsLimit limit;
+  const hipError_t e = limit.raise((const void *)fwd_mfma_kernel<W, PREC, MODE, PE, NT>, lds);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((fwd_mfma_kernel<W, PREC, MODE, PE, NT>), dim3(grid), dim3(kThreads), lds,
                      stream, a);
   return hipGetLastError();

@@ -44,6 +44,7 @@
 #include <type_traits>
 
 #include "gn_internal.h"
+#include "lds_limit.h"
 
 namespace gn {
 namespace {
@@ -808,14 +809,10 @@ hipError_t spatial_pack(const float *master, int W, uint8_t *packed, hipStream_t
 
 template <int MT>
 static hipError_t sp_slots_launch(const SpSlotsArgs &a, hipStream_t s) {
-  static bool attr = false;
   const size_t lds = (size_t)(kSlotSteps1 + MT) * MT * kFrag + 2 * 16 * MT * sizeof(float);
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void *)sp_slots_kernel<MT>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static LdsLimit limit;
+  const hipError_t e = limit.raise((const void *)sp_slots_kernel<MT>, lds);
+  if (e != hipSuccess) return e;
   const int64_t nseg = (int64_t)a.n * a.H * ((a.Wd + 15) / 16);
   const int64_t ntiles = (nseg + kWaves - 1) / kWaves;
   // persistent: one workgroup per CU (the weights fill most of its LDS), a
@@ -828,10 +825,10 @@ static hipError_t sp_slots_launch(const SpSlotsArgs &a, hipStream_t s) {
 template <int MT, int TR, int CB0, int SRC1, int CB1, bool PLANES, int EPI>
 static hipError_t sp_launch(const SpConvArgs &a, hipStream_t s) {
   constexpr int lds = ConvLds<MT, TR, CB0, SRC1, CB1>::kBytes;
-  static const hipError_t attr =
-      hipFuncSetAttribute((const void *)sp_conv_kernel<MT, TR, CB0, SRC1, CB1, PLANES, EPI>,
-                          hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  if (attr != hipSuccess) return attr;
+  static LdsLimit limit;
+  const hipError_t e =
+      limit.raise((const void *)sp_conv_kernel<MT, TR, CB0, SRC1, CB1, PLANES, EPI>, lds);
+  if (e != hipSuccess) return e;
   const int64_t tiles = (int64_t)a.n * ((a.H + TR - 1) / TR) * ((a.Wd + kTC - 1) / kTC);
   hipLaunchKernelGGL((sp_conv_kernel<MT, TR, CB0, SRC1, CB1, PLANES, EPI>), dim3((unsigned)tiles),
                      dim3(kConvThreads), lds, s, a);
