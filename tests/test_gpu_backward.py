@@ -363,3 +363,18 @@ def test_backward_in_slabs_matches_oracle(W, k):
     with GlassNet(wts, W, k_max=k, precision="fp32") as net:
         worst = check(gpu_grad(net, fr, dy), ref, W)
     log(f"  backward in slabs W={W} k={k}: worst per-tensor relF {worst:.3e}")
+
+
+@pytest.mark.parametrize("W", [64, 128])
+@pytest.mark.parametrize("h,w_", [(131, 127), (129, 255)])
+def test_backward_at_eight_wave_tile_edges(W, h, w_):
+    """16,637 and 32,895 pixels: just past 64 and 128 for each of 256 CUs, where
+    the deltas' workgroups have eight waves, the last of them a remainder,
+    and some take a second tile."""
+    wts, fr, s = frame(1, h, w_, 3, W, seed=h)
+    dy = s["noise"].normal(size=(1, 3, h, w_)).astype(np.float32)
+    dy *= kink_free(wts, W, fr, "mean")[:, None]
+    ref = oracle.grad_from_dy(wts, W, fr.gbuf, fr.layers, fr.scene, dy, pool="mean")
+    with GlassNet(wts, W, k_max=4, precision="fp32") as net:
+        worst = check(gpu_grad(net, fr, dy), ref, W)
+    log(f"  backward {h}x{w_} W={W}: worst per-tensor relF {worst:.3e}")

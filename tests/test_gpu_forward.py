@@ -496,3 +496,17 @@ def test_fp32_handle_holds_no_form_that_it_does_not_read():
     n = synth.num_params(W)
     with GlassNet(None, W, precision="fp32") as net:
         assert net.workspace_bytes() == 4 * n + 48 * 24576 + 4 * 12 * W + 4 * 4 * cus
+
+
+@pytest.mark.parametrize("W", [64, 128])
+@pytest.mark.parametrize("pe", [0, 1])
+@pytest.mark.parametrize("h,w_", [(131, 127), (129, 255)])
+def test_fp32_at_eight_wave_tile_edges(W, pe, h, w_):
+    """16,637 and 32,895 pixels: just past 64 and 128 for each of 256 CUs, where
+    the fp32 forward's workgroups have eight waves, the last of them a
+    remainder, and some take a second tile."""
+    _, fr = frame(1, h, w_, 3, W, seed=h)
+    wts = synth.make_weights(W, np.random.default_rng(h), pe)
+    ref = oracle.forward(wts, W, fr.gbuf, fr.layers, fr.scene, pool="mean", pe_levels=pe)
+    with GlassNet(wts, W, k_max=3, precision="fp32", pe_levels=pe) as net:
+        gate(run(net, fr), ref, TOL["fp32"], f"fp32 {h}x{w_} W={W} pe={pe}")
