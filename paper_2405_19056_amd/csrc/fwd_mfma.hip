@@ -66,6 +66,7 @@ struct MfmaArgs {
                                        // last t in the stage buffers' idle tails
   uint8_t *state;                      // object streaming: per-tile state (modes other than FULL)
   int state_load;                      // 1: the state holds a running sum to continue from
+  int dense;                           // 1: the state's layout for few tiles (StreamTile)
   int canon;                           // FULL: pool each pixel's slots in canonical order
   int kpad;                            // bytes per pixel of the LDS slot-order table
   int aslots;                          // slots whose alphas the LDS alpha table holds
@@ -385,14 +386,22 @@ struct LdsMap {
 template <int W, int MODE, int PE>
 constexpr bool all_resident() { return W == 64 && MODE == FWD_FULL && PE == 0; }
 
-// Object-streaming state of one tile (modes other than FWD_FULL), pixel by
-// pixel: sigma as bf16 B fragments [pixel][ks][g], the running masked sum Z of
-// h's hidden layer as fp32 accumulator rows [pixel][mt][g] (16-byte lane vectors
-// each), the active-slot count [pixel].  What bounds the accumulate calls is
-// this state's traffic, and with a pixel's values side by side the pixels an
-// object does not cover move none of it (512^2, W = 128, half of the pixels
-// covered: 35 us a call, 54 when all of it moved).  A pixel whose count is zero
-// has no valid Z: nobody reads it.
+// Object-streaming state of one tile (modes other than FWD_FULL): sigma as bf16 B
+// fragments, the running masked sum Z of h's hidden layer as fp32 accumulator rows
+// (16-byte lane vectors each), the active-slot count [pixel].
+//
+// Where there are many tiles, pixel by pixel: sigma [pixel][ks][g], Z [pixel][mt]
+// [g].  What bounds the accumulate calls is this state's traffic, and with a
+// pixel's values side by side the pixels an object does not cover move none of
+// it (512^2, W = 128, half of the pixels covered: 35 us a call, 54 when all of it
+// moved).  A pixel whose count is zero has no valid Z: nobody reads it.
+//
+// Where there are few, at most nine for 16 CUs (dense), 16 pixels at a time: sigma
+// [16 pixels][ks][g][pixel], Z [16 pixels][mt][g][pixel], all of it moved.  A call
+// is then one chain of latencies, shorter by the wait for the alphas, and an
+// instruction's lanes read 1 KiB in one piece instead of 64 bytes from each of
+// 16 pixels.  A frame of 8 objects, one a call: 64^2 88 -> 78 us, 128^2 93 -> 86,
+// 176^2 102 -> 100; 192^2 105 either way; 224^2 114 -> 123.
 template <int W>
 struct StreamTile {
   static constexpr int64_t kSig = (int64_t)kTilePx * W * 2;
@@ -405,12 +414,13 @@ struct StreamTile {
 // whose offset lies outside it loads zeros and stores nothing.
 constexpr int kOutside = 0x40000000;
 
-__device__ __forceinline__ u32x4 state_load16(__amdgpu_buffer_rsrc_t r, int off) {
-  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+// (off: the lane's first vector; at: the uniform offset of the one meant)
+__device__ __forceinline__ u32x4 state_load16(__amdgpu_buffer_rsrc_t r, int off, int at) {
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, at, 0));
 }
 
-__device__ __forceinline__ void state_store16(__amdgpu_buffer_rsrc_t r, int off, u32x4 v) {
-  __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, 0);
+__device__ __forceinline__ void state_store16(__amdgpu_buffer_rsrc_t r, int off, int at, u32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, r, off, at, 0);
 }
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -614,8 +624,14 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
                                              (int)ST::kBytes, 0x00020000);
   };
   auto st_px = [&](int ln, int t) { return wave * (kNT * 16) + t * 16 + (ln & 15); };
-  auto st_sig = [&](int ln, int t) { return st_px(ln, t) * (W * 2) + (ln >> 4) * 16; };
-  auto st_z = [&](int ln, int t) { return (int)ST::kSig + st_px(ln, t) * (W * 4) + (ln >> 4) * 16; };
+  const bool dense = MODE != FWD_FULL && a.dense;
+  const int st_next = dense ? kFrag : 64;            // from a lane's vector to its next
+  auto st_lane = [&](int ln, int t, int px_bytes) {
+    return (wave * kNT + t) * 16 * px_bytes + (ln & 15) * (dense ? 16 : px_bytes) +
+           (ln >> 4) * (dense ? 256 : 16);
+  };
+  auto st_sig = [&](int ln, int t) { return st_lane(ln, t, W * 2); };
+  auto st_z = [&](int ln, int t) { return (int)ST::kSig + st_lane(ln, t, W * 4); };
   auto st_cnt = [&](int ln, int t) { return (int)(ST::kSig + ST::kZ) + st_px(ln, t) * 4; };
   auto load_cnt = [&](int tile, int ln, float (&c)[kNT]) {
     const auto r = st_rsrc(tile);
@@ -636,14 +652,15 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
         al[t] = fmaxf(al[t], ti.L[((size_t)j * kNL + kAlpha) * ti.hw + q]);
     }
   };
-  // FINISH: the running sum of the pixels that have one
+  // FINISH: the running sum of the pixels that have one (dense: of all)
   auto load_z = [&](int tile, int ln, const float (&c)[kNT], f32x4 (&z)[kNT][MT]) {
     const auto r = st_rsrc(tile);
 #pragma unroll
     for (int t = 0; t < kNT; ++t) {
-      const int off = c[t] > 0.0f ? st_z(ln, t) : kOutside;
+      const int off = (dense ? a.state_load != 0 : c[t] > 0.0f) ? st_z(ln, t) : kOutside;
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) z[t][mt] = __builtin_bit_cast(f32x4, state_load16(r, off + mt * 64));
+      for (int mt = 0; mt < MT; ++mt)
+        z[t][mt] = __builtin_bit_cast(f32x4, state_load16(r, off, mt * st_next));
     }
   };
   float xr[kNT][8];
@@ -653,7 +670,8 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
   if ((int)blockIdx.x < a.ntiles) {
     nti = resolve(blockIdx.x);
     if constexpr (kTrunk) load_x(nti, lane0, xr);
-    if constexpr (MODE == FWD_ACC) load_alpha(nti, lane0, nal);
+    if constexpr (MODE == FWD_ACC)
+      if (!dense) load_alpha(nti, lane0, nal);
     if constexpr (MODE == FWD_ACC || MODE == FWD_FINISH) load_cnt(blockIdx.x, lane0, ncnt);
     if constexpr (MODE == FWD_FINISH) load_z(blockIdx.x, lane0, ncnt, nz);
   }
@@ -692,18 +710,18 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
       bool any = false;
 #pragma unroll
       for (int t = 0; t < kNT; ++t) {
-        touched[t] = nal[t] > 0.0f;
+        touched[t] = dense || nal[t] > 0.0f;
         cnt[t] = ncnt[t];
         any = any || touched[t];
       }
       if (has_next) {
         nti = resolve(tile + gridDim.x);
-        load_alpha(nti, lane, nal);
+        if (!dense) load_alpha(nti, lane, nal);
         load_cnt(tile + gridDim.x, lane, ncnt);
       }
       // no pixel of this wave's part takes part: only a first call's counts
       // are left to write
-      if (__builtin_amdgcn_ballot_w64(any) == 0) {
+      if (!dense && __builtin_amdgcn_ballot_w64(any) == 0) {
         if (!a.state_load && g == 0) {
           const auto sr = st_rsrc(tile);
 #pragma unroll
@@ -889,7 +907,7 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
 #pragma unroll
         for (int t = 0; t < kNT; ++t)
 #pragma unroll
-          for (int k = 0; k < KS; ++k) state_store16(sr, st_sig(lane, t) + k * 64, sig[t][k]);
+          for (int k = 0; k < KS; ++k) state_store16(sr, st_sig(lane, t), k * st_next, sig[t][k]);
         if constexpr (PE > 0) {
           // the next tile's first stage has landed; this stage's buffer is free
           next_stage();
@@ -927,14 +945,15 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
         for (int t = 0; t < kNT; ++t) {
           const int off = touched[t] ? st_sig(lane, t) : kOutside;
 #pragma unroll
-          for (int k = 0; k < KS; ++k) sig[t][k] = state_load16(sr, off + k * 64);
+          for (int k = 0; k < KS; ++k) sig[t][k] = state_load16(sr, off, k * st_next);
         }
 #pragma unroll
         for (int t = 0; t < kNT; ++t) {
-          const int off = touched[t] && cnt[t] > 0.0f ? st_z(lane, t) : kOutside;
+          const bool has = dense ? a.state_load != 0 : touched[t] && cnt[t] > 0.0f;
+          const int off = has ? st_z(lane, t) : kOutside;
 #pragma unroll
           for (int mt = 0; mt < MT; ++mt)
-            Z[t][mt] = __builtin_bit_cast(f32x4, state_load16(sr, off + mt * 64));
+            Z[t][mt] = __builtin_bit_cast(f32x4, state_load16(sr, off, mt * st_next));
         }
       }
       {
@@ -1170,7 +1189,7 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
           const int off = touched[t] ? st_z(lane, t) : kOutside;
 #pragma unroll
           for (int mt = 0; mt < MT; ++mt)
-            state_store16(sr, off + mt * 64, __builtin_bit_cast(u32x4, Z[t][mt]));
+            state_store16(sr, off, mt * st_next, __builtin_bit_cast(u32x4, Z[t][mt]));
           __builtin_amdgcn_raw_buffer_store_b32(
               __builtin_bit_cast(uint32_t, cnt[t]), sr,
               g == 0 && (touched[t] || !a.state_load) ? st_cnt(lane, t) : kOutside, 0, 0);
@@ -1193,7 +1212,7 @@ __global__ __launch_bounds__(kThreads) void fwd_mfma_kernel(MfmaArgs a) {
 #pragma unroll
           for (int mt = 0; mt < MT; ++mt) Z[t][mt] = nz[t][mt];
 #pragma unroll
-          for (int k = 0; k < KS; ++k) sig2[t][k] = state_load16(sr, st_sig(lane, t) + k * 64);
+          for (int k = 0; k < KS; ++k) sig2[t][k] = state_load16(sr, st_sig(lane, t), k * st_next);
         }
       } else if (sig_in_lds) {
 #pragma unroll
@@ -1575,6 +1594,7 @@ static hipError_t launch_impl(int W, int precision, int pool, const uint8_t *pac
   a.sig_scratch = sig_scratch;
   a.state = state;
   a.state_load = state_load;
+  a.dense = mode != FWD_FULL && 16 * ntiles <= 9 * grid;
   // canonical order: a table of slot_kmax bytes per pixel, rounded up to 4
   a.canon = slot_kmax > 1 ? 1 : 0;
   a.kpad = a.canon ? (slot_kmax + 3) / 4 * 4 : 0;

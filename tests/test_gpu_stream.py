@@ -227,3 +227,29 @@ def test_full_512sq_k8_one_object_per_call(precision):
         y_ref = fused(net, fr)
         y, _ = streamed(net, fr, [1] * 8)
     assert np.array_equal(y, y_ref)
+
+
+@pytest.mark.parametrize("precision,W", [("bf16", 128), ("bf16", 64), ("fp8_t", 128)])
+@pytest.mark.parametrize("h,w_", [(192, 192), (193, 192), (262, 271)])
+def test_partly_covered_frames_of_few_and_many_tiles(precision, W, h, w_):
+    """144 tiles (nine for 16 of 256 CUs: the state kept 16 pixels at a time), 145,
+    and 278 (some workgroups take two); state memory that held NaN, objects that
+    cover nothing, stripes and a rectangle, a result after every call."""
+    torch = torch_dev()
+    log(f"stream {precision} W={W} {h}x{w_} in parts")
+    wts, fr = frame(1, h, w_, 4, W, seed=h)
+    alpha = np.zeros((4, h, w_), np.float32)
+    alpha[1].reshape(-1)[::3] = 0.5
+    alpha[2, h // 4:h - 40, 30:w_ - 50] = 0.25
+    alpha[3, :, : w_ // 2] = 1.0
+    fr.layers[0, :, 9] = alpha
+    with open_net(wts, W, precision) as net:
+        g, sc = dev(fr.gbuf), dev(fr.scene)
+        st = net.stream_state(1, h, w_)
+        st[: st.numel() // 4 * 4].view(torch.float32).fill_(float("nan"))
+        net.stream_begin(g, sc, st)
+        np.testing.assert_array_equal(host(net.stream_finish(g, st)), fused(net, fr, k=0))
+        for first, last in ((0, 1), (1, 2), (2, 4)):
+            net.stream_accumulate(dev(fr.layers[:, first:last]), st)
+            np.testing.assert_array_equal(host(net.stream_finish(g, st)), fused(net, fr, k=last))
+        net.stream_release(st)
