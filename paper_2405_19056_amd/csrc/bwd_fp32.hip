@@ -45,6 +45,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "fp32_core.h"
 #include "gn_api_state.h"
@@ -591,7 +592,7 @@ struct DeltaArgs {
 //
 // What bounds it: HBM and the matrix cores in turn.  16 x 128^2, K = 4, W = 128:
 // 2.0 GB of deltas written (390 us at the copy rate) and 340 us of matrix-core
-// work take 909 us (864 with the K-steps in one chain, whose gradient is 2 to
+// work take 855 us (837 with the K-steps in one chain, whose gradient is 2 to
 // 15 times further from 64 bits); on the fp32 instruction, with 900 us of such
 // work, 1132.
 template <int W, int WAVES>
@@ -758,8 +759,11 @@ constexpr int part_floats(int W, int MI) { return W * 16 * MI + W + 16 * MI; }
 // 16-byte unit c at c ^ swz(p), so that the four pixels that the lane groups
 // read fall into distinct banks.  A step is one 32-deep group of the bf16 matrix
 // cores on operands split in three (fp32_core.h), summed by itself before it is
-// added (16 x 128^2, K = 4, W = 128: 945 us a square product's launch, 907 in one
-// chain), a workgroup's with the sign of its place, as the deltas are.
+// added, a workgroup's with the sign of its place, as the deltas are.  The plain
+// split is used, and the values are watched as they are stored: a segment with
+// one that it does not take is run again with the wide one (16 x 128^2, K = 4,
+// W = 128, the square products' launch: 983 us with the wide split throughout,
+// 910 as it is; 890 with the K-steps in one chain).
 template <int W, int MI>
 __global__ __launch_bounds__(kThreads, 2) void f32_dw_kernel(DwArgs a) {
   constexpr int MO = W / 16;
@@ -771,6 +775,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dw_kernel(DwArgs a) {
   constexpr int NA = (kStep * AU + kThreads - 1) / kThreads;
   __shared__ f32x4 ld[2][kStep * DU], la[2][kStep * AU];
   __shared__ float lw[2][kStep];
+  __shared__ int l_wide;             // some value of the segment needs the wide split
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, l = lane & 15;
   const int wr = wave / WC, wc = wave % WC;
   const float sign = sign_of(blockIdx.x);
@@ -814,6 +819,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dw_kernel(DwArgs a) {
       if (job.wgt && tid < kStep) hw = job.wgt[px + tid];
     };
     auto store = [&](int b) {
+      float sum = 0.0f;
 #pragma unroll
       for (int i = 0; i < ND; ++i) {
         const int e = tid + i * kThreads, p = e / DU, u = e % DU;
@@ -822,68 +828,83 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dw_kernel(DwArgs a) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) v[r] = hm[i] & (1u << r) ? v[r] : 0.0f;
         }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sum = watch(v[r], sum);
         ld[b][p * DU + (u ^ dswz(p))] = v;
       }
 #pragma unroll
       for (int i = 0; i < NA; ++i) {
         const int e = tid + i * kThreads, p = e / AU, u = e % AU;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sum = watch(ha[i][r], sum);
         if (kStep * AU % kThreads == 0 || e < kStep * AU)
           la[b][p * AU + (u ^ aswz(p))] = sign * ha[i];
       }
       if (tid < kStep) lw[b][tid] = hw;
+      if (found(sum)) l_wide = 1;
     };
     f32x4 acc[TO][TI];
     float dsum[TO], asum[TI];
-#pragma unroll
-    for (int o = 0; o < TO; ++o) {
-      dsum[o] = 0.0f;
-#pragma unroll
-      for (int i = 0; i < TI; ++i) acc[o][i] = zero4();
-    }
-#pragma unroll
-    for (int i = 0; i < TI; ++i) asum[i] = 0.0f;
-    // both buffers are free: every wave is past the last segment's reads
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    load(s0);
-    store(0);
-    load(s0 + 1);
-    for (int64_t s = s0; s < s1; ++s) {
-      const int b = (int)(s - s0) & 1;
-      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-      store(b ^ 1);
-      load(s + 2);
-      __builtin_amdgcn_sched_barrier(0);
-      const float *D = (const float *)ld[b], *A = (const float *)la[b];
-      // a lane's eight pixels of a row: 4 t + g (dswz(p) = 4 g for each)
-      float w8[8];
-#pragma unroll
-      for (int t = 0; t < 8; ++t) w8[t] = lw[b][4 * t + g];
-      Split d[TO];
+    auto segment = [&](auto wide) {
+      constexpr bool kWide = decltype(wide)::value;
 #pragma unroll
       for (int o = 0; o < TO; ++o) {
-        float v[8];
+        dsum[o] = 0.0f;
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const int p = 4 * t + g;
-          v[t] = D[p * W + ((4 * (wr * TO + o)) ^ dswz(p)) * 4 + l];
-          if (wc == 0) dsum[o] = fmaf(v[t], w8[t], dsum[o]);
-        }
-        d[o] = split8(v);
+        for (int i = 0; i < TI; ++i) acc[o][i] = zero4();
       }
 #pragma unroll
-      for (int i = 0; i < TI; ++i) {
-        float v[8];
+      for (int i = 0; i < TI; ++i) asum[i] = 0.0f;
+      // both buffers are free: every wave is past the last run's reads
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      load(s0);
+      store(0);
+      load(s0 + 1);
+      for (int64_t s = s0; s < s1; ++s) {
+        const int b = (int)(s - s0) & 1;
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        store(b ^ 1);
+        load(s + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        const float *D = (const float *)ld[b], *A = (const float *)la[b];
+        // a lane's eight pixels of a row: 4 t + g (dswz(p) = 4 g for each)
+        float w8[8];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const int p = 4 * t + g;
-          v[t] = A[p * 16 * MI + ((4 * (wc * TI + i)) ^ aswz(p)) * 4 + l];
-          if (!kSquare) asum[i] += v[t];
+        for (int t = 0; t < 8; ++t) w8[t] = lw[b][4 * t + g];
+        Split d[TO];
+#pragma unroll
+        for (int o = 0; o < TO; ++o) {
+          float v[8];
+#pragma unroll
+          for (int t = 0; t < 8; ++t) {
+            const int p = 4 * t + g;
+            v[t] = D[p * W + ((4 * (wr * TO + o)) ^ dswz(p)) * 4 + l];
+            if (wc == 0) dsum[o] = fmaf(v[t], w8[t], dsum[o]);
+          }
+          d[o] = split8<kWide>(v);
         }
-        const Split x = split8(v);
 #pragma unroll
-        for (int o = 0; o < TO; ++o) acc[o][i] += mma_split(d[o], x, zero4());
+        for (int i = 0; i < TI; ++i) {
+          float v[8];
+#pragma unroll
+          for (int t = 0; t < 8; ++t) {
+            const int p = 4 * t + g;
+            v[t] = A[p * 16 * MI + ((4 * (wc * TI + i)) ^ aswz(p)) * 4 + l];
+            if (!kSquare) asum[i] += v[t];
+          }
+          const Split x = split8<kWide>(v);
+#pragma unroll
+          for (int o = 0; o < TO; ++o) acc[o][i] += mma_split(d[o], x, zero4());
+        }
       }
-    }
+    };
+    // Set back before the run's first barrier: no wave sets it before that, and
+    // where it is set, every wave has read it before the second run's first.
+    if (tid == 0) l_wide = 0;
+    segment(std::false_type());
+    // again from the start where a value asks for it
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (__builtin_amdgcn_readfirstlane(l_wide)) segment(std::true_type());
     float *P = a.part + (size_t)(blockIdx.x + j) * part_floats(W, MI);
     auto put = [&](float *dst, float v) { *dst = a.accumulate ? *dst + v : v; };
 #pragma unroll

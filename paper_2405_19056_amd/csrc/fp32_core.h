@@ -49,20 +49,28 @@ __device__ __forceinline__ float part(float x) {
   return __builtin_amdgcn_fmed3f(x, -kMost, kMost);
 }
 
+// WIDE: any values; else none that watch() would find.
+template <bool WIDE = true>
 __device__ __forceinline__ Split split8(const float (&x)[8]) {
   Split s;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const float a = x[2 * i], b = x[2 * i + 1];
-    const uint32_t h = pk_bf16(part<true>(a), part<true>(b));
+    const uint32_t h = WIDE ? pk_bf16(part<true>(a), part<true>(b)) : pk_bf16(a, b);
     const float ra = a - bf16_lo(h), rb = b - bf16_hi(h);
-    const uint32_t m = pk_bf16(part<false>(ra), part<false>(rb));
+    const uint32_t m = WIDE ? pk_bf16(part<false>(ra), part<false>(rb)) : pk_bf16(ra, rb);
     s.hi[i] = h;
     s.mid[i] = m;
     s.lo[i] = pk_bf16(ra - bf16_lo(m), rb - bf16_hi(m));
   }
   return s;
 }
+
+// Whether values need the WIDE split, for many of them together (one operation
+// a value against the clamps' two): the running sum of 4 x stays finite unless
+// some are infinite, NaN or beyond 2^126, or add up to that.
+__device__ __forceinline__ float watch(float x, float sum) { return fmaf(x, 4.0f, sum); }
+__device__ __forceinline__ bool found(float sum) { return !(fabsf(sum) < __builtin_inff()); }
 
 __device__ __forceinline__ f32x4 mma_bf16(u32x4 a, u32x4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
@@ -231,6 +239,18 @@ struct SplitPipe {
   template <class X>
   __device__ __forceinline__ void stage(f32x4 (&acc)[MT], int s0, int steps, X x) {
     constexpr int kPer = MT / 2;                 // tile pairs per K-step
+    f32x4 late[2];                               // FRESH: the sums of the pair before
+    // adds them while the next pair's MFMAs run (pinned: left to itself the
+    // compiler keeps all sums and adds them at the map's end)
+    auto add = [&](int i) {
+      if (s0 + i / kPer >= steps) return;
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        f32x4 &c = acc[2 * (i % kPer) + m];
+        c = s0 + i / kPer > 0 ? c + late[m] : late[m];
+        asm volatile("" : "+v"(c));
+      }
+    };
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int m0 = 2 * (i % kPer);
@@ -238,10 +258,12 @@ struct SplitPipe {
       if (i < 3) fetch(w[(i + 1) & 1], cur, i + 1);
       else fetch(w[0], after(cur), 0);
       __builtin_amdgcn_sched_barrier(0);
+      f32x4 sum[2];
       if (s0 + i / kPer < steps) {
         const Split &b = x(i / kPer);
         const u32x4(&a)[6] = w[i & 1];
-        f32x4 sum[2] = {FRESH ? zero4() : acc[m0], FRESH ? zero4() : acc[m0 + 1]};
+#pragma unroll
+        for (int m = 0; m < 2; ++m) sum[m] = FRESH ? zero4() : acc[m0 + m];
         // small partial products first, the two tiles in turn
 #pragma unroll
         for (int p = 0; p < 6; ++p) {
@@ -250,15 +272,19 @@ struct SplitPipe {
 #pragma unroll
           for (int m = 0; m < 2; ++m) sum[m] = mma_bf16(a[3 * m + kA[p]], bv, sum[m]);
         }
+        if constexpr (!FRESH) {
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
-          acc[m0 + m] = FRESH && s0 + i / kPer > 0 ? acc[m0 + m] + sum[m] : sum[m];
-          // (here: left to itself the compiler keeps the sums and adds them at the map's end)
-          if constexpr (FRESH) asm volatile("" : "+v"(acc[m0 + m]));
+          for (int m = 0; m < 2; ++m) acc[m0 + m] = sum[m];
         }
+      }
+      if constexpr (FRESH) {
+        if (i > 0) add(i - 1);
+#pragma unroll
+        for (int m = 0; m < 2; ++m) late[m] = sum[m];
       }
       __builtin_amdgcn_sched_barrier(0);
     }
+    if constexpr (FRESH) add(3);
     cur = after(cur);
   }
   // A map over W inputs, in[s] K-step s.
