@@ -213,7 +213,11 @@ gn_status glassnet_forward(gn_handle *h, const gn_frame *frame, float *out, void
  * The library keeps a workspace between calls that does not grow with k past
  * four slots: what those take for the call's pixels, or for 32,768 of them if
  * it has fewer (15.5 KB per pixel at W = 128, 8.1 KB at 64, without encoding),
- * at most 16 GiB, and 62 MB of partial sums (31 MB). */
+ * at most 16 GiB, and 62 MB of partial sums (31 MB).  Calls of one handle share
+ * it: calls on different streams must be ordered by the caller.
+ * The recompute sums in another order than the GN_FP32 forward: a
+ * pre-activation within rounding of zero may take the other side of its ReLU
+ * than it took there. */
 gn_status glassnet_backward(gn_handle *h, const gn_frame *frame, const float *grad_out,
                             float *grad_w, void *hip_stream);
 
@@ -285,7 +289,7 @@ gn_status glassnet_adam_step(gn_handle *h, const float *grad_w, float *state, si
  *   gbuf_hi  device [n][14][2 height][2 width], channels as in gn_frame.
  *   out      device [n][3][2 height][2 width]; must not overlap the inputs.
  * Independent of the handle's width and precision: the handle supplies the
- * device and a 97 KB copy of sr_w re-laid for the kernels (allocated on the
+ * device and a 202 KB copy of sr_w re-laid for the kernels (allocated on the
  * first call), which calls on different streams share: order them.
  * GN_E_INVAL for n outside 1..65535, height or width outside 1..2^18, NULL or
  * misaligned pointers, or out overlapping an input. */
@@ -382,8 +386,10 @@ gn_status glassnet_workspace_bytes(gn_handle *h, uint64_t *bytes);
  * hidden layer and the active-slot count, in a layout private to the library
  * (GN_BF16 / GN_FP8_T: sigma in bf16, 772 bytes per pixel at W = 128, 388 at
  * W = 64; GN_FP32: sigma, the running sum and the count in fp32, (2 W + 1) x
- * 4 bytes per pixel, with the FP32 forward's pixel limit).  Pixels that an
- * object does not cover are neither read nor written by its accumulate call.
+ * 4 bytes per pixel, with the FP32 forward's pixel limit).  An accumulate call
+ * of GN_BF16 / GN_FP8_T on a frame of many tiles neither reads nor writes sigma
+ * and the sum of a pixel that its objects do not cover; small frames, GN_FP32
+ * and the counts are moved whole.
  * Calls on one state are ordered on the hip_stream each passes; calls on
  * different streams must be ordered by the caller. */
 gn_status glassnet_stream_state_bytes(gn_handle *h, int32_t n, int32_t hgt, int32_t wid,
