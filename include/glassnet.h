@@ -61,7 +61,8 @@ typedef int32_t gn_status;
  *   GN_FP32    fp32 weights and activations: one fused kernel on the bf16
  *              matrix cores, every operand split in three bf16 parts (fp32
  *              products and sums to within fp32's own rounding), without a
- *              workspace.
+ *              workspace.  Infinities give what fp32 products give, where the
+ *              values that they meet are at most 256 in magnitude.
  *   GN_BF16    bf16 weights/activations on MFMA, fp32 accumulation, fp32 pool.
  *   GN_FP8_T   the per-slot hidden layer of h in FP8-E4M3 (per-output-channel
  *              fp32 weight scales, static activation scale), the rest as GN_BF16.
