@@ -19,8 +19,8 @@
 // Then one fixed-order reduction of the workgroups' partial sums into grad_w
 // (deterministic, no atomics).
 //
-// Slabs bound the workspace (plane_bytes): it does not depend on the number of
-// slots, whose activations are recomputed for a slab at a time.
+// Slabs bound the workspace (most_plane_bytes): it does not grow with the number
+// of slots past four; their activations are recomputed for a slab at a time.
 //
 // Formulation of the recompute (the deltas' weights: SplitPipe of fp32_core.h).
 // A wave owns 16 pixels.  Every map is D = A X with a 16-row

@@ -192,10 +192,10 @@ struct ConvLds {
 // What bounds it: at W = 128 and 8 rows a wave's K-step is 16 MFMAs (256
 // cycles) for 4 KiB of LDS reads and 4 KiB of weights, 64 bytes of each per
 // cycle and CU: half the LDS rate, the whole of L1's.  Two workgroups share a
-// CU (one, in B's first layer at W = 128: 90 KiB of LDS); a 256^2 frame is one round of them, so a launch's halo loads and
-// epilogues (about half of its 19 us) overlap little.  256^2, W -> W: 19-24 us
-// against 35-40 with inputs read nine times through L2; the whole forward
-// (K = 4) 248 us against 470.
+// CU (one, in B's first layer at W = 128: 90 KiB of LDS); a 256^2 frame is one
+// round of them, so a launch's halo loads and epilogues (about half of its 19 us)
+// overlap little.  256^2, W -> W: 19-24 us against 35-40 with inputs read nine
+// times through L2; the whole forward (K = 4) 258 us against 470.
 template <int MT, int TR, int CB0, int SRC1, int CB1, bool PLANES, int EPI>
 __global__ __launch_bounds__(kConvThreads, 2) void sp_conv_kernel(SpConvArgs a) {
   constexpr int MW = MT / 2, NT = TR / 2;               // a wave's tiles

@@ -141,6 +141,35 @@ def test_backward_of_an_infinite_loss_gradient(W, value):
     assert err <= 1e-5
 
 
+@pytest.mark.parametrize("W", [64, 128])
+@pytest.mark.parametrize("h,w", [(2, 5), (24, 40)])
+def test_backward_of_the_largest_finite_deltas(W, h, w):
+    """dL/dy of one pixel, R's last layer +-1, scaled by the power of two that takes
+    the gradient's largest entry just below 2^128: with deltas from 2^126 on (a
+    bias's gradient is that pixel's delta) the weight gradients take the split
+    with clamps.  Every rounding commutes with the factor: all bits are the same."""
+    torch = torch_dev()
+    wts, g, L, s = frame(W)
+    # (small inputs: no entry is much larger than the deltas)
+    g, L, s = (0.25 * t for t in (g[..., :h, :w], L[..., :h, :w], s))
+    last = wts.size - 3 * W - 3
+    wts[last:-3] = np.sign(wts[last:-3])
+    dy = torch.zeros((1, 3, h, w), device="cuda:0")
+    dy[0, 1, 1, 3] = 1.0
+    with GlassNet(wts, W, k_max=K, precision="fp32") as net:
+        one = net.backward(g, L, s, dy)
+        factor = 2.0 ** int(127.9 - np.log2(float(one.abs().max())))
+        out = net.backward(g, L, s, dy * factor)
+    at, deltas = 0, []
+    for o, i in synth.layer_shapes(W):
+        deltas.append(float(out[at + o * i:at + o * i + o].abs().max()))
+        at += o * i + o
+    assert sum(d >= 2.0 ** 126 for d in deltas) >= 1
+    assert int((one != 0).sum()) > one.numel() // 8
+    assert bool(torch.isfinite(out).all())
+    assert torch.equal(out, one * factor)
+
+
 def sr_inputs(n=1, h=20, w=24):
     torch = torch_dev()
     gen = torch.Generator(device="cuda:0").manual_seed(2)
